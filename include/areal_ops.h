@@ -20,7 +20,8 @@ extern "C" {
  *   mode 2: C half    [M,N]  = silu(A W0^T) * (A W1^T)      (W0 gate, W1 up)
  * A half [M,K], W0/W1 half [N,K] (IEEE fp16), row-major, 16-byte aligned, K % 8 == 0.
  * cfg = tile configuration 0 .. areal_op_gemm_num_configs()-1, or -1 for the
- * library's own choice; splits = K split (>1 accumulates with float32 atomics:
+ * library's own choice (22, 23 and 25 do not serve mode 2, 24 serves mode 1 only,
+ * 7 and above need K % 64 == 0: AREAL_E_INVAL); splits = K split (>1 accumulates with float32 atomics:
  * in mode 0 C must be zero beforehand), or -1 for the library's choice.
  * Returns 0 or AREAL_E_INVAL / AREAL_E_HIP. */
 int areal_op_gemm(void* hip_stream, const void* A, const void* W0, const void* W1, void* C,

@@ -788,13 +788,14 @@ hipError_t dispatch(hipStream_t s, int cfg, const f16* A, const GemmW& W, void* 
     case 25:   // 64-column tiles, one 32-column panel per wave (twice the work-groups of 22)
       if constexpr (MODE != GEMM_SWIGLU_F16) return run_dma<32, 64, 1, 2, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
       else return hipErrorInvalidValue;
-    // 192-row and 192-column tiles: other shapes of the last round (1,536 columns = 8 x 192)
+    // 192-row and 192-column tiles: other shapes of the last round (1,536 columns = 8 x 192).  Gate/up
+    // needs whole pairs of 32-column panels in a wave: there every wave takes all six panels.
     case 26:
       if constexpr (MODE != GEMM_SWIGLU_F16) return run_dma<256, 192, 4, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
-      else return hipErrorInvalidValue;      // three 32-column panels per wave: no gate/up pairs
+      else return run_dma<256, 192, 8, 1, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 27:
       if constexpr (MODE != GEMM_SWIGLU_F16) return run_dma<128, 192, 4, 2, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
-      else return hipErrorInvalidValue;
+      else return run_dma<128, 192, 4, 1, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 28: return run_dma<192, 256, 2, 4, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
     default: return hipErrorInvalidValue;
   }
