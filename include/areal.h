@@ -174,7 +174,8 @@ int areal_decode_step(areal_ctx* ctx, int32_t n_seqs, const int32_t* seq_ids,
  *   the first kept id, ascending, whose running mass exceeds r.
  *   logp_behav = log(c_tok / S_nuc); logp_full = log_softmax(z)[tok].
  * The token id is a pure function of (logits row, T, top_p, seed, seq_id,
- * position).  Logits must be finite.
+ * position).  Logits must be finite, and stay finite times 1/T: a row whose maximum is not
+ * has no mass, and draws token 0 with logp_behav -inf and logp_full NaN.
  *   logits    device float32 [n, vocab]
  *   seq_ids, positions  host [n]  (position = index the sampled token will have)
  *   forced_tokens  device int32 [n] or NULL.  Given: no draw; tokens_out =

@@ -192,7 +192,9 @@ __device__ __forceinline__ int find_bin(const u64* hist, u64 need, int lane, u64
 
 // The last step of both variants.  segmass[s] = kept mass of segment s (LDS), segtie[s] = ties
 // at the threshold before segment s (top-p < 1 only); draws (or takes the forced token), walks
-// the chosen segment in id order and writes the outputs of `row`.
+// the chosen segment in id order and writes the outputs of `row`.  A row without mass (its maximum is
+// not finite: every mass is 0) has nothing to draw from: token 0, or the forced one, with a behaviour
+// log-prob of -inf.
 __device__ __forceinline__ void choose_token(const Row& R, int row, int nseg, float m, u64 S_total, u64 S_nuc,
                                              bool all_in, u64 tau, u64 n_take, const u64* segmass,
                                              const uint32_t* segtie, u64* wave_tot, u64* sh_u64, int* sh_int,
@@ -212,6 +214,7 @@ __device__ __forceinline__ void choose_token(const Row& R, int row, int nseg, fl
   } else {
     const u64 Rbits = philox_draw(seed, (uint32_t)seq_ids[row], (uint32_t)positions[row]);
     r = __umul64hi(Rbits, S_nuc);
+    if (tid == 0) { sh_int[2] = 0; sh_u64[1] = 0; }      // the scan's barriers order this before the one write below
     u64 tot;
     const u64 mine = tid < nseg ? segmass[tid] : 0;
     const u64 incl = block_incl_scan_u64(mine, wave_tot, tot);
@@ -272,6 +275,7 @@ __device__ __forceinline__ void choose_token(const Row& R, int row, int nseg, fl
           }
         }
       }
+      if (S_nuc == 0 && lane == 0) k_sel = 0;
     }
     if (k_sel >= 0) {
       const int t = sseg * SEG + lane * 4 + k_sel;
@@ -451,9 +455,11 @@ __global__ __launch_bounds__(TPB) void sampler_kernel(
 
   // ---- nucleus (top_p < 1) -----------------------------------------------------
   u64 tau = 0, n_take = 0, S_nuc = S_total;
-  if (!all_in) {
+  if (!all_in && S_total > 0) {
     nucleus_of_row(R, nseg, m, top_p, S_total, L, tau, n_take, S_nuc);
     fold_ties(L, nseg, tau, n_take);
+  } else if (!all_in) {
+    L.segtie[tid] = 0;                 // no mass, no nucleus (choose_token's barriers publish this)
   }
 
   choose_token(R, row, nseg, m, S_total, S_nuc, all_in, tau, n_take, L.segmass, L.segtie, L.wave_tot, L.sh_u64,
@@ -607,8 +613,8 @@ __global__ __launch_bounds__(SPLIT_TPB) void sampler_split_hist_kernel(int V, co
     if (hist[b]) atomicAdd(&sc.hist[b], hist[b]);
 }
 
-// Total mass, and the bin the threshold falls into with the mass of the bins above it.  All
-// NW * 64 threads of the work-group take part; results in every thread.
+// Total mass, and the bin the threshold falls into with the mass of the bins above it (bin 0 for a
+// row without mass).  All NW * 64 threads of the work-group take part; results in every thread.
 template <int NW>
 __device__ __forceinline__ int threshold_bin(const SplitScratch& sc, float top_p, u64* wtot, u64* res_u64, int* res_int,
                                              u64& S_total, u64& target, u64& above) {
@@ -623,6 +629,7 @@ __device__ __forceinline__ int threshold_bin(const SplitScratch& sc, float top_p
   }
   const u64 incl_w = wave_incl_scan_u64(mine, lane);
   if (lane == 63) wtot[wave] = incl_w;
+  if (tid == 0) { *res_int = 0; *res_u64 = 0; }
   __syncthreads();
   u64 before = 0, all = 0;
 #pragma unroll
@@ -634,7 +641,7 @@ __device__ __forceinline__ int threshold_bin(const SplitScratch& sc, float top_p
   S_total = all;
   target = nucleus_target(top_p, all);
   const u64 incl = before + incl_w;
-  if (incl >= target && incl - mine < target) {        // exactly one thread
+  if (incl >= target && incl - mine < target) {        // exactly one thread (none if there is no mass)
     u64 a = incl - mine;
     int sel = 0;
     bool found = false;
@@ -712,7 +719,11 @@ __global__ __launch_bounds__(TPB) void sampler_split_nucleus_pick_kernel(
   u64 S_total, target, mass_above;
   const int tb = threshold_bin<NWAVES>(sc, top_p, L.wave_tot, &L.sh_u64[2], &L.sh_int[3], S_total, target, mass_above);
   u64 tau = 0, n_take = 0, S_nuc = 0;
-  if (n > LIST_CAP) {                                  // uniform over the work-group
+  if (S_total == 0) {                                  // uniform over the work-group, as is n
+    L.segmass[tid] = 0;
+    L.segtie[tid] = 0;
+    __syncthreads();
+  } else if (n > LIST_CAP) {
     nucleus_of_row(R, nseg, m, top_p, S_total, L, tau, n_take, S_nuc);
   } else {
     const u64 low = log_bin_low(tb);

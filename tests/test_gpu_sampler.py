@@ -130,3 +130,33 @@ def test_nucleus_of_more_rows_than_the_scratch_buffer_holds():
     _check(eng, logits, 1.0, 0.9, seed=3)
     _check(eng, logits, 1.0, 0.9, seed=3, forced=rng.integers(0, 9001, size=131))
     eng.close()
+
+
+@pytest.mark.parametrize("V", [1000, 20003])                    # one work-group per row / spread over several
+@pytest.mark.parametrize("top_p", [1.0, 0.9])
+def test_rows_without_mass(V, top_p):
+    """A row whose scaled maximum is not finite has no mass: token 0 (or the forced one) with a behaviour
+    log-prob of -inf; the rows around it are drawn as ever."""
+    import torch
+    from oracle import sampler
+    from paper_2505_24298_amd import binding
+    rng = np.random.default_rng(V)
+    logits = rng.standard_normal((6, V)).astype(np.float32)
+    logits[0, V - 1] = np.inf
+    logits[2] = np.nan
+    logits[4] = -np.inf
+    void, fine = [0, 2, 4], [1, 3, 5]
+    ids = np.arange(6, dtype=np.int32)
+    want = sampler.sample_batch(logits[fine], 0.7, top_p, 3, ids[fine], ids[fine])[0]
+    d, i = torch.from_numpy(logits).cuda(), torch.from_numpy(ids).cuda()
+    toks, lb, lf = (t.cpu().numpy() for t in binding.sample_logprob_static(d, i, i, 0.7, top_p, 3))
+    assert toks[fine].tolist() == want.tolist() and np.isfinite(lb[fine]).all()
+    assert (toks[void] == 0).all() and (lb[void] == -np.inf).all() and np.isnan(lf[void]).all()
+    forced = torch.full((6,), V - 2, dtype=torch.int32, device="cuda")
+    toks, lb, lf = (t.cpu().numpy() for t in binding.sample_logprob_static(d, i, i, 0.7, top_p, 3,
+                                                                           forced_tokens=forced))
+    assert (toks == V - 2).all() and (lb[void] == -np.inf).all()
+    # finite logits that a tiny temperature takes to infinity
+    toks, lb, lf = (t.cpu().numpy() for t in binding.sample_logprob_static(d[1:2].abs() + 1, i[1:2], i[1:2], 1e-38,
+                                                                           top_p, 3))
+    assert toks[0] == 0 and lb[0] == -np.inf
