@@ -18,6 +18,7 @@
 // feeds an integer decision is a single IEEE float32 operation; contraction
 // into fused multiply-add is switched off for this whole file.
 #include <algorithm>
+#include <type_traits>
 #include <mutex>
 #include <string>
 
@@ -37,9 +38,10 @@ static_assert(AREAL_SAMPLE_STATIC_MAX_VOCAB == SEG * MAX_SEG, "header limit = se
 namespace {
 
 constexpr int TPB = 1024, NWAVES = 16;
-// Segments from which the nucleus is spread (about 8,192 ids): one work-group per row / spread take 29 us / at
-// best the same at 4,096 ids, 43-46 / 22-36 us (1 / 128 rows) at 8,192, 133 / 23-44 at 32,768.
-constexpr int NUCLEUS_SPLIT_MIN_SEG = 32;
+// Segments from which the nucleus is spread: 32 (about 8,192 ids) up to 64 rows, 48 above.  Logits N(0, 0.4), top-p
+// 0.95, one work-group per row / spread: 8,192 ids 27 / 24 us at 1 row, 28.4 / 27.7 at 64, 28.9 / 30.9 at 128; 10,240 ids
+// 31.5 / 33.2 at 128 rows; 12,288 ids 36.7 / 33.2; 32,768 ids 71 / 24 at 1 row, 72 / 40 at 128.
+constexpr int NUCLEUS_SPLIT_MIN_SEG = 32, NUCLEUS_SPLIT_MIN_SEG_MANY = 48, NUCLEUS_FEW_ROWS = 64;
 constexpr int NBINS = 257;   // masses are 33-bit (0 .. 2^32); top level bins = c >> 24
 
 
@@ -310,6 +312,28 @@ __device__ __forceinline__ u64 nucleus_target(float top_p, u64 S_total) {
   return target > S_total ? S_total : target;
 }
 
+// Mass above tau and number of ids at tau, per segment of a row.
+__device__ __forceinline__ void segments_above(const Row& R, int nseg, float m, u64 tau, NucleusLds& L) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int s = wave; s < nseg; s += NWAVES) {
+    float z[4];
+    load_z4(R, s * SEG + lane * 4, z);
+    u64 gt = 0;
+    uint32_t tie = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const u64 c = mass_of(z[k], m);
+      const bool in = s * SEG + lane * 4 + k < R.V;
+      if (in && c > tau) gt += c;
+      if (in && c == tau) tie += 1;
+    }
+    gt = wave_sum_u64(gt);
+    tie = (uint32_t)wave_sum_u64(tie);
+    if (lane == 0) { L.segmass[s] = gt; L.segtie[s] = tie; }
+  }
+  __syncthreads();
+}
+
 // One work-group selects the nucleus of a whole row: threshold tau, number of ids at tau that
 // are taken (in id order), mass S_nuc, and the kept mass / ties before each segment in `L`.
 __device__ __forceinline__ void nucleus_of_row(const Row& R, int nseg, float m, float top_p, u64 S_total,
@@ -372,24 +396,7 @@ __device__ __forceinline__ void nucleus_of_row(const Row& R, int nseg, float m, 
   if (n_take > cnt_tau) n_take = cnt_tau;                 // cannot happen; keeps indices sane
   S_nuc = mass_above + n_take * tau;
 
-  // per-segment mass above tau and tie counts
-  for (int s = wave; s < nseg; s += NWAVES) {
-    float z[4];
-    load_z4(R, s * SEG + lane * 4, z);
-    u64 gt = 0;
-    uint32_t tie = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const u64 c = mass_of(z[k], m);
-      const bool in = s * SEG + lane * 4 + k < V;
-      if (in && c > tau) gt += c;
-      if (in && c == tau) tie += 1;
-    }
-    gt = wave_sum_u64(gt);
-    tie = (uint32_t)wave_sum_u64(tie);
-    if (lane == 0) { L.segmass[s] = gt; L.segtie[s] = tie; }
-  }
-  __syncthreads();
+  segments_above(R, nseg, m, tau, L);
 }
 
 // Fold the ties that are taken into the segments' kept mass; segtie becomes its exclusive prefix.
@@ -478,7 +485,10 @@ constexpr int LIST_CAP = 4096;                 // ids of one bin that the scratc
 struct SplitScratch {                          // one row's share of the scratch buffer
   u64 segmass[MAX_SEG];                        // mass per segment (top-p < 1: of the bins above the threshold's)
   u64 hist[LOG_BINS];                          // mass per bin
-  uint32_t list[LIST_CAP][2];                  // {id, low 32 bits of its mass} of the threshold's bin
+  union {                                      // of the threshold's bin:
+    uint32_t list[LIST_CAP][2];                // {id, low 32 bits of its mass}
+    uint32_t segtie[MAX_SEG];                  // or, where the bin is one value, its ids per segment
+  };
   float pmax[SAMPLER_MAX_PARTS];
   uint32_t n_list, pad[15];                    // ids in that bin (may exceed LIST_CAP)
 };
@@ -491,6 +501,10 @@ __device__ __forceinline__ int log_bin(u64 c) {
 }
 __device__ __forceinline__ u64 log_bin_low(int b) {    // smallest mass of a bin
   return b < 64 ? (u64)b : (u64)(64 + (b & 63)) << ((b >> 6) - 1);
+}
+
+__device__ __forceinline__ int log_bin_width(int b) {  // bits of a mass's offset in its bin (the last bin holds 2^32 only)
+  return b < 64 || b == LOG_BINS - 64 ? 0 : (b >> 6) - 1;
 }
 
 __device__ __forceinline__ Row make_row(const float* logits, int row, int V, float inv_t) {
@@ -579,8 +593,9 @@ __global__ __launch_bounds__(TPB) void sampler_split_pick_kernel(
 // kept mass of the bins above, per segment, and the list of that one bin's ids; (4) per row, the exact
 // threshold by radix select over the list, ties in id order, the draw.  The exponential is evaluated
 // twice per id, on all compute units: 64 rows of 151,936 logits 566 -> 61 us, 1 row 530 -> 27, 128 rows
-// 576 -> 90 (bound by the exponential's arithmetic and four launches).  A bin that overflows the list (heavily tied logits) falls
-// back to the selection over the whole row by one work-group in step 4.
+// 576 -> 90 (bound by the exponential's arithmetic and four launches).  A bin of one value (every mass
+// below 128, and 2^32: the maximum itself) needs no list but its ids per segment; for a bin that
+// overflows the list see nucleus_in_bin.
 __global__ __launch_bounds__(SPLIT_TPB) void sampler_split_hist_kernel(int V, const float* __restrict__ logits,
                                                                        float inv_t, int parts,
                                                                        SplitScratch* __restrict__ scratch) {
@@ -613,18 +628,19 @@ __global__ __launch_bounds__(SPLIT_TPB) void sampler_split_hist_kernel(int V, co
     if (hist[b]) atomicAdd(&sc.hist[b], hist[b]);
 }
 
-// Total mass, and the bin the threshold falls into with the mass of the bins above it (bin 0 for a
-// row without mass).  All NW * 64 threads of the work-group take part; results in every thread.
-template <int NW>
-__device__ __forceinline__ int threshold_bin(const SplitScratch& sc, float top_p, u64* wtot, u64* res_u64, int* res_int,
-                                             u64& S_total, u64& target, u64& above) {
-  constexpr int NT = NW * 64, PER = (LOG_BINS + NT - 1) / NT;
+// The bin in which the mass summed from the top reaches need(total mass), and the mass of the bins
+// above it (bin 0 if there is no mass).  All NW * 64 threads of the work-group take part; results in
+// every thread.
+template <int NW, int BINS, class Need>
+__device__ __forceinline__ int bin_from_top(const u64* hist, Need need_of, u64* wtot, u64* res_u64, int* res_int,
+                                            u64& above) {
+  constexpr int NT = NW * 64, PER = (BINS + NT - 1) / NT;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   u64 h[PER], mine = 0;
 #pragma unroll
   for (int k = 0; k < PER; ++k) {                      // thread 0 holds the highest bins
-    const int b = LOG_BINS - 1 - (tid * PER + k);
-    h[k] = b >= 0 ? sc.hist[b] : 0;
+    const int b = BINS - 1 - (tid * PER + k);
+    h[k] = b >= 0 ? hist[b] : 0;
     mine += h[k];
   }
   const u64 incl_w = wave_incl_scan_u64(mine, lane);
@@ -638,17 +654,15 @@ __device__ __forceinline__ int threshold_bin(const SplitScratch& sc, float top_p
     if (w < wave) before += t;
     all += t;
   }
-  S_total = all;
-  target = nucleus_target(top_p, all);
-  const u64 incl = before + incl_w;
-  if (incl >= target && incl - mine < target) {        // exactly one thread (none if there is no mass)
+  const u64 need = need_of(all), incl = before + incl_w;
+  if (incl >= need && incl - mine < need) {            // exactly one thread (none if there is no mass)
     u64 a = incl - mine;
     int sel = 0;
     bool found = false;
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
       if (!found) {
-        if (a + h[k] >= target) { sel = LOG_BINS - 1 - (tid * PER + k); found = true; }
+        if (a + h[k] >= need) { sel = BINS - 1 - (tid * PER + k); found = true; }
         else a += h[k];
       }
     }
@@ -658,6 +672,62 @@ __device__ __forceinline__ int threshold_bin(const SplitScratch& sc, float top_p
   __syncthreads();
   above = *res_u64;
   return *res_int;
+}
+// Total mass of a row, the nucleus's target, and the logarithmic bin its threshold falls into.
+template <int NW>
+__device__ __forceinline__ int threshold_bin(const SplitScratch& sc, float top_p, u64* wtot, u64* res_u64, int* res_int,
+                                             u64& S_total, u64& target, u64& above) {
+  return bin_from_top<NW, LOG_BINS>(sc.hist, [&](u64 all) {
+    S_total = all;
+    return target = nucleus_target(top_p, all);
+  }, wtot, res_u64, res_int, above);
+}
+
+// The exact threshold in a bin with more ids than the list holds (flat rows: at worst a spread
+// of z below 0.23 over 152k ids or 0.4 over 262k, a high temperature; or ties): one work-group walks the row again, 13 bits of the
+// offset at a time, two passes at the widest bin, and once more for the segments.  Selecting over the
+// whole row instead (four passes of 8 bits) took 331 / 546 us for 128 rows of 152k / 262k ids with a spread of
+// 0.02, 322 / 539 without the spread launches; this way 232 / 374.
+constexpr int OFFSET_BITS = 13, OFFSET_BINS = 1 << OFFSET_BITS;
+__device__ __forceinline__ void nucleus_in_bin(const Row& R, int nseg, float m, int tb, u64 target, u64 mass_above,
+                                               u64* hist, NucleusLds& L, u64& tau, u64& n_take, u64& S_nuc) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const u64 low = log_bin_low(tb);
+  u64 prefix = 0;
+  for (int top = log_bin_width(tb); top > 0;) {
+    const int shift = max(0, top - OFFSET_BITS), bits = top - shift;
+    for (int b = tid; b < OFFSET_BINS; b += TPB) hist[b] = 0;
+    __syncthreads();
+    for (int s = wave; s < nseg; s += NWAVES) {
+      float z[4];
+      load_z4(R, s * SEG + lane * 4, z);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const u64 c = mass_of(z[k], m), d = c - low;   // below the bin d wraps: its high bits are set
+        const bool in = (d >> top) == prefix;          // (masses beyond the vocabulary are 0: below it)
+        const int bin = (int)(d >> shift) & ((1 << bits) - 1);
+        const int bin0 = __builtin_amdgcn_readfirstlane(bin);
+        if (__all(in && bin == bin0)) {
+          const u64 tot = wave_sum_u64(c);
+          if (lane == 0) atomicAdd(&hist[bin0], tot);
+        } else if (in) {
+          atomicAdd(&hist[bin], c);
+        }
+      }
+    }
+    __syncthreads();
+    u64 above;
+    const int b = bin_from_top<NWAVES, OFFSET_BINS>(hist, [&](u64) { return target - mass_above; }, L.wave_tot,
+                                                    &L.sh_u64[2], &L.sh_int[3], above);
+    mass_above += above;
+    prefix = (prefix << bits) | (u64)b;
+    top = shift;
+    __syncthreads();                                   // the histogram and the broadcast slots are free again
+  }
+  tau = low + prefix;
+  n_take = (target - mass_above + tau - 1) / tau;
+  S_nuc = mass_above + n_take * tau;
+  segments_above(R, nseg, m, tau, L);
 }
 
 __global__ __launch_bounds__(SPLIT_TPB) void sampler_split_collect_kernel(int V, const float* __restrict__ logits,
@@ -675,23 +745,34 @@ __global__ __launch_bounds__(SPLIT_TPB) void sampler_split_collect_kernel(int V,
   if (threadIdx.x == 0) n_list = 0;
   u64 S_total, target, above;
   const int tb = threshold_bin<SPLIT_WAVES>(sc, top_p, wtot, &res_u64, &res_int, S_total, target, above);
-  for (int sg = part * SPLIT_WAVES + wave; sg < nseg; sg += parts * SPLIT_WAVES) {
-    float z[4];
-    load_z4(R, sg * SEG + lane * 4, z);
-    u64 gt = 0;
+  auto walk = [&](auto one_value) {
+    for (int sg = part * SPLIT_WAVES + wave; sg < nseg; sg += parts * SPLIT_WAVES) {
+      float z[4];
+      load_z4(R, sg * SEG + lane * 4, z);
+      u64 gt = 0;
+      int ties = 0;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const u64 c = mass_of(z[k], m);
-      const int bin = log_bin(c);
-      if (bin > tb) gt += c;
-      if (bin == tb && sg * SEG + lane * 4 + k < V) {
-        const uint32_t at = atomicAdd(&n_list, 1u);
-        if (at < LIST_CAP) { list[at][0] = sg * SEG + lane * 4 + k; list[at][1] = (uint32_t)c; }
+      for (int k = 0; k < 4; ++k) {
+        const u64 c = mass_of(z[k], m);
+        const int bin = log_bin(c);
+        const bool in = bin == tb && sg * SEG + lane * 4 + k < V;
+        if (bin > tb) gt += c;
+        if constexpr (decltype(one_value)::value) {
+          ties += __popcll(__ballot(in));
+        } else if (in) {
+          const uint32_t at = atomicAdd(&n_list, 1u);
+          if (at < LIST_CAP) { list[at][0] = sg * SEG + lane * 4 + k; list[at][1] = (uint32_t)c; }
+        }
+      }
+      gt = wave_sum_u64(gt);
+      if (lane == 0) {
+        sc.segmass[sg] = gt;
+        if constexpr (decltype(one_value)::value) sc.segtie[sg] = ties;
       }
     }
-    gt = wave_sum_u64(gt);
-    if (lane == 0) sc.segmass[sg] = gt;
-  }
+  };
+  if (log_bin_width(tb) == 0) walk(std::true_type{});
+  else walk(std::false_type{});
   __syncthreads();
   const uint32_t n = n_list;
   if (threadIdx.x == 0 && n) base = atomicAdd(&sc.n_list, n);
@@ -708,6 +789,7 @@ __global__ __launch_bounds__(TPB) void sampler_split_nucleus_pick_kernel(
     int parts, const SplitScratch* __restrict__ scratch, int32_t* __restrict__ tokens_out,
     float* __restrict__ logp_behav, float* __restrict__ logp_full) {
   __shared__ NucleusLds L;
+  __shared__ u64 offset_hist[OFFSET_BINS];
   constexpr int PER = LIST_CAP / TPB;
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const Row R = make_row(logits, row, V, inv_t);
@@ -723,8 +805,14 @@ __global__ __launch_bounds__(TPB) void sampler_split_nucleus_pick_kernel(
     L.segmass[tid] = 0;
     L.segtie[tid] = 0;
     __syncthreads();
+  } else if (log_bin_width(tb) == 0) {                 // the bin's one value is the threshold
+    tau = log_bin_low(tb);
+    n_take = (target - mass_above + tau - 1) / tau;
+    S_nuc = mass_above + n_take * tau;
+    if (tid < nseg) { L.segmass[tid] = sc.segmass[tid]; L.segtie[tid] = sc.segtie[tid]; }
+    __syncthreads();
   } else if (n > LIST_CAP) {
-    nucleus_of_row(R, nseg, m, top_p, S_total, L, tau, n_take, S_nuc);
+    nucleus_in_bin(R, nseg, m, tb, target, mass_above, offset_hist, L, tau, n_take, S_nuc);
   } else {
     const u64 low = log_bin_low(tb);
 #pragma unroll
@@ -735,7 +823,7 @@ __global__ __launch_bounds__(TPB) void sampler_split_nucleus_pick_kernel(
     }
     if (tid < nseg) { L.segmass[tid] = sc.segmass[tid]; L.segtie[tid] = 0; }
     // radix select on the offsets, 8 bits at a time from the bin's own width down
-    const int width_bits = tb < 64 ? 0 : (tb >> 6) - 1;
+    const int width_bits = log_bin_width(tb);
     uint32_t prefix = 0, cnt = n;
     for (int top = width_bits; top > 0;) {
       const int shift = max(0, top - 8), bits = top - shift;
@@ -812,7 +900,7 @@ hipError_t launch_sampler(hipStream_t s, int n, int vocab, const float* logits, 
                                                 forced, parts, sc, tokens_out, logp_behav, logp_full);
     return hipGetLastError();
   }
-  if (scratch && top_p < 1.0f && nseg >= NUCLEUS_SPLIT_MIN_SEG) {
+  if (scratch && top_p < 1.0f && nseg >= (n > NUCLEUS_FEW_ROWS ? NUCLEUS_SPLIT_MIN_SEG_MANY : NUCLEUS_SPLIT_MIN_SEG)) {
     for (int r0 = 0; r0 < n; r0 += SAMPLER_SPLIT_MAX_ROWS) {     // the scratch buffer's rows at a time
       const int rows = std::min(n - r0, SAMPLER_SPLIT_MAX_ROWS);
       const int pt = std::max(1, std::min(std::min(SAMPLER_MAX_PARTS, 1024 / rows), (nseg + SPLIT_WAVES - 1) / SPLIT_WAVES));

@@ -160,3 +160,25 @@ def test_rows_without_mass(V, top_p):
     toks, lb, lf = (t.cpu().numpy() for t in binding.sample_logprob_static(d[1:2].abs() + 1, i[1:2], i[1:2], 1e-38,
                                                                            top_p, 3))
     assert toks[0] == 0 and lb[0] == -np.inf
+
+
+@pytest.mark.parametrize("V,n", [(12032, 65), (12033, 65),      # last size of many rows kept by one work-group each
+                                 (20003, 3), (151936, 4), (262144, 2)])
+@pytest.mark.parametrize("top_p", [0.95, 0.5, 0.01])
+def test_nucleus_of_flat_rows(V, n, top_p):
+    """Rows so flat that the threshold's bin holds more ids than the list: the exact threshold comes from
+    two passes over the offsets in that bin, or from one where they fit 13 bits; masses that differ by
+    single units, ties among them, and rows where the bin is one value."""
+    rng = np.random.default_rng(V + n)
+    logits = rng.standard_normal((n, V)).astype(np.float32)
+    logits[0] *= 0.02
+    logits[1] *= 1e-7                                           # masses of 2^32 and just below
+    if n > 2:
+        logits[2] = np.round(logits[2] * 2) * 0.01              # a few values, each with many ids
+    if n > 3:
+        logits[3] = -20.0 - np.abs(logits[3]) * 1e-3            # all but one id share a narrow bin of few bits
+        logits[3, V // 2] = 0.0
+    eng = _engine_for_vocab(V)
+    _check(eng, logits, 1.0, top_p, seed=21)
+    _check(eng, logits, 5.0, top_p, seed=4, forced=rng.integers(0, V, size=n))
+    eng.close()
