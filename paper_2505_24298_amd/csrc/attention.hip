@@ -492,7 +492,7 @@ __global__ __launch_bounds__(D < 64 ? 64 : D) void attn_merge_kernel(const float
 // One work-group per (tile of 16 or 32 query positions, kv head): its rows are
 // those positions x the G query heads that share the kv head, cut into
 // row-groups of 16 (positions of one head), RGW row-groups per wave.  KV blocks
-// travel HBM -> LDS once per work-group (global_load_lds, a ring of PF_STAGES
+// travel HBM -> LDS once per work-group (buffer_load ... lds, a ring of PF_STAGES
 // stages of two blocks each) and every wave multiplies all its row-groups
 // against them, so each K/V byte fetched serves up to 32*G query rows.
 // Both products use the 16x16x32 MFMA: for P.V the 32-deep contraction runs
@@ -678,6 +678,8 @@ __global__ __launch_bounds__(256, (D == 128 && RGW == 3) ? 2 : 1) void attn_pref
 #pragma unroll
   for (int s = 0; s < PF_STAGES - 1; ++s) issue(min(s, n_pairs - 1), s);
   auto step = [&](int p, auto masked) {
+    // the stage that is refilled below was read in the step before: those reads are complete, for every wave
+    wait_lgkmcnt0();
     wait_vmcnt((PF_STAGES - 2) * NI);
     __builtin_amdgcn_s_barrier();
     issue(min(p + PF_STAGES - 1, n_pairs - 1), (p + PF_STAGES - 1) % PF_STAGES);
