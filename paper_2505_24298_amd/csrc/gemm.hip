@@ -88,8 +88,8 @@ __device__ __forceinline__ bool tile_of_block(int id, int M, int m_tiles, int n_
   return true;
 }
 
-// The reciprocal is the hardware's (1 ulp): the product is rounded to half precision right after.
-__device__ __forceinline__ float silu_f(float z) { return z * __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
+// A correctly rounded quotient, in every tile: the hardware's reciprocal (1 ulp) times z is another half now and then.
+__device__ __forceinline__ float silu_f(float z) { return z / (1.0f + __expf(-z)); }
 
 template <int BM, int BN, int WM, int WN, int MODE, bool RAGGED_K>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const f16* __restrict__ A, GemmW W,
