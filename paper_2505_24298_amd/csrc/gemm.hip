@@ -949,6 +949,14 @@ void gemm_choose(int M, int N, int K, GemmMode mode, int* cfg, int* splits) {
   *splits = sp;
 }
 
+// The forms a configuration is made for.  Asked before a shape is passed on to other tiles, so that what it does not
+// serve is refused at every shape.
+static bool config_serves(int cfg, GemmMode mode, int K) {
+  if (cfg >= gemm_num_configs() || (cfg >= 7 && K % BK)) return false;
+  if (mode == GEMM_SWIGLU_F16) return cfg != 22 && cfg != 23 && cfg != 24 && cfg != 25;
+  return cfg != 24 || mode == GEMM_ADD_F32;
+}
+
 hipError_t launch_gemm_cfg(hipStream_t s, const f16* A, GemmW W, void* C, int M, int N, int K, int ldc,
                            GemmMode mode, int cfg, int splits) {
   if (M <= 0 || N <= 0 || K <= 0 || K % 8 || ldc < N || !A || !C || !W.ptr[0]) return hipErrorInvalidValue;
@@ -957,6 +965,7 @@ hipError_t launch_gemm_cfg(hipStream_t s, const f16* A, GemmW W, void* C, int M,
   int c0, s0;
   gemm_choose(M, N, K, mode, &c0, &s0);
   if (cfg < 0) cfg = c0;
+  if (!config_serves(cfg, mode, K)) return hipErrorInvalidValue;
   if (splits < 0) splits = s0;
   // the direct-to-LDS tiles load W in groups of 8 rows that lie in one segment, with 32-bit offsets
   // inside a row tile: other shapes go through the register-staged tiles

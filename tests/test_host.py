@@ -401,3 +401,21 @@ def test_tile_choice_for_the_decoder_shapes(L):
     c, s = C.c_int32(), C.c_int32()
     assert L.areal_op_gemm_choose(0, 8, 8, 0, C.byref(c), C.byref(s)) != 0
     assert L.areal_op_gemm_choose(8, 8, 8, 3, C.byref(c), C.byref(s)) != 0
+
+
+def test_refused_products_stay_refused(L):
+    """areal_op_gemm: a configuration that does not exist, or does not serve the mode or a ragged K, is refused
+    whatever the shape, also where the shape would go to other tiles (odd widths of the gate/up product, K
+    beyond 32-bit offsets).  The addresses are never used: nothing of this reaches a launch."""
+    import ctypes as C
+    p = [C.c_void_p(4096 * k) for k in range(1, 5)]
+    n_cfg, INVAL = L.areal_op_gemm_num_configs(), binding.E_INVAL
+
+    def refused(M, N, K, mode, cfg):
+        return L.areal_op_gemm(None, *p, M, N, K, mode, cfg, 1) == INVAL
+
+    assert all(refused(40, N, 128, 2, cfg) for N in (94, 95) for cfg in (22, 23, 24, 25, n_cfg, n_cfg + 70))
+    assert all(refused(40, N, 72, 2, cfg) for N in (94, 95) for cfg in (7, 12, 21, 28))
+    assert all(refused(3, 24, K, mode, n_cfg) for K in (128, 1 << 22) for mode in (0, 1))
+    assert all(refused(3, 24, K, 0, 24) for K in (128, 1 << 22))
+    assert all(refused(3, 24, (1 << 22) + 8, mode, 12) for mode in (0, 1, 2))
