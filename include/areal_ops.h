@@ -22,7 +22,8 @@ extern "C" {
  * cfg = tile configuration 0 .. areal_op_gemm_num_configs()-1, or -1 for the
  * library's own choice (22, 23 and 25 do not serve mode 2, 24 serves mode 1 only,
  * 7 and above need K % 64 == 0: AREAL_E_INVAL); splits = K split (>1 accumulates with float32 atomics:
- * in mode 0 C must be zero beforehand), or -1 for the library's choice.
+ * in mode 0 C must be zero beforehand), or -1 for the library's choice (in mode 0 C must be zero
+ * beforehand up to 256 rows; above, C is overwritten: where the choice splits, a launch clears it first).
  * Returns 0 or AREAL_E_INVAL / AREAL_E_HIP. */
 int areal_op_gemm(void* hip_stream, const void* A, const void* W0, const void* W1, void* C,
                   int32_t M, int32_t N, int32_t K, int32_t mode, int32_t cfg, int32_t splits);

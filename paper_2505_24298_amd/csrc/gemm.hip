@@ -949,6 +949,10 @@ void gemm_choose(int M, int N, int K, GemmMode mode, int* cfg, int* splits) {
   *splits = sp;
 }
 
+__global__ __launch_bounds__(256) void clear_rows_kernel(float* __restrict__ C, int N, int ldc) {
+  for (int n = threadIdx.x; n < N; n += 256) C[(int64_t)blockIdx.x * ldc + n] = 0.f;
+}
+
 // The forms a configuration is made for.  Asked before a shape is passed on to other tiles, so that what it does not
 // serve is refused at every shape.
 static bool config_serves(int cfg, GemmMode mode, int K) {
@@ -958,7 +962,7 @@ static bool config_serves(int cfg, GemmMode mode, int K) {
 }
 
 hipError_t launch_gemm_cfg(hipStream_t s, const f16* A, GemmW W, void* C, int M, int N, int K, int ldc,
-                           GemmMode mode, int cfg, int splits) {
+                           GemmMode mode, int cfg, int splits, bool overwrite) {
   if (M <= 0 || N <= 0 || K <= 0 || K % 8 || ldc < N || !A || !C || !W.ptr[0]) return hipErrorInvalidValue;
   if (((uintptr_t)A | (uintptr_t)W.ptr[0] | (uintptr_t)W.ptr[1] | (uintptr_t)W.ptr[2]) & 15)
     return hipErrorInvalidValue;
@@ -966,6 +970,7 @@ hipError_t launch_gemm_cfg(hipStream_t s, const f16* A, GemmW W, void* C, int M,
   gemm_choose(M, N, K, mode, &c0, &s0);
   if (cfg < 0) cfg = c0;
   if (!config_serves(cfg, mode, K)) return hipErrorInvalidValue;
+  const bool clear = overwrite && splits < 0 && s0 > 1 && M > DECODE_ROWS;
   if (splits < 0) splits = s0;
   // the direct-to-LDS tiles load W in groups of 8 rows that lie in one segment, with 32-bit offsets
   // inside a row tile: other shapes go through the register-staged tiles
@@ -976,6 +981,7 @@ hipError_t launch_gemm_cfg(hipStream_t s, const f16* A, GemmW W, void* C, int M,
       if (W.end[0] > N || (W.end[0] < N && (!W.ptr[1] || W.end[1] > N)) ||
           (W.end[0] < N && W.end[1] < N && (!W.ptr[2] || W.end[2] != N)))
         return hipErrorInvalidValue;
+      if (clear) clear_rows_kernel<<<M, 256, 0, s>>>(reinterpret_cast<float*>(C), N, ldc);
       return dispatch<GEMM_STORE_F32>(s, cfg, A, W, C, M, N, K, ldc, splits);
     case GEMM_ADD_F32:
       if (W.end[0] != N) return hipErrorInvalidValue;

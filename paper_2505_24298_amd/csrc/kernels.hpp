@@ -72,9 +72,10 @@ hipError_t launch_gemm(hipStream_t s, const f16* A, GemmW W, void* C, int M, int
                        GemmMode mode);
 // Same with an explicit tile configuration (0 .. gemm_num_configs()-1) and K
 // split; -1 = take the tuned choice.  A split > 1 accumulates with float32
-// atomics: for GEMM_STORE_F32 the caller must have zeroed C.
+// atomics: for GEMM_STORE_F32 the caller must have zeroed C, or asks with `overwrite`
+// for a clearing launch where the split is the tuned choice above 256 rows.
 hipError_t launch_gemm_cfg(hipStream_t s, const f16* A, GemmW W, void* C, int M, int N, int K, int ldc,
-                           GemmMode mode, int cfg, int splits);
+                           GemmMode mode, int cfg, int splits, bool overwrite = false);
 void gemm_choose(int M, int N, int K, GemmMode mode, int* cfg, int* splits);
 int gemm_num_configs();
 

@@ -1294,7 +1294,8 @@ int areal_op_gemm(void* stream, const void* A, const void* W0, const void* W1, v
                   int32_t N, int32_t K, int32_t mode, int32_t cfg, int32_t splits) {
   if (mode < 0 || mode > 2 || !A || !W0 || !C || (mode == 2 && !W1)) return AREAL_E_INVAL;
   GemmW w{{(const f16*)W0, mode == 2 ? (const f16*)W1 : nullptr, nullptr}, {N, 0, 0}};
-  hipError_t e = launch_gemm_cfg((hipStream_t)stream, (const f16*)A, w, C, M, N, K, N, (GemmMode)mode, cfg, splits);
+  hipError_t e = launch_gemm_cfg((hipStream_t)stream, (const f16*)A, w, C, M, N, K, N, (GemmMode)mode, cfg, splits,
+                                 true);
   if (e == hipErrorInvalidValue) return AREAL_E_INVAL;
   return e == hipSuccess ? AREAL_OK : AREAL_E_HIP;
 }
