@@ -652,7 +652,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_dma_kernel(const f16* __res
 }
 
 // The same tiles with the last, partly filled round of work-groups evened out (one work-group
-// per compute unit; the residual-add products only, whose pieces add into C with float32 atomics).
+// per compute unit; the residual-add products only: the pieces of a cut tile add into C with float32
+// atomics, a whole tile has one owner and adds without).
 // XCD x takes the x-th eighth of the tiles (numbered row tile slowest: a block of neighbouring
 // tiles, so its work-groups share A and W panels in one L2).  Its G work-groups take whole
 // tiles G at a time; the `rem` tiles left over (rem < G) are cut along K: work-group j < rem walks
@@ -672,7 +673,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_dma_even_kernel(const f16* 
   const GemmLse none{nullptr, nullptr, 1.f};
   auto piece = [&](int tile, int kt0, int kt1) {
     dma_tile<BM, BN, WM, WN, STAGES, GEMM_ADD_F32>(A, W, C, M, N, K, ldc, tile / n_tiles, tile % n_tiles, kt0, kt1,
-                                                   1, none, lds);
+                                                   kt1 - kt0 < nk, none, lds);
     __syncthreads();            // every wave is done with the ring before the next piece refills it
   };
   for (int r = 0; r < rounds; ++r) piece(t0 + r * G + j, 0, nk);
@@ -739,12 +740,49 @@ hipError_t run(hipStream_t s, const f16* A, const GemmW& W, void* C, int M, int 
   return hipGetLastError();
 }
 
-// Residual adds with a long K go to configuration 24: whole tiles of 256 x 192 where these fill the
-// rounds of 256 compute units to nine tenths (8,192 x 1,536: 256 tiles, 216 us against 237 evened
-// out and 241 in tiles of 256 x 256), else 256 x 256 tiles with the last round evened out along K.
-static bool whole_256x192(int M, int N) {
-  const float load = (float)((N + 191) / 192) * (float)((M + 255) / 256) / 256.0f;
-  return load >= 0.9f * ceilf(load);
+// Prices of tiles and K splits above 256 rows.  No one rule holds from 257 to 8,192 rows: what decides is how the
+// last round of work-groups fills 256 compute units, and below about 1,000 rows whether there is a
+// round at all (36 tiles of 128 x 128 for the down projection of a 301-token prompt: 58 us with 2
+// splits, 22 with 6).  So every candidate is priced in microseconds: a fixed part, the K slabs one
+// compute unit walks (slower the fuller the chip: clocks and L2 are shared), and the adds into C per
+// million elements (with atomics for every split, or read and written once).  Constants: fitted to
+// about 700 times of a sweep over 25 row counts x 4 products of the 1.5B shape and 18 x 4 of the 7B
+// shape; over it the choice is 0.4 % from the best of all tiles and splits on average, and nowhere
+// more than 7 % but for the O projection at 3,000 - 4,096 rows (28 us against 23).
+struct PrefillTile {
+  int cfg, bm, bn, per_cu;        // work-groups of this tile a compute unit holds
+  float fixed, slab_few, slab_all, add_split, add_whole;
+};
+constexpr PrefillTile TILE_256x192 = {26, 256, 192, 1, 3.12f, 1.20f, 1.44f, 2.66f, 2.50f};
+constexpr PrefillTile prefill_tiles[] = {
+    {19, 256, 256, 1, 5.58f, 1.26f, 1.79f, 2.21f, 1.14f},  {28, 192, 256, 1, 4.39f, 1.02f, 1.41f, 2.33f, 0.41f},
+    TILE_256x192,                                          {27, 128, 192, 1, 5.07f, 0.56f, 0.752f, 2.06f, 1.71f},
+    {21, 128, 128, 1, 5.11f, 0.319f, 0.57f, 1.85f, 0.32f}, {20, 128, 128, 2, 3.64f, 0.571f, 1.06f, 2.02f, 0.25f},
+};
+static float prefill_us(const PrefillTile& t, int M, int N, int K, int mode, int splits) {
+  const int cols = mode == GEMM_SWIGLU_F16 ? t.bn / 2 : t.bn, nk = K / BK;
+  const float melem = (float)M * (float)N * 1e-6f;
+  const float n_wg = (float)((N + cols - 1) / cols) * (float)((M + t.bm - 1) / t.bm);
+  const int sps = (nk + splits - 1) / splits, parts = (nk + sps - 1) / sps;
+  const float load = n_wg * (float)parts / (256.0f * t.per_cu), rounds = ceilf(load);
+  float us = t.fixed * (1.0f + 0.4f * (rounds - 1.0f)) +
+             (float)sps * rounds * (t.slab_few + (t.slab_all - t.slab_few) * load / rounds);
+  if (parts > 1) us += t.add_split * melem * (float)parts;
+  else if (mode == GEMM_ADD_F32) us += t.add_whole * melem;
+  return us;
+}
+// Residual adds with a long K: tiles of 256 x 256 with the last round evened out along K.
+constexpr int EVENED_MIN_K = 4096;
+static float evened_us(int M, int N, int K) {
+  const float tiles = (float)((N + 255) / 256) * (float)((M + 255) / 256);
+  return 40.3f + tiles * (float)(K / BK) / 256.0f * 1.95f + 0.05f * (float)M * (float)N * 1e-6f;
+}
+// Configuration 24 takes tiles of 192 columns instead where these fill every round of 256 compute units, so that
+// nothing is left to cut, and are the cheaper ones: 8,192 x 1,536 x 8,960 (256 tiles) 220 us, 237 in tiles of 256
+// columns; 12,400 x 3,584 x 18,944 (3.6 rounds) 1,514 us evened out, 1,760 in whole tiles of 256 x 192.
+static bool evened_192(int M, int N, int K) {
+  return K >= EVENED_MIN_K && (int64_t)((N + 191) / 192) * ((M + 255) / 256) % 256 == 0 &&
+         prefill_us(TILE_256x192, M, N, K, GEMM_ADD_F32, 1) <= evened_us(M, N, K);
 }
 
 template <int MODE>
@@ -780,9 +818,10 @@ hipError_t dispatch(hipStream_t s, int cfg, const f16* A, const GemmW& W, void* 
     case 23:
       if constexpr (MODE != GEMM_SWIGLU_F16) return run_dma<64, 128, 2, 4, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
       else return hipErrorInvalidValue;
-    case 24:   // residual adds: whole tiles of 256 x 192, or 256 x 256 with the last round evened out along K
+    case 24:   // residual adds with the last round of work-groups evened out along K
       if constexpr (MODE == GEMM_ADD_F32) {
-        if (whole_256x192(M, N)) return run_dma<256, 192, 4, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, 1);
+        if (evened_192(M, N, K))
+          return run_dma_even<256, 192, 4, 2, 2>(s, A, W, reinterpret_cast<float*>(C), M, N, K, ldc, 256);
         return run_dma_even<256, 256, 2, 4, 2>(s, A, W, reinterpret_cast<float*>(C), M, N, K, ldc, 256);
       } else return hipErrorInvalidValue;
     case 25:   // 64-column tiles, one 32-column panel per wave (twice the work-groups of 22)
@@ -833,51 +872,23 @@ static int split_for(int M, int bm, int n_tiles, int nk) {
   return 1;
 }
 
-// Tile and K split above 256 rows.  No one rule holds from 257 to 8,192 rows: what decides is how the
-// last round of work-groups fills 256 compute units, and below about 1,000 rows whether there is a
-// round at all (36 tiles of 128 x 128 for the down projection of a 301-token prompt: 58 us with 2
-// splits, 22 with 6).  So every candidate is priced in microseconds: a fixed part, the K slabs one
-// compute unit walks (slower the fuller the chip: clocks and L2 are shared), and the adds into C per
-// million elements (with atomics for every split, or read and written once).  Constants: fitted to
-// about 700 times of a sweep over 25 row counts x 4 products of the 1.5B shape and 18 x 4 of the 7B
-// shape; over it the choice is 0.4 % from the best of all tiles and splits on average, and nowhere
-// more than 7 % but for the O projection at 3,000 - 4,096 rows (28 us against 23).
+// Tile and K split above 256 rows: the cheapest by prefill_us and evened_us.
 static void prefill_choose(int M, int N, int K, GemmMode mode, int* cfg, int* splits) {
-  struct Tile {
-    int cfg, bm, bn, per_cu;      // work-groups of this tile a compute unit holds
-    float fixed, slab_few, slab_all, add_split, add_whole;
-  };
-  static const Tile tiles[] = {
-      {19, 256, 256, 1, 5.58f, 1.26f, 1.79f, 2.21f, 1.14f},  {28, 192, 256, 1, 4.39f, 1.02f, 1.41f, 2.33f, 0.41f},
-      {26, 256, 192, 1, 3.12f, 1.20f, 1.44f, 2.66f, 2.50f},  {27, 128, 192, 1, 5.07f, 0.56f, 0.752f, 2.06f, 1.71f},
-      {21, 128, 128, 1, 5.11f, 0.319f, 0.57f, 1.85f, 0.32f}, {20, 128, 128, 2, 3.64f, 0.571f, 1.06f, 2.02f, 0.25f},
-  };
   static const int steps[] = {1, 2, 3, 4, 6, 8, 12};
   const int nk = K / BK;
-  const float melem = (float)M * (float)N * 1e-6f;
   float best = 1e30f;
-  for (const Tile& t : tiles) {
+  for (const PrefillTile& t : prefill_tiles) {
     if (mode == GEMM_SWIGLU_F16 && (t.cfg == 26 || t.cfg == 27)) continue;
-    const int cols = mode == GEMM_SWIGLU_F16 ? t.bn / 2 : t.bn;
-    const float n_wg = (float)((N + cols - 1) / cols) * (float)((M + t.bm - 1) / t.bm);
     for (int sp : steps) {
       if (sp > 1 && (mode == GEMM_SWIGLU_F16 || sp > max_splits() || 3 * sp > nk)) break;
-      const int sps = (nk + sp - 1) / sp, parts = (nk + sps - 1) / sps;
-      const float load = n_wg * (float)parts / (256.0f * t.per_cu), rounds = ceilf(load);
-      float us = t.fixed * (1.0f + 0.4f * (rounds - 1.0f)) +
-                 (float)sps * rounds * (t.slab_few + (t.slab_all - t.slab_few) * load / rounds);
-      if (parts > 1) us += t.add_split * melem * (float)parts;
-      else if (mode == GEMM_ADD_F32) us += t.add_whole * melem;
+      const float us = prefill_us(t, M, N, K, mode, sp);
       if (us < best) { best = us; *cfg = t.cfg; *splits = sp; }
     }
   }
-  if (mode == GEMM_ADD_F32 && K >= 4096) {
-    const float t256 = (float)((N + 255) / 256) * (float)((M + 255) / 256);
-    const float evened = 40.3f + t256 * (float)nk / 256.0f * 1.95f + 0.05f * melem;
-    const bool whole = whole_256x192(M, N);
-    // the evened-out pieces add with atomics: not under a limit of one split
-    const bool takes = whole ? (evened < best || (*cfg == 26 && *splits == 1)) : (evened < best && max_splits() > 1);
-    if (t256 >= 96.0f && takes) {
+  if (mode == GEMM_ADD_F32 && K >= EVENED_MIN_K && (int64_t)((N + 255) / 256) * ((M + 255) / 256) >= 96) {
+    // Configuration 24, by the price of the tiles that it launches: of 192 columns, the work of configuration 26
+    // without a split; of 256, whose cut tiles add with atomics: not under a limit of one split.
+    if (evened_192(M, N, K) ? *cfg == 26 && *splits == 1 : evened_us(M, N, K) < best && max_splits() > 1) {
       *cfg = 24;
       *splits = 1;
     }

@@ -403,6 +403,23 @@ def test_tile_choice_for_the_decoder_shapes(L):
     assert L.areal_op_gemm_choose(8, 8, 8, 3, C.byref(c), C.byref(s)) != 0
 
 
+def test_long_k_choice_names_the_kernel_it_launches(L):
+    """Residual adds with a long K: 24 is the launch that is evened out along K, 26 and 28 the whole tiles of
+    256 x 192 and 192 x 256.  Where whole tiles are the cheaper ones the choice says so, also where 192-column
+    tiles fill their rounds to nine tenths only."""
+    import ctypes as C
+
+    def choose(M, N, K):
+        c, s = C.c_int32(), C.c_int32()
+        assert L.areal_op_gemm_choose(M, N, K, 1, C.byref(c), C.byref(s)) == 0
+        return c.value, s.value
+
+    assert choose(6400, 3584, 18944) == choose(12400, 3584, 18944) == choose(5200, 4096, 11008) == (24, 1)
+    assert choose(2560, 4736, 8960) == choose(3457, 3456, 18944) == (26, 1)      # 250 and 252 tiles of 256 x 192
+    assert choose(8192, 1536, 8960) == (24, 1)                                   # 256 of them: nothing to cut
+    assert choose(8000, 1536, 8960) == choose(7000, 1536, 8960) == (28, 1)       # 252 and 222 of 192 x 256
+
+
 def test_refused_products_stay_refused(L):
     """areal_op_gemm: a configuration that does not exist, or does not serve the mode or a ragged K, is refused
     whatever the shape, also where the shape would go to other tiles (odd widths of the gate/up product, K
