@@ -99,7 +99,8 @@ typedef struct {
  * Reproducibility: projections whose K range is split over work-groups accumulate with
  * float32 atomic adds in no fixed order, so logits can differ from run to run in the last
  * bits (about 1e-7 relative); AREAL_GEMM_MAX_SPLITS=1 in the environment removes the splits,
- * and with them the run-to-run differences, at a cost in decode speed.  The sampler is a
+ * and with them the run-to-run differences, at a cost in the speed of decode steps and of prefill,
+ * update and scoring passes of a few hundred rows or a long K.  The sampler is a
  * pure function of the logits it is given. */
 typedef struct {
   int32_t dtype;                                    /* AREAL_DTYPE_F16, _BF16 or _F32        */
@@ -202,8 +203,8 @@ int areal_sample_logprob(areal_ctx* ctx, int32_t n, const float* logits,
  * Same results as areal_sample_logprob (token ids bit for bit).  At most
  * AREAL_SAMPLE_STATIC_MAX_ROWS rows of at most AREAL_SAMPLE_STATIC_MAX_VOCAB logits per
  * call; more returns AREAL_E_NOMEM and does nothing (split the batch).  Every call on a
- * GPU uses that GPU's one array: calls that overlap on one GPU (different streams or
- * threads) race; calls on one stream are ordered.  Errors: text via areal_last_error(NULL). */
+ * GPU uses that GPU's one array, with top_p < 1 too: calls that overlap on one GPU (different
+ * streams or threads) race; calls on one stream are ordered.  Errors: text via areal_last_error(NULL). */
 #define AREAL_SAMPLE_STATIC_MAX_ROWS  128
 #define AREAL_SAMPLE_STATIC_MAX_VOCAB 262144
 int areal_sample_logprob_static(void* hip_stream, int32_t n, int32_t vocab, const float* logits,

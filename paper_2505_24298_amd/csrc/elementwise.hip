@@ -110,8 +110,8 @@ hipError_t launch_rmsnorm(hipStream_t s, const float* x, const f16* gain, f16* y
 // Bound by memory (12 KB a row at the 1.5B shape): a thread takes eight neighbouring dims, two
 // 16-byte loads for each half of a rotation pair and one 16-byte store (v, whose tile is laid out
 // by token, is stored in halves); a row's items share the threads of a work-group with other rows'.
-// One element per thread and load took 25.7 us at 8,192 rows; with this a scoring pass (112
-// launches) went from 123.2 to 122.4 ms, a prefill of 301 tokens from 2,971 to 2,921 us.
+// 8,192 rows took 30.7 us with one element per thread and load, 24.9 with this (kernel trace of a
+// scoring pass; 100 MB at the 1.5B shape: 4.0 TB/s).
 __device__ __forceinline__ void load8(const float* p, float (&x)[8]) {
   const f32x4 a = *reinterpret_cast<const f32x4*>(p), b = *reinterpret_cast<const f32x4*>(p + 4);
 #pragma unroll

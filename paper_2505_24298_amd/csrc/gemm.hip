@@ -260,7 +260,9 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const f16* __restric
 // inside the matrix and no element is checked.  Row addresses are wave-uniform (scalar registers);
 // a lane adds one 32-bit offset.  With 24 slabs per tile (K = 1,536) the two waves of a SIMD spent about
 // a seventh of a gate/up tile here on bounds, 64-bit addresses, divisions and half-word stores:
-// 8,192 x 17,920 x 1,536 took 454 us, 424 with this form.
+// 8,192 x 17,920 x 1,536 took 454 us, 424 with this form (on one card, with the loads and the slab order of that
+// time; see dma_tile).  The division in silu is 16 us of such a product: 422 us with an approximate reciprocal
+// in its place, 437 with it.
 template <int BM, int BN, int WM, int WN, int MODE, bool FULL>
 __device__ __forceinline__ void store_tile_part(const f32x16 (&acc)[BM / WM / 32][BN / WN / 32],
                                                 void* __restrict__ Cv, int M, int N, int ldc, int tile_m,
@@ -305,7 +307,8 @@ __device__ __forceinline__ void store_tile_part(const f32x16 (&acc)[BM / WM / 32
     if (MODE == GEMM_ADD_F32 && !atomic) {
       // Nobody else adds into this tile: the residual's values of 32 rows are fetched together, one
       // batch ahead of the stores (a plain += waits for every load in turn, an atomic is a read and
-      // a write in the L2: 8,192 x 1,536 x 1,536 took 74 us with atomics, 56 with this).
+      // a write in the L2).  The O projection of 8,192 rows, 8,192 x 1,536 x 1,536, went from 82 us with
+      // atomics to 55 inside a scoring pass, together with the even tile map and the buffer loads.
       // The opaque row strides keep one batch's addresses from staying in registers for another.
       float old[2][TN][16];
       auto fetch = [&](int i) {
@@ -580,7 +583,8 @@ __device__ __forceinline__ void dma_tile(const f16* __restrict__ A, const GemmW&
   // 2,048 cycles of MFMAs and about as many of LDS traffic (192 KB read, 64 KB written), so what is not
   // overlapped shows: with the barrier at the slab's start and every wait for fragments a wait for all
   // of them, gate/up at 8,192 rows took 444 us and at 2,048 rows 136; so 423 and 127 (7B shape, 4,096
-  // rows: 1,012 -> 961 us; its down projection 532 -> 500).
+  // rows: 1,012 -> 961 us; its down projection 532 -> 500; another card than the 424 us of the epilogue's
+  // comment).  In a scoring pass gate/up at 8,192 rows takes 420 us, 450 before epilogue, loads and this order.
   Frags f0, f1;
   if (kt0 >= kt1) return;
   const int k_last = (kt1 - 1) * BK;
@@ -745,10 +749,12 @@ hipError_t run(hipStream_t s, const f16* A, const GemmW& W, void* C, int M, int 
 // round at all (36 tiles of 128 x 128 for the down projection of a 301-token prompt: 58 us with 2
 // splits, 22 with 6).  So every candidate is priced in microseconds: a fixed part, the K slabs one
 // compute unit walks (slower the fuller the chip: clocks and L2 are shared), and the adds into C per
-// million elements (with atomics for every split, or read and written once).  Constants: fitted to
-// about 700 times of a sweep over 25 row counts x 4 products of the 1.5B shape and 18 x 4 of the 7B
-// shape; over it the choice is 0.4 % from the best of all tiles and splits on average, and nowhere
-// more than 7 % but for the O projection at 3,000 - 4,096 rows (28 us against 23).
+// million elements (with atomics for every split, or read and written once).  Constants: fitted to a
+// sweep over row counts, products of the 1.5B and the 7B shape, tiles and splits, taken before the loads
+// became buffer loads.  Over a sweep taken since (20 row counts x 4 products of the 1.5B shape, 11 x 4 of the
+// 7B shape, 4,154 times) the choice is 1.3 % from the best on average; farthest off are the O and QKV
+// projections at 512 - 900 rows (split 2 would save 2 - 3 us of 19) and O at 3,000 - 4,096 (37 us against 33)
+// and 8,192 (64 against 58).
 struct PrefillTile {
   int cfg, bm, bn, per_cu;        // work-groups of this tile a compute unit holds
   float fixed, slab_few, slab_all, add_split, add_whole;

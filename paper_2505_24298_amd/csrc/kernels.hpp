@@ -124,8 +124,8 @@ hipError_t launch_attn_prefill(hipStream_t s, const f16* q, const AttnWork* work
 
 // ---- sampler.hip ------------------------------------------------------------
 // `scratch` (optional, device, 16-byte aligned, sampler_scratch_bytes()): lets the launch spread a
-// row over several work-groups when few rows are sampled with top-p = 1; its contents are
-// overwritten.  Without it every row is one work-group.
+// row over several work-groups: up to 128 rows with top-p = 1, and any number of rows with top-p < 1
+// over a large vocabulary; its contents are overwritten.  Without it every row is one work-group.
 hipError_t launch_sampler(hipStream_t s, int n, int vocab, const float* logits, const int32_t* seq_ids,
                           const int32_t* positions, float inv_temperature, float top_p, uint64_t seed,
                           const int32_t* forced, int32_t* tokens_out, float* logp_behav, float* logp_full,

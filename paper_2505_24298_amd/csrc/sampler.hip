@@ -594,8 +594,8 @@ __global__ __launch_bounds__(TPB) void sampler_split_pick_kernel(
 // threshold by radix select over the list, ties in id order, the draw.  The exponential is evaluated
 // twice per id, on all compute units: 64 rows of 151,936 logits 566 -> 61 us, 1 row 530 -> 27, 128 rows
 // 576 -> 90 (bound by the exponential's arithmetic and four launches).  A bin of one value (every mass
-// below 128, and 2^32: the maximum itself) needs no list but its ids per segment; for a bin that
-// overflows the list see nucleus_in_bin.
+// below 128, and 2^32: the maximum itself) needs no list but its ids per segment; for a bin with more
+// ids than the list holds see nucleus_in_bin.
 __global__ __launch_bounds__(SPLIT_TPB) void sampler_split_hist_kernel(int V, const float* __restrict__ logits,
                                                                        float inv_t, int parts,
                                                                        SplitScratch* __restrict__ scratch) {
@@ -683,11 +683,11 @@ __device__ __forceinline__ int threshold_bin(const SplitScratch& sc, float top_p
   }, wtot, res_u64, res_int, above);
 }
 
-// The exact threshold in a bin with more ids than the list holds (flat rows: at worst a spread
-// of z below 0.23 over 152k ids or 0.4 over 262k, a high temperature; or ties): one work-group walks the row again, 13 bits of the
-// offset at a time, two passes at the widest bin, and once more for the segments.  Selecting over the
-// whole row instead (four passes of 8 bits) took 331 / 546 us for 128 rows of 152k / 262k ids with a spread of
-// 0.02, 322 / 539 without the spread launches; this way 232 / 374.
+// The exact threshold in a bin with more ids than the list holds (flat rows: a spread of z below 0.23 over
+// 152k ids or 0.4 over 262k, which a high temperature gives; or ties): one work-group walks the row again,
+// 13 bits of the offset at a time, two passes at the widest bin, and once more for the segments.  Selecting
+// over the whole row instead (four passes of 8 bits) took 331 / 546 us for 128 rows of 152k / 262k ids with a
+// spread of 0.02, 322 / 539 without the spread launches; this way 232 / 374.
 constexpr int OFFSET_BITS = 13, OFFSET_BINS = 1 << OFFSET_BITS;
 __device__ __forceinline__ void nucleus_in_bin(const Row& R, int nseg, float m, int tb, u64 target, u64 mass_above,
                                                u64* hist, NucleusLds& L, u64& tau, u64& n_take, u64& S_nuc) {

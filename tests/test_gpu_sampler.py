@@ -71,7 +71,7 @@ def test_masses_far_below_the_maximum_are_zero():
 @pytest.mark.parametrize("V", [151936, 5000])
 def test_rows_spread_over_work_groups(V):
     """With few rows and top-p = 1 a row is spread over 2 .. 64 work-groups (partial maxima and
-    segment masses through a scratch buffer); 129 rows and more, and top-p < 1, keep one
+    segment masses through a scratch buffer); 129 rows and more keep one
     work-group per row.  Token ids must not depend on the split: 1, 23 and 128 rows (64, 44
     and 8 work-groups per row at the full vocabulary) against the oracle, and the same rows
     sampled as part of a batch of 129 (one work-group each) against the rows sampled alone."""
@@ -102,7 +102,7 @@ def test_nucleus_spread_over_work_groups(V, n, top_p):
     """top-p < 1 over a large vocabulary: the threshold's bin is located by a histogram on all
     work-groups and the exact threshold found among its ids.  Rows where that bin is nearly empty
     (peaked), crowded (narrow), made of ties, and overfull (all logits equal, two values: the list does
-    not hold the bin and one work-group selects over the whole row)."""
+    not hold the bin; one work-group goes through the row again)."""
     rng = np.random.default_rng(V + n)
     logits = (rng.standard_normal((n, V)) * rng.uniform(0.5, 4.0, size=(n, 1))).astype(np.float32)
     eng = _engine_for_vocab(V)
