@@ -14,8 +14,8 @@
       rocprofv3 --pmc: bytes fetched against weight bytes, matrix-core busy cycles).
       The weights rotate over 1.2 GB (every launch reads them from HBM) or over the
       given working set (150: they sit in the 256 MB memory-side cache, in no L2).
-  python3 paper_2505_24298_amd/microbench.py gemm [M,M,...] [shape,...]
-      every tile configuration x K split of the projection GEMM at the decoder's
+  python3 paper_2505_24298_amd/microbench.py gemm [M,M,...] [shape,...] [configuration,...]
+      every tile configuration (or the given ones) x K split of the projection GEMM at the decoder's
       shapes (qkv, o, gateup, down, lmhead of the 1.5B shape; qkv7 ... lmhead7 of the 7B shape);
       weights rotate over
       > 1 GB so they come from HBM.
@@ -176,11 +176,11 @@ GEMM_SHAPES = {"qkv": (2048, 1536, 0), "o": (1536, 1536, 1), "gateup": (8960, 15
                "down7": (3584, 18944, 1), "lmhead7": (152064, 3584, 0)}
 
 
-def gemm(ms_arg, shapes_arg):
+def gemm(ms_arg, shapes_arg, cfgs_arg=""):
     import torch
     from paper_2505_24298_amd import binding
     L = binding.lib()
-    ncfg = L.areal_op_gemm_num_configs()
+    cfgs = [int(x) for x in cfgs_arg.split(",")] if cfgs_arg else range(L.areal_op_gemm_num_configs())
     shapes = GEMM_SHAPES
     Ms = [int(x) for x in ms_arg.split(",")]
     g = torch.Generator(device="cuda").manual_seed(0)
@@ -197,7 +197,7 @@ def gemm(ms_arg, shapes_arg):
             As = [torch.randn((M, K), generator=g, device="cuda").to(torch.float16) for _ in range(ncopy)]
             Cs = [torch.zeros((M, N), device="cuda", dtype=torch.float16 if mode == 2 else torch.float32)
                   for _ in range(ncopy)]
-            for cfg in range(ncfg):
+            for cfg in cfgs:
                 for splits in ([1] if mode == 2 or name.startswith("lmhead") else [1, 2, 3, 4, 6, 8, 12]):
                     if cfg >= 7 and K % 64:
                         continue
@@ -308,7 +308,8 @@ if __name__ == "__main__":
                     working_set=float(sys.argv[4]) * 1e6 if len(sys.argv) > 4 else 1.2e9)
     elif what == "gemm":
         gemm(sys.argv[2] if len(sys.argv) > 2 else "32,64,128,256",
-             sys.argv[3] if len(sys.argv) > 3 else "qkv,o,gateup,down,lmhead")
+             sys.argv[3] if len(sys.argv) > 3 else "qkv,o,gateup,down,lmhead",
+             sys.argv[4] if len(sys.argv) > 4 else "")
     elif what == "prefill":
         prefill(sys.argv[2] if len(sys.argv) > 2 else "qwen2-1.5b")
     elif what == "score":
