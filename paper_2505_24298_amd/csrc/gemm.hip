@@ -11,6 +11,7 @@
 
 #include "kernels.hpp"
 #include <cstdlib>
+#include <type_traits>
 
 namespace areal {
 
@@ -378,103 +379,6 @@ __device__ __forceinline__ void lse_pair_combine(float& m, float& s, float m2, f
   m = mn;
 }
 
-// Reduction of 16 values per lane over the 32 lanes of equal lane >> 5: at every step a lane gives
-// half of its values to a partner and takes the partner's other half, so 8 + 4 + 2 + 1 + 1 exchanges
-// do what 16 separate butterflies do in 80.  Returns the value of index fold16_row(lane & 31).
-template <class Op>
-__device__ __forceinline__ float fold16(const float (&x)[16], int fr, Op op) {
-  float a8[8], a4[4], a2[2];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {          // partner: lane ^ 16
-    const float keep = (fr & 16) ? x[k + 8] : x[k], send = (fr & 16) ? x[k] : x[k + 8];
-    a8[k] = op(keep, __shfl_xor(send, 16));
-  }
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {          // lane ^ 8
-    const float keep = (fr & 8) ? a8[k + 4] : a8[k], send = (fr & 8) ? a8[k] : a8[k + 4];
-    a4[k] = op(keep, dpp_f32<0x128>(send));
-  }
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {          // lane ^ 7: the mirror image inside each 8 lanes
-    const float keep = (fr & 4) ? a4[k + 2] : a4[k], send = (fr & 4) ? a4[k] : a4[k + 2];
-    a2[k] = op(keep, dpp_f32<0x141>(send));
-  }
-  const float keep = (fr & 2) ? a2[1] : a2[0], send = (fr & 2) ? a2[0] : a2[1];
-  const float r = op(keep, dpp_f32<0x4E>(send));          // lane ^ 2
-  return op(r, dpp_f32<0xB1>(r));                         // lane ^ 1
-}
-__device__ __forceinline__ int fold16_row(int fr) { return fr >> 1; }
-
-// Epilogue of launch_gemm_lse: nothing of the tile is stored but, per row, the (max, sum of
-// exponentials) pair over the tile's columns and the value at the row's target column.  The
-// ring's LDS is reused (all its loads have landed and all waves are past their last read).
-template <int BM, int BN, int WM, int WN>
-__device__ __forceinline__ void store_tile_lse(const f32x16 (&acc)[BM / WM / 32][BN / WN / 32], char* lds,
-                                               float2* __restrict__ part, int ld_rows, int M, int N, int tile_m,
-                                               int tile_n, int wm, int wn, int fr, int fh, const GemmLse& lse) {
-  constexpr int TM = BM / WM / 32, TN = BN / WN / 32, NT = WM * WN * 64;
-  float2* red = reinterpret_cast<float2*>(lds);                       // [BM][WN]
-  int32_t* tgt = reinterpret_cast<int32_t*>(lds + BM * WN * 8);       // [BM]
-  const int m0 = tile_m * BM;
-  wait_vmcnt(0);
-  __syncthreads();
-  for (int r = threadIdx.x; r < BM; r += NT) tgt[r] = m0 + r < M ? lse.target[m0 + r] : -1;
-  __syncthreads();
-  float* wmax = reinterpret_cast<float*>(lds + BM * WN * 8 + BM * 4) + (wm * WN + wn) * 32;   // [32] per wave
-#pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int r0 = wm * (BM / WM) + i * 32;                 // rows r0 + 8*(v/4) + 4*fh + v%4 of the tile
-    float z[TN][16], red16[16];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int4 t4 = *reinterpret_cast<const int4*>(tgt + r0 + 8 * q + 4 * fh);
-      const int t[4] = {t4.x, t4.y, t4.z, t4.w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int v = 4 * q + e;
-        float m = -INFINITY;
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const int n = tile_n * BN + wn * (BN / WN) + j * 32 + fr;
-          z[j][v] = n < N ? acc[i][j][v] * lse.inv_t : -INFINITY;
-          if (n == t[e]) lse.target_z[m0 + r0 + 8 * q + 4 * fh + e] = z[j][v];
-          m = fmaxf(m, z[j][v]);
-        }
-        red16[v] = m;
-      }
-    }
-    // The row's maximum over the wave's columns first, then the exponentials once, against it.
-    // fold16 leaves row v's result in the two lanes with fold16_row(fr) == v of each half.
-    const float mrow = fold16(red16, fr, [](float a, float b) { return fmaxf(a, b); });
-    const int vrow = fold16_row(fr), rrow = 8 * (vrow >> 2) + 4 * fh + (vrow & 3);
-    wmax[rrow] = mrow;                                      // a wave's own slots: in order, no barrier
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const f32x4 m4 = *reinterpret_cast<const f32x4*>(wmax + 8 * q + 4 * fh);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float mu = m4[e] == -INFINITY ? 0.f : m4[e];
-        float sum = 0.f;
-#pragma unroll
-        for (int j = 0; j < TN; ++j) sum += __expf(z[j][4 * q + e] - mu);
-        red16[4 * q + e] = sum;
-      }
-    }
-    __builtin_amdgcn_wave_barrier();
-    const float srow = fold16(red16, fr, [](float a, float b) { return a + b; });
-    red[(r0 + rrow) * WN + wn] = float2{mrow, srow};
-  }
-  __syncthreads();
-  for (int r = threadIdx.x; r < BM; r += NT) {
-    if (m0 + r >= M) continue;
-    float m = -INFINITY, sum = 0.f;
-#pragma unroll
-    for (int w = 0; w < WN; ++w) lse_pair_combine(m, sum, red[r * WN + w].x, red[r * WN + w].y);
-    part[(int64_t)tile_n * ld_rows + m0 + r] = float2{m, sum};
-  }
-}
-
 // ---- direct-to-LDS variant ---------------------------------------------------
 // Same tiling, but the K-slabs travel HBM -> LDS with buffer_load_dwordx4 ... lds
 // (no register staging) into a ring of STAGES slab buffers, so STAGES-1 slabs
@@ -489,7 +393,7 @@ constexpr int GROUP_BYTES = 1024 + 128;   // 8 rows x 128 B, + 128 B skew betwee
 template <int BM, int BN, int WM, int WN, int STAGES, int MODE>
 __device__ __forceinline__ void dma_tile(const f16* __restrict__ A, const GemmW& W, void* __restrict__ Cv, int M,
                                          int N, int K, int ldc, int tile_m, int tile_n, int kt0, int kt1,
-                                         int atomic, const GemmLse& lse, char* lds) {
+                                         int atomic, char* lds) {
   constexpr int NW = WM * WN;
   constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
   constexpr int GA = BM / 8, GB = BN / 8;              // row groups per slab
@@ -632,11 +536,7 @@ __device__ __forceinline__ void dma_tile(const f16* __restrict__ A, const GemmW&
   }
   // (all remaining in-flight loads target LDS only; the epilogue does not touch LDS)
 
-  if constexpr (MODE == GEMM_LSE)
-    store_tile_lse<BM, BN, WM, WN>(acc, lds, reinterpret_cast<float2*>(Cv), ldc, M, N, tile_m, tile_n, wm, wn, fr,
-                                   fh, lse);
-  else
-    store_tile<BM, BN, WM, WN, MODE>(acc, Cv, M, N, ldc, tile_m, tile_n, wm, wn, fr, fh, atomic);
+  store_tile<BM, BN, WM, WN, MODE>(acc, Cv, M, N, ldc, tile_m, tile_n, wm, wn, fr, fh, atomic);
   // drain the loads that were requested past the end before the LDS is released
   wait_vmcnt(0);
 }
@@ -646,13 +546,374 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_dma_kernel(const f16* __res
                                                                 void* __restrict__ Cv, int M, int N,
                                                                 int K, int ldc, int m_tiles,
                                                                 int n_tiles, int splits, int slabs_per_split,
-                                                                int atomic, GemmLse lse) {
+                                                                int atomic) {
   __shared__ __attribute__((aligned(16))) char lds[STAGES * (BM / 8 + BN / 8) * GROUP_BYTES];
   int tile_m, tile_n, split;
   if (!tile_of_block(blockIdx.x, M, m_tiles, n_tiles, splits, tile_m, tile_n, split)) return;
   const int kt0 = split * slabs_per_split;
   dma_tile<BM, BN, WM, WN, STAGES, MODE>(A, W, Cv, M, N, K, ldc, tile_m, tile_n, kt0,
-                                         min(K / BK, kt0 + slabs_per_split), atomic, lse, lds);
+                                         min(K / BK, kt0 + slabs_per_split), atomic, lds);
+}
+
+// ---- direct-to-LDS tiles on the 16x16x32 MFMA: the prefill sizes --------------
+// What bounds a long run of the large products is the package's power: with operands drawn at random the
+// 256 x 256 tile runs at 1.67 GHz, with zeros at 2.3 (407 against 294 us for 8,192 x 17,920 x 1,536 on the
+// 32x32x16 MFMA).  Fed from registers alone, the 32x32x16 MFMA reaches 1.71 PFLOP/s on random operands
+// and the 16x16x32 one, which adds into its accumulators half as often, 1.97; with the tile's
+// fragment reads 1.58 and 1.78, and 1.86 in the order below (zeros: 2.45 all of them).
+//
+// Tile, ring and loads are those of dma_tile.  A slab is two K-steps of 32; a wave's (BM/WM) x (BN/WN)
+// part is TM x TN MFMAs of 16 x 16, taken in blocks of 2 x 2 that turn round at the end of a row of
+// blocks, so that of two MFMAs in a row one operand is the same wherever possible: fewer bits toggle.
+// Gate/up and scoring form W A^T: a lane then holds neighbouring columns of one row (lane & 15), which it stores as
+// 16 bytes or folds by itself.  Stored and added float32 tiles are A W^T, column lane & 15 of four neighbouring
+// rows in a lane: an atomic instruction then adds 64 contiguous bytes per row, not 16 (2.4 times the time for QKV
+// of 301 rows in 3 K splits).
+// Measured, one card, 1.5B shape: gate/up of 8,192 rows 440 -> 387 us (1,165 TFLOP/s), of 2,048 127 -> 117; down of
+// 8,192 222 -> 209, of 6,768 207 -> 193; QKV of 6,768 54.4 -> 51.6.  128 x 128 tiles gain nothing (their runs are short) and
+// stay with dma_tile.
+template <int TM, int TN>
+struct Wide {
+  f32x4 acc[TM][TN];
+  struct Frags { f16x8 a[TM], b[TN]; };
+  static constexpr int BLOCKS = (TM / 2) * (TN / 2), READS = TM + TN;
+  // block z of the 2 x 2 walk -> its first row and column
+  static constexpr int block_i(int z) { return z / (TN / 2) * 2; }
+  static constexpr int block_j(int z) {
+    const int j = z % (TN / 2);
+    return ((z / (TN / 2)) & 1) ? (TN / 2 - 1 - j) * 2 : j * 2;
+  }
+};
+
+// Row of the W tile that LDS row `b` holds.  Gate/up: of 64 rows the first 32 are gate rows, then come the up
+// rows of the same features, each as two MFMA tiles of 16 whose rows 4g + v are the features 8g + v and
+// 8g + 4 + v: a lane of group g ends up with eight neighbouring features.
+template <int MODE>
+__device__ __forceinline__ int wide_w_row(int b) {
+  if (MODE != GEMM_SWIGLU_F16) return b;
+  const int t = (b >> 4) & 1, r = b & 15;
+  return (b & ~31) + 8 * (r >> 2) + 4 * t + (r & 3);
+}
+
+template <int BM, int BN, int WM, int WN, int MODE, bool FULL>
+__device__ __forceinline__ void store_wide_part(const f32x4 (&acc)[BM / WM / 16][BN / WN / 16], void* __restrict__ Cv,
+                                                int M, int N, int ldc, int tile_m, int tile_n, int wm, int wn,
+                                                int fr, int fh, int atomic) {
+  constexpr int TM = BM / WM / 16, TN = BN / WN / 16;
+  const int m_wave = tile_m * BM + wm * (BM / WM);
+  if constexpr (MODE == GEMM_SWIGLU_F16) {
+    static_assert(TN % 4 == 0, "gate and up of a feature in one wave");
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; j += 4) {
+        const int f0 = tile_n * (BN / 2) + (wn * (BN / WN) + j * 16) / 2;
+        f16* Cw = reinterpret_cast<f16*>(Cv) + (int64_t)(m_wave + i * 16) * ldc + f0;
+        f16* p = Cw + fr * ldc + fh * 8;
+        f16x8 y;
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) y[4 * t + v] = f2h_sat(silu_f(acc[i][j + t][v]) * acc[i][j + 2 + t][v]);
+        if (FULL) {
+          *reinterpret_cast<f16x8*>(p) = y;
+        } else if (m_wave + i * 16 + fr < M) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (f0 + fh * 8 + e < N) p[e] = y[e];
+        }
+      }
+  } else {
+    const int n_wave = tile_n * BN + wn * (BN / WN);
+    float* Cw = reinterpret_cast<float*>(Cv) + (int64_t)m_wave * ldc + n_wave;
+    // the opaque row stride keeps one batch's addresses from staying in registers for another
+    auto stride = [&] { int ld = ldc; asm volatile("" : "+s"(ld)); return ld; };
+    auto at = [&](int i, int j, int v, int ld) { return Cw + (int64_t)(i * 16 + v) * ld + j * 16 + (4 * fh * ld + fr); };
+    auto inside = [&](int i, int j, int v) {
+      return FULL || (m_wave + i * 16 + 4 * fh + v < M && n_wave + j * 16 + fr < N);
+    };
+    if (MODE == GEMM_ADD_F32 && !atomic) {
+      float old[2][TN][4];
+      auto fetch = [&](int i) {
+        const int ld = stride();
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) old[i & 1][j][v] = inside(i, j, v) ? *at(i, j, v, ld) : 0.f;
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      fetch(0);
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        if (i + 1 < TM) fetch(i + 1);
+        const int ld = stride();
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            if (inside(i, j, v)) *at(i, j, v, ld) = old[i & 1][j][v] + acc[i][j][v];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      return;
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const int ld = stride();
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (inside(i, j, v)) {
+            if (atomic) unsafeAtomicAdd(at(i, j, v, ld), acc[i][j][v]);
+            else *at(i, j, v, ld) = acc[i][j][v];
+          }
+    }
+  }
+}
+
+// Epilogue of launch_gemm_lse: nothing of the tile is stored but, per row, the (max, sum of exponentials) pair over
+// the tile's columns and the value at the row's target column.  A lane holds 4 TN columns of one row per row tile,
+// so a row is folded in the lane and over the four lanes that share it: its maximum first, then the
+// exponentials once, against it.  The ring's LDS is reused (all its loads have landed and all waves are past their
+// last read).
+template <int BM, int BN, int WM, int WN>
+__device__ __forceinline__ void store_wide_lse(const f32x4 (&acc)[BM / WM / 16][BN / WN / 16], char* lds,
+                                               float2* __restrict__ part, int ld_rows, int M, int N, int tile_m,
+                                               int tile_n, int wm, int wn, int fr, int fh, const GemmLse& lse) {
+  constexpr int TM = BM / WM / 16, TN = BN / WN / 16, NT = WM * WN * 64;
+  float2* red = reinterpret_cast<float2*>(lds);                       // [BM][WN]
+  const int m0 = tile_m * BM;
+  int tgt[TM];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const int m = m0 + wm * (BM / WM) + i * 16 + fr;
+    tgt[i] = m < M ? lse.target[m] : -1;
+  }
+  wait_vmcnt(0);
+  __syncthreads();                                                    // the ring is free
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const int row = wm * (BM / WM) + i * 16 + fr;
+    float z[TN][4], m = -INFINITY, sum = 0.f;
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int n = tile_n * BN + wn * (BN / WN) + j * 16 + fh * 4 + v;
+        z[j][v] = n < N ? acc[i][j][v] * lse.inv_t : -INFINITY;
+        if (n == tgt[i]) lse.target_z[m0 + row] = z[j][v];
+        m = fmaxf(m, z[j][v]);
+      }
+    m = fmaxf(m, __shfl_xor(m, 16));
+    m = fmaxf(m, __shfl_xor(m, 32));
+    const float mu = m == -INFINITY ? 0.f : m;
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) sum += __expf(z[j][v] - mu);
+    sum += __shfl_xor(sum, 16);
+    sum += __shfl_xor(sum, 32);
+    if (fh == 0) red[row * WN + wn] = float2{m, sum};
+  }
+  __syncthreads();
+  for (int r = threadIdx.x; r < BM; r += NT) {
+    if (m0 + r >= M) continue;
+    float m = -INFINITY, sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < WN; ++w) lse_pair_combine(m, sum, red[r * WN + w].x, red[r * WN + w].y);
+    part[(int64_t)tile_n * ld_rows + m0 + r] = float2{m, sum};
+  }
+}
+
+template <int BM, int BN, int WM, int WN, int STAGES, int MODE>
+__device__ __forceinline__ void wide_tile(const f16* __restrict__ A, const GemmW& W, void* __restrict__ Cv, int M,
+                                          int N, int K, int ldc, int tile_m, int tile_n, int kt0, int kt1,
+                                          int atomic, const GemmLse& lse, char* lds) {
+  constexpr int NW = WM * WN;
+  constexpr int TM = BM / WM / 16, TN = BN / WN / 16;
+  constexpr int GA = BM / 8, GB = BN / 8;              // row groups per slab
+  constexpr int LPS = (GA + GB) / NW;                  // load instructions per wave per slab
+  static_assert(GA % NW == 0 && GB % NW == 0 && TM % 2 == 0 && TN % 2 == 0, "tile does not divide over the waves");
+  constexpr int STAGE_BYTES = (GA + GB) * GROUP_BYTES;
+  typedef Wide<TM, TN> WideT;
+  constexpr bool TRANS = MODE == GEMM_SWIGLU_F16 || MODE == GEMM_LSE;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const int m0 = tile_m * BM;
+
+  const auto a_rsrc = buffer_rsrc(A + (int64_t)m0 * K, (uint32_t)min(M - m0, BM) * (uint32_t)K * 2u);
+  __amdgpu_buffer_rsrc_t b_rsrc[GB / NW];
+  int src[LPS], dst_off[LPS];
+  {
+    const int rin = lane >> 3, chunk = (lane & 7) ^ rin;
+#pragma unroll
+    for (int i = 0; i < LPS; ++i) {
+      const bool is_a = i < GA / NW;
+      const int gi = is_a ? wave * (GA / NW) + i : wave * (GB / NW) + (i - GA / NW);
+      if (is_a) {
+        src[i] = (min(gi * 8 + rin, M - 1 - m0) * K + chunk * 8) * 2;
+        dst_off[i] = gi * GROUP_BYTES;
+      } else {
+        // the group's rows start at row b0 of the tile (gate/up: two runs of four, eight rows apart, of one
+        // segment); rows outside the matrix are replaced by one inside: their products are never stored
+        const int b0 = wide_w_row<MODE>(gi * 8), down = wide_w_row<MODE>(gi * 8 + rin) - b0;
+        const int left = w_rows_left<BN, MODE>(tile_n, b0, N);
+        const f16* p = left > 0 ? w_row_ptr<BN, MODE>(W, tile_n, b0, N, K) : W.ptr[0];
+        b_rsrc[i - GA / NW] = buffer_rsrc(p, (MODE == GEMM_SWIGLU_F16 ? 12u : 8u) * (uint32_t)K * 2u);
+        src[i] = ((down < left ? down : 0) * K + chunk * 8) * 2;
+        dst_off[i] = (GA + gi) * GROUP_BYTES;
+      }
+    }
+  }
+  auto issue1 = [&](int stage, int k0, int i) {
+    dma16(i < GA / NW ? a_rsrc : b_rsrc[i < GA / NW ? 0 : i - GA / NW], src[i], k0 * 2,
+          lds + stage * STAGE_BYTES + dst_off[i]);
+  };
+
+  WideT t;
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) t.acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  const int fr = lane & 15, fh = lane >> 4;
+  // fragment addresses inside a stage: tile row R -> group R>>3, slot (R&7)*8 + (chunk ^ (R&7)); the 16-row tiles of a
+  // wave are two groups apart
+  int a_at[2], b_at[2];
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk) {
+    const int ko = ((kk * 4 + fh) ^ (fr & 7)) << 4;
+    const int ra = wm * (BM / WM) + fr, rb = wn * (BN / WN) + fr;
+    a_at[kk] = (ra >> 3) * GROUP_BYTES + (ra & 7) * 128 + ko;
+    b_at[kk] = (GA + (rb >> 3)) * GROUP_BYTES + (rb & 7) * 128 + ko;
+  }
+  typename WideT::Frags f0, f1;
+  // the fragment reads of a K-step in the order in which the walk needs them
+  auto read1 = [&](typename WideT::Frags& f, const char* base, int kk, int r) {
+    // a0 a1 b0 b1 | b2 .. | a2 ..
+    const bool is_a = r < 2 || r >= 2 + TN;
+    const int x = r < 2 ? r : (r < 2 + TN ? r - 2 : r - TN);
+    if (is_a) f.a[x] = *reinterpret_cast<const f16x8*>(base + a_at[kk] + x * 2 * GROUP_BYTES);
+    else f.b[x] = *reinterpret_cast<const f16x8*>(base + b_at[kk] + x * 2 * GROUP_BYTES);
+  };
+  auto mma1 = [&](const typename WideT::Frags& f, int i, int j) {
+    t.acc[i][j] = TRANS ? __builtin_amdgcn_mfma_f32_16x16x32_f16(f.b[j], f.a[i], t.acc[i][j], 0, 0, 0)
+                        : __builtin_amdgcn_mfma_f32_16x16x32_f16(f.a[i], f.b[j], t.acc[i][j], 0, 0, 0);
+  };
+  if (kt0 >= kt1) return;
+  const int k_last = (kt1 - 1) * BK;
+  // prologue: STAGES slabs in flight (past the end: re-read the last slab, never consumed)
+#pragma unroll
+  for (int s = 0; s < STAGES; ++s)
+#pragma unroll
+    for (int i = 0; i < LPS; ++i) issue1(s, min((kt0 + s) * BK, k_last), i);
+  wait_vmcnt((STAGES - 1) * LPS);
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int r = 0; r < WideT::READS; ++r) read1(f0, lds, 0, r);
+  int cur = 0, kt = kt0;
+  const std::true_type yes{};
+  const std::false_type no{};
+  // One slab: 2 B blocks of four MFMAs, everything else placed between them in a fixed order: RPB fragment reads
+  // a block from the start of a K-step on, DPB loads a block from the second K-step on.  One barrier, between the
+  // K-steps: every wave has its last fragments of the stage (which the loads of slab kt + STAGES then refill), and
+  // slab kt + 1 has landed for every wave.  LOAD: slab kt + STAGES exists; NEXT: slab kt + 1 does.
+  // Tried for gate/up of 8,192 rows, 365 us in a long run: loads two, four or eight a block 366, 373, 385; a barrier
+  // each for freeing and landing, half a K-step apart, 382; a ring of four or five stages of 32 along K, whose loads
+  // fetch half lines, 396 and 403.
+  constexpr int B = WideT::BLOCKS, READS_B = (WideT::READS + B - 1) / B;
+  constexpr int RPB = READS_B > 2 ? READS_B : 2, DPB = (LPS + B - 1) / B;
+  auto slab = [&](auto load, auto next) {
+    constexpr bool LOAD = decltype(load)::value, NEXT = decltype(next)::value;
+    const int nxt = cur + 1 == STAGES ? 0 : cur + 1, k_load = min((kt + STAGES) * BK, k_last);
+    const char *base = lds + cur * STAGE_BYTES, *base_next = lds + nxt * STAGE_BYTES;
+    __builtin_amdgcn_sched_barrier(0);
+    int dn = 0, rn = 0;
+#pragma unroll
+    for (int z = 0; z < 2 * B; ++z) {
+      const typename WideT::Frags& f = z < B ? f0 : f1;
+      const int i = WideT::block_i(z % B), j = WideT::block_j(z % B);
+      if (NEXT && z == B) {
+        // a plain barrier: a fence would drain every outstanding load
+        wait_lgkmcnt0();
+        wait_vmcnt((STAGES - 2) * LPS);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      mma1(f, i, j);
+      mma1(f, i, j + 1);
+#pragma unroll
+      for (int r = z * RPB; r < (z + 1) * RPB; ++r)
+        if (z < B && r < WideT::READS) read1(f1, base, 1, r);
+      if (LOAD && z >= B) {
+#pragma unroll
+        for (int d = 0; d < DPB; ++d)
+          if (dn < LPS) issue1(cur, k_load, dn++);
+      }
+      if (NEXT && z >= B) {
+#pragma unroll
+        for (int r = 0; r < RPB; ++r)
+          if (rn < WideT::READS) read1(f0, base_next, 0, rn++);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      mma1(f, i + 1, j + 1);
+      mma1(f, i + 1, j);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    cur = nxt;
+    ++kt;
+  };
+  // with two stages nothing is requested past the end
+  const int n_load = kt1 - kt0 - (STAGES == 2 ? 2 : 1);
+  for (int i = 0; i < n_load; ++i) slab(yes, yes);
+  if (STAGES == 2 && kt1 - kt0 >= 2) slab(no, yes);
+  slab(no, no);
+
+  if constexpr (MODE == GEMM_LSE) {
+    store_wide_lse<BM, BN, WM, WN>(t.acc, lds, reinterpret_cast<float2*>(Cv), ldc, M, N, tile_m, tile_n, wm, wn, fr, fh,
+                                   lse);
+  } else {
+    constexpr int NC = MODE == GEMM_SWIGLU_F16 ? BN / 2 : BN;
+    // gate/up: a lane's eight features go out as 16 bytes where rows start on 16 bytes
+    const bool whole = MODE != GEMM_SWIGLU_F16 || ((ldc & 7) == 0 && ((uintptr_t)Cv & 15) == 0);
+    if (whole && (tile_m + 1) * BM <= M && (tile_n + 1) * NC <= N)
+      store_wide_part<BM, BN, WM, WN, MODE, true>(t.acc, Cv, M, N, ldc, tile_m, tile_n, wm, wn, fr, fh, atomic);
+    else
+      store_wide_part<BM, BN, WM, WN, MODE, false>(t.acc, Cv, M, N, ldc, tile_m, tile_n, wm, wn, fr, fh, atomic);
+  }
+  // drain the loads that were requested past the end before the LDS is released
+  wait_vmcnt(0);
+}
+
+template <int BM, int BN, int WM, int WN, int STAGES, int MODE>
+__global__ __launch_bounds__(WM * WN * 64) void gemm_wide_kernel(const f16* __restrict__ A, GemmW W,
+                                                                 void* __restrict__ Cv, int M, int N, int K,
+                                                                 int ldc, int m_tiles, int n_tiles, int splits,
+                                                                 int slabs_per_split, int atomic, GemmLse lse) {
+  __shared__ __attribute__((aligned(16))) char lds[STAGES * (BM / 8 + BN / 8) * GROUP_BYTES];
+  int tile_m, tile_n, split;
+  if (!tile_of_block(blockIdx.x, M, m_tiles, n_tiles, splits, tile_m, tile_n, split)) return;
+  const int kt0 = split * slabs_per_split;
+  wide_tile<BM, BN, WM, WN, STAGES, MODE>(A, W, Cv, M, N, K, ldc, tile_m, tile_n, kt0,
+                                                                min(K / BK, kt0 + slabs_per_split), atomic, lse, lds);
+}
+
+template <int BM, int BN, int WM, int WN, int STAGES, int MODE>
+hipError_t run_wide(hipStream_t s, const f16* A, const GemmW& W, void* C, int M, int N, int K, int ldc,
+                    int splits, GemmLse lse = GemmLse{nullptr, nullptr, 1.f}) {
+  if (K % BK) return hipErrorInvalidValue;
+  constexpr int n_out_per_tile = MODE == GEMM_SWIGLU_F16 ? BN / 2 : BN;
+  const int n_tiles = (N + n_out_per_tile - 1) / n_out_per_tile, m_tiles = (M + BM - 1) / BM;
+  const int nk = K / BK;
+  splits = std::max(1, std::min(splits, nk));
+  const int sps = (nk + splits - 1) / splits;
+  splits = (nk + sps - 1) / sps;
+  const int grid = grid_blocks(M, m_tiles, n_tiles, splits);
+  gemm_wide_kernel<BM, BN, WM, WN, STAGES, MODE><<<grid, WM * WN * 64, 0, s>>>(
+      A, W, C, M, N, K, ldc, m_tiles, n_tiles, splits, sps, splits > 1 ? 1 : 0, lse);
+  return hipGetLastError();
 }
 
 // The same tiles with the last, partly filled round of work-groups evened out (one work-group
@@ -666,7 +927,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_dma_kernel(const f16* __res
 // tile count leaves compute units idle in the last round (1,536 output columns: 192 tiles of
 // 256 x 256 at 8,192 rows on 256 units).
 template <int BM, int BN, int WM, int WN, int STAGES>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_dma_even_kernel(const f16* __restrict__ A, GemmW W,
+__global__ __launch_bounds__(WM * WN * 64) void gemm_even_kernel(const f16* __restrict__ A, GemmW W,
                                                                      float* __restrict__ C, int M, int N, int K,
                                                                      int ldc, int n_tiles, int tiles) {
   __shared__ __attribute__((aligned(16))) char lds[STAGES * (BM / 8 + BN / 8) * GROUP_BYTES];
@@ -675,43 +936,50 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_dma_even_kernel(const f16* 
   const int t0 = (int)((int64_t)tiles * xcd / 8), t1 = (int)((int64_t)tiles * (xcd + 1) / 8);
   const int rounds = (t1 - t0) / G, rem = (t1 - t0) % G;
   const GemmLse none{nullptr, nullptr, 1.f};
-  auto piece = [&](int tile, int kt0, int kt1) {
-    dma_tile<BM, BN, WM, WN, STAGES, GEMM_ADD_F32>(A, W, C, M, N, K, ldc, tile / n_tiles, tile % n_tiles, kt0, kt1,
-                                                   kt1 - kt0 < nk, none, lds);
-    __syncthreads();            // every wave is done with the ring before the next piece refills it
-  };
-  for (int r = 0; r < rounds; ++r) piece(t0 + r * G + j, 0, nk);
-  if (rem == 0) return;
   const int last = t0 + rounds * G;
   const int S = (rem * nk + G - 1) / G;                  // slabs per work-group in the last round, < nk
-  if (j < rem) {
-    piece(last + j, 0, S);
-  } else {
-    const int tail = nk - S;                             // slabs left of each of the rem tiles
-    int u = (j - rem) * S;
-    const int u_end = min((j - rem + 1) * S, rem * tail);
-    while (u < u_end) {
-      const int t = u / tail, k0 = S + u % tail;
-      const int k1 = min(nk, k0 + (u_end - u));
-      piece(last + t, k0, k1);
+  const int tail = nk - S;                               // slabs left of each of the rem tiles
+  int r = 0, u = (j - rem) * S;
+  const int u_end = min((j - rem + 1) * S, rem * tail);
+  // one call, so that the tile is compiled into the kernel once
+  for (;;) {
+    int tile, k0, k1;
+    if (r < rounds) {
+      tile = t0 + r * G + j;
+      k0 = 0;
+      k1 = nk;
+    } else if (j < rem) {
+      if (r > rounds) break;
+      tile = last + j;
+      k0 = 0;
+      k1 = S;
+    } else {
+      if (u >= u_end) break;
+      tile = last + u / tail;
+      k0 = S + u % tail;
+      k1 = min(nk, k0 + (u_end - u));
       u += k1 - k0;
     }
+    ++r;
+    wide_tile<BM, BN, WM, WN, STAGES, GEMM_ADD_F32>(A, W, C, M, N, K, ldc, tile / n_tiles, tile % n_tiles, k0,
+                                                           k1, k1 - k0 < nk, none, lds);
+    __syncthreads();            // every wave is done with the ring before the next piece refills it
   }
 }
 
 template <int BM, int BN, int WM, int WN, int STAGES>
-hipError_t run_dma_even(hipStream_t s, const f16* A, const GemmW& W, float* C, int M, int N, int K, int ldc,
+hipError_t run_even(hipStream_t s, const f16* A, const GemmW& W, float* C, int M, int N, int K, int ldc,
                         int n_groups) {
   if (K % BK || n_groups <= 0 || n_groups % 8) return hipErrorInvalidValue;
   const int n_tiles = (N + BN - 1) / BN, m_tiles = (M + BM - 1) / BM;
-  gemm_dma_even_kernel<BM, BN, WM, WN, STAGES><<<n_groups, WM * WN * 64, 0, s>>>(A, W, C, M, N, K, ldc, n_tiles,
+  gemm_even_kernel<BM, BN, WM, WN, STAGES><<<n_groups, WM * WN * 64, 0, s>>>(A, W, C, M, N, K, ldc, n_tiles,
                                                                                n_tiles * m_tiles);
   return hipGetLastError();
 }
 
 template <int BM, int BN, int WM, int WN, int STAGES, int MODE>
 hipError_t run_dma(hipStream_t s, const f16* A, const GemmW& W, void* C, int M, int N, int K, int ldc,
-                   int splits, GemmLse lse = GemmLse{nullptr, nullptr, 1.f}) {
+                   int splits) {
   if (K % BK) return hipErrorInvalidValue;
   constexpr int n_out_per_tile = MODE == GEMM_SWIGLU_F16 ? BN / 2 : BN;
   const int n_tiles = (N + n_out_per_tile - 1) / n_out_per_tile, m_tiles = (M + BM - 1) / BM;
@@ -721,7 +989,7 @@ hipError_t run_dma(hipStream_t s, const f16* A, const GemmW& W, void* C, int M, 
   splits = (nk + sps - 1) / sps;
   const int grid = grid_blocks(M, m_tiles, n_tiles, splits);
   gemm_dma_kernel<BM, BN, WM, WN, STAGES, MODE><<<grid, WM * WN * 64, 0, s>>>(
-      A, W, C, M, N, K, ldc, m_tiles, n_tiles, splits, sps, splits > 1 ? 1 : 0, lse);
+      A, W, C, M, N, K, ldc, m_tiles, n_tiles, splits, sps, splits > 1 ? 1 : 0);
   return hipGetLastError();
 }
 
@@ -814,8 +1082,8 @@ hipError_t dispatch(hipStream_t s, int cfg, const f16* A, const GemmW& W, void* 
     case 15: return run_dma<128, 128, 2, 2, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 16: return run_dma<256, 256, 2, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 17: return run_dma<256, 128, 2, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
-    case 18: return run_dma<256, 256, 4, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
-    case 19: return run_dma<256, 256, 2, 4, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
+    case 18: return run_wide<256, 256, 4, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
+    case 19: return run_wide<256, 256, 2, 4, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 20: return run_dma<128, 128, 4, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 21: return run_dma<128, 128, 4, 2, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 22:   // one 32-column panel per wave: no room for a gate/up pair
@@ -827,8 +1095,8 @@ hipError_t dispatch(hipStream_t s, int cfg, const f16* A, const GemmW& W, void* 
     case 24:   // residual adds with the last round of work-groups evened out along K
       if constexpr (MODE == GEMM_ADD_F32) {
         if (evened_192(M, N, K))
-          return run_dma_even<256, 192, 4, 2, 2>(s, A, W, reinterpret_cast<float*>(C), M, N, K, ldc, 256);
-        return run_dma_even<256, 256, 2, 4, 2>(s, A, W, reinterpret_cast<float*>(C), M, N, K, ldc, 256);
+          return run_even<256, 192, 4, 2, 2>(s, A, W, reinterpret_cast<float*>(C), M, N, K, ldc, 256);
+        return run_even<256, 256, 2, 4, 2>(s, A, W, reinterpret_cast<float*>(C), M, N, K, ldc, 256);
       } else return hipErrorInvalidValue;
     case 25:   // 64-column tiles, one 32-column panel per wave (twice the work-groups of 22)
       if constexpr (MODE != GEMM_SWIGLU_F16) return run_dma<32, 64, 1, 2, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
@@ -836,12 +1104,12 @@ hipError_t dispatch(hipStream_t s, int cfg, const f16* A, const GemmW& W, void* 
     // 192-row and 192-column tiles: other shapes of the last round (1,536 columns = 8 x 192).  Gate/up
     // needs whole pairs of 32-column panels in a wave: there every wave takes all six panels.
     case 26:
-      if constexpr (MODE != GEMM_SWIGLU_F16) return run_dma<256, 192, 4, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
-      else return run_dma<256, 192, 8, 1, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
+      if constexpr (MODE != GEMM_SWIGLU_F16) return run_wide<256, 192, 4, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
+      else return run_wide<256, 192, 8, 1, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 27:
-      if constexpr (MODE != GEMM_SWIGLU_F16) return run_dma<128, 192, 4, 2, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
-      else return run_dma<128, 192, 4, 1, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
-    case 28: return run_dma<192, 256, 2, 4, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
+      if constexpr (MODE != GEMM_SWIGLU_F16) return run_wide<128, 192, 4, 2, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
+      else return run_wide<128, 192, 4, 1, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
+    case 28: return run_wide<192, 256, 2, 4, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1022,8 +1290,8 @@ hipError_t launch_gemm_lse(hipStream_t s, const f16* A, GemmW W, int M, int N, i
       !lse.target || !lse.target_z || !(lse.inv_t > 0.f) ||
       (((uintptr_t)A | (uintptr_t)W.ptr[0]) & 15) || ((uintptr_t)part & 7))
     return hipErrorInvalidValue;
-  if (M > 256) return run_dma<256, 256, 2, 4, 2, GEMM_LSE>(s, A, W, part, M, N, K, ld_rows, 1, lse);
-  return run_dma<128, 128, 4, 2, 3, GEMM_LSE>(s, A, W, part, M, N, K, ld_rows, 1, lse);
+  if (M > 256) return run_wide<256, 256, 2, 4, 2, GEMM_LSE>(s, A, W, part, M, N, K, ld_rows, 1, lse);
+  return run_wide<128, 128, 4, 2, 3, GEMM_LSE>(s, A, W, part, M, N, K, ld_rows, 1, lse);
 }
 
 hipError_t launch_gemm(hipStream_t s, const f16* A, GemmW W, void* C, int M, int N, int K, int ldc,
