@@ -572,28 +572,37 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_dma_kernel(const f16* __res
 // Measured, one card, 1.5B shape: gate/up of 8,192 rows 440 -> 387 us (1,165 TFLOP/s), of 2,048 127 -> 117; down of
 // 8,192 222 -> 209, of 6,768 207 -> 193; QKV of 6,768 54.4 -> 51.6.  128 x 128 tiles gain nothing (their runs are short) and
 // stay with dma_tile.
+constexpr int WIDE_GROUP = 1024;        // 8 tile rows x 128 B: these reads have no bank conflicts without a skew
 template <int TM, int TN>
 struct Wide {
   f32x4 acc[TM][TN];
   struct Frags { f16x8 a[TM], b[TN]; };
-  static constexpr int BLOCKS = (TM / 2) * (TN / 2), READS = TM + TN;
-  // block z of the 2 x 2 walk -> its first row and column
-  static constexpr int block_i(int z) { return z / (TN / 2) * 2; }
-  static constexpr int block_j(int z) {
-    const int j = z % (TN / 2);
-    return ((z / (TN / 2)) & 1) ? (TN / 2 - 1 - j) * 2 : j * 2;
+  static constexpr int MFMAS = TM * TN, READS = TM + TN;
+  // MFMA z of the walk -> its row and column: bands of two rows, column by column, there and back
+  static constexpr int row(int z) {
+    const int band = z / (2 * TN), h = TM - 2 * band < 2 ? 1 : 2, q = z - band * 2 * TN;
+    return h == 1 ? 2 * band : 2 * band + ((q & 1) ^ ((q >> 1) & 1));
+  }
+  static constexpr int col(int z) {
+    const int band = z / (2 * TN), h = TM - 2 * band < 2 ? 1 : 2, c = (z - band * 2 * TN) / h;
+    return band & 1 ? TN - 1 - c : c;
   }
 };
 
-// Row of the W tile that LDS row `b` holds.  Gate/up: of 64 rows the first 32 are gate rows, then come the up
-// rows of the same features, each as two MFMA tiles of 16 whose rows 4g + v are the features 8g + v and
-// 8g + 4 + v: a lane of group g ends up with eight neighbouring features.
-template <int MODE>
-__device__ __forceinline__ int wide_w_row(int b) {
-  if (MODE != GEMM_SWIGLU_F16) return b;
+// Gate/up: which row of the weights LDS row `b` of a W tile holds, as feature of the tile and gate (0) or up (1).
+//  * waves of whole 64-row groups (TN % 4 == 0): 32 gate rows, then the up rows of the same features, each as two MFMA
+//    tiles whose rows 4g + v are the features 8g + v and 8g + 4 + v: a lane of group g ends up with eight
+//    neighbouring features of a row;
+//  * others: every MFMA tile of 16 rows is 8 gate rows, then the up rows of the same features; lanes trade
+//    halves afterwards, and a tile can be any multiple of 8 features wide.
+template <int TN>
+__device__ __forceinline__ int wide_feature(int b) {
+  if (TN % 4) return (b >> 4) * 8 + (b & 7);
   const int t = (b >> 4) & 1, r = b & 15;
-  return (b & ~31) + 8 * (r >> 2) + 4 * t + (r & 3);
+  return (b >> 6) * 32 + 8 * (r >> 2) + 4 * t + (r & 3);
 }
+template <int TN>
+__device__ __forceinline__ int wide_is_up(int b) { return TN % 4 ? (b >> 3) & 1 : (b >> 5) & 1; }
 
 template <int BM, int BN, int WM, int WN, int MODE, bool FULL>
 __device__ __forceinline__ void store_wide_part(const f32x4 (&acc)[BM / WM / 16][BN / WN / 16], void* __restrict__ Cv,
@@ -602,7 +611,38 @@ __device__ __forceinline__ void store_wide_part(const f32x4 (&acc)[BM / WM / 16]
   constexpr int TM = BM / WM / 16, TN = BN / WN / 16;
   const int m_wave = tile_m * BM + wm * (BM / WM);
   if constexpr (MODE == GEMM_SWIGLU_F16) {
-    static_assert(TN % 4 == 0, "gate and up of a feature in one wave");
+    if constexpr (TN % 4 != 0) {
+      // Gate in the lower half of the lanes, up in the upper: of two tiles, the lower lanes take the first and give their
+      // part of the second for it, so that every lane holds four neighbouring features whole (a last odd tile: the
+      // lower lanes do).
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; j += 2) {
+          const bool two = j + 1 < TN;
+          const int f = tile_n * (BN / 2) + (wn * TN + j + (two ? fh >> 1 : 0)) * 8 + (fh & 1) * 4, m = m_wave + i * 16 + fr;
+          f16* p = reinterpret_cast<f16*>(Cv) + (int64_t)m * ldc + f;
+          f16x4 y;
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const float first = acc[i][j][v], second = acc[i][two ? j + 1 : j][v];
+            const auto gu = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, first),
+                                                             __builtin_bit_cast(uint32_t, second), false, false);
+            const uint32_t gate = gu[0], up = gu[1];
+            y[v] = f2h_sat(silu_f(__builtin_bit_cast(float, gate)) * __builtin_bit_cast(float, up));
+          }
+          if (two || fh < 2) {
+            if (FULL) {
+              *reinterpret_cast<f16x4*>(p) = y;
+            } else if (m < M) {
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                if (f + e < N) p[e] = y[e];
+            }
+          }
+        }
+      return;
+    } else {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -623,6 +663,7 @@ __device__ __forceinline__ void store_wide_part(const f32x4 (&acc)[BM / WM / 16]
             if (f0 + fh * 8 + e < N) p[e] = y[e];
         }
       }
+    }
   } else {
     const int n_wave = tile_n * BN + wn * (BN / WN);
     float* Cw = reinterpret_cast<float*>(Cv) + (int64_t)m_wave * ldc + n_wave;
@@ -732,9 +773,10 @@ __device__ __forceinline__ void wide_tile(const f16* __restrict__ A, const GemmW
   constexpr int NW = WM * WN;
   constexpr int TM = BM / WM / 16, TN = BN / WN / 16;
   constexpr int GA = BM / 8, GB = BN / 8;              // row groups per slab
-  constexpr int LPS = (GA + GB) / NW;                  // load instructions per wave per slab
-  static_assert(GA % NW == 0 && GB % NW == 0 && TM % 2 == 0 && TN % 2 == 0, "tile does not divide over the waves");
-  constexpr int STAGE_BYTES = (GA + GB) * GROUP_BYTES;
+  constexpr int LPS = (GA + GB + NW - 1) / NW;         // load instructions per slab of the first waves,
+  constexpr int SHORT = (GA + GB) % NW;                // of which waves >= SHORT > 0 have one less
+  static_assert(BM % (WM * 16) == 0 && BN % (WN * 16) == 0, "tile does not divide over the waves");
+  constexpr int STAGE_BYTES = (GA + GB) * WIDE_GROUP;
   typedef Wide<TM, TN> WideT;
   constexpr bool TRANS = MODE == GEMM_SWIGLU_F16 || MODE == GEMM_LSE;
 
@@ -742,33 +784,49 @@ __device__ __forceinline__ void wide_tile(const f16* __restrict__ A, const GemmW
   const int wm = wave / WN, wn = wave % WN;
   const int m0 = tile_m * BM;
 
-  const auto a_rsrc = buffer_rsrc(A + (int64_t)m0 * K, (uint32_t)min(M - m0, BM) * (uint32_t)K * 2u);
-  __amdgpu_buffer_rsrc_t b_rsrc[GB / NW];
+  // Groups of 8 rows are dealt to the waves in turn, A's first.  A is based at the tile's first row, a group of W at its
+  // own first row (its rows lie in one segment).
+  __amdgpu_buffer_rsrc_t rsrc[LPS];
   int src[LPS], dst_off[LPS];
   {
     const int rin = lane >> 3, chunk = (lane & 7) ^ rin;
 #pragma unroll
     for (int i = 0; i < LPS; ++i) {
-      const bool is_a = i < GA / NW;
-      const int gi = is_a ? wave * (GA / NW) + i : wave * (GB / NW) + (i - GA / NW);
-      if (is_a) {
+      const int gi = min(i * NW + wave, GA + GB - 1);
+      dst_off[i] = gi * WIDE_GROUP;
+      if (gi < GA) {
+        rsrc[i] = buffer_rsrc(A + (int64_t)m0 * K, (uint32_t)min(M - m0, BM) * (uint32_t)K * 2u);
         src[i] = (min(gi * 8 + rin, M - 1 - m0) * K + chunk * 8) * 2;
-        dst_off[i] = gi * GROUP_BYTES;
       } else {
-        // the group's rows start at row b0 of the tile (gate/up: two runs of four, eight rows apart, of one
-        // segment); rows outside the matrix are replaced by one inside: their products are never stored
-        const int b0 = wide_w_row<MODE>(gi * 8), down = wide_w_row<MODE>(gi * 8 + rin) - b0;
-        const int left = w_rows_left<BN, MODE>(tile_n, b0, N);
-        const f16* p = left > 0 ? w_row_ptr<BN, MODE>(W, tile_n, b0, N, K) : W.ptr[0];
-        b_rsrc[i - GA / NW] = buffer_rsrc(p, (MODE == GEMM_SWIGLU_F16 ? 12u : 8u) * (uint32_t)K * 2u);
-        src[i] = ((down < left ? down : 0) * K + chunk * 8) * 2;
-        dst_off[i] = (GA + gi) * GROUP_BYTES;
+        // rows outside the matrix are replaced by one inside: their products are never stored
+        const int b0 = (gi - GA) * 8;
+        int row0, down, span = 8;
+        const f16* p;
+        if (MODE == GEMM_SWIGLU_F16) {
+          row0 = tile_n * (BN / 2) + wide_feature<TN>(b0);
+          down = wide_feature<TN>(b0 + rin) - wide_feature<TN>(b0);
+          span = TN % 4 ? 8 : 12;
+          p = W.ptr[wide_is_up<TN>(b0)];
+          if (row0 < N) p += (int64_t)row0 * K;
+        } else {
+          row0 = tile_n * BN + b0;
+          down = rin;
+          p = row0 < N ? w_row_ptr<BN, MODE>(W, tile_n, b0, N, K) : W.ptr[0];
+        }
+        rsrc[i] = buffer_rsrc(p, (uint32_t)span * (uint32_t)K * 2u);
+        src[i] = ((down < N - row0 ? down : 0) * K + chunk * 8) * 2;
       }
     }
   }
   auto issue1 = [&](int stage, int k0, int i) {
-    dma16(i < GA / NW ? a_rsrc : b_rsrc[i < GA / NW ? 0 : i - GA / NW], src[i], k0 * 2,
-          lds + stage * STAGE_BYTES + dst_off[i]);
+    if (SHORT == 0 || i < LPS - 1 || wave < SHORT)      // wave-uniform
+      dma16(rsrc[i], src[i], k0 * 2, lds + stage * STAGE_BYTES + dst_off[i]);
+  };
+  // waits until at most `slabs` slabs of this wave's loads are in flight
+  auto wait_slabs = [&](auto slabs) {
+    constexpr int S = decltype(slabs)::value;
+    if (SHORT == 0 || S == 0 || wave < SHORT) wait_vmcnt(S * LPS);
+    else wait_vmcnt(S * (LPS - 1));
   };
 
   WideT t;
@@ -785,17 +843,17 @@ __device__ __forceinline__ void wide_tile(const f16* __restrict__ A, const GemmW
   for (int kk = 0; kk < 2; ++kk) {
     const int ko = ((kk * 4 + fh) ^ (fr & 7)) << 4;
     const int ra = wm * (BM / WM) + fr, rb = wn * (BN / WN) + fr;
-    a_at[kk] = (ra >> 3) * GROUP_BYTES + (ra & 7) * 128 + ko;
-    b_at[kk] = (GA + (rb >> 3)) * GROUP_BYTES + (rb & 7) * 128 + ko;
+    a_at[kk] = (ra >> 3) * WIDE_GROUP + (ra & 7) * 128 + ko;
+    b_at[kk] = (GA + (rb >> 3)) * WIDE_GROUP + (rb & 7) * 128 + ko;
   }
   typename WideT::Frags f0, f1;
-  // the fragment reads of a K-step in the order in which the walk needs them
+  // the fragment reads of a K-step in the order in which the walk needs them: a0 a1 | b0 b1 .. | a2 a3 ..
+  constexpr int A0 = TM < 2 ? TM : 2;
   auto read1 = [&](typename WideT::Frags& f, const char* base, int kk, int r) {
-    // a0 a1 b0 b1 | b2 .. | a2 ..
-    const bool is_a = r < 2 || r >= 2 + TN;
-    const int x = r < 2 ? r : (r < 2 + TN ? r - 2 : r - TN);
-    if (is_a) f.a[x] = *reinterpret_cast<const f16x8*>(base + a_at[kk] + x * 2 * GROUP_BYTES);
-    else f.b[x] = *reinterpret_cast<const f16x8*>(base + b_at[kk] + x * 2 * GROUP_BYTES);
+    const bool is_a = r < A0 || r >= A0 + TN;
+    const int x = r < A0 ? r : (r < A0 + TN ? r - A0 : r - TN);
+    if (is_a) f.a[x] = *reinterpret_cast<const f16x8*>(base + a_at[kk] + x * 2 * WIDE_GROUP);
+    else f.b[x] = *reinterpret_cast<const f16x8*>(base + b_at[kk] + x * 2 * WIDE_GROUP);
   };
   auto mma1 = [&](const typename WideT::Frags& f, int i, int j) {
     t.acc[i][j] = TRANS ? __builtin_amdgcn_mfma_f32_16x16x32_f16(f.b[j], f.a[i], t.acc[i][j], 0, 0, 0)
@@ -808,7 +866,7 @@ __device__ __forceinline__ void wide_tile(const f16* __restrict__ A, const GemmW
   for (int s = 0; s < STAGES; ++s)
 #pragma unroll
     for (int i = 0; i < LPS; ++i) issue1(s, min((kt0 + s) * BK, k_last), i);
-  wait_vmcnt((STAGES - 1) * LPS);
+  wait_slabs(std::integral_constant<int, STAGES - 1>{});
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -816,50 +874,43 @@ __device__ __forceinline__ void wide_tile(const f16* __restrict__ A, const GemmW
   int cur = 0, kt = kt0;
   const std::true_type yes{};
   const std::false_type no{};
-  // One slab: 2 B blocks of four MFMAs, everything else placed between them in a fixed order: RPB fragment reads
-  // a block from the start of a K-step on, DPB loads a block from the second K-step on.  One barrier, between the
-  // K-steps: every wave has its last fragments of the stage (which the loads of slab kt + STAGES then refill), and
-  // slab kt + 1 has landed for every wave.  LOAD: slab kt + STAGES exists; NEXT: slab kt + 1 does.
-  // Tried for gate/up of 8,192 rows, 365 us in a long run: loads two, four or eight a block 366, 373, 385; a barrier
+  // One slab: two K-steps of P pairs of MFMAs, everything else placed between them in a fixed order: fragment reads from
+  // the start of a K-step on, loads spread over the second.  One barrier, between the K-steps: every
+  // wave has its last fragments of the stage (which the loads of slab kt + STAGES then refill), and slab
+  // kt + 1 has landed for every wave.  LOAD: slab kt + STAGES exists; NEXT: slab kt + 1 does.
+  // Tried for gate/up of 8,192 rows, 365 us in a long run: loads two, four or eight at a time 366, 373, 385; a barrier
   // each for freeing and landing, half a K-step apart, 382; a ring of four or five stages of 32 along K, whose loads
   // fetch half lines, 396 and 403.
-  constexpr int B = WideT::BLOCKS, READS_B = (WideT::READS + B - 1) / B;
-  constexpr int RPB = READS_B > 2 ? READS_B : 2, DPB = (LPS + B - 1) / B;
+  constexpr int P = (WideT::MFMAS + 1) / 2, RPP = (WideT::READS * 4 + P * 3 - 1) / (P * 3);
   auto slab = [&](auto load, auto next) {
     constexpr bool LOAD = decltype(load)::value, NEXT = decltype(next)::value;
     const int nxt = cur + 1 == STAGES ? 0 : cur + 1, k_load = min((kt + STAGES) * BK, k_last);
     const char *base = lds + cur * STAGE_BYTES, *base_next = lds + nxt * STAGE_BYTES;
     __builtin_amdgcn_sched_barrier(0);
-    int dn = 0, rn = 0;
 #pragma unroll
-    for (int z = 0; z < 2 * B; ++z) {
-      const typename WideT::Frags& f = z < B ? f0 : f1;
-      const int i = WideT::block_i(z % B), j = WideT::block_j(z % B);
-      if (NEXT && z == B) {
+    for (int z = 0; z < 2 * P; ++z) {
+      const typename WideT::Frags& f = z < P ? f0 : f1;
+      const int q = z < P ? z : z - P;
+      if (NEXT && z == P) {
         // a plain barrier: a fence would drain every outstanding load
         wait_lgkmcnt0();
-        wait_vmcnt((STAGES - 2) * LPS);
+        wait_slabs(std::integral_constant<int, STAGES - 2>{});
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
       }
-      mma1(f, i, j);
-      mma1(f, i, j + 1);
+      mma1(f, WideT::row(2 * q), WideT::col(2 * q));
+      if (2 * q + 1 < WideT::MFMAS) mma1(f, WideT::row(2 * q + 1), WideT::col(2 * q + 1));
+      if (LOAD && z >= P) {
 #pragma unroll
-      for (int r = z * RPB; r < (z + 1) * RPB; ++r)
-        if (z < B && r < WideT::READS) read1(f1, base, 1, r);
-      if (LOAD && z >= B) {
-#pragma unroll
-        for (int d = 0; d < DPB; ++d)
-          if (dn < LPS) issue1(cur, k_load, dn++);
+        for (int d = 0; d < LPS; ++d)
+          if (d * P / LPS == q) issue1(cur, k_load, d);
       }
-      if (NEXT && z >= B) {
 #pragma unroll
-        for (int r = 0; r < RPB; ++r)
-          if (rn < WideT::READS) read1(f0, base_next, 0, rn++);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      mma1(f, i + 1, j + 1);
-      mma1(f, i + 1, j);
+      for (int r = q * RPP; r < (q + 1) * RPP; ++r)
+        if (r < WideT::READS) {
+          if (z < P) read1(f1, base, 1, r);
+          else if (NEXT) read1(f0, base_next, 0, r);
+        }
       __builtin_amdgcn_sched_barrier(0);
     }
     cur = nxt;
@@ -876,8 +927,9 @@ __device__ __forceinline__ void wide_tile(const f16* __restrict__ A, const GemmW
                                    lse);
   } else {
     constexpr int NC = MODE == GEMM_SWIGLU_F16 ? BN / 2 : BN;
-    // gate/up: a lane's eight features go out as 16 bytes where rows start on 16 bytes
-    const bool whole = MODE != GEMM_SWIGLU_F16 || ((ldc & 7) == 0 && ((uintptr_t)Cv & 15) == 0);
+    // gate/up: a lane's eight (four) features go out as 16 (8) bytes where rows start on 16 (8) bytes
+    const bool whole = MODE != GEMM_SWIGLU_F16 ||
+                       (TN % 4 ? ((ldc & 3) == 0 && ((uintptr_t)Cv & 7) == 0) : ((ldc & 7) == 0 && ((uintptr_t)Cv & 15) == 0));
     if (whole && (tile_m + 1) * BM <= M && (tile_n + 1) * NC <= N)
       store_wide_part<BM, BN, WM, WN, MODE, true>(t.acc, Cv, M, N, ldc, tile_m, tile_n, wm, wn, fr, fh, atomic);
     else
@@ -892,7 +944,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_wide_kernel(const f16* __re
                                                                  void* __restrict__ Cv, int M, int N, int K,
                                                                  int ldc, int m_tiles, int n_tiles, int splits,
                                                                  int slabs_per_split, int atomic, GemmLse lse) {
-  __shared__ __attribute__((aligned(16))) char lds[STAGES * (BM / 8 + BN / 8) * GROUP_BYTES];
+  __shared__ __attribute__((aligned(16))) char lds[STAGES * (BM / 8 + BN / 8) * WIDE_GROUP];
   int tile_m, tile_n, split;
   if (!tile_of_block(blockIdx.x, M, m_tiles, n_tiles, splits, tile_m, tile_n, split)) return;
   const int kt0 = split * slabs_per_split;
@@ -930,7 +982,7 @@ template <int BM, int BN, int WM, int WN, int STAGES>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_even_kernel(const f16* __restrict__ A, GemmW W,
                                                                      float* __restrict__ C, int M, int N, int K,
                                                                      int ldc, int n_tiles, int tiles) {
-  __shared__ __attribute__((aligned(16))) char lds[STAGES * (BM / 8 + BN / 8) * GROUP_BYTES];
+  __shared__ __attribute__((aligned(16))) char lds[STAGES * (BM / 8 + BN / 8) * WIDE_GROUP];
   const int nk = K / BK;
   const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3, G = gridDim.x >> 3;
   const int t0 = (int)((int64_t)tiles * xcd / 8), t1 = (int)((int64_t)tiles * (xcd + 1) / 8);
@@ -1059,6 +1111,61 @@ static bool evened_192(int M, int N, int K) {
          prefill_us(TILE_256x192, M, N, K, GEMM_ADD_F32, 1) <= evened_us(M, N, K);
 }
 
+// Gate/up, and the narrow products of a decode step.  A launch of one round of work-groups lives on what a
+// compute unit takes in: a stream of weights that come from memory stays at about 45 GB/s per compute unit, however
+// many bytes are in flight (32, 64 or 128 KB: the same), and rows of A that come from L2 queue behind them, so
+// that (rows + columns) of a tile times 2 K bytes at 41 GB/s is its time, where all weights at 5.9 TB/s do not take longer.
+// So tiles are chosen whose work-groups come as close to 256 as the width allows (8,960 features: 224 of 40,
+// 125 x 2 of 72; 18,944: 237 of 80), with no more rows than the launch has.  Measured against tiles of
+// 64 features, 1.5B shape: 15.1 -> 13.4 us at 24 rows, 18.9 -> 15.4 at 64, 20.4 -> 18.4 at 88, 34.7 -> 24.8 at 256,
+// 32.8 -> 28.8 at 301; 7B shape: 58.5 -> 48.7 at 24, 66 -> 51 at 64, 80 -> 59.5 at 128, 133 -> 95 at 256.  Over 27 + 17
+// (rows, shape) the choice is 0.4 % from the best of 14 tiles on average (gate/up of 512 rows: 9 %).
+struct StreamTile { int cfg, bm, bn; };
+constexpr StreamTile stream_tiles[] = {{12, 32, 80},   {10, 64, 80},   {29, 96, 80},   {21, 128, 80},  {20, 128, 144},
+                                       {30, 64, 160},  {31, 96, 160},  {32, 128, 160}, {33, 160, 160}, {34, 192, 160}};
+static float stream_us(const StreamTile& t, int M, int N, int K) {
+  const float load = (float)((2 * N + t.bn - 1) / t.bn) * (float)((M + t.bm - 1) / t.bm) / 256.0f;
+  const float rounds = std::max(1.0f, 0.5f * (load + ceilf(load)));      // a last round that is partly filled
+  return 4.5f + std::max(rounds * (float)(t.bm + t.bn) * (float)K * (2e-3f / 41.0f), (float)N * (float)K * (4e-6f / 5.9f));
+}
+// The tiles of a prefill pass by prefill_us, fitted to the same sweep.
+constexpr PrefillTile gateup_tiles[] = {
+    {19, 256, 256, 1, 9.05f, 1.29f, 1.56f, 0.f, 0.f}, {28, 192, 256, 1, 8.13f, 1.24f, 1.28f, 0.f, 0.f},
+    {26, 256, 192, 1, 8.44f, 1.18f, 1.30f, 0.f, 0.f}, {27, 128, 192, 1, 8.22f, 0.64f, 0.71f, 0.f, 0.f},
+};
+static int gateup_choose(int M, int N, int K) {
+  int cfg = 0;
+  float best = 1e30f;
+  for (const StreamTile& t : stream_tiles) {
+    const float us = stream_us(t, M, N, K);
+    if (us < best) { best = us; cfg = t.cfg; }
+  }
+  if (M > DECODE_ROWS)
+    for (const PrefillTile& t : gateup_tiles) {
+      const float us = prefill_us(t, M, N, K, GEMM_SWIGLU_F16, 1);
+      if (us < best) { best = us; cfg = t.cfg; }
+    }
+  return cfg;
+}
+// QKV, O and down projection at up to 256 rows: tile and K split by the same two streams (added as fourth powers: neither
+// hides the other wholly) and the adds of all splits, fitted to a sweep of 6 products x 6 row counts.  64 x 96
+// for 64 x 128 tiles: down of 88 rows 13.5 -> 11.9 us, of 256 rows 22.8 -> 20.6, O of the 7B shape at 128 rows 15.5 -> 13.6.
+struct NarrowTile {
+  int cfg, bm, bn;
+  float fixed, cu_gbs, add;            // us, GB/s per compute unit, us per million elements added
+};
+constexpr NarrowTile narrow_tiles[] = {{22, 32, 128, 4.27f, 67.3f, 2.48f}, {23, 64, 96, 4.28f, 70.7f, 2.12f},
+                                       {35, 128, 96, 4.90f, 73.7f, 3.11f}, {21, 128, 128, 3.73f, 66.2f, 2.85f}};
+static float narrow_us(const NarrowTile& t, int M, int N, int K, int splits) {
+  const int nk = K / BK, sps = (nk + splits - 1) / splits, parts = (nk + sps - 1) / sps;
+  const float load = (float)((N + t.bn - 1) / t.bn) * (float)((M + t.bm - 1) / t.bm) * (float)parts / 256.0f;
+  const float rounds = std::max(1.0f, 0.5f * (load + ceilf(load)));
+  const float cu = rounds * (float)sps * (float)(t.bm + t.bn) * (0.128f / t.cu_gbs);
+  const float mem = (float)N * (float)K * (2e-6f / 7.0f);
+  return t.fixed + sqrtf(sqrtf(cu * cu * cu * cu + mem * mem * mem * mem)) +
+         t.add * (float)M * (float)N * 1e-6f * (parts > 1 ? (float)parts : 0.4f);
+}
+
 template <int MODE>
 hipError_t dispatch(hipStream_t s, int cfg, const f16* A, const GemmW& W, void* C, int M, int N, int K,
                     int ldc, int splits) {
@@ -1074,9 +1181,13 @@ hipError_t dispatch(hipStream_t s, int cfg, const f16* A, const GemmW& W, void* 
     case 7: return run_dma<128, 128, 2, 2, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 8: return run_dma<128, 128, 2, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 9: return run_dma<256, 128, 4, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
-    case 10: return run_dma<64, 128, 1, 2, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
+    case 10:
+      if constexpr (MODE == GEMM_SWIGLU_F16) return run_wide<64, 80, 4, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
+      else return run_dma<64, 128, 1, 2, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 11: return run_dma<64, 128, 1, 2, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
-    case 12: return run_dma<32, 128, 1, 2, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
+    case 12:
+      if constexpr (MODE == GEMM_SWIGLU_F16) return run_wide<32, 80, 2, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
+      else return run_dma<32, 128, 1, 2, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 13: return run_dma<128, 64, 2, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 14: return run_dma<256, 64, 4, 1, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 15: return run_dma<128, 128, 2, 2, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
@@ -1084,13 +1195,17 @@ hipError_t dispatch(hipStream_t s, int cfg, const f16* A, const GemmW& W, void* 
     case 17: return run_dma<256, 128, 2, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 18: return run_wide<256, 256, 4, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 19: return run_wide<256, 256, 2, 4, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
-    case 20: return run_dma<128, 128, 4, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
-    case 21: return run_dma<128, 128, 4, 2, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
+    case 20:
+      if constexpr (MODE == GEMM_SWIGLU_F16) return run_wide<128, 144, 8, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
+      else return run_dma<128, 128, 4, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
+    case 21:
+      if constexpr (MODE == GEMM_SWIGLU_F16) return run_wide<128, 80, 8, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
+      else return run_dma<128, 128, 4, 2, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 22:   // one 32-column panel per wave: no room for a gate/up pair
       if constexpr (MODE != GEMM_SWIGLU_F16) return run_dma<32, 128, 1, 4, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
       else return hipErrorInvalidValue;
-    case 23:
-      if constexpr (MODE != GEMM_SWIGLU_F16) return run_dma<64, 128, 2, 4, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
+    case 23:   // narrow products of a decode step
+      if constexpr (MODE != GEMM_SWIGLU_F16) return run_wide<64, 96, 2, 2, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
       else return hipErrorInvalidValue;
     case 24:   // residual adds with the last round of work-groups evened out along K
       if constexpr (MODE == GEMM_ADD_F32) {
@@ -1110,13 +1225,21 @@ hipError_t dispatch(hipStream_t s, int cfg, const f16* A, const GemmW& W, void* 
       if constexpr (MODE != GEMM_SWIGLU_F16) return run_wide<128, 192, 4, 2, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
       else return run_wide<128, 192, 4, 1, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 28: return run_wide<192, 256, 2, 4, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
+    // see StreamTile
+    case 29: return run_wide<96, 80, 6, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
+    case 30: return run_wide<64, 160, 4, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
+    case 31: return run_wide<96, 160, 6, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
+    case 32: return run_wide<128, 160, 4, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
+    case 33: return run_wide<160, 160, 5, 1, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
+    case 34: return run_wide<192, 160, 6, 1, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
+    case 35: return run_wide<128, 96, 4, 2, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
     default: return hipErrorInvalidValue;
   }
 }
 
 }  // namespace
 
-int gemm_num_configs() { return 29; }
+int gemm_num_configs() { return 36; }
 
 // Tile configuration and K split for a product of this shape: rules read off
 // sweeps over every configuration on the MI355X at the decoder's shapes
@@ -1152,9 +1275,8 @@ static void prefill_choose(int M, int N, int K, GemmMode mode, int* cfg, int* sp
   const int nk = K / BK;
   float best = 1e30f;
   for (const PrefillTile& t : prefill_tiles) {
-    if (mode == GEMM_SWIGLU_F16 && (t.cfg == 26 || t.cfg == 27)) continue;
     for (int sp : steps) {
-      if (sp > 1 && (mode == GEMM_SWIGLU_F16 || sp > max_splits() || 3 * sp > nk)) break;
+      if (sp > 1 && (sp > max_splits() || 3 * sp > nk)) break;
       const float us = prefill_us(t, M, N, K, mode, sp);
       if (us < best) { best = us; *cfg = t.cfg; *splits = sp; }
     }
@@ -1170,68 +1292,36 @@ static void prefill_choose(int M, int N, int K, GemmMode mode, int* cfg, int* sp
 }
 
 void gemm_choose(int M, int N, int K, GemmMode mode, int* cfg, int* splits) {
-  const bool dma_ok = (K % BK) == 0;
-  const int n_tiles = mode == GEMM_SWIGLU_F16 ? (N + 63) / 64 : (N + 127) / 128;
-  const int nk = (K + BK - 1) / BK;
-  int c, bm;
-  if (!dma_ok) {                       // register-staged path (ragged K)
-    if (M <= 32) { c = 4; bm = 32; }
-    else if (M <= 64) { c = 2; bm = 64; }
-    else { c = 0; bm = 128; }
-  } else if (M > 256) {                // prefill: MFMA-bound, large tiles
+  const bool wide_out = (N + 127) / 128 >= 100;
+  *splits = 1;
+  if (K % BK) {                        // register-staged path (ragged K)
+    *cfg = M <= 32 ? 4 : (M <= 64 ? 2 : 0);
+    const int bm = M <= 32 ? 32 : (M <= 64 ? 64 : 128);
+    if (mode != GEMM_SWIGLU_F16 && M <= DECODE_ROWS) *splits = split_for(M, bm, (N + 127) / 128, (K + BK - 1) / BK);
+  } else if (mode == GEMM_SWIGLU_F16) {
+    *cfg = gateup_choose(M, N, K);
+  } else if (M > DECODE_ROWS) {        // prefill: MFMA-bound, large tiles
     prefill_choose(M, N, K, mode, cfg, splits);
-    return;
-  } else if (n_tiles >= 100) {         // wide outputs: one work-group per column panel
-    if (M <= 32) { c = 12; bm = 32; }
-    else if (M <= 64) { c = 10; bm = 64; }
-    else if (M <= 128) { c = 21; bm = 128; }
-    else { c = 20; bm = 128; }         // two 128-row work-groups per CU beat one 256-row tile
-    if (mode != GEMM_SWIGLU_F16 && c == 12) c = 22;       // output projection: one more wave pair
-    if (mode != GEMM_SWIGLU_F16 && c == 10) c = 23;
-    if (mode != GEMM_SWIGLU_F16 && c == 20) { c = 19; bm = 256; }   // output projection above 128 rows
-    // gate/up with a long K (7B shape, 56 slabs): the register-staged tiles come out 8-10 % ahead
-    if (mode == GEMM_SWIGLU_F16 && K >= 3072 && c == 12) c = 4;
-    if (mode == GEMM_SWIGLU_F16 && K >= 3072 && c == 10) c = 6;
-    if (mode == GEMM_SWIGLU_F16 && K >= 3072 && c == 21) c = 20;
-  } else if (mode == GEMM_SWIGLU_F16) { // narrow gate/up (small models): no K split
-    if (M <= 32) { c = 12; bm = 32; }
-    else if (M <= 64) { c = 10; bm = 64; }
-    else { c = 21; bm = 128; }
+  } else if (wide_out) {
+    // output projection: one row tile where the rows fit one (152k columns, 160 rows: 135 us in tiles of 160 x 160,
+    // 155 in 256 x 256)
+    *cfg = M <= 32 ? 22 : (M <= 64 ? 30 : (M <= 96 ? 31 : (M <= 128 ? 21 : (M <= 160 ? 33 : (M <= 192 ? 34 : 19)))));
   } else if (mode == GEMM_ADD_F32 && M <= 32 && K >= 4096 && N <= 2048) {
     // down projection at few rows: 64-column tiles, 8 splits = twice the work-groups of the
     // 128-column tile at 12 splits (8.1 / 8.9 us against 8.7 / 9.8 at 16 / 32 rows of the 1.5B shape)
     *cfg = 25;
     *splits = std::min(8, max_splits());
-    return;
   } else {
-    // Narrow outputs (QKV, O, down): row tiles of 32 / 64 / 128 with a K split.  Every
-    // (tile height, split) with the split no larger than what keeps each XCD at one round
-    // of work-groups is priced in microseconds -- a fixed part, the K slabs one work-group
-    // walks, and the atomic adds of all splits -- with constants fitted to the sweeps at
-    // the 1.5B and 7B shapes; the cheapest wins.
-    static const int cand_cfg[3] = {22, 23, 21}, cand_bm[3] = {32, 64, 128};
-    static const float slab_us[3] = {0.38f, 0.55f, 0.75f}, fixed_us[3] = {2.f, 2.f, 3.f};
-    const float atomic_us = 3.3e-6f * (float)M * (float)N;        // per split
-    static const int steps[] = {12, 8, 6, 4, 3, 2, 1};
+    static const int steps[] = {1, 2, 3, 4, 6, 8, 12};
     float best = 1e30f;
-    c = 22; bm = 32;
-    int best_sp = 1;
-    for (int k = 0; k < 3; ++k) {
-      const int sp_max = split_for(M, cand_bm[k], n_tiles, nk);
-      for (int sp_k : steps) {
-        if (sp_k > sp_max) continue;
-        const float cost = fixed_us[k] + (float)((nk + sp_k - 1) / sp_k) * slab_us[k] + atomic_us * (float)sp_k;
-        if (cost < best) { best = cost; c = cand_cfg[k]; bm = cand_bm[k]; best_sp = sp_k; }
+    *cfg = 22;
+    for (const NarrowTile& t : narrow_tiles)
+      for (int sp : steps) {
+        if ((sp > 1 && (sp > max_splits() || 3 * sp > K / BK)) || t.bm > 2 * std::max(M, 32)) continue;
+        const float us = narrow_us(t, M, N, K, sp);
+        if (us < best) { best = us; *cfg = t.cfg; *splits = sp; }
       }
-    }
-    *cfg = c;
-    *splits = best_sp;
-    return;
   }
-  int sp = 1;
-  if (mode != GEMM_SWIGLU_F16 && M <= 256) sp = split_for(M, bm, n_tiles, nk);
-  *cfg = c;
-  *splits = sp;
 }
 
 __global__ __launch_bounds__(256) void clear_rows_kernel(float* __restrict__ C, int N, int ldc) {

@@ -403,6 +403,27 @@ def test_tile_choice_for_the_decoder_shapes(L):
     assert L.areal_op_gemm_choose(8, 8, 8, 3, C.byref(c), C.byref(s)) != 0
 
 
+def test_gate_up_tiles_by_rows_and_width(L):
+    """Gate/up: the tile with the least to take in per compute unit, no taller than the launch needs; whole
+    sums, so never a K split.  Narrow products never take a tile of more than twice the rows (of 32 at least)."""
+    import ctypes as C
+
+    def choose(M, N, K, mode):
+        c, s = C.c_int32(), C.c_int32()
+        assert L.areal_op_gemm_choose(M, N, K, mode, C.byref(c), C.byref(s)) == 0
+        return c.value, s.value
+
+    rows = (1, 32, 33, 64, 65, 96, 97, 128, 256, 257, 320, 321, 384)
+    assert [choose(M, 8960, 1536, 2)[0] for M in rows] == [12, 12, 10, 10, 29, 29, 21, 21, 20, 33, 33, 34, 34]
+    assert [choose(M, 18944, 3584, 2)[0] for M in rows[:9]] == [12, 12, 30, 30, 31, 31, 32, 32, 32]
+    assert all(choose(M, N, 1536, 2)[1] == 1 for M in rows for N in (344, 8960))
+    height = {22: 32, 23: 64, 25: 32, 35: 128, 21: 128}
+    for N, K, mode in ((2048, 1536, 0), (1536, 1536, 1), (1536, 8960, 1), (3584, 18944, 1)):
+        for M in (1, 16, 32, 33, 64, 65, 256):
+            cfg, splits = choose(M, N, K, mode)
+            assert height[cfg] <= 2 * max(M, 32) and 1 <= splits <= 12
+
+
 def test_long_k_choice_names_the_kernel_it_launches(L):
     """Residual adds with a long K: 24 is the launch that is evened out along K, 26 and 28 the whole tiles of
     256 x 192 and 192 x 256.  Where whole tiles are the cheaper ones the choice says so, also where 192-column
