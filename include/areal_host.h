@@ -46,6 +46,14 @@ void areal_kvalloc_shuffle(areal_kvalloc* a, uint64_t seed);
 int32_t areal_plan_passes(int32_t n_spans, const int32_t* lens, int32_t max_rows, int32_t* out,
                           int32_t cap);
 
+/* Cut the attention of a decode step into work-group segments, as areal_decode_step does.  Row i has own[i] >= 1 tokens,
+ * the one it appends included; rows with equal home[i] hold leading KV blocks together.  target = 0: segment length
+ * by price; else about that many work-groups, none aimed shorter than min_tokens.  Writes up to `cap`
+ * records of 4 int32 {row or -1, first token, tokens, slot} by launch index (which modulo 8 is the XCD) to out
+ * (host) and returns the number of records, or AREAL_E_INVAL. */
+int32_t areal_plan_decode(int32_t n, const int32_t* own, const int32_t* home, int32_t n_kv_heads, int32_t max_slots,
+                          int32_t target, int32_t min_tokens, int32_t* out, int32_t cap);
+
 /* Section 5.1 (staleness-aware training): the rollout controller submits the
  * N-th generation request only if floor((N-1)/B) <= i + eta, with B the
  * training batch size, i the current policy version and eta the maximum

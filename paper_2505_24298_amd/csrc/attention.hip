@@ -200,31 +200,28 @@ __device__ __forceinline__ void rotate(RawHead<D>& r, const f16* __restrict__ bi
   }
 }
 
-// The leading KV blocks that a set of rows has in common (work-groups blockIdx.x >= n_splits of
-// the decode launch: x - n_splits = chunk of the shared part, y = kv head, z = set).  Wave w
+// The leading KV blocks that a set of rows has in common (the work-groups of the decode launch behind the
+// segments': u = chunk of the shared part).  Wave w
 // owns tile w of the set: 16 MFMA rows = floor(16 / G) sequences x their G query heads, so
 // every lane has its own sequence, position and query head.  Each wave walks all blocks of the
 // chunk (the four waves read the same tiles: one fetch from L2 per work-group) and writes
 // its rows' partial (max, sum, accumulator) into slot n_splits + chunk of those rows; the
 // merge kernel folds them into the rows' own partials.  Every shared position precedes every
-// row's position, so nothing is masked but the tail of the last block pair.  Block ids: row
-// M + set of the per-step table.
+// row's position, so nothing is masked but the tail of the last block pair.
 template <int D>
 __device__ __forceinline__ void decode_shared_set(
     const float* __restrict__ qkv, const RowMeta& rm, const f16* __restrict__ bq,
     const float* __restrict__ cos_tab, const float* __restrict__ sin_tab,
-    const f16* __restrict__ arena, const KvGeom& geom, int nq, int n_splits, int n_slots,
-    float scale_log2, float* __restrict__ part_o, float* __restrict__ part_ml,
-    const int32_t* __restrict__ step_table, int step_stride, const DecodeGroups& grp, int M) {
-  const int set = blockIdx.z, kvh = blockIdx.y, u = (int)blockIdx.x - n_splits;
-  if (set >= grp.n_sets) return;
+    const f16* __restrict__ arena, const KvGeom& geom, int nq, int n_own, int n_slots,
+    float scale_log2, float* __restrict__ part_o, float* __restrict__ part_ml, const DecodeGroups& grp, int set, int kvh,
+    int u) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane >> 4, j = lane & 15;
   const int nkv = geom.n_kv_heads, G = nq / nkv, P = 16 / G;
   const int chunk = grp.sh_chunk;
   const int t0 = u * chunk, b0 = t0 / kBlockTokens;
-  const int32_t* table = step_table + (int64_t)(M + set) * step_stride;
-  const int b_cap = min(b0 + chunk / kBlockTokens, step_stride);
+  const int32_t* table = grp.set_table + (int64_t)set * grp.set_stride;
+  const int b_cap = min(b0 + chunk / kBlockTokens, grp.set_stride);
   BlockIds ids;
   ids.lo = b0 + lane < b_cap ? table[b0 + lane] : 0;
   ids.hi = b0 + 64 + lane < b_cap ? table[b0 + 64 + lane] : 0;
@@ -265,7 +262,7 @@ __device__ __forceinline__ void decode_shared_set(
   }
   l += __shfl_xor(l, 16);
   l += __shfl_xor(l, 32);
-  const int slot = n_splits + u;
+  const int slot = n_own + u;
   if (g == 0 && r >= 0) {
     const int64_t pi = ((int64_t)r * nq + head) * n_slots + slot;
     part_ml[pi * 2] = m;
@@ -282,70 +279,70 @@ __device__ __forceinline__ void decode_shared_set(
   }
 }
 
-// One work-group per (split, kv head, sequence); the partials of a sequence cut
-// into several splits are combined by attn_merge_kernel.  The row's query heads
+// One work-group per (segment, kv head); the partials of a row cut into several segments
+// are combined by attn_merge_kernel.  Bound by HBM: work-groups are handed out by decode_plan.hpp (segments of
+// about equal length, an eighth of the tokens to each XCD), a segment's block ids lie by launch index, so
+// that they travel together with its descriptor.  The row's query heads
 // are taken from the float32 QKV row (bias, RoPE, rounding done here).  The
 // cached positions 0 .. pos-1 come from the paged arena; the token being
-// appended (position pos) is handled by the work-group whose split contains
-// pos: it rotates and rounds the new key, stores key and value into the
-// sequence's block for later steps, and folds the new token into its softmax
+// appended (position pos) is handled by the work-group whose segment contains
+// pos: its last wave, which has the fewest blocks, rotates and rounds the new key and stores key and value into the
+// sequence's block for later steps, and the new token is folded into the softmax
 // state as one more (score, value) pair.
 template <int D>
 __global__ __launch_bounds__(256) void attn_decode_kernel(
-    const float* __restrict__ qkv, RowMeta rm, SeqState st, const f16* __restrict__ bq,
+    const float* __restrict__ qkv, RowMeta rm, const f16* __restrict__ bq,
     const f16* __restrict__ bk, const f16* __restrict__ bv, const float* __restrict__ cos_tab,
-    const float* __restrict__ sin_tab, f16* __restrict__ arena, KvGeom geom, int nq, int chunk,
-    int n_splits, float scale_log2, float* __restrict__ part_o, float* __restrict__ part_ml,
-    f16* __restrict__ out, const int32_t* __restrict__ step_table, int step_stride, DecodeGroups grp) {
+    const float* __restrict__ sin_tab, f16* __restrict__ arena, KvGeom geom, int nq, DecodeSegs sg,
+    float scale_log2, float* __restrict__ part_o, float* __restrict__ part_ml,
+    f16* __restrict__ out, DecodeGroups grp) {
   __shared__ float sm[4][16], sl[4][16];
   __shared__ float so[4][16][D];
   __shared__ float s_new[16], v_new[D];
-  const int n_slots = n_splits + grp.n_shared;           // partial slots per (row, head)
-  if ((int)blockIdx.x >= n_splits) {                     // the shared leading blocks of a set of rows
-    if ((int)blockIdx.x >= n_slots) return;             // padding column (the launch keeps gridDim.x odd)
-    decode_shared_set<D>(qkv, rm, bq, cos_tab, sin_tab, arena, geom, nq, n_splits, n_slots,
-                         scale_log2, part_o, part_ml, step_table, step_stride, grp, (int)gridDim.z);
+  const int nkv = geom.n_kv_heads;
+  const int n_slots = sg.max_own + grp.n_shared;         // partial slots per (row, head)
+  // segment q of XCD x: work-groups 8 (q nkv .. q nkv + nkv - 1) + x, one per kv head
+  const int id = blockIdx.x, n_seg_wgs = sg.n * nkv;
+  if (id >= n_seg_wgs) {                                 // the shared leading blocks of a set of rows
+    const int r = id - n_seg_wgs, u = r % grp.n_shared, rest = r / grp.n_shared;
+    decode_shared_set<D>(qkv, rm, bq, cos_tab, sin_tab, arena, geom, nq, sg.max_own, n_slots,
+                         scale_log2, part_o, part_ml, grp, rest / nkv, rest % nkv, u);
     return;
   }
-  const int i = blockIdx.z, kvh = blockIdx.y, split = blockIdx.x;
+  const int seg = (id >> 3) / nkv * 8 + (id & 7), kvh = (id >> 3) % nkv;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane >> 4, j = lane & 15;
-  const int nkv = geom.n_kv_heads, G = nq / nkv;
-  // Token and block indices below are relative to the first position this row's own
-  // work-groups cover (t_start, a multiple of the block size; the row of the per-step table
-  // starts at that block too), so that no address depends on t_start.
-  const int t0 = split * chunk;
-  const int b0 = t0 / kBlockTokens;
-  // the table entries of the whole split are requested at once with the row's position (entries
-  // past the sequence's last block are stale but inside the table row, and never used)
-  // (with the per-step table, row i of which lists the blocks of this launch's row i, the
-  // address depends on the block index alone: one load fewer in front of the first tile)
-  const int32_t* table = step_table ? step_table + (int64_t)i * step_stride
-                                    : st.table + (int64_t)rm.slot[i] * st.max_blocks;
-  const int b_cap = min(b0 + chunk / kBlockTokens, step_table ? step_stride : st.max_blocks);
+  const int G = nq / nkv;
+  const int32_t* table = sg.table + (int64_t)seg * sg.stride;
   BlockIds ids;
-  ids.lo = b0 + lane < b_cap ? table[b0 + lane] : 0;
-  ids.hi = b0 + 64 + lane < b_cap ? table[b0 + 64 + lane] : 0;
-  const int pos_abs = rm.pos[i];
-  const int pos = pos_abs - (grp.t_start ? grp.t_start[i] : 0);
-  if (t0 > pos) return;
-  const bool owner = pos < t0 + chunk;                 // this split holds the appended position
-  const int t1 = min(pos, t0 + chunk);                 // cached tokens [t0, t1)
+  ids.lo = lane < sg.stride ? table[lane] : 0;
+  ids.hi = 64 + lane < sg.stride ? table[64 + lane] : 0;
+  const int4 d = sg.desc[seg];
+  const int i = __builtin_amdgcn_readfirstlane(d.x);
+  if (i < 0) return;
+  // Token and block indices below are relative to the first position this row's own work-groups cover.
+  const int pos_abs = __builtin_amdgcn_readfirstlane(d.y), pos = __builtin_amdgcn_readfirstlane(d.z);
+  const int packed = __builtin_amdgcn_readfirstlane(d.w);
+  const int t0 = (packed & 0xFFF) * 32, n_tok = ((packed >> 12) & 0x7F) * 32, slot = (packed >> 19) & 31;
+  const bool single = (packed >> 24) & 1;              // the row has no other partial
+  const int b0 = t0 / kBlockTokens;
+  const bool owner = pos < t0 + n_tok;                 // this segment holds the appended position
+  const int t1 = min(pos, t0 + n_tok);                 // cached tokens [t0, t1)
   const int b1 = (t1 + kBlockTokens - 1) / kBlockTokens;
 
   // Loads go out in dependency order (the query row needs nothing, the angles need pos,
   // the K/V tiles need the block ids) and the rotation runs while the tiles are in flight.
   const float* row = qkv + (int64_t)i * (nq + 2 * nkv) * D;
   const int head = kvh * G + min(j, G - 1);
+
+  // wave w takes block groups w, w+4, ... of this segment
+  int b = b0 + wave * NB;
+  KvFrag<D> cur, nxt;
+  if (b < b1) load_group_ids<D>(cur, arena, geom, ids, b0, b, b1, kvh, lane);
   RawHead<D> qraw;
   load_raw<D>(qraw, row + head * D, g);
   RopeAngles<D> ang;
   load_angles<D>(ang, cos_tab + (int64_t)pos_abs * (D / 2), sin_tab + (int64_t)pos_abs * (D / 2), g);
-
-  // wave w takes block groups w, w+4, ... of this split
-  int b = b0 + wave * NB;
-  KvFrag<D> cur, nxt;
-  if (b < b1) load_group_ids<D>(cur, arena, geom, ids, b0, b, b1, kvh, lane);
 
   f16x8 qf[D / 32];
   rotate<D>(qraw, bq ? bq + head * D : nullptr, ang, g, qf);
@@ -354,7 +351,7 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(
 #pragma unroll
     for (int c = 0; c < D / 32; ++c) qf[c] = zero8;
   }
-  if (owner && wave == 0) {                            // wave-uniform
+  if (owner && wave == 3) {                            // wave-uniform
     RawHead<D> kraw;
     load_raw<D>(kraw, row + (nq + kvh) * D, g);
     f16x8 kf[D / 32];
@@ -367,7 +364,7 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(
     dot += __shfl_xor(dot, 16);
     dot += __shfl_xor(dot, 32);
     if (g == 0) s_new[j] = dot * scale_log2;
-    const int blk = table[pos / kBlockTokens], tin = pos % kBlockTokens;
+    const int blk = block_id(ids, pos / kBlockTokens - b0), tin = pos % kBlockTokens;
     if (j == 0) {
       f16* kt = arena + kv_tile_off(geom, blk, kvh, 0);
 #pragma unroll
@@ -424,10 +421,10 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(
       M = M2;
     }
     const int head = kvh * G + h;
-    if (n_slots == 1) {
+    if (single) {
       out[((int64_t)i * nq + head) * D + dd] = f2h_sat(O / L);
     } else {
-      const int64_t pi = ((int64_t)i * nq + head) * n_slots + split;
+      const int64_t pi = ((int64_t)i * nq + head) * n_slots + slot;
       part_o[pi * D + dd] = O;
       if (dd == 0) { part_ml[pi * 2] = M; part_ml[pi * 2 + 1] = L; }
     }
@@ -435,24 +432,24 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(
 }
 
 // Combine the split partials of one (row, head): out = sum_s O_s 2^(M_s-M) / sum_s L_s 2^(M_s-M).
-// Every load address depends only on the launch shape, so the row's position, the
+// Every load address depends only on the launch shape, so the row's slot count, the
 // statistics (lane s fetches (M_s, L_s)) and the first eight partial rows all go out
 // together; which slots really exist for this row is applied afterwards by selection.  The
 // other slots hold stale values of earlier launches: selected away, never multiplied.
 template <int D>
 __global__ __launch_bounds__(D < 64 ? 64 : D) void attn_merge_kernel(const float* __restrict__ part_o,
-                                                       const float* __restrict__ part_ml, RowMeta rm,
-                                                       int nq, int chunk, int n_splits, int n_shared,
-                                                       int sh_chunk, const int32_t* __restrict__ t_start,
-                                                       f16* __restrict__ out) {
+                                                       const float* __restrict__ part_ml,
+                                                       const int32_t* __restrict__ own, int nq, int max_own,
+                                                       int n_shared, int sh_chunk,
+                                                       const int32_t* __restrict__ t_start, f16* __restrict__ out) {
   constexpr int BATCH = 8;
-  const int n_slots = n_splits + n_shared;                    // <= 32
+  const int n_slots = max_own + n_shared;                     // <= 32
   const int i = blockIdx.x / nq;
   const int64_t base = (int64_t)blockIdx.x * n_slots;
   const int lane = threadIdx.x & 63;
   const int dd = min((int)threadIdx.x, D - 1);
   const float* po = part_o + base * D + dd;
-  const int pos_abs = rm.pos[i];
+  const int ns = own[i];
   const int ts = t_start ? t_start[i] : 0;
   float2 ml = {0.f, 0.f};
   if (lane < n_slots) ml = *reinterpret_cast<const float2*>(part_ml + (base + lane) * 2);
@@ -460,10 +457,10 @@ __global__ __launch_bounds__(D < 64 ? 64 : D) void attn_merge_kernel(const float
 #pragma unroll
   for (int u = 0; u < BATCH; ++u) v[u] = u < n_slots ? po[(int64_t)u * D] : 0.f;
 
-  // slots of this row: its own splits 0 .. ceil((pos + 1 - ts) / chunk) - 1, then the chunks of
-  // the part it shares with its set (slot n_splits + u exists while u * chunk < ts)
-  const int ns = min(n_splits, (pos_abs - ts + chunk) / chunk);
-  const bool mine = lane < n_splits ? lane < ns : (lane < n_slots && (lane - n_splits) * sh_chunk < ts);
+  // slots of this row: its own segments 0 .. ns - 1, then the chunks of
+  // the part it shares with its set (slot max_own + u exists while u * sh_chunk < ts)
+  if (ns == 1 && ts == 0) return;                             // nothing to combine: `out` is written
+  const bool mine = lane < max_own ? lane < ns : (lane < n_slots && (lane - max_own) * sh_chunk < ts);
   const uint64_t have = __ballot(mine);                       // slots live in lanes 0 .. 31
   const float ms = mine ? ml.x : -INFINITY, ls = mine ? ml.y : 0.f;
   const float M = wave_max(ms);                               // whole waves only: blockDim >= 64
@@ -726,35 +723,29 @@ static bool geom_ok(const KvGeom& g, int nq) {
   return true;
 }
 
-static bool groups_ok(const DecodeGroups& grp, int M, int n_splits, const int32_t* step_table) {
+static bool groups_ok(const DecodeGroups& grp, int M, int max_own) {
   if (grp.n_sets == 0 && grp.n_shared == 0 && !grp.t_start) return true;
-  return grp.n_sets > 0 && grp.n_sets <= M && grp.n_shared > 0 && n_splits + grp.n_shared <= 32 &&
+  return grp.n_sets > 0 && grp.n_sets <= M && grp.n_shared > 0 && max_own + grp.n_shared <= 32 &&
          grp.sh_chunk > 0 && grp.sh_chunk % (NB * kBlockTokens) == 0 && grp.sh_chunk <= 128 * kBlockTokens &&
-         grp.t_start && grp.set_rows && grp.set_start && step_table;
+         grp.t_start && grp.set_rows && grp.set_start && grp.set_table && grp.set_stride > 0;
 }
 
-hipError_t launch_attn_decode(hipStream_t s, const float* qkv, int M, RowMeta rm, SeqState st,
-                              const f16* bq, const f16* bk, const f16* bv, const float* cos_tab,
-                              const float* sin_tab, f16* arena_layer, KvGeom geom, int n_q_heads,
-                              int chunk, int n_splits, float* part_o, float* part_ml, f16* out,
-                              const int32_t* step_table, int step_stride, DecodeGroups grp) {
-  if (step_table && step_stride <= 0) return hipErrorInvalidValue;
-  if (M <= 0 || !geom_ok(geom, n_q_heads) || chunk <= 0 || chunk % (4 * NB * kBlockTokens) ||
-      chunk > 128 * kBlockTokens || n_splits <= 0 || !groups_ok(grp, M, n_splits, step_table) ||
-      (n_splits + grp.n_shared > 1 && (!part_o || !part_ml)) ||
+hipError_t launch_attn_decode(hipStream_t s, const float* qkv, int M, RowMeta rm, const f16* bq, const f16* bk,
+                              const f16* bv, const float* cos_tab, const float* sin_tab, f16* arena_layer, KvGeom geom,
+                              int n_q_heads, DecodeSegs segs, float* part_o, float* part_ml, f16* out,
+                              DecodeGroups grp) {
+  if (M <= 0 || !geom_ok(geom, n_q_heads) || segs.n <= 0 || segs.n % 8 || segs.max_own < 1 || segs.max_own > 32 ||
+      segs.stride <= 0 || segs.stride > 132 || !segs.desc || !segs.table || !segs.own ||
+      ((uintptr_t)segs.desc & 15) || !groups_ok(grp, M, segs.max_own) ||
+      (segs.max_own + grp.n_shared > 1 && (!part_o || !part_ml)) ||
       !qkv || !cos_tab || !sin_tab || (bq && (!bk || !bv)) ||
       (((uintptr_t)qkv | (uintptr_t)bq | (uintptr_t)bk | (uintptr_t)bv | (uintptr_t)arena_layer) & 15))
     return hipErrorInvalidValue;
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)geom.head_dim);
-  // Work-groups go to the eight XCDs round-robin in launch order (x fastest).  With an even
-  // gridDim.x a split index would always land on the same few XCDs, and the low splits, which
-  // every row has, would crowd them; an odd gridDim.x rotates the assignment row by row.
-  dim3 grid((n_splits + grp.n_shared) | 1, geom.n_kv_heads, M);
+  const unsigned grid = (unsigned)((segs.n + grp.n_sets * grp.n_shared) * geom.n_kv_heads);
 #define AREAL_DEC(DD)                                                                              \
-  attn_decode_kernel<DD><<<grid, 256, 0, s>>>(qkv, rm, st, bq, bk, bv, cos_tab, sin_tab,           \
-                                               arena_layer, geom, n_q_heads, chunk, n_splits,      \
-                                               scale_log2, part_o, part_ml, out, step_table,       \
-                                               step_stride, grp);
+  attn_decode_kernel<DD><<<grid, 256, 0, s>>>(qkv, rm, bq, bk, bv, cos_tab, sin_tab, arena_layer, geom, n_q_heads, \
+                                               segs, scale_log2, part_o, part_ml, out, grp);
   switch (geom.head_dim) {
     case 32: AREAL_DEC(32) break;
     case 64: AREAL_DEC(64) break;
@@ -764,17 +755,16 @@ hipError_t launch_attn_decode(hipStream_t s, const float* qkv, int M, RowMeta rm
   return hipGetLastError();
 }
 
-hipError_t launch_attn_merge(hipStream_t s, int M, RowMeta rm, int head_dim, int n_q_heads, int chunk,
-                             int n_splits, const float* part_o, const float* part_ml, f16* out,
-                             DecodeGroups grp) {
-  const int n_slots = n_splits + grp.n_shared;
-  if (M <= 0 || n_splits < 1 || n_slots < 2 || n_slots > 32 || chunk <= 0 || !part_o || !part_ml || !out ||
+hipError_t launch_attn_merge(hipStream_t s, int M, int head_dim, int n_q_heads, DecodeSegs segs, const float* part_o,
+                             const float* part_ml, f16* out, DecodeGroups grp) {
+  const int n_slots = segs.max_own + grp.n_shared;
+  if (M <= 0 || segs.max_own < 1 || n_slots < 2 || n_slots > 32 || !segs.own || !part_o || !part_ml || !out ||
       (grp.n_shared > 0 && (!grp.t_start || grp.sh_chunk <= 0)) || (head_dim != 32 && head_dim != 64 && head_dim != 128))
     return hipErrorInvalidValue;
 #define AREAL_MRG(DD)                                                                              \
-  attn_merge_kernel<DD><<<M * n_q_heads, DD < 64 ? 64 : DD, 0, s>>>(part_o, part_ml, rm, n_q_heads, \
-                                                                    chunk, n_splits, grp.n_shared,  \
-                                                                    grp.sh_chunk, grp.t_start, out);
+  attn_merge_kernel<DD><<<M * n_q_heads, DD < 64 ? 64 : DD, 0, s>>>(part_o, part_ml, segs.own, n_q_heads, \
+                                                                    segs.max_own, grp.n_shared, grp.sh_chunk, \
+                                                                    grp.t_start, out);
   switch (head_dim) {
     case 32: AREAL_MRG(32) break;
     case 64: AREAL_MRG(64) break;

@@ -1,0 +1,164 @@
+// How a decode step's attention is cut into work-groups: host-side, no GPU calls (exercised through
+// include/areal_host.h).
+#pragma once
+#include <stdint.h>
+
+#include <algorithm>
+#include <unordered_map>
+#include <vector>
+
+namespace areal {
+
+constexpr int kDecodeUnit = 32;           // tokens a wave takes at a time
+constexpr int kDecodeMaxUnits = 64;       // per segment: 128 block ids, two per lane
+constexpr int kDecodeXcds = 8;
+
+// A run of one row's tokens [t0, t0 + n), n > 0; the row's last segment holds the position it appends at.
+// `slot` numbers the segments of a row.
+struct DecodeSegment { int32_t row, t0, n, slot; };
+
+struct DecodePlan {
+  int share = 0;                          // units per segment aimed at
+  std::vector<DecodeSegment> order;       // by launch index, which modulo 8 is the XCD; row = -1: nothing to do
+  std::vector<int32_t> n_own;             // segments of each row
+  int max_own = 0, max_units = 0;         // most segments of a row, longest segment
+};
+
+// The cut replaces splits of one length for all rows (256 tokens and up, work-groups without tokens where a row was
+// shorter than the longest, a remainder per row).  Attention launch of a step, 1.5B shape: 256 rows of 420 - 650 tokens
+// 30.3 us and a merge of 4.9 -> 25.1 and none; 88 rows of 1,500 - 4,100 54.1 -> 51.1; 24 of 4,000 - 8,200 37.0 -> 32.5; one
+// of 700 10.1 -> 7.3; 7B shape, 128 rows of 500 - 3,800 116.8 -> 106.4.
+//
+// Units per segment, by price.  In microseconds: every unit of 32 tokens (16 KB a KV head) at 6.2 TB/s over the
+// chip's 512 resident work-groups, or in 0.65 where few work-groups run and a unit is a round trip; a work-group's start (block ids, then tiles: two round trips) and its end; what the last ones
+// leave idle, half a segment, or, where all are resident at once, what the longest takes more than the mean; and the
+// merge launch if any row is cut at all.
+inline int decode_share(const std::vector<int>& units, int n_kv_heads, int lo, int hi) {
+  static const int steps[] = {4, 5, 6, 8, 10, 12, 16, 20, 24, 28, 32, 40, 48, 64};
+  double total = 0;
+  for (int u : units) total += u;
+  total *= n_kv_heads;
+  int best = hi;
+  double best_us = 1e30;
+  for (int s : steps) {
+    if (s < lo || s > hi) continue;
+    int64_t segs = 0;
+    int longest = 0;
+    bool cut = false;
+    for (int u : units) {
+      const int k = (u + s - 1) / s;
+      segs += k;
+      longest = std::max(longest, (u + k - 1) / k);
+      cut |= k > 1;
+    }
+    const double wgs = (double)segs * n_kv_heads, rounds = wgs / 512.0, mean = total / wgs;
+    double us = std::max(total * (1.34 / 512.0), 0.65 * longest + 3.4) + rounds;
+    us += rounds > 1.0 ? 0.67 * longest : 0.5 * (longest - mean);
+    if (cut) us += 4.5;
+    if (us < best_us) { best_us = us; best = s; }
+  }
+  return best;
+}
+
+// The share that gives about `target` work-groups (tuning): whole rounds of a work-group's four waves.
+inline int decode_share_for(int64_t total_units, int n_kv_heads, int target, int min_tokens) {
+  const int share = (int)((total_units * n_kv_heads + target - 1) / target);
+  return (std::max(share, min_tokens / kDecodeUnit) + 3) / 4 * 4;
+}
+
+// own[i]: tokens of row i from its first own one to the one it appends (>= 1).  home[i]: the row's first KV block; rows
+// with the same one hold leading blocks together.  Rows are cut evenly into at most max_slots segments.  target > 0: so
+// that there are about that many work-groups, no segment aimed shorter than min_tokens (tuning); 0: by price.
+// at_least: lower limit of the share.
+//
+// Order: each XCD gets an eighth of the units, longest segments first.  Rows that share blocks are kept on as few XCDs
+// as the balance allows (pieces of a sixteenth of the work), where their common blocks meet in one L2: 16
+// prompts x 16 samples of 535 tokens, 288 shared, are 140 MB of K/V per layer, 69 MB of them distinct, of which 102
+// would cross the fabric with the samples of a prompt on all XCDs.
+inline DecodePlan plan_decode(const std::vector<int32_t>& own, const std::vector<int32_t>& home, int n_kv_heads,
+                              int max_slots, int target, int min_tokens, int at_least) {
+  const int n = (int)own.size();
+  DecodePlan p;
+  std::vector<int> units(n);
+  int64_t total = 0;
+  int longest = 1;
+  for (int i = 0; i < n; ++i) {
+    units[i] = (own[i] + kDecodeUnit - 1) / kDecodeUnit;
+    total += units[i];
+    longest = std::max(longest, units[i]);
+  }
+  const int lo = std::max(at_least, (longest + max_slots - 1) / max_slots);
+  if (target > 0) {
+    p.share = decode_share_for(total, n_kv_heads, target, min_tokens);
+  } else {
+    p.share = decode_share(units, n_kv_heads, lo, kDecodeMaxUnits);
+  }
+  p.share = std::min(std::max(p.share, lo), kDecodeMaxUnits);
+  p.n_own.resize(n);
+  std::vector<int> len(n);                                // units per segment of a row
+  for (int i = 0; i < n; ++i) {
+    const int k = (units[i] + p.share - 1) / p.share;
+    len[i] = (units[i] + k - 1) / k;
+    p.n_own[i] = (units[i] + len[i] - 1) / len[i];
+    p.max_own = std::max(p.max_own, (int)p.n_own[i]);
+    p.max_units = std::max(p.max_units, len[i]);
+  }
+  // rows -> XCD, or -1: their segments go wherever there is room
+  std::vector<int8_t> at(n, -1);
+  {
+    std::unordered_map<int32_t, std::vector<int>> by_home;
+    for (int i = 0; i < n; ++i) by_home[home[i]].push_back(i);
+    if ((int)by_home.size() < n) {
+      struct Piece { int64_t load; std::vector<int> rows; };
+      std::vector<Piece> pieces;
+      for (int i = 0; i < n; ++i) {                       // in row order, so that a plan does not depend on hashing
+        auto& rows = by_home[home[i]];
+        if (rows.size() < 2 || rows[0] != i) continue;
+        Piece piece{0, {}};
+        for (int r : rows) {
+          if (!piece.rows.empty() && (piece.load + units[r]) * 16 > total) {
+            pieces.push_back(std::move(piece));
+            piece = Piece{0, {}};
+          }
+          piece.load += units[r];
+          piece.rows.push_back(r);
+        }
+        pieces.push_back(std::move(piece));
+      }
+      std::stable_sort(pieces.begin(), pieces.end(), [](const Piece& a, const Piece& b) { return a.load > b.load; });
+      int64_t load[kDecodeXcds] = {};
+      for (const Piece& piece : pieces) {
+        const int x = (int)(std::min_element(load, load + kDecodeXcds) - load);
+        load[x] += piece.load;
+        for (int r : piece.rows) at[r] = (int8_t)x;
+      }
+      // more than a twentieth above an eighth of everything: the balance is worth more than the L2
+      if (*std::max_element(load, load + kDecodeXcds) * 160 > total * 21) std::fill(at.begin(), at.end(), (int8_t)-1);
+    }
+  }
+  std::vector<int> rows(n);
+  for (int i = 0; i < n; ++i) rows[i] = i;
+  std::stable_sort(rows.begin(), rows.end(), [&](int a, int b) { return len[a] > len[b]; });
+  std::vector<DecodeSegment> queue[kDecodeXcds];
+  int64_t load[kDecodeXcds] = {};
+  for (int i = 0; i < n; ++i)
+    if (at[i] >= 0) load[at[i]] += units[i];
+  for (int i : rows)
+    for (int k = 0, u = 0; u < units[i]; ++k, u += len[i]) {
+      const int m = std::min(len[i], units[i] - u);
+      int x = at[i];
+      if (x < 0) {
+        x = (int)(std::min_element(load, load + kDecodeXcds) - load);
+        load[x] += m;
+      }
+      queue[x].push_back(DecodeSegment{i, u * kDecodeUnit, m * kDecodeUnit, k});
+    }
+  size_t deepest = 0;
+  for (auto& q : queue) deepest = std::max(deepest, q.size());
+  p.order.assign(deepest * kDecodeXcds, DecodeSegment{-1, 0, 0, 0});
+  for (int x = 0; x < kDecodeXcds; ++x)
+    for (size_t j = 0; j < queue[x].size(); ++j) p.order[j * kDecodeXcds + x] = queue[x][j];
+  return p;
+}
+
+}  // namespace areal

@@ -8,6 +8,7 @@
 
 #include "../../include/areal.h"
 #include "../../include/areal_host.h"
+#include "decode_plan.hpp"
 #include "gate.hpp"
 #include "kv_alloc.hpp"
 
@@ -34,6 +35,22 @@ int32_t areal_kvalloc_table(const areal_kvalloc* a, int32_t seq, int32_t* out, i
   return (int32_t)b.size();
 }
 void areal_kvalloc_shuffle(areal_kvalloc* a, uint64_t seed) { a->a.shuffle_free(seed); }
+
+int32_t areal_plan_decode(int32_t n, const int32_t* own, const int32_t* home, int32_t n_kv_heads, int32_t max_slots,
+                          int32_t target, int32_t min_tokens, int32_t* out, int32_t cap) {
+  if (n < 1 || !own || !home || n_kv_heads < 1 || max_slots < 1 || target < 0 || min_tokens < 0 || !out)
+    return AREAL_E_INVAL;
+  for (int i = 0; i < n; ++i)
+    if (own[i] < 1 || own[i] > (int64_t)max_slots * kDecodeMaxUnits * kDecodeUnit) return AREAL_E_INVAL;
+  const DecodePlan p = plan_decode(std::vector<int32_t>(own, own + n), std::vector<int32_t>(home, home + n), n_kv_heads,
+                                   max_slots, target, min_tokens, 1);
+  for (size_t q = 0; q < p.order.size() && (int)q < cap; ++q) {
+    const DecodeSegment& s = p.order[q];
+    const int32_t rec[4] = {s.row, s.t0, s.n, s.slot};
+    for (int k = 0; k < 4; ++k) out[4 * q + k] = rec[k];
+  }
+  return (int32_t)p.order.size();
+}
 
 struct areal_gate { StalenessGate g; };
 areal_gate* areal_gate_create(int64_t batch_size, int64_t eta) {

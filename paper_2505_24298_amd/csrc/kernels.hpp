@@ -97,27 +97,33 @@ struct DecodeGroups {
   int n_sets = 0;                     // <= M
   int sh_chunk = 0;                   // tokens of the shared part per work-group (multiple of 32, at most 2048)
   int n_shared = 0;                   // partial slots per row for the shared part: ceil(max t_start / sh_chunk)
+  const int32_t* set_table = nullptr; // [n_sets][set_stride] the leading block ids of a set
+  int set_stride = 0;
+};
+// The rows' own tokens of a decode launch, cut into segments (decode_plan.hpp).  All arrays are device memory.
+struct DecodeSegs {
+  const int4* desc = nullptr;         // [n] {row or -1, position it appends at, the same counted from its first own token,
+                                      // (first own token / 32) | (tokens / 32) << 12 | slot << 19 | only partial << 24}
+  const int32_t* table = nullptr;     // [n][stride] block ids of the segment, the appended position's included
+  const int32_t* own = nullptr;       // [M] segments of row i
+  int n = 0;                          // multiple of 8: segment i runs on XCD i % 8
+  int stride = 0;                     // at most 132
+  int max_own = 0;                    // largest `own`
 };
 // decode: one query row per sequence (row i <-> rm.slot[i], rm.pos[i]), taken from the float32
 // QKV rows [M, (nq + 2 nkv) d] of the pass: bias, RoPE and rounding of q and of the appended
-// token's k happen inside, and the appended k, v are stored into the sequence's block
-// (table entry pos/16 must be installed).  Context = positions 0 .. pos.  Row i's own
-// work-groups cover positions t_start[i] .. pos in splits of `chunk` tokens (multiple of 128,
-// at most 2048), n_splits >= ceil((pos + 1 - t_start[i]) / chunk) for every row; positions
-// below t_start[i] are covered by the row's set.  With more than one partial slot per row
-// (n_splits + grp.n_shared > 1, at most 32) the partials go to `part_o` / `part_ml` and
-// launch_attn_merge (same chunk, n_splits, grp) combines them into `out`.  `step_table`
-// (optional, device int32 [M, step_stride]): the block ids of row i's sequence, entries
-// 0 .. pos/16 at least, laid out by launch row; replaces the lookup through st.table.
-hipError_t launch_attn_decode(hipStream_t s, const float* qkv, int M, RowMeta rm, SeqState st,
-                              const f16* bq, const f16* bk, const f16* bv, const float* cos_tab,
-                              const float* sin_tab, f16* arena_layer, KvGeom geom, int n_q_heads,
-                              int chunk, int n_splits, float* part_o, float* part_ml, f16* out,
-                              const int32_t* step_table = nullptr, int step_stride = 0,
+// token's k happen inside, and the appended k, v are stored into the sequence's block.
+// Context = positions 0 .. pos.  The segments cover positions t_start[i] .. pos of row i; positions
+// below t_start[i] are covered by the row's set.  A row with more than one partial slot
+// (own[i] + chunks of its set, max_own + grp.n_shared at most 32) leaves partials in `part_o` / `part_ml`
+// [M][nq][max_own + n_shared], which launch_attn_merge (same segs, grp) combines into `out`; other rows' outputs are
+// written at once and left alone by the merge.
+hipError_t launch_attn_decode(hipStream_t s, const float* qkv, int M, RowMeta rm, const f16* bq, const f16* bk,
+                              const f16* bv, const float* cos_tab, const float* sin_tab, f16* arena_layer, KvGeom geom,
+                              int n_q_heads, DecodeSegs segs, float* part_o, float* part_ml, f16* out,
                               DecodeGroups grp = DecodeGroups{});
-hipError_t launch_attn_merge(hipStream_t s, int M, RowMeta rm, int head_dim, int n_q_heads, int chunk,
-                             int n_splits, const float* part_o, const float* part_ml, f16* out,
-                             DecodeGroups grp = DecodeGroups{});
+hipError_t launch_attn_merge(hipStream_t s, int M, int head_dim, int n_q_heads, DecodeSegs segs, const float* part_o,
+                             const float* part_ml, f16* out, DecodeGroups grp = DecodeGroups{});
 hipError_t launch_attn_prefill(hipStream_t s, const f16* q, const AttnWork* work, int n_work,
                                SeqState st, const f16* arena_layer, KvGeom geom, int n_q_heads,
                                f16* out);

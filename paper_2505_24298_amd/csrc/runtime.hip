@@ -16,6 +16,7 @@
 #include <unordered_map>
 #include <unordered_set>
 
+#include "decode_plan.hpp"
 #include "kv_alloc.hpp"
 #include "gate.hpp"
 
@@ -144,7 +145,7 @@ struct areal_ctx {
   hipEvent_t seg_done[kRingSegs];
   bool seg_recorded[kRingSegs];
   std::string err;
-  int split_target = 3072;              // decode attention: work-groups per launch aimed at
+  int split_target = 0;                 // decode attention: work-groups per launch aimed at (0: by price)
   int min_chunk = 256;
   // Decode attention can walk the leading blocks that rows share once per set of rows: 1 = whenever
   // rows share, 0 = never, -1 = when the shared part is most of what the launch reads (measured on
@@ -308,15 +309,13 @@ struct PassArgs {
   const int32_t* tokens_in;       // device or null (read history)
   const int32_t* new_block;       // device or null
   bool decode;
-  int chunk, n_splits;            // decode attention partition
   const AttnWork* work;           // prefill attention work list (device)
   int n_work;
   const int32_t* last_rows;       // device: rows feeding the output projection (null: all rows)
   int n_out;                      // logits rows produced
   float* logits;                  // device [n_out, vocab]
   double attn_units;              // context tokens read (decode) / query-key pairs (prefill)
-  const int32_t* step_table = nullptr;   // decode: block ids by launch row (device), row stride below
-  int step_stride = 0;
+  DecodeSegs segs;                       // decode: attention work-groups
   DecodeGroups groups;                   // decode: sets of rows that share leading blocks
   // scoring passes (teacher-forced log-probs of every row's next token)
   const int32_t* target = nullptr;   // device [M]: token each row predicts, -1 = none
@@ -371,14 +370,12 @@ int run_pass(areal_ctx* c, const PassArgs& a) {
       // bias, RoPE and the store of the appended K/V are part of the attention kernel
       {
         ProfScope ps(c, AREAL_K_ATTN_DECODE, l, sampled, a.attn_units);
-        HIP_TRY(c, launch_attn_decode(s, qkv, a.M, a.rm, st, bq, bk, bv, cos_t, sin_t, arena_l, c->geom, nq,
-                                      a.chunk, a.n_splits, c->wsp<float>(c->lay.part_o),
-                                      c->wsp<float>(c->lay.part_ml), attn, a.step_table, a.step_stride,
-                                      a.groups));
+        HIP_TRY(c, launch_attn_decode(s, qkv, a.M, a.rm, bq, bk, bv, cos_t, sin_t, arena_l, c->geom, nq, a.segs,
+                                      c->wsp<float>(c->lay.part_o), c->wsp<float>(c->lay.part_ml), attn, a.groups));
       }
-      if (a.n_splits + a.groups.n_shared > 1) {
+      if (a.segs.max_own + a.groups.n_shared > 1) {
         ProfScope ps(c, AREAL_K_ATTN_MERGE, l, sampled, rows);
-        HIP_TRY(c, launch_attn_merge(s, a.M, a.rm, d, nq, a.chunk, a.n_splits, c->wsp<float>(c->lay.part_o),
+        HIP_TRY(c, launch_attn_merge(s, a.M, d, nq, a.segs, c->wsp<float>(c->lay.part_o),
                                      c->wsp<float>(c->lay.part_ml), attn, a.groups));
       }
     } else {
@@ -608,7 +605,10 @@ int areal_create(const areal_model_cfg* cfg, areal_ctx** out) {
   if (const char* e = getenv("AREAL_SCORE_FUSED")) c->fused_scoring = atoi(e) != 0;
   if (const char* e = getenv("AREAL_DECODE_MIN_CHUNK")) {
     const int v = atoi(e);
-    if (v >= 128 && v <= 2048 && v % 128 == 0) c->min_chunk = v;
+    if (v >= 128 && v <= 2048 && v % 128 == 0) {
+      c->min_chunk = v;
+      if (!c->split_target) c->split_target = 3072;
+    }
   }
   c->lay = lay;
   c->stream = reinterpret_cast<hipStream_t>(cfg->hip_stream);
@@ -856,18 +856,8 @@ int areal_decode_step(areal_ctx* c, int32_t n, const int32_t* seq_ids, const int
       max_shared_blocks = std::max(max_shared_blocks, common);
     }
   }
-  // split the KV walk so that the grid holds a few work-groups per compute unit
-  // (targets of 768 .. 6144 work-groups and minimum splits of 128 .. 512 tokens measured within
-  // 5 % of each other on the rollout's context mixes; environment knobs AREAL_DECODE_SPLIT_TARGET
-  // and AREAL_DECODE_MIN_CHUNK, read at areal_create, repeat that sweep)
   int64_t sum_ctx = 0;
-  int max_ctx = 0, max_own = 0;
-  for (int i = 0; i < n; ++i) {
-    const int ctx = c->seqs[seq_ids[i]].len + 1;
-    sum_ctx += ctx;
-    max_ctx = std::max(max_ctx, ctx);
-    max_own = std::max(max_own, ctx - t_start[i]);
-  }
+  for (int i = 0; i < n; ++i) sum_ctx += c->seqs[seq_ids[i]].len + 1;
   if (c->group_decode < 0 && !sets.empty()) {
     int64_t shared_sum = 0;
     for (int i = 0; i < n; ++i) shared_sum += t_start[i];
@@ -875,53 +865,65 @@ int areal_decode_step(areal_ctx* c, int32_t n, const int32_t* seq_ids, const int
       sets.clear();
       std::fill(t_start.begin(), t_start.end(), 0);
       max_shared_blocks = 0;
-      max_own = max_ctx;
     }
   }
-  int64_t chunk = (sum_ctx * g.n_kv_heads / c->split_target + 127) / 128 * 128;
-  chunk = std::min<int64_t>(std::max<int64_t>(chunk, c->min_chunk), 2048);   // a split spans at most 128 blocks
-  int n_splits = (int)((max_own + chunk - 1) / chunk);
   // the shared part goes in short pieces (a work-group of a set has each wave walk all blocks of
   // its piece, so a piece is two block pairs where eight partial slots suffice, longer for longer
   // prompts)
   const int max_shared = max_shared_blocks * AREAL_KV_BLOCK_TOKENS;
-  int sh_chunk = std::max(64, (max_shared + 8 * 64 - 1) / (8 * 64) * 64);
+  const int sh_chunk = std::max(64, (max_shared + 8 * 64 - 1) / (8 * 64) * 64);
   int n_shared = max_shared ? (max_shared + sh_chunk - 1) / sh_chunk : 0;
-  if (sh_chunk > 2048 || n_splits + n_shared > kMaxSplits) {   // very deep contexts: every row walks all its blocks itself
-    sets.clear();
+  std::vector<int32_t> own(n), home(n);
+  auto count_own = [&] {
+    for (int i = 0; i < n; ++i) own[i] = c->seqs[seq_ids[i]].len + 1 - t_start[i];
+  };
+  for (int i = 0; i < n; ++i) {
+    const auto& blocks = c->alloc->blocks(seq_ids[i]);
+    home[i] = blocks.empty() ? -1 - i : blocks[0];
+  }
+  count_own();
+  auto longest_own = [&] { return (*std::max_element(own.begin(), own.end()) + kDecodeUnit - 1) / kDecodeUnit; };
+  int aimed = kDecodeMaxUnits;           // units per segment that the rows' own tokens must fit the slots left with
+  if (c->split_target) {
+    int64_t units = 0;
+    for (int32_t t : own) units += (t + kDecodeUnit - 1) / kDecodeUnit;
+    aimed = std::min(aimed, decode_share_for(units, g.n_kv_heads, c->split_target, c->min_chunk));
+  }
+  if (sh_chunk > 2048 || (n_shared && (longest_own() + aimed - 1) / aimed + n_shared > kMaxSplits)) {
+    sets.clear();                        // very deep contexts: every row walks all its blocks itself
     std::fill(t_start.begin(), t_start.end(), 0);
     max_shared_blocks = 0;
     n_shared = 0;
-    n_splits = (int)((max_ctx + chunk - 1) / chunk);
-    if (n_splits > kMaxSplits) {
-      chunk = ((max_ctx + kMaxSplits - 1) / kMaxSplits + 127) / 128 * 128;
-      n_splits = (int)((max_ctx + chunk - 1) / chunk);
-    }
+    count_own();
   }
-  // per-step block table: row i lists the blocks of seq_ids[i] from block t_start[i] / 16 on (the
-  // attention kernel then finds its block ids from the launch row alone, without going through
-  // the sequence's slot); row n + k lists the leading blocks of set k
-  const int n_sets = (int)sets.size();
-  int longest_blocks = max_shared_blocks;
-  for (int i = 0; i < n; ++i)
-    longest_blocks = std::max(longest_blocks, c->alloc->blocks_for(c->seqs[seq_ids[i]].len + 1) -
-                                                  t_start[i] / AREAL_KV_BLOCK_TOKENS);
-  const int tab_stride = (longest_blocks + 3) / 4 * 4;
+  // Per step are staged: row metadata, the segments and their block ids by launch index, the leading blocks of the sets.
+  const int n_sets = (int)sets.size(), set_stride = (max_shared_blocks + 3) / 4 * 4;
   const uint64_t set_rows_bytes = (uint64_t)n_sets * kGroupTiles * 16 * 4;
-  int rc = ring_begin(c, align_up((uint64_t)n * 4, 64) * 4 + align_up((uint64_t)(n + n_sets) * tab_stride * 4, 64) +
-                             align_up(set_rows_bytes, 64) + align_up((uint64_t)n_sets * 4, 64));
+  DecodePlan plan;
+  uint64_t n_segs = 0, stride = 0, bytes = 0;
+  for (int at_least = 1;; at_least = 2 * plan.share) {   // longer segments, should their tables outgrow a ring segment
+    plan = plan_decode(own, home, g.n_kv_heads, kMaxSplits - n_shared, c->split_target, c->min_chunk, at_least);
+    n_segs = plan.order.size();
+    stride = ((uint64_t)plan.max_units * kDecodeUnit / AREAL_KV_BLOCK_TOKENS + 3) / 4 * 4;
+    bytes = align_up((uint64_t)n * 4, 64) * 5 + n_segs * 16 + align_up(n_segs * stride * 4, 64) +
+            align_up((uint64_t)n_sets * set_stride * 4, 64) + align_up(set_rows_bytes, 64) +
+            align_up((uint64_t)n_sets * 4, 64) + 64;
+    if (bytes <= c->seg_bytes || plan.share >= std::min(longest_own(), kDecodeMaxUnits)) break;
+  }
+  int rc = ring_begin(c, bytes);
   if (rc) return rc;
   const uint64_t start = c->seg_used;
   Staged s_slot = ring_take(c, (uint64_t)n * 4), s_pos = ring_take(c, (uint64_t)n * 4),
-         s_nb = ring_take(c, (uint64_t)n * 4), s_ts = ring_take(c, (uint64_t)n * 4),
-         s_tab = ring_take(c, (uint64_t)(n + n_sets) * tab_stride * 4);
-  Staged s_rows{nullptr, nullptr}, s_start{nullptr, nullptr};
+         s_nb = ring_take(c, (uint64_t)n * 4), s_ts = ring_take(c, (uint64_t)n * 4), s_own = ring_take(c, (uint64_t)n * 4),
+         s_desc = ring_take(c, n_segs * 16), s_tab = ring_take(c, n_segs * stride * 4);
+  Staged s_rows{nullptr, nullptr}, s_start{nullptr, nullptr}, s_set{nullptr, nullptr};
   if (n_sets) {
     s_rows = ring_take(c, set_rows_bytes);
     s_start = ring_take(c, (uint64_t)n_sets * 4);
+    s_set = ring_take(c, (uint64_t)n_sets * set_stride * 4);
   }
   int32_t *hslot = (int32_t*)s_slot.host, *hpos = (int32_t*)s_pos.host, *hnb = (int32_t*)s_nb.host,
-          *hts = (int32_t*)s_ts.host, *htab = (int32_t*)s_tab.host;
+          *hts = (int32_t*)s_ts.host, *htab = (int32_t*)s_tab.host, *hdesc = (int32_t*)s_desc.host;
   for (int i = 0; i < n; ++i) {
     const int id = seq_ids[i];
     SeqInfo& s = c->seqs[id];
@@ -929,25 +931,39 @@ int areal_decode_step(areal_ctx* c, int32_t n, const int32_t* seq_ids, const int
     const size_t had = c->alloc->blocks(id).size();
     c->alloc->reserve(id, pos + 1);
     const auto& blocks = c->alloc->blocks(id);
-    const int skip = t_start[i] / AREAL_KV_BLOCK_TOKENS;
     hslot[i] = id;
     hpos[i] = pos;
     hts[i] = t_start[i];
     hnb[i] = blocks.size() > had ? blocks.back() : -1;
-    int32_t* trow = htab + (size_t)i * tab_stride;
-    memcpy(trow, blocks.data() + skip, (blocks.size() - skip) * 4);
-    for (int b = (int)blocks.size() - skip; b < tab_stride; ++b) trow[b] = 0;
     s.versions.push_back(s.pending_version);
     s.len = pos + 1;
     s.kv_len = pos + 1;
     s.pending_version = c->version;
   }
+  memcpy(s_own.host, plan.n_own.data(), (size_t)n * 4);
+  for (uint64_t q = 0; q < n_segs; ++q) {
+    const DecodeSegment& sg = plan.order[q];
+    int32_t *dst = hdesc + q * 4, *trow = htab + q * stride;
+    dst[0] = sg.row;
+    size_t n_ids = 0;
+    if (sg.row >= 0) {
+      const auto& blocks = c->alloc->blocks(seq_ids[sg.row]);
+      const size_t b0 = (size_t)(t_start[sg.row] + sg.t0) / AREAL_KV_BLOCK_TOKENS;
+      n_ids = std::min(blocks.size() - b0, (size_t)sg.n / AREAL_KV_BLOCK_TOKENS);
+      memcpy(trow, blocks.data() + b0, n_ids * 4);
+      dst[1] = hpos[sg.row];
+      dst[2] = hpos[sg.row] - t_start[sg.row];
+      dst[3] = sg.t0 / kDecodeUnit | sg.n / kDecodeUnit << 12 | sg.slot << 19 |
+               (plan.n_own[sg.row] == 1 && t_start[sg.row] == 0 ? 1 : 0) << 24;
+    }
+    for (size_t b = n_ids; b < stride; ++b) trow[b] = 0;
+  }
   for (int k = 0; k < n_sets; ++k) {
     const RowSet& rs = sets[k];
-    int32_t* trow = htab + (size_t)(n + k) * tab_stride;
+    int32_t* trow = (int32_t*)s_set.host + (size_t)k * set_stride;
     const auto& lead = c->alloc->blocks(seq_ids[rs.rows[0]]);
     memcpy(trow, lead.data(), (size_t)rs.start_blocks * 4);
-    for (int b = rs.start_blocks; b < tab_stride; ++b) trow[b] = 0;
+    for (int b = rs.start_blocks; b < set_stride; ++b) trow[b] = 0;
     int32_t* hrows = (int32_t*)s_rows.host + (size_t)k * kGroupTiles * 16;
     for (int q = 0; q < kGroupTiles * 16; ++q) hrows[q] = -1;
     for (size_t q = 0; q < rs.rows.size(); ++q) hrows[(q / P) * 16 + q % P] = rs.rows[q];
@@ -961,14 +977,16 @@ int areal_decode_step(areal_ctx* c, int32_t n, const int32_t* seq_ids, const int
   a.tokens_in = tokens_in;
   a.new_block = (const int32_t*)s_nb.dev;
   a.decode = true;
-  a.chunk = (int)chunk;
-  a.n_splits = n_splits;
   a.last_rows = nullptr;
   a.n_out = n;
   a.logits = logits_out;
   a.attn_units = (double)sum_ctx;
-  a.step_table = (const int32_t*)s_tab.dev;
-  a.step_stride = tab_stride;
+  a.segs.desc = (const int4*)s_desc.dev;
+  a.segs.table = (const int32_t*)s_tab.dev;
+  a.segs.own = (const int32_t*)s_own.dev;
+  a.segs.n = (int)n_segs;
+  a.segs.stride = (int)stride;
+  a.segs.max_own = plan.max_own;
   for (const RowSet& rs : sets) {
     c->set_rows_sum += (int64_t)rs.rows.size();
     c->set_row_tokens_sum += (int64_t)rs.rows.size() * rs.start_blocks * AREAL_KV_BLOCK_TOKENS;
@@ -981,6 +999,8 @@ int areal_decode_step(areal_ctx* c, int32_t n, const int32_t* seq_ids, const int
     a.groups.n_sets = n_sets;
     a.groups.sh_chunk = sh_chunk;
     a.groups.n_shared = n_shared;
+    a.groups.set_table = (const int32_t*)s_set.dev;
+    a.groups.set_stride = set_stride;
   }
   return run_pass(c, a);
 }

@@ -365,6 +365,51 @@ def test_streaming_controller_follows_the_oracle_event_loop(eta):
         assert r["gen_tokens"] == int(outs.sum()) and not eng.live
 
 
+@pytest.mark.parametrize("own,group,nkv,max_slots,target,min_tokens", [
+    ([1], 1, 2, 32, 0, 256), ([701], 1, 2, 32, 0, 256), ([33, 32, 31, 1], 1, 1, 32, 0, 256),
+    ([65536] + [1] * 7, 1, 4, 32, 0, 256),                       # the longest context in 32 slots, next to one-token rows
+    ([8150, 64, 1000], 1, 1, 32, 65536, 128), ([8150, 64, 1000], 1, 1, 32, 64, 2048),
+    ([16384, 4000], 1, 2, 24, 65536, 128),                       # fewer slots: a set of rows takes the others
+    (list(range(420, 676)), 16, 2, 32, 0, 256),                  # 16 prompts x 16 samples
+    (list(range(1500, 4140, 30)), 1, 2, 32, 0, 256), ([5000] * 16, 16, 2, 32, 0, 256),   # one set: too big for one XCD
+    ([300] * 30 + [9000] * 3, 3, 2, 32, 0, 256)])
+def test_decode_plan_covers_every_token_once(own, group, nkv, max_slots, target, min_tokens):
+    """areal_plan_decode: the segments of a row follow each other without gap from token 0 to the one it appends, at
+    most max_slots of them and 2,048 tokens each; every XCD gets an eighth of the work to within a segment."""
+    H = binding.host_lib()
+    n = len(own)
+    home = [i - i % group for i in range(n)]
+    a, h = np.array(own, np.int32), np.array(home, np.int32)
+    ptr = lambda x: x.ctypes.data_as(binding._I32P)
+    out = np.zeros((4096, 4), np.int32)
+    k = H.areal_plan_decode(n, ptr(a), ptr(h), nkv, max_slots, target, min_tokens, ptr(out), len(out))
+    assert 0 < k <= len(out) and k % 8 == 0
+    out = out[:k]
+    units = -(-a.astype(int) // 32)
+    load = np.zeros(8, int)
+    seen = [[] for _ in range(n)]
+    for q, (row, t0, m, slot) in enumerate(out.tolist()):
+        if row < 0:
+            continue
+        assert 0 < m <= 2048 and m % 32 == 0 and t0 % 32 == 0
+        seen[row].append((slot, t0, m))
+        load[q % 8] += m // 32
+    for i, s in enumerate(seen):
+        s.sort()
+        assert [x[0] for x in s] == list(range(len(s))) and len(s) <= max_slots
+        at = 0
+        for _, t0, m in s:
+            assert t0 == at
+            at += m
+        assert at == units[i] * 32
+    longest = max(m for s in seen for _, _, m in s) // 32
+    assert load.sum() == units.sum() and load.max() <= units.sum() / 8 * 1.05 + longest
+    if group == 16 and n == 256:                                 # the samples of a prompt on at most two XCDs
+        where = [{q % 8 for q in range(k) if out[q, 0] // 16 == p and out[q, 0] >= 0} for p in range(16)]
+        assert max(len(w) for w in where) <= 2
+    assert H.areal_plan_decode(n, ptr(a), ptr(h), nkv, 0, 0, 0, ptr(out), 1) == binding.E_INVAL
+
+
 def test_tile_choice_for_the_decoder_shapes(L):
     """areal_op_gemm_choose (host only): the tile configuration and K split the library takes for
     the products of the 1.5B and 7B shapes, at the row counts where the rules change.  Pins the
