@@ -1154,12 +1154,20 @@ struct NarrowTile {
   int cfg, bm, bn;
   float fixed, cu_gbs, add;            // us, GB/s per compute unit, us per million elements added
 };
-constexpr NarrowTile narrow_tiles[] = {{22, 32, 128, 4.27f, 67.3f, 2.48f}, {23, 64, 96, 4.28f, 70.7f, 2.12f},
-                                       {35, 128, 96, 4.90f, 73.7f, 3.11f}, {21, 128, 128, 3.73f, 66.2f, 2.85f}};
+constexpr NarrowTile narrow_tiles[] = {{22, 32, 128, 4.28f, 67.4f, 2.48f}, {23, 64, 96, 4.30f, 70.1f, 2.11f},
+                                       {35, 128, 96, 4.50f, 70.0f, 3.05f}, {21, 128, 128, 3.73f, 66.2f, 2.85f}};
+// Above 256 rows the tiles of one round of work-groups compete with those of a prefill pass: O of 301 rows 11.1 -> 9.7 us,
+// of 768 19.8 -> 13.1, of 1,024 20.2 -> 13.7; QKV of 301 12.6 -> 10.5, of 512 18.5 -> 12.5, of 768 19.0 -> 13.8; down
+// of 257 22.1 -> 19.8.  Over 45 (product, rows) from 257 to 1,024 the choice is 2 % from the best of 14 tiles on average.
+constexpr NarrowTile one_round_tiles[] = {{23, 64, 96, 4.30f, 70.1f, 2.11f}, {29, 96, 80, 3.96f, 68.9f, 2.79f},
+                                          {35, 128, 96, 3.70f, 67.0f, 3.05f}};
+static float narrow_load(const NarrowTile& t, int M, int N, int K, int splits) {
+  const int nk = K / BK, sps = (nk + splits - 1) / splits, parts = (nk + sps - 1) / sps;
+  return (float)((N + t.bn - 1) / t.bn) * (float)((M + t.bm - 1) / t.bm) * (float)parts / 256.0f;
+}
 static float narrow_us(const NarrowTile& t, int M, int N, int K, int splits) {
   const int nk = K / BK, sps = (nk + splits - 1) / splits, parts = (nk + sps - 1) / sps;
-  const float load = (float)((N + t.bn - 1) / t.bn) * (float)((M + t.bm - 1) / t.bm) * (float)parts / 256.0f;
-  const float rounds = std::max(1.0f, 0.5f * (load + ceilf(load)));
+  const float load = narrow_load(t, M, N, K, splits), rounds = std::max(1.0f, 0.5f * (load + ceilf(load)));
   const float cu = rounds * (float)sps * (float)(t.bm + t.bn) * (0.128f / t.cu_gbs);
   const float mem = (float)N * (float)K * (2e-6f / 7.0f);
   return t.fixed + sqrtf(sqrtf(cu * cu * cu * cu + mem * mem * mem * mem)) +
@@ -1269,7 +1277,7 @@ static int split_for(int M, int bm, int n_tiles, int nk) {
   return 1;
 }
 
-// Tile and K split above 256 rows: the cheapest by prefill_us and evened_us.
+// Tile and K split above 256 rows: the cheapest by prefill_us, narrow_us and evened_us.
 static void prefill_choose(int M, int N, int K, GemmMode mode, int* cfg, int* splits) {
   static const int steps[] = {1, 2, 3, 4, 6, 8, 12};
   const int nk = K / BK;
@@ -1281,6 +1289,12 @@ static void prefill_choose(int M, int N, int K, GemmMode mode, int* cfg, int* sp
       if (us < best) { best = us; *cfg = t.cfg; *splits = sp; }
     }
   }
+  for (const NarrowTile& t : one_round_tiles)
+    for (int sp : steps) {
+      if ((sp > 1 && (sp > max_splits() || 3 * sp > nk)) || narrow_load(t, M, N, K, sp) > 1.0f) break;
+      const float us = narrow_us(t, M, N, K, sp);
+      if (us < best) { best = us; *cfg = t.cfg; *splits = sp; }
+    }
   if (mode == GEMM_ADD_F32 && K >= EVENED_MIN_K && (int64_t)((N + 255) / 256) * ((M + 255) / 256) >= 96) {
     // Configuration 24, by the price of the tiles that it launches: of 192 columns, the work of configuration 26
     // without a split; of 256, whose cut tiles add with atomics: not under a limit of one split.
