@@ -496,7 +496,7 @@ __global__ __launch_bounds__(D < 64 ? 64 : D) void attn_merge_kernel(const float
 // over the two blocks of a stage (slots 0-3: tokens 4g..4g+3 of the first
 // block, slots 4-7: of the second), which is the order the S^T accumulators and
 // the stored V tiles already have.
-constexpr int PF_STAGES = 3;
+constexpr int PF_STAGES = 3;   // eight of them, for passes of few work-groups: 15 -> 19 us for one prompt of 301 tokens
 
 
 // One online-softmax update of all RGW row-groups of a wave over the two blocks
@@ -605,8 +605,15 @@ __global__ __launch_bounds__(256, (D == 128 && RGW == 3) ? 2 : 1) void attn_pref
   constexpr int NI = TILE_B / 1024;       // load instructions per tile = per wave per stage
   __shared__ __attribute__((aligned(16))) char lds[PF_STAGES * STAGE_B];
 
-  const AttnWork wk = work[blockIdx.x];
-  const int kvh = blockIdx.y;
+  // Work comes longest walk first, all KV heads of a tile in a row.  In a pass of 8,192 rows all 512 work-groups are
+  // resident at once, two to a compute unit, and with the tiles in sequence order the two KV heads of the longest walk
+  // shared one: 15 trajectories of 512 - 3,900 tokens 110.7 -> 108.1 ms in whole, attention 145 -> 123 us a launch.  Of two work-groups that share a compute unit the
+  // second 256 are taken from the short end, so that long and short walks pair up; from then on a free place
+  // takes the longest left.
+  int rank = blockIdx.x;
+  if (rank >= 256 && rank < 512) rank = min(511, (int)gridDim.x - 1) - (rank - 256);
+  const AttnWork wk = work[rank / geom.n_kv_heads];
+  const int kvh = rank % geom.n_kv_heads;
   const int G = nq / geom.n_kv_heads;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, j = lane & 15;
@@ -774,7 +781,7 @@ hipError_t launch_attn_merge(hipStream_t s, int M, int head_dim, int n_q_heads, 
   return hipGetLastError();
 }
 
-int attn_prefill_tile_rows(int n_q_heads, int n_kv_heads) {
+int attn_prefill_tile_rows(int n_q_heads, int n_kv_heads, int tiles32) {
   // tuning knob for sweeps: AREAL_PREFILL_TILE_ROWS=16|32 (read once)
   static const int forced = [] {
     const char* e = getenv("AREAL_PREFILL_TILE_ROWS");
@@ -785,18 +792,20 @@ int attn_prefill_tile_rows(int n_q_heads, int n_kv_heads) {
   // (7B shape, 7 query heads per KV head: 532 TFLOP/s with 16 positions against 377 with 32)
   const int G = n_q_heads / n_kv_heads;
   if (forced && (forced == 16 || G <= 8)) return forced;
-  return G <= 6 ? 32 : 16;
+  // Few work-groups: shorter steps of 2 row-groups a wave (one prompt of 64 tokens 1,704 -> 1,683 us, of 301 2,785 ->
+  // 2,773, of 600 the same; 4 of 400 - 800, 150 work-groups: 8,740 -> 8,805).
+  return G <= 6 && tiles32 * n_kv_heads >= 48 ? 32 : 16;
 }
 
 hipError_t launch_attn_prefill(hipStream_t s, const f16* q, const AttnWork* work, int n_work,
-                               SeqState st, const f16* arena_layer, KvGeom geom, int n_q_heads,
+                               SeqState st, const f16* arena_layer, KvGeom geom, int n_q_heads, int tile,
                                f16* out) {
-  if (n_work <= 0 || !geom_ok(geom, n_q_heads)) return hipErrorInvalidValue;
+  if (n_work <= 0 || !geom_ok(geom, n_q_heads) || (tile != 16 && tile != 32) || (tile / 16) * (n_q_heads / geom.n_kv_heads) > 16)
+    return hipErrorInvalidValue;
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)geom.head_dim);
   const int G = n_q_heads / geom.n_kv_heads;
-  const int tile = attn_prefill_tile_rows(n_q_heads, geom.n_kv_heads);
   const int rgw = ((tile / 16) * G + 3) / 4;           // row-groups per wave: 1 .. 4
-  dim3 grid(n_work, geom.n_kv_heads);
+  const int grid = n_work * geom.n_kv_heads;
 #define AREAL_PF(DD, RR)                                                                          \
   attn_prefill_kernel<DD, RR><<<grid, 256, 0, s>>>(q, work, st, arena_layer, geom, n_q_heads, tile, \
                                                    scale_log2, out)

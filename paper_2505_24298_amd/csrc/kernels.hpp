@@ -81,9 +81,10 @@ int gemm_num_configs();
 
 // ---- attention.hip ----------------------------------------------------------
 struct AttnWork {              // prefill work item: a tile of consecutive query rows of one sequence
-  int32_t slot, row0, pos0, n_rows;   // n_rows <= attn_prefill_tile_rows()
+  int32_t slot, row0, pos0, n_rows;   // n_rows <= the pass's tile height
 };
-int attn_prefill_tile_rows(int n_q_heads, int n_kv_heads);   // 16 or 32
+// Query positions of a work item, 16 or 32, for a pass that has `tiles32` items of 32
+int attn_prefill_tile_rows(int n_q_heads, int n_kv_heads, int tiles32);
 // Rows of a decode launch whose sequences hold the same leading KV blocks (the samples of one
 // prompt): those blocks are walked once per set of rows instead of once per row.  A set is up
 // to kGroupTiles MFMA tiles of 16 rows = floor(16 / G) sequences x G query heads each; the
@@ -125,8 +126,8 @@ hipError_t launch_attn_decode(hipStream_t s, const float* qkv, int M, RowMeta rm
 hipError_t launch_attn_merge(hipStream_t s, int M, int head_dim, int n_q_heads, DecodeSegs segs, const float* part_o,
                              const float* part_ml, f16* out, DecodeGroups grp = DecodeGroups{});
 hipError_t launch_attn_prefill(hipStream_t s, const f16* q, const AttnWork* work, int n_work,
-                               SeqState st, const f16* arena_layer, KvGeom geom, int n_q_heads,
-                               f16* out);
+                               SeqState st, const f16* arena_layer, KvGeom geom, int n_q_heads, int tile_rows,
+                               f16* out);       // work: longest walk (pos0 + n_rows) first
 
 // ---- sampler.hip ------------------------------------------------------------
 // `scratch` (optional, device, 16-byte aligned, sampler_scratch_bytes()): lets the launch spread a

@@ -310,7 +310,7 @@ struct PassArgs {
   const int32_t* new_block;       // device or null
   bool decode;
   const AttnWork* work;           // prefill attention work list (device)
-  int n_work;
+  int n_work, tile_rows;
   const int32_t* last_rows;       // device: rows feeding the output projection (null: all rows)
   int n_out;                      // logits rows produced
   float* logits;                  // device [n_out, vocab]
@@ -384,7 +384,7 @@ int run_pass(areal_ctx* c, const PassArgs& a) {
         HIP_TRY(c, launch_rope_kvwrite(s, qkv, a.M, a.rm, st, bq, bk, bv, cos_t, sin_t, q, arena_l, c->geom, nq));
       }
       ProfScope ps(c, AREAL_K_ATTN_PREFILL, l, sampled, a.attn_units);
-      HIP_TRY(c, launch_attn_prefill(s, q, a.work, a.n_work, st, arena_l, c->geom, nq, attn));
+      HIP_TRY(c, launch_attn_prefill(s, q, a.work, a.n_work, st, arena_l, c->geom, nq, a.tile_rows, attn));
     }
     {
       ProfScope ps(c, AREAL_K_GEMM_O, l, sampled, rows);
@@ -466,17 +466,18 @@ int run_spans(areal_ctx* c, const std::vector<Span>& spans, const int32_t* token
               const ScoreArgs* score = nullptr) {
   const areal_model_cfg& g = c->cfg;
   auto passes = plan_passes(spans, g.max_batch_tokens);
-  const int tile_rows = attn_prefill_tile_rows(g.n_q_heads, g.n_kv_heads);
   // span index lookup for token offsets: pieces come in span order
   size_t span_i = 0;
   int done_in_span = 0;
   for (auto& pass : passes) {
-    int M = 0, n_work = 0, n_out = 0;
+    int M = 0, tiles32 = 0, n_work = 0, n_out = 0;
     for (auto& p : pass) {
       M += p.len;
-      n_work += (p.len + tile_rows - 1) / tile_rows;
+      tiles32 += (p.len + 31) / 32;
       if (p.out_index >= 0) ++n_out;
     }
+    const int tile_rows = attn_prefill_tile_rows(g.n_q_heads, g.n_kv_heads, tiles32);
+    for (auto& p : pass) n_work += (p.len + tile_rows - 1) / tile_rows;
     if (score) n_out = 0;                                 // no last-row logits
     const uint64_t bytes = align_up((uint64_t)M * 4, 64) * 5 + align_up((uint64_t)n_work * sizeof(AttnWork), 64) +
                            align_up((uint64_t)std::max(n_out, 1) * 4, 64);
@@ -520,6 +521,8 @@ int run_spans(areal_ctx* c, const std::vector<Span>& spans, const int32_t* token
         done_in_span = 0;
       }
     }
+    std::stable_sort(hwork, hwork + n_work,
+                     [](const AttnWork& x, const AttnWork& y) { return x.pos0 + x.n_rows > y.pos0 + y.n_rows; });
     rc = ring_flush(c, start);
     if (rc) return rc;
     PassArgs a{};
@@ -530,6 +533,7 @@ int run_spans(areal_ctx* c, const std::vector<Span>& spans, const int32_t* token
     a.decode = false;
     a.work = (const AttnWork*)s_work.dev;
     a.n_work = n_work;
+    a.tile_rows = tile_rows;
     a.last_rows = (const int32_t*)s_last.dev;
     a.n_out = n_out;
     a.logits = n_out > 0 ? logits_out + (int64_t)first_out * g.vocab : nullptr;
