@@ -874,14 +874,27 @@ __device__ __forceinline__ void wide_tile(const f16* __restrict__ A, const GemmW
   int cur = 0, kt = kt0;
   const std::true_type yes{};
   const std::false_type no{};
-  // One slab: two K-steps of P pairs of MFMAs, everything else placed between them in a fixed order: fragment reads from
-  // the start of a K-step on, loads spread over the second.  One barrier, between the K-steps: every
-  // wave has its last fragments of the stage (which the loads of slab kt + STAGES then refill), and slab
-  // kt + 1 has landed for every wave.  LOAD: slab kt + STAGES exists; NEXT: slab kt + 1 does.
-  // Tried for gate/up of 8,192 rows, 365 us in a long run: loads two, four or eight at a time 366, 373, 385; a barrier
-  // each for freeing and landing, half a K-step apart, 382; a ring of four or five stages of 32 along K, whose loads
-  // fetch half lines, 396 and 403.
-  constexpr int P = (WideT::MFMAS + 1) / 2, RPP = (WideT::READS * 4 + P * 3 - 1) / (P * 3);
+  // One slab: two K-steps of P pairs of MFMAs, everything else placed between them in a fixed order: fragment reads RPP a
+  // pair, loads one every LSTEP pairs.  LOAD: slab kt + STAGES exists; NEXT: slab kt + 1 does.
+  //   at FREE every wave has its last fragments of the stage (which the loads of slab kt + STAGES then refill),
+  //   at LAND slab kt + 1 has landed for every wave, and its first fragments are read from there on.
+  // Gate/up and scoring in 256 x 256 take both at one barrier between the K-steps.  Tried for gate/up of 8,192 rows, 365 us in
+  // a long run: loads two, four or eight at a time 366, 373, 385; a barrier each, half a K-step apart, 382; a
+  // ring of four or five stages of 32 along K, whose loads fetch half lines, 396 and 403.  The residual adds have
+  // two, which leaves the loads between one and one and a half slabs of time instead of a half and one: down of 2,048
+  // rows in 48 tiles 213 -> 195 us, of 8,192 229 -> 224, in the tiles of its choice 212 -> 186, in 192 x 256 tiles at
+  // 6,768 rows 190 -> 157 inside a prefill.  So have tiles of 24 MFMAs a K-step everywhere (gate/up of 1,024 rows in
+  // 192 x 256 75 -> 67 us, QKV of 4,096 40.3 -> 38.4) and stored 256 x 256 ones (QKV of 8,192 57.4 -> 55.7).
+  constexpr int P = (WideT::MFMAS + 1) / 2;
+  constexpr bool STORES = MODE == GEMM_ADD_F32 || MODE == GEMM_STORE_F32;
+  constexpr bool TWO = (WideT::MFMAS == 24 || (STORES && WideT::MFMAS > 24)) && SHORT == 0 && STAGES == 2;
+  constexpr int FREE = TWO ? P * 3 / 4 : P, LAND = TWO ? P + P / 2 : P;
+  constexpr int RPP = TWO ? (WideT::READS * 2 + P - 1) / P : (WideT::READS * 4 + P * 3 - 1) / (P * 3);
+  // pair behind which load d of a slab goes out, and how many go out ahead of LAND
+  constexpr auto load_at = [](int d) { return TWO ? FREE + 2 * d : FREE + d * P / LPS; };
+  constexpr int EARLY = TWO ? (LAND - FREE + 1) / 2 : 0;
+  static_assert(load_at(LPS - 1) < 2 * P && (!TWO || (EARLY <= LPS && RPP * FREE >= WideT::READS && RPP * (2 * P - LAND) >= WideT::READS)),
+                "a slab's loads and reads go out inside it");
   auto slab = [&](auto load, auto next) {
     constexpr bool LOAD = decltype(load)::value, NEXT = decltype(next)::value;
     const int nxt = cur + 1 == STAGES ? 0 : cur + 1, k_load = min((kt + STAGES) * BK, k_last);
@@ -891,26 +904,31 @@ __device__ __forceinline__ void wide_tile(const f16* __restrict__ A, const GemmW
     for (int z = 0; z < 2 * P; ++z) {
       const typename WideT::Frags& f = z < P ? f0 : f1;
       const int q = z < P ? z : z - P;
-      if (NEXT && z == P) {
-        // a plain barrier: a fence would drain every outstanding load
+      // plain barriers: a fence would drain every outstanding load
+      if (TWO && LOAD && z == FREE) {
         wait_lgkmcnt0();
-        wait_slabs(std::integral_constant<int, STAGES - 2>{});
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (NEXT && z == LAND) {
+        if (!TWO) wait_lgkmcnt0();
+        if constexpr (TWO) wait_vmcnt(LOAD ? EARLY : 0);
+        else wait_slabs(std::integral_constant<int, STAGES - 2>{});
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
       }
       mma1(f, WideT::row(2 * q), WideT::col(2 * q));
       if (2 * q + 1 < WideT::MFMAS) mma1(f, WideT::row(2 * q + 1), WideT::col(2 * q + 1));
-      if (LOAD && z >= P) {
+      if (LOAD) {
 #pragma unroll
         for (int d = 0; d < LPS; ++d)
-          if (d * P / LPS == q) issue1(cur, k_load, d);
+          if (load_at(d) == z) issue1(cur, k_load, d);
       }
 #pragma unroll
-      for (int r = q * RPP; r < (q + 1) * RPP; ++r)
-        if (r < WideT::READS) {
-          if (z < P) read1(f1, base, 1, r);
-          else if (NEXT) read1(f0, base_next, 0, r);
-        }
+      for (int r = 0; r < WideT::READS; ++r) {
+        if (z < P && r / RPP == z) read1(f1, base, 1, r);
+        if (NEXT && z >= LAND && r / RPP == z - LAND) read1(f0, base_next, 0, r);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
     cur = nxt;
@@ -1069,21 +1087,19 @@ hipError_t run(hipStream_t s, const f16* A, const GemmW& W, void* C, int M, int 
 // round at all (36 tiles of 128 x 128 for the down projection of a 301-token prompt: 58 us with 2
 // splits, 22 with 6).  So every candidate is priced in microseconds: a fixed part, the K slabs one
 // compute unit walks (slower the fuller the chip: clocks and L2 are shared), and the adds into C per
-// million elements (with atomics for every split, or read and written once).  Constants: fitted to a
-// sweep over row counts, products of the 1.5B and the 7B shape, tiles and splits, taken before the loads
-// became buffer loads.  Over a sweep taken since (20 row counts x 4 products of the 1.5B shape, 11 x 4 of the
-// 7B shape, 4,154 times) the choice is 1.3 % from the best on average; farthest off are the O and QKV
-// projections at 512 - 900 rows (split 2 would save 2 - 3 us of 19) and O at 3,000 - 4,096 (37 us against 33)
-// and 8,192 (64 against 58).
+// million elements (with atomics for every split, or read and written once).  Constants: fitted to a sweep of
+// 8 products (1.5B and 7B shape) x 8 - 18 row counts from 300 to 8,192 x tiles x splits, 5,558 times on
+// one card; over it the choice, gate/up, small tiles and the evened launch included, is 0.7 % from the best on average;
+// farthest off is down of the 7B shape at 2,048 rows (271 us for 244).
 struct PrefillTile {
   int cfg, bm, bn, per_cu;        // work-groups of this tile a compute unit holds
   float fixed, slab_few, slab_all, add_split, add_whole;
 };
-constexpr PrefillTile TILE_256x192 = {26, 256, 192, 1, 3.12f, 1.20f, 1.44f, 2.66f, 2.50f};
+constexpr PrefillTile TILE_256x192 = {26, 256, 192, 1, 12.54f, 0.715f, 1.157f, 1.758f, 0.846f};
 constexpr PrefillTile prefill_tiles[] = {
-    {19, 256, 256, 1, 5.58f, 1.26f, 1.79f, 2.21f, 1.14f},  {28, 192, 256, 1, 4.39f, 1.02f, 1.41f, 2.33f, 0.41f},
-    TILE_256x192,                                          {27, 128, 192, 1, 5.07f, 0.56f, 0.752f, 2.06f, 1.71f},
-    {21, 128, 128, 1, 5.11f, 0.319f, 0.57f, 1.85f, 0.32f}, {20, 128, 128, 2, 3.64f, 0.571f, 1.06f, 2.02f, 0.25f},
+    {19, 256, 256, 1, 15.0f, 0.878f, 1.549f, 1.691f, 0.911f}, {28, 192, 256, 1, 11.44f, 0.715f, 1.157f, 1.60f, 0.982f},
+    TILE_256x192,                                             {27, 128, 192, 1, 8.62f, 0.471f, 0.711f, 1.682f, 0.968f},
+    {21, 128, 128, 1, 7.57f, 0.368f, 0.58f, 1.297f, 0.599f},  {36, 128, 128, 2, 9.71f, 0.459f, 1.088f, 1.252f, 0.532f},
 };
 static float prefill_us(const PrefillTile& t, int M, int N, int K, int mode, int splits) {
   const int cols = mode == GEMM_SWIGLU_F16 ? t.bn / 2 : t.bn, nk = K / BK;
@@ -1101,11 +1117,11 @@ static float prefill_us(const PrefillTile& t, int M, int N, int K, int mode, int
 constexpr int EVENED_MIN_K = 4096;
 static float evened_us(int M, int N, int K) {
   const float tiles = (float)((N + 255) / 256) * (float)((M + 255) / 256);
-  return 40.3f + tiles * (float)(K / BK) / 256.0f * 1.95f + 0.05f * (float)M * (float)N * 1e-6f;
+  return 45.0f + tiles * (float)(K / BK) / 256.0f * 1.46f + 1.87f * (float)M * (float)N * 1e-6f;
 }
 // Configuration 24 takes tiles of 192 columns instead where these fill every round of 256 compute units, so that
-// nothing is left to cut, and are the cheaper ones: 8,192 x 1,536 x 8,960 (256 tiles) 220 us, 237 in tiles of 256
-// columns; 12,400 x 3,584 x 18,944 (3.6 rounds) 1,514 us evened out, 1,760 in whole tiles of 256 x 192.
+// nothing is left to cut, and are the cheaper ones: 8,192 x 1,536 x 8,960 (256 tiles) 186 us, 219 in whole tiles of 256
+// columns.
 static bool evened_192(int M, int N, int K) {
   return K >= EVENED_MIN_K && (int64_t)((N + 191) / 192) * ((M + 255) / 256) % 256 == 0 &&
          prefill_us(TILE_256x192, M, N, K, GEMM_ADD_F32, 1) <= evened_us(M, N, K);
@@ -1130,8 +1146,8 @@ static float stream_us(const StreamTile& t, int M, int N, int K) {
 }
 // The tiles of a prefill pass by prefill_us, fitted to the same sweep.
 constexpr PrefillTile gateup_tiles[] = {
-    {19, 256, 256, 1, 9.05f, 1.29f, 1.56f, 0.f, 0.f}, {28, 192, 256, 1, 8.13f, 1.24f, 1.28f, 0.f, 0.f},
-    {26, 256, 192, 1, 8.44f, 1.18f, 1.30f, 0.f, 0.f}, {27, 128, 192, 1, 8.22f, 0.64f, 0.71f, 0.f, 0.f},
+    {19, 256, 256, 1, 11.36f, 1.101f, 1.541f, 0.f, 0.f}, {28, 192, 256, 1, 9.03f, 0.833f, 1.17f, 0.f, 0.f},
+    {26, 256, 192, 1, 9.83f, 0.724f, 1.211f, 0.f, 0.f},  {27, 128, 192, 1, 9.73f, 0.837f, 0.687f, 0.f, 0.f},
 };
 static int gateup_choose(int M, int N, int K) {
   int cfg = 0;
@@ -1205,6 +1221,7 @@ hipError_t dispatch(hipStream_t s, int cfg, const f16* A, const GemmW& W, void* 
     case 19: return run_wide<256, 256, 2, 4, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 20:
       if constexpr (MODE == GEMM_SWIGLU_F16) return run_wide<128, 144, 8, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
+      else if constexpr (MODE == GEMM_ADD_F32) return run_wide<256, 192, 4, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
       else return run_dma<128, 128, 4, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 21:
       if constexpr (MODE == GEMM_SWIGLU_F16) return run_wide<128, 80, 8, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
@@ -1241,13 +1258,14 @@ hipError_t dispatch(hipStream_t s, int cfg, const f16* A, const GemmW& W, void* 
     case 33: return run_wide<160, 160, 5, 1, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 34: return run_wide<192, 160, 6, 1, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 35: return run_wide<128, 96, 4, 2, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
+    case 36: return run_dma<128, 128, 4, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
     default: return hipErrorInvalidValue;
   }
 }
 
 }  // namespace
 
-int gemm_num_configs() { return 36; }
+int gemm_num_configs() { return 37; }
 
 // Tile configuration and K split for a product of this shape: rules read off
 // sweeps over every configuration on the MI355X at the decoder's shapes
@@ -1286,7 +1304,8 @@ static void prefill_choose(int M, int N, int K, GemmMode mode, int* cfg, int* sp
     for (int sp : steps) {
       if (sp > 1 && (sp > max_splits() || 3 * sp > nk)) break;
       const float us = prefill_us(t, M, N, K, mode, sp);
-      if (us < best) { best = us; *cfg = t.cfg; *splits = sp; }
+      // residual adds: 20 is the 256 x 192 tile where K is short, 26 where it is long enough for configuration 24
+      if (us < best) { best = us; *cfg = t.cfg == 26 && mode == GEMM_ADD_F32 && K < EVENED_MIN_K ? 20 : t.cfg; *splits = sp; }
     }
   }
   for (const NarrowTile& t : one_round_tiles)
