@@ -68,11 +68,11 @@ __device__ __forceinline__ float scaled_sexp(float x) {
   p = p * r; p = p + 1.0f;
   return __int_as_float(__float_as_int(p) + (((int)n + 32) << 23));
 }
-__device__ __forceinline__ u64 mass_of(float z, float m) {
+__device__ __forceinline__ u64 mass_of_scaled(float w) {
   // below 2^32 the value fits the 32-bit truncating conversion; only w = 1 gives 2^32 itself
-  const float w = scaled_sexp(z - m);
   return w >= 4294967296.0f ? (1ull << 32) : (u64)__float2uint_rz(w);
 }
+__device__ __forceinline__ u64 mass_of(float z, float m) { return mass_of_scaled(scaled_sexp(z - m)); }
 
 // ---- Philox4x32-10 (Salmon et al., SC'11) ----------------------------------
 __device__ __forceinline__ u64 philox_draw(u64 seed, uint32_t seq_id, uint32_t position) {
@@ -90,35 +90,39 @@ __device__ __forceinline__ u64 philox_draw(u64 seed, uint32_t seq_id, uint32_t p
 }
 
 // ---- wave / block primitives on 64-bit integers -----------------------------
-__device__ __forceinline__ u64 shfl_xor_u64(u64 v, int o) {
-  uint32_t lo = __shfl_xor((uint32_t)v, o), hi = __shfl_xor((uint32_t)(v >> 32), o);
-  return ((u64)hi << 32) | lo;
-}
-__device__ __forceinline__ u64 shfl_up_u64(u64 v, int o) {
-  uint32_t lo = __shfl_up((uint32_t)v, o), hi = __shfl_up((uint32_t)(v >> 32), o);
-  return ((u64)hi << 32) | lo;
-}
+// Scans run on DPP adds, which cost an instruction where an exchange through LDS costs a round trip: a 64-bit
+// value as limbs of 24 bits, whose sums over 64 lanes fit 32.
 __device__ __forceinline__ u64 shfl_u64(u64 v, int src) {
   uint32_t lo = __shfl((uint32_t)v, src), hi = __shfl((uint32_t)(v >> 32), src);
   return ((u64)hi << 32) | lo;
 }
-__device__ __forceinline__ u64 wave_sum_u64(u64 v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += shfl_xor_u64(v, o);
-  return v;
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t add_from(uint32_t x) {   // lanes without a source add 0
+  return x + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, false);
 }
-__device__ __forceinline__ u64 wave_incl_scan_u64(u64 v, int lane) {
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const u64 t = shfl_up_u64(v, o);
-    if (lane >= o) v += t;
-  }
-  return v;
+__device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t x) {
+  x = add_from<0x111, 0xF>(x);           // row_shr:1, 2, 4, 8: inside each 16 lanes
+  x = add_from<0x112, 0xF>(x);
+  x = add_from<0x114, 0xF>(x);
+  x = add_from<0x118, 0xF>(x);
+  x = add_from<0x142, 0xA>(x);           // row_bcast:15 into rows 1 and 3
+  return add_from<0x143, 0xC>(x);        // row_bcast:31 into rows 2 and 3
+}
+__device__ __forceinline__ uint32_t last_lane(uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, 63); }
+constexpr uint32_t LIMB = (1u << 24) - 1;
+__device__ __forceinline__ u64 wave_incl_scan_u64(u64 v) {
+  const uint32_t a = wave_incl_scan_u32((uint32_t)v & LIMB), b = wave_incl_scan_u32((uint32_t)(v >> 24) & LIMB),
+                 c = wave_incl_scan_u32((uint32_t)(v >> 48));
+  return (u64)a + ((u64)b << 24) + ((u64)c << 48);
+}
+__device__ __forceinline__ u64 wave_sum_u64(u64 v) {         // v < 2^50 in every lane
+  return (u64)last_lane(wave_incl_scan_u32((uint32_t)v & LIMB)) +
+         ((u64)last_lane(wave_incl_scan_u32((uint32_t)(v >> 24))) << 24);
 }
 // Inclusive scan over the 1024 threads of the block; `total` = sum of all.
 __device__ __forceinline__ u64 block_incl_scan_u64(u64 v, u64* wave_tot, u64& total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  v = wave_incl_scan_u64(v, lane);
+  v = wave_incl_scan_u64(v);
   __syncthreads();                       // wave_tot may still be read from a previous use
   if (lane == 63) wave_tot[wave] = v;
   __syncthreads();
@@ -167,12 +171,7 @@ __device__ __forceinline__ int find_bin(const u64* hist, u64 need, int lane, u64
     if (b < NBINS) chunk += hist[b];
   }
   // suffix[lane] = sum of chunks of lanes >= lane
-  u64 suf = chunk;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const u64 t = shfl_u64(suf, min(lane + o, 63));
-    if (lane + o < 64) suf += t;
-  }
+  const u64 incl = wave_incl_scan_u64(chunk), suf = shfl_u64(incl, 63) - incl + chunk;
   const u64 ok = __ballot(suf >= need);
   const int L = 63 - __builtin_clzll(ok);        // ok != 0: total mass >= need
   int bsel = 0;
@@ -241,8 +240,7 @@ __device__ __forceinline__ void choose_token(const Row& R, int row, int nseg, fl
     // ties before this lane's first id
     uint32_t tie_before = 0;
     if (!all_in) {
-      const u64 incl = wave_incl_scan_u64(tie_lane, lane);
-      tie_before = segtie[sseg] + (uint32_t)(incl - tie_lane);
+      tie_before = segtie[sseg] + wave_incl_scan_u32(tie_lane) - tie_lane;
     }
     u64 lane_sum = 0;
     bool member[4];
@@ -266,7 +264,7 @@ __device__ __forceinline__ void choose_token(const Row& R, int row, int nseg, fl
     if (forced) {
       if ((tok % SEG) / 4 == lane) k_sel = tok & 3;
     } else {
-      const u64 incl = wave_incl_scan_u64(lane_sum, lane);
+      const u64 incl = wave_incl_scan_u64(lane_sum);
       u64 run = base + incl - lane_sum;
       if (run <= r && r < run + lane_sum) {
 #pragma unroll
@@ -328,7 +326,7 @@ __device__ __forceinline__ void segments_above(const Row& R, int nseg, float m, 
       if (in && c == tau) tie += 1;
     }
     gt = wave_sum_u64(gt);
-    tie = (uint32_t)wave_sum_u64(tie);
+    tie = last_lane(wave_incl_scan_u32(tie));
     if (lane == 0) { L.segmass[s] = gt; L.segtie[s] = tie; }
   }
   __syncthreads();
@@ -494,10 +492,11 @@ struct SplitScratch {                          // one row's share of the scratch
 };
 static_assert(sizeof(SplitScratch) == SAMPLER_SCRATCH_ROW && sizeof(SplitScratch) % 16 == 0, "scratch layout");
 
-__device__ __forceinline__ int log_bin(u64 c) {
-  if (c < 64) return (int)c;
-  const int e = 63 - __builtin_clzll(c);       // 6 .. 32
-  return (e - 5) * 64 + ((int)(c >> (e - 6)) & 63);
+// Bin of the mass of a scaled exponential w >= 0: c itself below 64, else octave and next six bits of c = trunc(w), which
+// are exponent and leading fraction bits of w, for truncation leaves the leading seven bits of a number of 64 and more.
+__device__ __forceinline__ int log_bin(float w) {
+  const int top = (__float_as_int(fminf(w, 4294967296.0f)) >> 17) - ((127 + 5) << 6);
+  return w < 64.0f ? (int)w : top;
 }
 __device__ __forceinline__ u64 log_bin_low(int b) {    // smallest mass of a bin
   return b < 64 ? (u64)b : (u64)(64 + (b & 63)) << ((b >> 6) - 1);
@@ -592,8 +591,9 @@ __global__ __launch_bounds__(TPB) void sampler_split_pick_kernel(
 // of logarithmic bins, which locates the bin the threshold falls into to 1.6 % of its value; (3) the
 // kept mass of the bins above, per segment, and the list of that one bin's ids; (4) per row, the exact
 // threshold by radix select over the list, ties in id order, the draw.  The exponential is evaluated
-// twice per id, on all compute units: 64 rows of 151,936 logits 566 -> 61 us, 1 row 530 -> 27, 128 rows
-// 576 -> 90 (bound by the exponential's arithmetic and four launches).  A bin of one value (every mass
+// twice per id, on all compute units: 64 rows of 151,936 logits 566 -> 57 us, 1 row 530 -> 28, 128 rows
+// 576 -> 84 (bound by the exponential's arithmetic and four launches; 61 and 91 us with exchanges through LDS for the
+// wave sums, 64-bit shifts for the bins and 8 bits at a time in the list.  Loading four segments ahead: no change).  A bin of one value (every mass
 // below 128, and 2^32: the maximum itself) needs no list but its ids per segment; for a bin with more
 // ids than the list holds see nucleus_in_bin.
 __global__ __launch_bounds__(SPLIT_TPB) void sampler_split_hist_kernel(int V, const float* __restrict__ logits,
@@ -612,8 +612,9 @@ __global__ __launch_bounds__(SPLIT_TPB) void sampler_split_hist_kernel(int V, co
     load_z4(R, sg * SEG + lane * 4, z);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const u64 c = mass_of(z[k], m);                  // 0 beyond the vocabulary
-      const int bin = log_bin(c);
+      const float w = scaled_sexp(z[k] - m);
+      const u64 c = mass_of_scaled(w);                 // 0 beyond the vocabulary
+      const int bin = log_bin(w);
       const int bin0 = __builtin_amdgcn_readfirstlane(bin);
       if (__all(bin == bin0)) {                        // heavily tied logits: once per wave
         const u64 tot = wave_sum_u64(c);
@@ -643,7 +644,7 @@ __device__ __forceinline__ int bin_from_top(const u64* hist, Need need_of, u64* 
     h[k] = b >= 0 ? hist[b] : 0;
     mine += h[k];
   }
-  const u64 incl_w = wave_incl_scan_u64(mine, lane);
+  const u64 incl_w = wave_incl_scan_u64(mine);
   if (lane == 63) wtot[wave] = incl_w;
   if (tid == 0) { *res_int = 0; *res_u64 = 0; }
   __syncthreads();
@@ -745,6 +746,10 @@ __global__ __launch_bounds__(SPLIT_TPB) void sampler_split_collect_kernel(int V,
   if (threadIdx.x == 0) n_list = 0;
   u64 S_total, target, above;
   const int tb = threshold_bin<SPLIT_WAVES>(sc, top_p, wtot, &res_u64, &res_int, S_total, target, above);
+  // Ids below the threshold's bin add nothing, and for a wave whose ids all are the exponential need not be
+  // evaluated: below x_skip their masses are less than the bin's lowest by a thousandth at least, far beyond
+  // the specified exponential's error.
+  const float x_skip = (float)(log((double)log_bin_low(tb)) - 32.0 * 0.69314718055994530942) - 1e-3f;   // -inf for bin 0
   auto walk = [&](auto one_value) {
     for (int sg = part * SPLIT_WAVES + wave; sg < nseg; sg += parts * SPLIT_WAVES) {
       float z[4];
@@ -753,8 +758,10 @@ __global__ __launch_bounds__(SPLIT_TPB) void sampler_split_collect_kernel(int V,
       int ties = 0;
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const u64 c = mass_of(z[k], m);
-        const int bin = log_bin(c);
+        if (!__any(!(z[k] - m < x_skip))) continue;
+        const float w = scaled_sexp(z[k] - m);
+        const u64 c = mass_of_scaled(w);
+        const int bin = log_bin(w);
         const bool in = bin == tb && sg * SEG + lane * 4 + k < V;
         if (bin > tb) gt += c;
         if constexpr (decltype(one_value)::value) {
@@ -791,7 +798,7 @@ __global__ __launch_bounds__(TPB) void sampler_split_nucleus_pick_kernel(
   __shared__ NucleusLds L;
   __shared__ u64 offset_hist[OFFSET_BINS];
   constexpr int PER = LIST_CAP / TPB;
-  const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int row = blockIdx.x, tid = threadIdx.x;
   const Row R = make_row(logits, row, V, inv_t);
   const SplitScratch& sc = scratch[row];
   const int nseg = (V + SEG - 1) / SEG;
@@ -822,43 +829,28 @@ __global__ __launch_bounds__(TPB) void sampler_split_nucleus_pick_kernel(
       d[k] = i < n ? sc.list[i][1] - (uint32_t)low : 0;          // < 2^26: the width of the widest bin
     }
     if (tid < nseg) { L.segmass[tid] = sc.segmass[tid]; L.segtie[tid] = 0; }
-    // radix select on the offsets, 8 bits at a time from the bin's own width down
-    const int width_bits = log_bin_width(tb);
-    uint32_t prefix = 0, cnt = n;
-    for (int top = width_bits; top > 0;) {
-      const int shift = max(0, top - 8), bits = top - shift;
-      for (int b = tid; b < NBINS; b += TPB) { L.hist_mass[b] = 0; L.hist_cnt[b] = 0; }
+    // radix select on the offsets, 13 bits at a time from the bin's own width down: two rounds at the widest bin
+    uint32_t prefix = 0;
+    for (int top = log_bin_width(tb); top > 0;) {
+      const int shift = max(0, top - OFFSET_BITS), bits = top - shift;
+      for (int b = tid; b < OFFSET_BINS; b += TPB) offset_hist[b] = 0;
       __syncthreads();
 #pragma unroll
-      for (int k = 0; k < PER; ++k) {
-        if (tid + k * TPB < n && (d[k] >> top) == prefix) {
-          const int bin = (d[k] >> shift) & ((1u << bits) - 1u);
-          atomicAdd(&L.hist_mass[bin], low + d[k]);
-          atomicAdd(&L.hist_cnt[bin], 1u);
-        }
-      }
+      for (int k = 0; k < PER; ++k)
+        if (tid + k * TPB < n && (d[k] >> top) == prefix)
+          atomicAdd(&offset_hist[(d[k] >> shift) & ((1u << bits) - 1u)], low + d[k]);
       __syncthreads();
-      if (wave == 0) {
-        u64 above;
-        const int b = find_bin(L.hist_mass, target - mass_above, lane, above);
-        if (lane == 0) {
-          L.sh_int[0] = b;
-          L.sh_u64[0] = mass_above + above;
-          L.sh_int[1] = (int)L.hist_cnt[b];
-        }
-      }
-      __syncthreads();
-      prefix = (prefix << bits) | (uint32_t)L.sh_int[0];
-      mass_above = L.sh_u64[0];
-      cnt = (uint32_t)L.sh_int[1];
-      __syncthreads();
+      u64 above;
+      const int b = bin_from_top<NWAVES, OFFSET_BINS>(offset_hist, [&](u64) { return target - mass_above; }, L.wave_tot,
+                                                      &L.sh_u64[2], &L.sh_int[3], above);
+      mass_above += above;
+      prefix = (prefix << bits) | (uint32_t)b;
       top = shift;
+      __syncthreads();                                 // the histogram and the broadcast slots are free again
     }
     tau = low + prefix;
     n_take = (target - mass_above + tau - 1) / tau;
-    if (n_take > cnt) n_take = cnt;                    // cannot happen; keeps indices sane
     S_nuc = mass_above + n_take * tau;
-    __syncthreads();                                   // segmass, segtie before the atomics
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
       if (tid + k * TPB < n) {

@@ -182,3 +182,27 @@ def test_nucleus_of_flat_rows(V, n, top_p):
     _check(eng, logits, 1.0, top_p, seed=21)
     _check(eng, logits, 5.0, top_p, seed=4, forced=rng.integers(0, V, size=n))
     eng.close()
+
+
+@pytest.mark.parametrize("top_p", [0.3, 0.6, 0.9])
+@pytest.mark.parametrize("octave", [0, -3, -9])
+def test_nucleus_threshold_next_to_a_bin_boundary(octave, top_p):
+    """Runs of ids whose masses lie on the lowest mass of a bin and one float above and below it: whole waves fall on
+    either side of what the collecting pass leaves out, and the bins come from the floats' leading bits."""
+    V = 48 * 256
+    eng = _engine_for_vocab(V)
+    rng = np.random.default_rng(17)
+    n = 8
+    logits = np.full((n, V), -30.0, np.float32)
+    for i in range(n):
+        edge = np.float32(np.log(2.0 ** octave * (1 + i / 64.0)) - 2.0)      # bins have 64 steps per octave
+        near = [edge]
+        for _ in range(2):
+            near = [np.nextafter(near[0], np.float32(-90))] + near + [np.nextafter(near[-1], np.float32(90))]
+        near += [np.float32(edge - 1e-3), np.float32(edge - 2e-3), np.float32(edge + 1e-3)]
+        for k, x in enumerate(near):
+            logits[i, 512 * k:512 * k + 256 + k] = x
+        logits[i, rng.integers(0, V, 3)] = 0.0
+    _check(eng, logits, 1.0, top_p, seed=5)
+    _check(eng, logits, 1.0, top_p, seed=6, forced=rng.integers(0, V, size=n))
+    eng.close()
