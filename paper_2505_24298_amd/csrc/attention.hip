@@ -598,7 +598,7 @@ __device__ __forceinline__ void attend_pairs(const char* __restrict__ stage, con
 template <int D, int RGW>
 __global__ __launch_bounds__(256, (D == 128 && RGW == 3) ? 2 : 1) void attn_prefill_kernel(
     const f16* __restrict__ q, const AttnWork* __restrict__ work, SeqState st,
-    const f16* __restrict__ arena, KvGeom geom, int nq, int tile_pos, float scale_log2,
+    const f16* __restrict__ arena, KvGeom geom, int nq, int tile_pos, int head_parts, float scale_log2,
     f16* __restrict__ out) {
   constexpr int TILE_B = 16 * D * 2;      // bytes of one K or V tile
   constexpr int STAGE_B = 4 * TILE_B;     // two blocks x (K, V)
@@ -612,9 +612,12 @@ __global__ __launch_bounds__(256, (D == 128 && RGW == 3) ? 2 : 1) void attn_pref
   // takes the longest left.
   int rank = blockIdx.x;
   if (rank >= 256 && rank < 512) rank = min(511, (int)gridDim.x - 1) - (rank - 256);
-  const AttnWork wk = work[rank / geom.n_kv_heads];
-  const int kvh = rank % geom.n_kv_heads;
-  const int G = nq / geom.n_kv_heads;
+  const int of_tile = geom.n_kv_heads * head_parts;
+  const AttnWork wk = work[rank / of_tile];
+  const int kvh = rank % of_tile / head_parts, part = rank % head_parts;
+  // this work-group's query heads: head0 .. head0 + n_heads - 1 of the G that share the kv head
+  const int G = (nq / geom.n_kv_heads + head_parts - 1) / head_parts;
+  const int head0 = kvh * (nq / geom.n_kv_heads) + part * G, n_heads = min(G, nq / geom.n_kv_heads - part * G);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, j = lane & 15;
   const int n_rg = (tile_pos / 16) * G;
@@ -631,9 +634,9 @@ __global__ __launch_bounds__(256, (D == 128 && RGW == 3) ? 2 : 1) void attn_pref
 #pragma unroll
   for (int r = 0; r < RGW; ++r) {
     const int rg = wave * RGW + r;
-    const int pos_blk = rg / G, head = kvh * G + rg % G;
+    const int pos_blk = rg / G, head = head0 + rg % G;
     const int row_in = pos_blk * 16 + j;
-    const bool active = rg < n_rg && pos_blk * 16 < wk.n_rows;
+    const bool active = rg < n_rg && rg % G < n_heads && pos_blk * 16 < wk.n_rows;
     const bool ok = active && row_in < wk.n_rows;
     gmax[r] = active ? wk.pos0 + min(wk.n_rows, pos_blk * 16 + 16) - 1 : -1;
     rpos[r] = ok ? wk.pos0 + row_in : gmax[r];
@@ -700,7 +703,7 @@ __global__ __launch_bounds__(256, (D == 128 && RGW == 3) ? 2 : 1) void attn_pref
 #pragma unroll
   for (int r = 0; r < RGW; ++r) {
     const int rg = wave * RGW + r;
-    const int pos_blk = rg / G, head = kvh * G + rg % G;
+    const int pos_blk = rg / G, head = head0 + rg % G;
     float lr = l[r];
     lr += __shfl_xor(lr, 16);
     lr += __shfl_xor(lr, 32);
@@ -792,9 +795,8 @@ int attn_prefill_tile_rows(int n_q_heads, int n_kv_heads, int tiles32) {
   // (7B shape, 7 query heads per KV head: 532 TFLOP/s with 16 positions against 377 with 32)
   const int G = n_q_heads / n_kv_heads;
   if (forced && (forced == 16 || G <= 8)) return forced;
-  // Few work-groups: shorter steps of 2 row-groups a wave (one prompt of 64 tokens 1,704 -> 1,683 us, of 301 2,785 ->
-  // 2,773, of 600 the same; 4 of 400 - 800, 150 work-groups: 8,740 -> 8,805).
-  return G <= 6 && tiles32 * n_kv_heads >= 48 ? 32 : 16;
+  // Up to one 32-row work-group per compute unit: 16 rows, their heads over two work-groups (launch_attn_prefill)
+  return G <= 6 && tiles32 * n_kv_heads > 256 ? 32 : 16;
 }
 
 hipError_t launch_attn_prefill(hipStream_t s, const f16* q, const AttnWork* work, int n_work,
@@ -804,11 +806,17 @@ hipError_t launch_attn_prefill(hipStream_t s, const f16* q, const AttnWork* work
     return hipErrorInvalidValue;
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)geom.head_dim);
   const int G = n_q_heads / geom.n_kv_heads;
-  const int rgw = ((tile / 16) * G + 3) / 4;           // row-groups per wave: 1 .. 4
-  const int grid = n_work * geom.n_kv_heads;
+  // A launch of few work-groups lives on its longest walk: a tile's query heads go to two work-groups, whose
+  // steps have one row-group a wave (32 rows: three, 16: two).  Whole prefill at the 1.5B shape, one head part of 32 or
+  // 16 rows -> two of 16: one prompt of 301 tokens 2,766 -> 2,640 us, 600 3,886 -> 3,685, 1,000 5,769 -> 5,415, 2,000
+  // 8,568 -> 8,020; 4 of 400 - 800 8,731 -> 8,598; 2 of 1,800 - 2,000 12,795 -> 12,406; beyond 512 work-groups of 16
+  // rows it costs (8 of 500 - 700: 14,320 -> 14,390; a scoring pass of 8,192 rows 104.8 -> 107.4 ms).
+  const int head_parts = tile == 16 && G >= 5 && G <= 8 && 2 * n_work * geom.n_kv_heads <= 1024 ? 2 : 1;
+  const int rgw = ((tile / 16) * ((G + head_parts - 1) / head_parts) + 3) / 4;           // row-groups per wave: 1 .. 4
+  const int grid = n_work * geom.n_kv_heads * head_parts;
 #define AREAL_PF(DD, RR)                                                                          \
   attn_prefill_kernel<DD, RR><<<grid, 256, 0, s>>>(q, work, st, arena_layer, geom, n_q_heads, tile, \
-                                                   scale_log2, out)
+                                                   head_parts, scale_log2, out)
 #define AREAL_PF_D(DD)                                                                            \
   switch (rgw) {                                                                                  \
     case 1: AREAL_PF(DD, 1); break;                                                               \

@@ -226,6 +226,19 @@ def test_head_geometries(torch, binding, nq, nkv, d):
     assert dl <= LOGIT_TOL and dlb <= LOGP_TOL and dlf <= LOGP_TOL
 
 
+@pytest.mark.parametrize("nq,nkv,d", [(5, 1, 128), (12, 2, 64), (7, 1, 32)])
+def test_query_heads_of_a_tile_over_two_work_groups(torch, binding, nq, nkv, d):
+    """Small passes give the query heads of a prefill tile to two work-groups: uneven halves (3 + 2, 4 + 3), prompts that
+    end on and next to the 16 positions of a tile, and a pass of one row."""
+    cfg = synth.shape("tiny", n_q_heads=nq, n_kv_heads=nkv, head_dim=d, hidden=128, ffn=192)
+    w = synth.random_gains(synth.make_weights(cfg, 60 + nq, qkv_bias=True, std=0.04), 7)
+    rng = np.random.default_rng(nq)
+    prompts = [rng.integers(0, cfg["vocab"], size=n).astype(np.int32) for n in (1, 16, 17, 31, 160)]
+    dl, dlb, dlf = _teacher_forced_run(torch, binding, cfg, w, prompts, 3, qkv_bias=True, max_batch_tokens=65, kv_blocks=64)
+    print(f"heads {nq}/{nkv} d{d}: logits {dl:.2e}  logp_behav {dlb:.2e}  logp_full {dlf:.2e}")
+    assert dl <= LOGIT_TOL and dlb <= LOGP_TOL and dlf <= LOGP_TOL
+
+
 @pytest.mark.parametrize("hidden,ffn", [(200, 344), (4608, 320), (8192, 192)])
 def test_hidden_sizes(torch, binding, hidden, ffn):
     """Hidden sizes off the 64-wide K slabs (register-staged GEMM path for every
