@@ -29,32 +29,50 @@ struct DecodePlan {
 // 30.3 us and a merge of 4.9 -> 25.1 and none; 88 rows of 1,500 - 4,100 54.1 -> 51.1; 24 of 4,000 - 8,200 37.0 -> 32.5; one
 // of 700 10.1 -> 7.3; 7B shape, 128 rows of 500 - 3,800 116.8 -> 106.4.
 //
+// Units of a row's segments (its last one may be shorter), aimed at `share`: cut evenly, then up to whole rounds of a
+// work-group's four waves (a wave takes every fourth unit, so an uneven round leaves some without one).
+inline int decode_segment_units(int units, int share) {
+  const int k = (units + share - 1) / share;
+  return k == 1 ? units : std::min(((units + k - 1) / k + 3) / 4 * 4, kDecodeMaxUnits);
+}
+
 // Units per segment, by price.  In microseconds: every unit of 32 tokens (16 KB a KV head) at 6.2 TB/s over the
-// chip's 512 resident work-groups, or in 0.65 where few work-groups run and a unit is a round trip; a work-group's start (block ids, then tiles: two round trips) and its end; what the last ones
-// leave idle, half a segment, or, where all are resident at once, what the longest takes more than the mean; and the
-// merge launch if any row is cut at all.
+// chip's 512 resident work-groups; a work-group's start (block ids, then tiles: two round trips), its end and its
+// partials; what the last ones leave idle; and the merge launch if any row is cut at all.  Where all are resident at
+// once, a compute unit that has two still takes 1.34 us for a unit of each, however few others there are (352
+// work-groups of 51 units: 68 us, 880 of 24: 62), one that has one about 0.65.  With that and with whole rounds, against
+// even cuts priced as if any number of work-groups streamed at the full rate: launches of 157 rows of 1,725 tokens
+// 71.9 -> 61.8 us, 88 of 3,217 71.4 -> 66.4, 44 of 5,204 57.7 -> 53.0 (steps 3.52 -> 3.40 ms, 3.26 -> 3.14, 2.77 -> 2.62);
+// rows of many lengths, as in the figures above, the same to 2 % better.
+inline double decode_price(const std::vector<int>& units, int n_kv_heads, int share) {
+  int64_t segs = 0, total = 0;
+  int longest = 0;
+  bool cut = false;
+  for (int u : units) {
+    const int len = decode_segment_units(u, share);
+    segs += (u + len - 1) / len;
+    total += u;
+    longest = std::max(longest, len);
+    cut |= len < u;
+  }
+  const double wgs = (double)segs * n_kv_heads, rounds = wgs / 512.0, mean = (double)total * n_kv_heads / wgs;
+  const double streamed = (double)total * n_kv_heads * (1.34 / 512.0);
+  double us;
+  if (rounds > 1.0) {
+    us = streamed + 1.5 * rounds + 0.25 * longest;
+  } else {
+    us = std::max(wgs > 256.0 ? 1.34 * mean : std::max(streamed, 0.65 * mean), 0.65 * longest + 3.4);
+    us += rounds + 0.5 * (longest - mean);
+  }
+  return us + (cut ? 4.5 : 0.0);
+}
 inline int decode_share(const std::vector<int>& units, int n_kv_heads, int lo, int hi) {
-  static const int steps[] = {4, 5, 6, 8, 10, 12, 16, 20, 24, 28, 32, 40, 48, 64};
-  double total = 0;
-  for (int u : units) total += u;
-  total *= n_kv_heads;
+  static const int steps[] = {4, 8, 12, 16, 20, 24, 28, 32, 40, 48, 64};
   int best = hi;
   double best_us = 1e30;
   for (int s : steps) {
     if (s < lo || s > hi) continue;
-    int64_t segs = 0;
-    int longest = 0;
-    bool cut = false;
-    for (int u : units) {
-      const int k = (u + s - 1) / s;
-      segs += k;
-      longest = std::max(longest, (u + k - 1) / k);
-      cut |= k > 1;
-    }
-    const double wgs = (double)segs * n_kv_heads, rounds = wgs / 512.0, mean = total / wgs;
-    double us = std::max(total * (1.34 / 512.0), 0.65 * longest + 3.4) + rounds;
-    us += rounds > 1.0 ? 0.67 * longest : 0.5 * (longest - mean);
-    if (cut) us += 4.5;
+    const double us = decode_price(units, n_kv_heads, s);
     if (us < best_us) { best_us = us; best = s; }
   }
   return best;
@@ -93,12 +111,11 @@ inline DecodePlan plan_decode(const std::vector<int32_t>& own, const std::vector
   } else {
     p.share = decode_share(units, n_kv_heads, lo, kDecodeMaxUnits);
   }
-  p.share = std::min(std::max(p.share, lo), kDecodeMaxUnits);
+  p.share = std::min((std::max(p.share, lo) + 3) / 4 * 4, kDecodeMaxUnits);
   p.n_own.resize(n);
   std::vector<int> len(n);                                // units per segment of a row
   for (int i = 0; i < n; ++i) {
-    const int k = (units[i] + p.share - 1) / p.share;
-    len[i] = (units[i] + k - 1) / k;
+    len[i] = decode_segment_units(units[i], p.share);
     p.n_own[i] = (units[i] + len[i] - 1) / len[i];
     p.max_own = std::max(p.max_own, (int)p.n_own[i]);
     p.max_units = std::max(p.max_units, len[i]);

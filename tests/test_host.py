@@ -402,6 +402,8 @@ def test_decode_plan_covers_every_token_once(own, group, nkv, max_slots, target,
             assert t0 == at
             at += m
         assert at == units[i] * 32
+        # all but a cut row's last segment are whole rounds of four waves of 32 tokens
+        assert all(m % 128 == 0 for _, _, m in s[:-1])
     longest = max(m for s in seen for _, _, m in s) // 32
     assert load.sum() == units.sum() and load.max() <= units.sum() / 8 * 1.05 + longest
     if group == 16 and n == 256:                                 # the samples of a prompt on at most two XCDs
