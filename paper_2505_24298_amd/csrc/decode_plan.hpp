@@ -85,7 +85,7 @@ inline int decode_share_for(int64_t total_units, int n_kv_heads, int target, int
 }
 
 // own[i]: tokens of row i from its first own one to the one it appends (>= 1).  home[i]: the row's first KV block; rows
-// with the same one hold leading blocks together.  Rows are cut evenly into at most max_slots segments.  target > 0: so
+// with the same one hold leading blocks together.  Rows are cut into at most max_slots segments.  target > 0: so
 // that there are about that many work-groups, no segment aimed shorter than min_tokens (tuning); 0: by price.
 // at_least: lower limit of the share.
 //

@@ -262,7 +262,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const f16* __restric
 // a lane adds one 32-bit offset.  With 24 slabs per tile (K = 1,536) the two waves of a SIMD spent about
 // a seventh of a gate/up tile here on bounds, 64-bit addresses, divisions and half-word stores:
 // 8,192 x 17,920 x 1,536 took 454 us, 424 with this form (on one card, with the loads and the slab order of that
-// time; see dma_tile).  The division in silu is 16 us of such a product: 422 us with an approximate reciprocal
+// time: dma_tile; wide_tile has these products now).  The division in silu is 16 us of such a product: 422 us with an approximate reciprocal
 // in its place, 437 with it.
 template <int BM, int BN, int WM, int WN, int MODE, bool FULL>
 __device__ __forceinline__ void store_tile_part(const f32x16 (&acc)[BM / WM / 32][BN / WN / 32],
@@ -488,7 +488,7 @@ __device__ __forceinline__ void dma_tile(const f16* __restrict__ A, const GemmW&
   // overlapped shows: with the barrier at the slab's start and every wait for fragments a wait for all
   // of them, gate/up at 8,192 rows took 444 us and at 2,048 rows 136; so 423 and 127 (7B shape, 4,096
   // rows: 1,012 -> 961 us; its down projection 532 -> 500; another card than the 424 us of the epilogue's
-  // comment).  In a scoring pass gate/up at 8,192 rows takes 420 us, 450 before epilogue, loads and this order.
+  // comment).  These products have since gone over to wide_tile.
   Frags f0, f1;
   if (kt0 >= kt1) return;
   const int k_last = (kt1 - 1) * BK;
@@ -562,16 +562,18 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_dma_kernel(const f16* __res
 // and the 16x16x32 one, which adds into its accumulators half as often, 1.97; with the tile's
 // fragment reads 1.58 and 1.78, and 1.86 in the order below (zeros: 2.45 all of them).
 //
-// Tile, ring and loads are those of dma_tile.  A slab is two K-steps of 32; a wave's (BM/WM) x (BN/WN)
-// part is TM x TN MFMAs of 16 x 16, taken in blocks of 2 x 2 that turn round at the end of a row of
-// blocks, so that of two MFMAs in a row one operand is the same wherever possible: fewer bits toggle.
+// Ring and swizzle are those of dma_tile, without the skew; the row groups of a slab are dealt to the waves in turn, so
+// that a tile need not divide evenly over them.  A slab is two K-steps of 32; a wave's (BM/WM) x (BN/WN) part is
+// TM x TN MFMAs of 16 x 16, taken in bands of two rows, column by column, there and back: of two MFMAs in a row
+// one operand is always the same, and fewer bits toggle.
 // Gate/up and scoring form W A^T: a lane then holds neighbouring columns of one row (lane & 15), which it stores as
 // 16 bytes or folds by itself.  Stored and added float32 tiles are A W^T, column lane & 15 of four neighbouring
 // rows in a lane: an atomic instruction then adds 64 contiguous bytes per row, not 16 (2.4 times the time for QKV
 // of 301 rows in 3 K splits).
-// Measured, one card, 1.5B shape: gate/up of 8,192 rows 440 -> 387 us (1,165 TFLOP/s), of 2,048 127 -> 117; down of
-// 8,192 222 -> 209, of 6,768 207 -> 193; QKV of 6,768 54.4 -> 51.6.  128 x 128 tiles gain nothing (their runs are short) and
-// stay with dma_tile.
+// Measured, 1.5B shape, inside scoring passes of 8,192 rows, against the 32x32x16 MFMA (two cards): gate/up 401 -> 370 us
+// (1,218 TFLOP/s, matrix cores busy 70 % of the time at 1.75 GHz), down 206 -> 182 (with two barriers a slab, below),
+// QKV 52 -> 49, O in 256 x 192 for 128 x 128 tiles 54 -> 46, output projection with its log-sum-exp 3,462 -> 3,035.  128 x 128 tiles of stored and added results gain nothing (their runs are short) and stay
+// with dma_tile.
 constexpr int WIDE_GROUP = 1024;        // 8 tile rows x 128 B: these reads have no bank conflicts without a skew
 template <int TM, int TN>
 struct Wide {
@@ -875,7 +877,8 @@ __device__ __forceinline__ void wide_tile(const f16* __restrict__ A, const GemmW
   const std::true_type yes{};
   const std::false_type no{};
   // One slab: two K-steps of P pairs of MFMAs, everything else placed between them in a fixed order: fragment reads RPP a
-  // pair, loads one every LSTEP pairs.  LOAD: slab kt + STAGES exists; NEXT: slab kt + 1 does.
+  // pair, loads spread over the second K-step, or one every second pair (TWO).  LOAD: slab kt + STAGES exists; NEXT:
+  // slab kt + 1 does.
   //   at FREE every wave has its last fragments of the stage (which the loads of slab kt + STAGES then refill),
   //   at LAND slab kt + 1 has landed for every wave, and its first fragments are read from there on.
   // Gate/up and scoring in 256 x 256 take both at one barrier between the K-steps.  Tried for gate/up of 8,192 rows, 365 us in
@@ -1250,7 +1253,7 @@ hipError_t dispatch(hipStream_t s, int cfg, const f16* A, const GemmW& W, void* 
       if constexpr (MODE != GEMM_SWIGLU_F16) return run_wide<128, 192, 4, 2, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
       else return run_wide<128, 192, 4, 1, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 28: return run_wide<192, 256, 2, 4, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
-    // see StreamTile
+    // gate/up by StreamTile; 29 and 35 also stored and added by NarrowTile
     case 29: return run_wide<96, 80, 6, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 30: return run_wide<64, 160, 4, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 31: return run_wide<96, 160, 6, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
@@ -1267,9 +1270,9 @@ hipError_t dispatch(hipStream_t s, int cfg, const f16* A, const GemmW& W, void* 
 
 int gemm_num_configs() { return 37; }
 
-// Tile configuration and K split for a product of this shape: rules read off
-// sweeps over every configuration on the MI355X at the decoder's shapes
-// (`cfg` / `splits` >= 0 in launch_gemm_cfg override them).
+// Tile configuration and K split for a product of this shape: the cheapest by prices fitted to
+// sweeps over the configurations on the MI355X at the decoder's shapes, a few rules by row count
+// beside them (`cfg` / `splits` >= 0 in launch_gemm_cfg override them).
 // Upper limit of the K split (tuning knob for sweeps: AREAL_GEMM_MAX_SPLITS, read once).
 static int max_splits() {
   static const int v = [] {
@@ -1280,7 +1283,7 @@ static int max_splits() {
   return v;
 }
 
-// Largest K split that keeps every XCD at one round of work-groups (32 CUs, one
+// Ragged K: the largest K split that keeps every XCD at one round of work-groups (32 CUs, one
 // work-group each): units of (column tile, split) go to the XCDs round-robin, each with
 // m_tiles work-groups.  Each split keeps at least 3 slabs.  Beyond 8 (12 with a single
 // row tile) the atomic adds outweigh the shorter K walk.
