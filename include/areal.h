@@ -97,10 +97,12 @@ typedef struct {
  * are produced from finite values).  The residual stream, norm statistics,
  * accumulators, softmax statistics and logits are float32.
  * Reproducibility: projections whose K range is split over work-groups accumulate with
- * float32 atomic adds in no fixed order, so logits can differ from run to run in the last
- * bits (about 1e-7 relative); AREAL_GEMM_MAX_SPLITS=1 in the environment removes the splits,
- * and with them the run-to-run differences, at a cost in the speed of decode steps and of prefill,
- * update and scoring passes of a few hundred rows or a long K.  The sampler is a
+ * float32 atomic adds in no fixed order (about 1e-7 of a sum), so that here and there an activation
+ * rounds to the next half and logits can differ from run to run (4e-4 of their norm measured).  Split are the
+ * projections of decode steps, those of passes that leave compute units idle (at the 1.5B shape up to
+ * 2,048 rows), and the long-K down projection of larger passes where that saves more than it is worth (7B shape).
+ * AREAL_GEMM_MAX_SPLITS=1 in the environment removes the splits,
+ * and with them the run-to-run differences, at a cost in speed there.  The sampler is a
  * pure function of the logits it is given. */
 typedef struct {
   int32_t dtype;                                    /* AREAL_DTYPE_F16, _BF16 or _F32        */

@@ -1298,29 +1298,53 @@ static int split_for(int M, int bm, int n_tiles, int nk) {
   return 1;
 }
 
-// Tile and K split above 256 rows: the cheapest by prefill_us, narrow_us and evened_us.
+// Tile and K split above 256 rows: the cheapest by prefill_us, narrow_us and evened_us, where a cut along K has to earn
+// what it takes away.  Its parts add into C with float32 atomics in no fixed order, so that a pass no longer repeats
+// itself bit for bit; whole tiles all give the same bits, whatever their size.  Where tiles of 128 x 128 leave a
+// quarter of the compute units without work a cut is taken whenever it is the cheaper one (down of 1,024 rows 46 us,
+// 58 in the best whole tiles).  Beyond that a split has to save a ninth by price, and so has the evened launch below a
+// whole round of tiles, where it cuts them all; from a round on, a thirty-second.  Down of 2,304 rows 86 us split, 88
+// whole; of 3,500 113 and 106; of 4,272 138 and 144; QKV of the 7B shape at 1,285 rows 70 and 59, its O at 1,700 71
+// and 64, down at 1,600 211 and 222, at 4,000 507 and 483, at 6,500 766 and 755; but down at 1,500 rows 195 and 219, at
+// 2,048 274 and 310, at 8,192 921 and 975.
 static void prefill_choose(int M, int N, int K, GemmMode mode, int* cfg, int* splits) {
   static const int steps[] = {1, 2, 3, 4, 6, 8, 12};
+  constexpr float SPLIT_SAVES = 1.0f - 1.0f / 9.0f, EVENED_SAVES = 1.0f - 1.0f / 32.0f;
   const int nk = K / BK;
-  float best = 1e30f;
-  for (const PrefillTile& t : prefill_tiles) {
+  const bool filled = (int64_t)((N + 127) / 128) * ((M + 127) / 128) > 192;
+  float whole = 1e30f, split = 1e30f;
+  int split_cfg = -1, parts = 1;
+  auto take = [&](int c, int sp, float us) {
+    // residual adds: 20 is the 256 x 192 tile where K is short, 26 where it is long enough for configuration 24
+    if (c == 26 && mode == GEMM_ADD_F32 && K < EVENED_MIN_K) c = 20;
+    if (sp == 1 && us < whole) { whole = us; *cfg = c; }
+    if (sp > 1 && us < split) { split = us; split_cfg = c; parts = sp; }
+  };
+  for (const PrefillTile& t : prefill_tiles)
     for (int sp : steps) {
       if (sp > 1 && (sp > max_splits() || 3 * sp > nk)) break;
-      const float us = prefill_us(t, M, N, K, mode, sp);
-      // residual adds: 20 is the 256 x 192 tile where K is short, 26 where it is long enough for configuration 24
-      if (us < best) { best = us; *cfg = t.cfg == 26 && mode == GEMM_ADD_F32 && K < EVENED_MIN_K ? 20 : t.cfg; *splits = sp; }
+      take(t.cfg, sp, prefill_us(t, M, N, K, mode, sp));
     }
-  }
   for (const NarrowTile& t : one_round_tiles)
     for (int sp : steps) {
       if ((sp > 1 && (sp > max_splits() || 3 * sp > nk)) || narrow_load(t, M, N, K, sp) > 1.0f) break;
-      const float us = narrow_us(t, M, N, K, sp);
-      if (us < best) { best = us; *cfg = t.cfg; *splits = sp; }
+      take(t.cfg, sp, narrow_us(t, M, N, K, sp));
     }
-  if (mode == GEMM_ADD_F32 && K >= EVENED_MIN_K && (int64_t)((N + 255) / 256) * ((M + 255) / 256) >= 96) {
+  float best = whole;
+  *splits = 1;
+  if (split < (filled ? whole * SPLIT_SAVES : whole)) {
+    best = split;
+    *cfg = split_cfg;
+    *splits = parts;
+  }
+  const int64_t evened_tiles = (int64_t)((N + 255) / 256) * ((M + 255) / 256);
+  if (mode == GEMM_ADD_F32 && K >= EVENED_MIN_K && evened_tiles >= 96) {
     // Configuration 24, by the price of the tiles that it launches: of 192 columns, the work of configuration 26
     // without a split; of 256, whose cut tiles add with atomics: not under a limit of one split.
-    if (evened_192(M, N, K) ? *cfg == 26 && *splits == 1 : evened_us(M, N, K) < best && max_splits() > 1) {
+    const float us = evened_us(M, N, K);
+    if (evened_192(M, N, K) ? *cfg == 26 && *splits == 1
+                            : us < best && us < whole * (evened_tiles < 256 ? SPLIT_SAVES : EVENED_SAVES) &&
+                                  max_splits() > 1) {
       *cfg = 24;
       *splits = 1;
     }

@@ -450,6 +450,27 @@ def test_tile_choice_for_the_decoder_shapes(L):
     assert L.areal_op_gemm_choose(8, 8, 8, 3, C.byref(c), C.byref(s)) != 0
 
 
+def test_passes_that_fill_the_chip_are_not_cut_along_k(L):
+    """Above 256 rows a cut along K (float32 atomics: a pass then differs from run to run) is for launches that leave
+    compute units idle, or where it saves enough by price.  At the
+    1.5B shape every pass of more than 2,048 rows repeats; at the 7B shape all of more than 512 but for its down
+    projection."""
+    import ctypes as C
+
+    def cut(M, N, K, mode):
+        c, s = C.c_int32(), C.c_int32()
+        assert L.areal_op_gemm_choose(M, N, K, mode, C.byref(c), C.byref(s)) == 0
+        # 24 cuts tiles of 256 x 256; where its tiles of 192 columns fill whole rounds it cuts none
+        return s.value > 1 or (c.value == 24 and (-(-N // 192) * -(-M // 256)) % 256 != 0)
+
+    rows = sorted(set(range(257, 8193, 37)) | {r + d for r in range(512, 8193, 64) for d in (0, 1) if r + d <= 8192})
+    for N, K, mode, above in ((2048, 1536, 0, 505), (1536, 1536, 1, 737), (1536, 8960, 1, 2048),
+                              (4608, 3584, 0, 384), (3584, 3584, 1, 512)):
+        assert not [M for M in rows if M > above and cut(M, N, K, mode)], (N, K)
+    for lo, hi in ((1537, 1664), (2817, 3456), (3841, 4608), (6145, 6336), (6401, 6912)):
+        assert not [M for M in rows if lo <= M <= hi and cut(M, 3584, 18944, 1)], (lo, hi)
+
+
 def test_gate_up_tiles_by_rows_and_width(L):
     """Gate/up: the tile with the least to take in per compute unit, no taller than the launch needs; whole
     sums, so never a K split.  Narrow products never take a tile of more than twice the rows (of 32 at least)."""
@@ -482,7 +503,8 @@ def test_long_k_choice_names_the_kernel_it_launches(L):
         assert L.areal_op_gemm_choose(M, N, K, 1, C.byref(c), C.byref(s)) == 0
         return c.value, s.value
 
-    assert choose(6400, 3584, 18944) == choose(12400, 3584, 18944) == choose(5200, 4096, 11008) == (24, 1)
+    assert choose(6400, 3584, 18944) == choose(12400, 3584, 18944) == (24, 1)
+    assert choose(5200, 4096, 11008) == (28, 1)                                  # 407 us; 427 evened out
     assert choose(2560, 4736, 8960) == choose(3457, 3456, 18944) == (26, 1)      # 250 and 252 tiles of 256 x 192
     assert choose(8192, 1536, 8960) == (24, 1)                                   # 256 of them: nothing to cut
     assert choose(8000, 1536, 8960) == choose(7000, 1536, 8960) == (28, 1)       # 252 and 222 of 192 x 256
