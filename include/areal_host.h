@@ -50,7 +50,7 @@ int32_t areal_plan_passes(int32_t n_spans, const int32_t* lens, int32_t max_rows
  * the one it appends included; rows with equal home[i] hold leading KV blocks together.  target = 0: segment length
  * by price; else about that many work-groups, none aimed shorter than min_tokens.  Writes up to `cap`
  * records of 4 int32 {row or -1, first token, tokens, slot} by launch index (which modulo 8 is the XCD) to out
- * (host) and returns the number of records, or AREAL_E_INVAL. */
+ * (host) and returns the number of records, or AREAL_E_INVAL / AREAL_E_NOMEM. */
 int32_t areal_plan_decode(int32_t n, const int32_t* own, const int32_t* home, int32_t n_kv_heads, int32_t max_slots,
                           int32_t target, int32_t min_tokens, int32_t* out, int32_t cap);
 

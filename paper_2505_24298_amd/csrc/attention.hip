@@ -281,8 +281,8 @@ __device__ __forceinline__ void decode_shared_set(
 
 // One work-group per (segment, kv head); the partials of a row cut into several segments
 // are combined by attn_merge_kernel.  Bound by HBM: work-groups are handed out by decode_plan.hpp (segments of
-// about equal length, an eighth of the tokens to each XCD), a segment's block ids lie by launch index, so
-// that they travel together with its descriptor.  The row's query heads
+// about equal length, an eighth of the tokens to each XCD), and where a segment's block ids lie depends on the
+// launch index alone, so that they travel together with its descriptor.  The row's query heads
 // are taken from the float32 QKV row (bias, RoPE, rounding done here).  The
 // cached positions 0 .. pos-1 come from the paged arena; the token being
 // appended (position pos) is handled by the work-group whose segment contains
@@ -302,14 +302,22 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(
   const int nkv = geom.n_kv_heads;
   const int n_slots = sg.max_own + grp.n_shared;         // partial slots per (row, head)
   // segment q of XCD x: work-groups 8 (q nkv .. q nkv + nkv - 1) + x, one per kv head
-  const int id = blockIdx.x, n_seg_wgs = sg.n * nkv;
+  const int id = blockIdx.x, n_seg_wgs = 8 * sg.depth * nkv;
   if (id >= n_seg_wgs) {                                 // the shared leading blocks of a set of rows
     const int r = id - n_seg_wgs, u = r % grp.n_shared, rest = r / grp.n_shared;
     decode_shared_set<D>(qkv, rm, bq, cos_tab, sin_tab, arena, geom, nq, sg.max_own, n_slots,
                          scale_log2, part_o, part_ml, grp, rest / nkv, rest % nkv, u);
     return;
   }
-  const int seg = (id >> 3) / nkv * 8 + (id & 7), kvh = (id >> 3) % nkv;
+  const int kvh = (id >> 3) % nkv;
+  int seg = sg.base[0], seg_end = sg.base[1];
+#pragma unroll
+  for (int x = 1; x < 8; ++x) {
+    seg = (id & 7) == x ? sg.base[x] : seg;
+    seg_end = (id & 7) == x ? sg.base[x + 1] : seg_end;
+  }
+  seg += (id >> 3) / nkv;
+  if (seg >= seg_end) return;                            // this XCD has fewer
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane >> 4, j = lane & 15;
   const int G = nq / nkv;
@@ -319,7 +327,6 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(
   ids.hi = 64 + lane < sg.stride ? table[64 + lane] : 0;
   const int4 d = sg.desc[seg];
   const int i = __builtin_amdgcn_readfirstlane(d.x);
-  if (i < 0) return;
   // Token and block indices below are relative to the first position this row's own work-groups cover.
   const int pos_abs = __builtin_amdgcn_readfirstlane(d.y), pos = __builtin_amdgcn_readfirstlane(d.z);
   const int packed = __builtin_amdgcn_readfirstlane(d.w);
@@ -744,7 +751,9 @@ hipError_t launch_attn_decode(hipStream_t s, const float* qkv, int M, RowMeta rm
                               const f16* bv, const float* cos_tab, const float* sin_tab, f16* arena_layer, KvGeom geom,
                               int n_q_heads, DecodeSegs segs, float* part_o, float* part_ml, f16* out,
                               DecodeGroups grp) {
-  if (M <= 0 || !geom_ok(geom, n_q_heads) || segs.n <= 0 || segs.n % 8 || segs.max_own < 1 || segs.max_own > 32 ||
+  bool base_ok = segs.base[0] == 0 && segs.base[8] > 0;
+  for (int x = 0; x < 8; ++x) base_ok &= segs.base[x] <= segs.base[x + 1] && segs.base[x + 1] - segs.base[x] <= segs.depth;
+  if (M <= 0 || !geom_ok(geom, n_q_heads) || !base_ok || segs.max_own < 1 || segs.max_own > 32 ||
       segs.stride <= 0 || segs.stride > 132 || !segs.desc || !segs.table || !segs.own ||
       ((uintptr_t)segs.desc & 15) || !groups_ok(grp, M, segs.max_own) ||
       (segs.max_own + grp.n_shared > 1 && (!part_o || !part_ml)) ||
@@ -752,7 +761,7 @@ hipError_t launch_attn_decode(hipStream_t s, const float* qkv, int M, RowMeta rm
       (((uintptr_t)qkv | (uintptr_t)bq | (uintptr_t)bk | (uintptr_t)bv | (uintptr_t)arena_layer) & 15))
     return hipErrorInvalidValue;
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)geom.head_dim);
-  const unsigned grid = (unsigned)((segs.n + grp.n_sets * grp.n_shared) * geom.n_kv_heads);
+  const unsigned grid = (unsigned)((8 * segs.depth + grp.n_sets * grp.n_shared) * geom.n_kv_heads);
 #define AREAL_DEC(DD)                                                                              \
   attn_decode_kernel<DD><<<grid, 256, 0, s>>>(qkv, rm, bq, bk, bv, cos_tab, sin_tab, arena_layer, geom, n_q_heads, \
                                                segs, scale_log2, part_o, part_ml, out, grp);

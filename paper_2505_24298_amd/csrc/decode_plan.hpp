@@ -18,11 +18,22 @@ constexpr int kDecodeXcds = 8;
 struct DecodeSegment { int32_t row, t0, n, slot; };
 
 struct DecodePlan {
-  int share = 0;                          // units per segment aimed at
-  std::vector<DecodeSegment> order;       // by launch index, which modulo 8 is the XCD; row = -1: nothing to do
+  std::vector<DecodeSegment> segs;        // XCD by XCD: those of XCD x are [base[x], base[x + 1])
+  int32_t base[kDecodeXcds + 1] = {};
+  int depth = 0;                          // most segments of an XCD
   std::vector<int32_t> n_own;             // segments of each row
   int max_own = 0, max_units = 0;         // most segments of a row, longest segment
 };
+
+// Most bytes that the descriptors and block ids of the segments of n rows take, whatever their lengths up to
+// `max_tokens`: 16 bytes a segment, and 4 for each of the longest one's blocks (rounded up to 4) in every segment.
+// With X units in the longest row and segments of up to S units (4 <= S <= 64) a row has at most 1 + X / S of them, so that
+// 24 bytes and 8 min(S, X) each are at most 24 + 24 X / S + 8 min(S, X) + 8 X, which no S in that range makes larger
+// than the sum below.
+inline uint64_t decode_segment_bytes(uint64_t n, uint64_t max_tokens) {
+  const uint64_t X = (max_tokens + kDecodeUnit - 1) / kDecodeUnit;
+  return n * (14 * X + 8 * std::min<uint64_t>(X, kDecodeMaxUnits) + 56);
+}
 
 // The cut replaces splits of one length for all rows (256 tokens and up, work-groups without tokens where a row was
 // shorter than the longest, a remainder per row).  Attention launch of a step, 1.5B shape: 256 rows of 420 - 650 tokens
@@ -87,14 +98,16 @@ inline int decode_share_for(int64_t total_units, int n_kv_heads, int target, int
 // own[i]: tokens of row i from its first own one to the one it appends (>= 1).  home[i]: the row's first KV block; rows
 // with the same one hold leading blocks together.  Rows are cut into at most max_slots segments.  target > 0: so
 // that there are about that many work-groups, no segment aimed shorter than min_tokens (tuning); 0: by price.
-// at_least: lower limit of the share.
 //
 // Order: each XCD gets an eighth of the units, longest segments first.  Rows that share blocks are kept on as few XCDs
 // as the balance allows (pieces of a sixteenth of the work), where their common blocks meet in one L2: 16
 // prompts x 16 samples of 535 tokens, 288 shared, are 140 MB of K/V per layer, 69 MB of them distinct, of which 102
-// would cross the fabric with the samples of a prompt on all XCDs.
+// would cross the fabric with the samples of a prompt on all XCDs.  No XCD gets more than a quarter above an eighth of the
+// segments, and four: the launch has as many work-groups on each XCD as the one with the most segments needs, and among
+// many rows of one unit the units alone would let one XCD have most of them (2,063 rows, 256 to a prompt, 1,637 of
+// one unit: 12,512 work-groups a KV head without the limit, 2,160 with it).
 inline DecodePlan plan_decode(const std::vector<int32_t>& own, const std::vector<int32_t>& home, int n_kv_heads,
-                              int max_slots, int target, int min_tokens, int at_least) {
+                              int max_slots, int target, int min_tokens) {
   const int n = (int)own.size();
   DecodePlan p;
   std::vector<int> units(n);
@@ -105,76 +118,89 @@ inline DecodePlan plan_decode(const std::vector<int32_t>& own, const std::vector
     total += units[i];
     longest = std::max(longest, units[i]);
   }
-  const int lo = std::max(at_least, (longest + max_slots - 1) / max_slots);
-  if (target > 0) {
-    p.share = decode_share_for(total, n_kv_heads, target, min_tokens);
-  } else {
-    p.share = decode_share(units, n_kv_heads, lo, kDecodeMaxUnits);
-  }
-  p.share = std::min((std::max(p.share, lo) + 3) / 4 * 4, kDecodeMaxUnits);
+  const int lo = (longest + max_slots - 1) / max_slots;
+  const int aimed = target > 0 ? decode_share_for(total, n_kv_heads, target, min_tokens)
+                               : decode_share(units, n_kv_heads, lo, kDecodeMaxUnits);
+  const int share = std::min((std::max(aimed, lo) + 3) / 4 * 4, kDecodeMaxUnits);
   p.n_own.resize(n);
   std::vector<int> len(n);                                // units per segment of a row
+  int64_t n_segs = 0;
   for (int i = 0; i < n; ++i) {
-    len[i] = decode_segment_units(units[i], p.share);
+    len[i] = decode_segment_units(units[i], share);
     p.n_own[i] = (units[i] + len[i] - 1) / len[i];
+    n_segs += p.n_own[i];
     p.max_own = std::max(p.max_own, (int)p.n_own[i]);
     p.max_units = std::max(p.max_units, len[i]);
   }
+  const int64_t most = (n_segs + kDecodeXcds - 1) / kDecodeXcds * 5 / 4 + 4;       // segments of an XCD
+  int64_t load[kDecodeXcds] = {}, count[kDecodeXcds] = {};
+  // The XCD with the least to do among those with room for `segs` more (-1: none).
+  auto least = [&](int64_t segs) {
+    int x = -1;
+    for (int k = 0; k < kDecodeXcds; ++k)
+      if (count[k] + segs <= most && (x < 0 || load[k] < load[x])) x = k;
+    return x;
+  };
   // rows -> XCD, or -1: their segments go wherever there is room
   std::vector<int8_t> at(n, -1);
   {
     std::unordered_map<int32_t, std::vector<int>> by_home;
     for (int i = 0; i < n; ++i) by_home[home[i]].push_back(i);
     if ((int)by_home.size() < n) {
-      struct Piece { int64_t load; std::vector<int> rows; };
+      struct Piece { int64_t load, segs; std::vector<int> rows; };
       std::vector<Piece> pieces;
       for (int i = 0; i < n; ++i) {                       // in row order, so that a plan does not depend on hashing
         auto& rows = by_home[home[i]];
         if (rows.size() < 2 || rows[0] != i) continue;
-        Piece piece{0, {}};
+        Piece piece{0, 0, {}};
         for (int r : rows) {
           if (!piece.rows.empty() && (piece.load + units[r]) * 16 > total) {
             pieces.push_back(std::move(piece));
-            piece = Piece{0, {}};
+            piece = Piece{0, 0, {}};
           }
           piece.load += units[r];
+          piece.segs += p.n_own[r];
           piece.rows.push_back(r);
         }
         pieces.push_back(std::move(piece));
       }
       std::stable_sort(pieces.begin(), pieces.end(), [](const Piece& a, const Piece& b) { return a.load > b.load; });
-      int64_t load[kDecodeXcds] = {};
       for (const Piece& piece : pieces) {
-        const int x = (int)(std::min_element(load, load + kDecodeXcds) - load);
+        const int x = least(piece.segs);
+        if (x < 0) continue;
         load[x] += piece.load;
+        count[x] += piece.segs;
         for (int r : piece.rows) at[r] = (int8_t)x;
       }
       // more than a twentieth above an eighth of everything: the balance is worth more than the L2
-      if (*std::max_element(load, load + kDecodeXcds) * 160 > total * 21) std::fill(at.begin(), at.end(), (int8_t)-1);
+      if (*std::max_element(load, load + kDecodeXcds) * 160 > total * 21) {
+        std::fill(at.begin(), at.end(), (int8_t)-1);
+        std::fill(load, load + kDecodeXcds, 0);
+        std::fill(count, count + kDecodeXcds, 0);
+      }
     }
   }
   std::vector<int> rows(n);
   for (int i = 0; i < n; ++i) rows[i] = i;
   std::stable_sort(rows.begin(), rows.end(), [&](int a, int b) { return len[a] > len[b]; });
   std::vector<DecodeSegment> queue[kDecodeXcds];
-  int64_t load[kDecodeXcds] = {};
-  for (int i = 0; i < n; ++i)
-    if (at[i] >= 0) load[at[i]] += units[i];
   for (int i : rows)
     for (int k = 0, u = 0; u < units[i]; ++k, u += len[i]) {
       const int m = std::min(len[i], units[i] - u);
       int x = at[i];
       if (x < 0) {
-        x = (int)(std::min_element(load, load + kDecodeXcds) - load);
+        x = least(1);
         load[x] += m;
+        ++count[x];
       }
       queue[x].push_back(DecodeSegment{i, u * kDecodeUnit, m * kDecodeUnit, k});
     }
-  size_t deepest = 0;
-  for (auto& q : queue) deepest = std::max(deepest, q.size());
-  p.order.assign(deepest * kDecodeXcds, DecodeSegment{-1, 0, 0, 0});
-  for (int x = 0; x < kDecodeXcds; ++x)
-    for (size_t j = 0; j < queue[x].size(); ++j) p.order[j * kDecodeXcds + x] = queue[x][j];
+  p.segs.reserve(n_segs);
+  for (int x = 0; x < kDecodeXcds; ++x) {
+    p.segs.insert(p.segs.end(), queue[x].begin(), queue[x].end());
+    p.base[x + 1] = (int32_t)p.segs.size();
+    p.depth = std::max(p.depth, (int)queue[x].size());
+  }
   return p;
 }
 

@@ -4,6 +4,7 @@
 // sanitizers (build.py build_host_sanitized) for the CPU tests.
 #include <stdint.h>
 
+#include <new>
 #include <vector>
 
 #include "../../include/areal.h"
@@ -42,14 +43,19 @@ int32_t areal_plan_decode(int32_t n, const int32_t* own, const int32_t* home, in
     return AREAL_E_INVAL;
   for (int i = 0; i < n; ++i)
     if (own[i] < 1 || own[i] > (int64_t)max_slots * kDecodeMaxUnits * kDecodeUnit) return AREAL_E_INVAL;
-  const DecodePlan p = plan_decode(std::vector<int32_t>(own, own + n), std::vector<int32_t>(home, home + n), n_kv_heads,
-                                   max_slots, target, min_tokens, 1);
-  for (size_t q = 0; q < p.order.size() && (int)q < cap; ++q) {
-    const DecodeSegment& s = p.order[q];
-    const int32_t rec[4] = {s.row, s.t0, s.n, s.slot};
-    for (int k = 0; k < 4; ++k) out[4 * q + k] = rec[k];
+  try {
+    const DecodePlan p = plan_decode(std::vector<int32_t>(own, own + n), std::vector<int32_t>(home, home + n), n_kv_heads,
+                                     max_slots, target, min_tokens);
+    for (int q = 0; q < p.depth * kDecodeXcds && q < cap; ++q) {
+      const int x = q % kDecodeXcds, at = p.base[x] + q / kDecodeXcds;
+      const DecodeSegment s = at < p.base[x + 1] ? p.segs[at] : DecodeSegment{-1, 0, 0, 0};
+      const int32_t rec[4] = {s.row, s.t0, s.n, s.slot};
+      for (int k = 0; k < 4; ++k) out[4 * (int64_t)q + k] = rec[k];
+    }
+    return p.depth * kDecodeXcds;
+  } catch (const std::bad_alloc&) {
+    return AREAL_E_NOMEM;
   }
-  return (int32_t)p.order.size();
 }
 
 struct areal_gate { StalenessGate g; };

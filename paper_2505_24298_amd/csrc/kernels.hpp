@@ -101,13 +101,15 @@ struct DecodeGroups {
   const int32_t* set_table = nullptr; // [n_sets][set_stride] the leading block ids of a set
   int set_stride = 0;
 };
-// The rows' own tokens of a decode launch, cut into segments (decode_plan.hpp).  All arrays are device memory.
+// The rows' own tokens of a decode launch, cut into segments (decode_plan.hpp), XCD by XCD: segment q of XCD x
+// is number base[x] + q of `desc` and `table`, where that is below base[x + 1].  All arrays are device memory.
 struct DecodeSegs {
-  const int4* desc = nullptr;         // [n] {row or -1, position it appends at, the same counted from its first own token,
+  const int4* desc = nullptr;         // [n] {row, position it appends at, the same counted from its first own token,
                                       // (first own token / 32) | (tokens / 32) << 12 | slot << 19 | only partial << 24}
   const int32_t* table = nullptr;     // [n][stride] block ids of the segment, the appended position's included
   const int32_t* own = nullptr;       // [M] segments of row i
-  int n = 0;                          // multiple of 8: segment i runs on XCD i % 8
+  int base[9] = {};                   // base[0] = 0, base[8] = n
+  int depth = 0;                      // most segments of an XCD
   int stride = 0;                     // at most 132
   int max_own = 0;                    // largest `own`
 };

@@ -85,9 +85,9 @@ Layout make_layout(const areal_model_cfg& c) {
   L.cos_t = take((uint64_t)c.max_seq_len * (d / 2) * 4);
   L.sin_t = take((uint64_t)c.max_seq_len * (d / 2) * 4);
   // per pass: slot, pos, token, new_block per row + work items + last rows
-  // (+ in a decode step the block ids of every row's sequence, laid out by row)
+  // (+ in a decode step the descriptors and block ids of the segments)
   const uint64_t per_pass = M * 16 + (M / 16 + 2 * (uint64_t)c.max_seqs + 64) * 16 + (uint64_t)c.max_seqs * 16 +
-                            (uint64_t)c.max_seqs * (L.max_blocks + 4) * 4 +
+                            decode_segment_bytes(c.max_seqs, c.max_seq_len) +
                             // decode step: t_start per row, tile rows and start per set, block ids per set
                             (uint64_t)c.max_seqs * (4 + (kGroupTiles * 16 * 4 + 4 + (L.max_blocks + 4) * 4) / 2) + 256;
   L.ring_bytes = align_up(std::max<uint64_t>(per_pass * 2, 1u << 20), 4096) * kRingSegs;
@@ -903,17 +903,13 @@ int areal_decode_step(areal_ctx* c, int32_t n, const int32_t* seq_ids, const int
   // Per step are staged: row metadata, the segments and their block ids by launch index, the leading blocks of the sets.
   const int n_sets = (int)sets.size(), set_stride = (max_shared_blocks + 3) / 4 * 4;
   const uint64_t set_rows_bytes = (uint64_t)n_sets * kGroupTiles * 16 * 4;
-  DecodePlan plan;
-  uint64_t n_segs = 0, stride = 0, bytes = 0;
-  for (int at_least = 1;; at_least = 2 * plan.share) {   // longer segments, should their tables outgrow a ring segment
-    plan = plan_decode(own, home, g.n_kv_heads, kMaxSplits - n_shared, c->split_target, c->min_chunk, at_least);
-    n_segs = plan.order.size();
-    stride = ((uint64_t)plan.max_units * kDecodeUnit / AREAL_KV_BLOCK_TOKENS + 3) / 4 * 4;
-    bytes = align_up((uint64_t)n * 4, 64) * 5 + n_segs * 16 + align_up(n_segs * stride * 4, 64) +
-            align_up((uint64_t)n_sets * set_stride * 4, 64) + align_up(set_rows_bytes, 64) +
-            align_up((uint64_t)n_sets * 4, 64) + 64;
-    if (bytes <= c->seg_bytes || plan.share >= std::min(longest_own(), kDecodeMaxUnits)) break;
-  }
+  const DecodePlan plan =
+      plan_decode(own, home, g.n_kv_heads, kMaxSplits - n_shared, c->split_target, c->min_chunk);
+  const uint64_t n_segs = plan.segs.size();
+  const uint64_t stride = ((uint64_t)plan.max_units * kDecodeUnit / AREAL_KV_BLOCK_TOKENS + 3) / 4 * 4;
+  const uint64_t bytes = align_up((uint64_t)n * 4, 64) * 5 + n_segs * 16 + align_up(n_segs * stride * 4, 64) +
+                         align_up((uint64_t)n_sets * set_stride * 4, 64) + align_up(set_rows_bytes, 64) +
+                         align_up((uint64_t)n_sets * 4, 64) + 64;
   int rc = ring_begin(c, bytes);
   if (rc) return rc;
   const uint64_t start = c->seg_used;
@@ -946,20 +942,17 @@ int areal_decode_step(areal_ctx* c, int32_t n, const int32_t* seq_ids, const int
   }
   memcpy(s_own.host, plan.n_own.data(), (size_t)n * 4);
   for (uint64_t q = 0; q < n_segs; ++q) {
-    const DecodeSegment& sg = plan.order[q];
+    const DecodeSegment& sg = plan.segs[q];
     int32_t *dst = hdesc + q * 4, *trow = htab + q * stride;
+    const auto& blocks = c->alloc->blocks(seq_ids[sg.row]);
+    const size_t b0 = (size_t)(t_start[sg.row] + sg.t0) / AREAL_KV_BLOCK_TOKENS;
+    const size_t n_ids = std::min(blocks.size() - b0, (size_t)sg.n / AREAL_KV_BLOCK_TOKENS);
+    memcpy(trow, blocks.data() + b0, n_ids * 4);
     dst[0] = sg.row;
-    size_t n_ids = 0;
-    if (sg.row >= 0) {
-      const auto& blocks = c->alloc->blocks(seq_ids[sg.row]);
-      const size_t b0 = (size_t)(t_start[sg.row] + sg.t0) / AREAL_KV_BLOCK_TOKENS;
-      n_ids = std::min(blocks.size() - b0, (size_t)sg.n / AREAL_KV_BLOCK_TOKENS);
-      memcpy(trow, blocks.data() + b0, n_ids * 4);
-      dst[1] = hpos[sg.row];
-      dst[2] = hpos[sg.row] - t_start[sg.row];
-      dst[3] = sg.t0 / kDecodeUnit | sg.n / kDecodeUnit << 12 | sg.slot << 19 |
-               (plan.n_own[sg.row] == 1 && t_start[sg.row] == 0 ? 1 : 0) << 24;
-    }
+    dst[1] = hpos[sg.row];
+    dst[2] = hpos[sg.row] - t_start[sg.row];
+    dst[3] = sg.t0 / kDecodeUnit | sg.n / kDecodeUnit << 12 | sg.slot << 19 |
+             (plan.n_own[sg.row] == 1 && t_start[sg.row] == 0 ? 1 : 0) << 24;
     for (size_t b = n_ids; b < stride; ++b) trow[b] = 0;
   }
   for (int k = 0; k < n_sets; ++k) {
@@ -988,7 +981,8 @@ int areal_decode_step(areal_ctx* c, int32_t n, const int32_t* seq_ids, const int
   a.segs.desc = (const int4*)s_desc.dev;
   a.segs.table = (const int32_t*)s_tab.dev;
   a.segs.own = (const int32_t*)s_own.dev;
-  a.segs.n = (int)n_segs;
+  memcpy(a.segs.base, plan.base, sizeof(plan.base));
+  a.segs.depth = plan.depth;
   a.segs.stride = (int)stride;
   a.segs.max_own = plan.max_own;
   for (const RowSet& rs : sets) {

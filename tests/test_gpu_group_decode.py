@@ -213,3 +213,35 @@ def test_more_slots_than_a_row_has_every_row_walks_its_own_blocks():
                 os.environ.pop(k, None)
             else:
                 os.environ[k] = v
+
+
+def test_many_short_rows_next_to_long_ones():
+    """A step of 2,063 rows: 426 of 1,539 - 1,709 tokens and 1,637 of 18, of which every 256 hold their first block
+    together.  The block ids of all segments have to fit the staging buffer that a context of this size
+    has.  Against the same step in batches of 400 rows (the K/V are whatever the arena holds: no oracle)."""
+    import torch
+    from paper_2505_24298_amd import binding
+    cfg = synth.shape("tiny", n_layers=1)
+    w = binding.weights_to_device(synth.make_weights(cfg, 3, qkv_bias=True, std=0.03), bf16=False)
+    lens = [1538 + i * 37 % 171 for i in range(426)] + [17] * 1637
+    n = len(lens)
+    toks = torch.from_numpy(np.random.default_rng(1).integers(0, cfg["vocab"], size=n).astype(np.int32)).cuda()
+    out = []
+    for batch in (n, 400):
+        eng = binding.Areal(cfg, max_seqs=n, max_seq_len=1709, max_batch_tokens=8192,
+                            kv_blocks=sum(v // 16 + 2 for v in lens), convert_weights=True)
+        eng.load_weights(w, 0)
+        g = torch.Generator(device="cuda").manual_seed(5)
+        eng.kv_arena.view(torch.float16).normal_(generator=g)
+        for i, v in enumerate(lens):
+            lead = i - i % 256
+            if i == lead:
+                eng.adopt_seq(i, v, 1)
+            else:
+                eng.adopt_seq(i, v, 1, src_id=lead, n_shared_blocks=1)
+        out.append(np.concatenate([eng.decode_step(list(range(k, min(n, k + batch))), toks[k:k + batch].contiguous())
+                                   .cpu().numpy() for k in range(0, n, batch)]))
+        eng.close()
+    diff = float(np.abs(out[0] - out[1]).max())
+    print(f"all rows at once against batches of 400: {diff:.2e}", flush=True)
+    assert np.isfinite(out[0]).all() and diff <= 2e-3

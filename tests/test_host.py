@@ -412,6 +412,27 @@ def test_decode_plan_covers_every_token_once(own, group, nkv, max_slots, target,
     assert H.areal_plan_decode(n, ptr(a), ptr(h), nkv, 0, 0, 0, ptr(out), 1) == binding.E_INVAL
 
 
+@pytest.mark.parametrize("n_long,group", [(426, 256), (470, 256), (483, 128), (0, 1), (2063, 16), (3, 2063)])
+def test_decode_plan_of_many_rows_is_bounded(n_long, group):
+    """Long rows that share blocks next to many of one unit: no XCD gets more than a quarter above its share of
+    the segments (the launch pads all to the deepest), and the segments' descriptors and block ids fit the space
+    that a context has for them, whatever the lengths (22 bytes a row and unit of the longest, and 56)."""
+    H = binding.host_lib()
+    n, longest = 2063, 1709
+    own = np.array([1539 + i * 37 % 171 for i in range(n_long)] + [17] * (n - n_long), np.int32)
+    home = np.array([i - i % group for i in range(n)], np.int32)
+    ptr = lambda x: x.ctypes.data_as(binding._I32P)
+    for target, min_tokens in ((0, 256), (65536, 128), (64, 2048)):
+        out = np.zeros((65536, 4), np.int32)
+        k = H.areal_plan_decode(n, ptr(own), ptr(home), 2, 32, target, min_tokens, ptr(out), len(out))
+        assert 0 < k <= len(out) and k % 8 == 0
+        real = out[:k][out[:k, 0] >= 0]
+        assert k <= 8 * (-(-len(real) // 8) * 5 // 4 + 4)
+        ids = -(-(int(real[:, 2].max()) // 16) // 4) * 4
+        units = -(-longest // 32)
+        assert len(real) * (16 + 4 * ids) <= n * (14 * units + 8 * min(units, 64) + 56)
+
+
 def test_tile_choice_for_the_decoder_shapes(L):
     """areal_op_gemm_choose (host only): the tile configuration and K split the library takes for
     the products of the 1.5B and 7B shapes, at the row counts where the rules change.  Pins the
