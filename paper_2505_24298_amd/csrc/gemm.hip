@@ -606,7 +606,10 @@ __device__ __forceinline__ int wide_feature(int b) {
 template <int TN>
 __device__ __forceinline__ int wide_is_up(int b) { return TN % 4 ? (b >> 3) & 1 : (b >> 5) & 1; }
 
-template <int BM, int BN, int WM, int WN, int MODE, bool FULL>
+// ROWS, COLS: every row (column) of the tile lies inside the matrix; gate/up with COLS stores a lane's features at once,
+// rows checked one by one where not all are inside.  Without that (every tile at the lower edge element by element)
+// gate/up of 704 rows took 51.2 us, 46.4 with it; of 720 53.2 and 46.0, of 1,500 95.2 and 88.7, of 350 32.1 and 29.8.
+template <int BM, int BN, int WM, int WN, int MODE, bool ROWS, bool COLS>
 __device__ __forceinline__ void store_wide_part(const f32x4 (&acc)[BM / WM / 16][BN / WN / 16], void* __restrict__ Cv,
                                                 int M, int N, int ldc, int tile_m, int tile_n, int wm, int wn,
                                                 int fr, int fh, int atomic) {
@@ -634,8 +637,8 @@ __device__ __forceinline__ void store_wide_part(const f32x4 (&acc)[BM / WM / 16]
             y[v] = f2h_sat(silu_f(__builtin_bit_cast(float, gate)) * __builtin_bit_cast(float, up));
           }
           if (two || fh < 2) {
-            if (FULL) {
-              *reinterpret_cast<f16x4*>(p) = y;
+            if (COLS) {
+              if (ROWS || m < M) *reinterpret_cast<f16x4*>(p) = y;
             } else if (m < M) {
 #pragma unroll
               for (int e = 0; e < 4; ++e)
@@ -657,8 +660,8 @@ __device__ __forceinline__ void store_wide_part(const f32x4 (&acc)[BM / WM / 16]
         for (int t = 0; t < 2; ++t)
 #pragma unroll
           for (int v = 0; v < 4; ++v) y[4 * t + v] = f2h_sat(silu_f(acc[i][j + t][v]) * acc[i][j + 2 + t][v]);
-        if (FULL) {
-          *reinterpret_cast<f16x8*>(p) = y;
+        if (COLS) {
+          if (ROWS || m_wave + i * 16 + fr < M) *reinterpret_cast<f16x8*>(p) = y;
         } else if (m_wave + i * 16 + fr < M) {
 #pragma unroll
           for (int e = 0; e < 8; ++e)
@@ -673,7 +676,7 @@ __device__ __forceinline__ void store_wide_part(const f32x4 (&acc)[BM / WM / 16]
     auto stride = [&] { int ld = ldc; asm volatile("" : "+s"(ld)); return ld; };
     auto at = [&](int i, int j, int v, int ld) { return Cw + (int64_t)(i * 16 + v) * ld + j * 16 + (4 * fh * ld + fr); };
     auto inside = [&](int i, int j, int v) {
-      return FULL || (m_wave + i * 16 + 4 * fh + v < M && n_wave + j * 16 + fr < N);
+      return (ROWS && COLS) || (m_wave + i * 16 + 4 * fh + v < M && n_wave + j * 16 + fr < N);
     };
     if (MODE == GEMM_ADD_F32 && !atomic) {
       float old[2][TN][4];
@@ -951,10 +954,13 @@ __device__ __forceinline__ void wide_tile(const f16* __restrict__ A, const GemmW
     // gate/up: a lane's eight (four) features go out as 16 (8) bytes where rows start on 16 (8) bytes
     const bool whole = MODE != GEMM_SWIGLU_F16 ||
                        (TN % 4 ? ((ldc & 3) == 0 && ((uintptr_t)Cv & 7) == 0) : ((ldc & 7) == 0 && ((uintptr_t)Cv & 15) == 0));
-    if (whole && (tile_m + 1) * BM <= M && (tile_n + 1) * NC <= N)
-      store_wide_part<BM, BN, WM, WN, MODE, true>(t.acc, Cv, M, N, ldc, tile_m, tile_n, wm, wn, fr, fh, atomic);
+    const bool rows = (tile_m + 1) * BM <= M, cols = whole && (tile_n + 1) * NC <= N;
+    if (rows && cols)
+      store_wide_part<BM, BN, WM, WN, MODE, true, true>(t.acc, Cv, M, N, ldc, tile_m, tile_n, wm, wn, fr, fh, atomic);
+    else if (MODE == GEMM_SWIGLU_F16 && cols)   // rows below the matrix only
+      store_wide_part<BM, BN, WM, WN, MODE, false, true>(t.acc, Cv, M, N, ldc, tile_m, tile_n, wm, wn, fr, fh, atomic);
     else
-      store_wide_part<BM, BN, WM, WN, MODE, false>(t.acc, Cv, M, N, ldc, tile_m, tile_n, wm, wn, fr, fh, atomic);
+      store_wide_part<BM, BN, WM, WN, MODE, false, false>(t.acc, Cv, M, N, ldc, tile_m, tile_n, wm, wn, fr, fh, atomic);
   }
   // drain the loads that were requested past the end before the LDS is released
   wait_vmcnt(0);
