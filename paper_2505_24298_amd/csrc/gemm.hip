@@ -1096,19 +1096,20 @@ hipError_t run(hipStream_t s, const f16* A, const GemmW& W, void* C, int M, int 
 // round at all (36 tiles of 128 x 128 for the down projection of a 301-token prompt: 58 us with 2
 // splits, 22 with 6).  So every candidate is priced in microseconds: a fixed part, the K slabs one
 // compute unit walks (slower the fuller the chip: clocks and L2 are shared), and the adds into C per
-// million elements (with atomics for every split, or read and written once).  Constants: fitted to a sweep of
-// 8 products (1.5B and 7B shape) x 8 - 18 row counts from 300 to 8,192 x tiles x splits, 5,558 times on
-// one card; over it the choice, gate/up, small tiles and the evened launch included, is 0.7 % from the best on average;
-// farthest off is down of the 7B shape at 2,048 rows (271 us for 244).
+// million elements (with atomics for every split, or read and written once).  Constants: fitted to sweeps of
+// 8 products (1.5B and 7B shape) x 18 - 50 row counts from 257 to 8,192 x tiles x splits; over the last one (10,458 times
+// on one card) the choice, small tiles, evened launch and whole tiles included, is 0.6 % from the best on average.
+// Farthest off are down of the 7B shape at 1,345 - 1,408 rows (212 us for 183 with a split that adds with atomics, see
+// prefill_choose), its O at 317 - 320 (24.1 for 21.5), and QKV of 3,969 - 4,096 rows (37.4 for 34.7).
 struct PrefillTile {
   int cfg, bm, bn, per_cu;        // work-groups of this tile a compute unit holds
   float fixed, slab_few, slab_all, add_split, add_whole;
 };
 constexpr PrefillTile TILE_256x192 = {26, 256, 192, 1, 12.54f, 0.715f, 1.157f, 1.758f, 0.846f};
 constexpr PrefillTile prefill_tiles[] = {
-    {19, 256, 256, 1, 15.0f, 0.878f, 1.549f, 1.691f, 0.911f}, {28, 192, 256, 1, 11.44f, 0.715f, 1.157f, 1.60f, 0.982f},
+    {19, 256, 256, 1, 15.0f, 0.878f, 1.549f, 1.691f, 0.911f}, {28, 192, 256, 1, 11.44f, 0.715f, 1.157f, 1.80f, 0.982f},
     TILE_256x192,                                             {27, 128, 192, 1, 8.62f, 0.471f, 0.711f, 1.682f, 0.968f},
-    {21, 128, 128, 1, 7.57f, 0.368f, 0.58f, 1.297f, 0.599f},  {36, 128, 128, 2, 9.71f, 0.459f, 1.088f, 1.252f, 0.532f},
+    {21, 128, 128, 1, 7.57f, 0.368f, 0.58f, 1.297f, 0.599f},  {36, 128, 128, 2, 10.2f, 0.49f, 1.02f, 1.252f, 0.532f},
 };
 static float prefill_us(const PrefillTile& t, int M, int N, int K, int mode, int splits) {
   const int cols = mode == GEMM_SWIGLU_F16 ? t.bn / 2 : t.bn, nk = K / BK;
@@ -1122,11 +1123,13 @@ static float prefill_us(const PrefillTile& t, int M, int N, int K, int mode, int
   else if (mode == GEMM_ADD_F32) us += t.add_whole * melem;
   return us;
 }
-// Residual adds with a long K: tiles of 256 x 256 with the last round evened out along K.
+// Residual adds with a long K: tiles of 256 x 256 with the last round evened out along K.  Below a round every tile is cut,
+// into about 256 / tiles parts that all add.
 constexpr int EVENED_MIN_K = 4096;
 static float evened_us(int M, int N, int K) {
   const float tiles = (float)((N + 255) / 256) * (float)((M + 255) / 256);
-  return 45.0f + tiles * (float)(K / BK) / 256.0f * 1.46f + 1.87f * (float)M * (float)N * 1e-6f;
+  return 45.0f + tiles * (float)(K / BK) / 256.0f * 1.46f +
+         1.87f * (float)M * (float)N * 1e-6f * std::max(1.0f, 256.0f / tiles);
 }
 // Configuration 24 takes tiles of 192 columns instead where these fill every round of 256 compute units, so that
 // nothing is left to cut, and are the cheaper ones: 8,192 x 1,536 x 8,960 (256 tiles) 186 us, 219 in whole tiles of 256
@@ -1143,8 +1146,8 @@ static bool evened_192(int M, int N, int K) {
 // So tiles are chosen whose work-groups come as close to 256 as the width allows (8,960 features: 224 of 40,
 // 125 x 2 of 72; 18,944: 237 of 80), with no more rows than the launch has.  Measured against tiles of
 // 64 features, 1.5B shape: 15.1 -> 13.4 us at 24 rows, 18.9 -> 15.4 at 64, 20.4 -> 18.4 at 88, 34.7 -> 24.8 at 256,
-// 32.8 -> 28.8 at 301; 7B shape: 58.5 -> 48.7 at 24, 66 -> 51 at 64, 80 -> 59.5 at 128, 133 -> 95 at 256.  Over 27 + 17
-// (rows, shape) the choice is 0.4 % from the best of 14 tiles on average (gate/up of 512 rows: 9 %).
+// 32.8 -> 28.8 at 301; 7B shape: 58.5 -> 48.7 at 24, 66 -> 51 at 64, 80 -> 59.5 at 128, 133 -> 95 at 256.  Over 65 + 30 row
+// counts from 257 to 8,192 (1.5B and 7B shape) the choice is 0.5 % from the best of 14 tiles on average, 6 % at most.
 struct StreamTile { int cfg, bm, bn; };
 constexpr StreamTile stream_tiles[] = {{12, 32, 80},   {10, 64, 80},   {29, 96, 80},   {21, 128, 80},  {20, 128, 144},
                                        {30, 64, 160},  {31, 96, 160},  {32, 128, 160}, {33, 160, 160}, {34, 192, 160}};
@@ -1153,10 +1156,12 @@ static float stream_us(const StreamTile& t, int M, int N, int K) {
   const float rounds = std::max(1.0f, 0.5f * (load + ceilf(load)));      // a last round that is partly filled
   return 4.5f + std::max(rounds * (float)(t.bm + t.bn) * (float)K * (2e-3f / 41.0f), (float)N * (float)K * (4e-6f / 5.9f));
 }
-// The tiles of a prefill pass by prefill_us, fitted to the same sweep.
+// The tiles of a prefill pass by prefill_us, fitted to the same sweep.  128 x 128, two to a compute unit, where row tiles of
+// 192 and 256 end badly: 769 - 896 rows of the 1.5B shape 64 us in 192 x 256, 59 in 128 x 128.
 constexpr PrefillTile gateup_tiles[] = {
     {19, 256, 256, 1, 11.36f, 1.101f, 1.541f, 0.f, 0.f}, {28, 192, 256, 1, 9.03f, 0.833f, 1.17f, 0.f, 0.f},
     {26, 256, 192, 1, 9.83f, 0.724f, 1.211f, 0.f, 0.f},  {27, 128, 192, 1, 9.73f, 0.837f, 0.687f, 0.f, 0.f},
+    {36, 128, 128, 2, 7.50f, 0.733f, 1.073f, 0.f, 0.f},
 };
 static int gateup_choose(int M, int N, int K) {
   int cfg = 0;
@@ -1173,19 +1178,20 @@ static int gateup_choose(int M, int N, int K) {
   return cfg;
 }
 // QKV, O and down projection at up to 256 rows: tile and K split by the same two streams (added as fourth powers: neither
-// hides the other wholly) and the adds of all splits, fitted to a sweep of 6 products x 6 row counts.  64 x 96
+// hides the other wholly) and the adds of all splits, fitted to sweeps of 6 products x 35 row counts; over the last one the
+// choice is 0.3 % (down 7B) to 7 % (O of the 1.5B shape: half a microsecond) from the best measured.  64 x 96
 // for 64 x 128 tiles: down of 88 rows 13.5 -> 11.9 us, of 256 rows 22.8 -> 20.6, O of the 7B shape at 128 rows 15.5 -> 13.6.
 struct NarrowTile {
   int cfg, bm, bn;
   float fixed, cu_gbs, add;            // us, GB/s per compute unit, us per million elements added
 };
-constexpr NarrowTile narrow_tiles[] = {{22, 32, 128, 4.28f, 67.4f, 2.48f}, {23, 64, 96, 4.30f, 70.1f, 2.11f},
-                                       {35, 128, 96, 4.50f, 70.0f, 3.05f}, {21, 128, 128, 3.73f, 66.2f, 2.85f}};
+constexpr NarrowTile narrow_tiles[] = {{22, 32, 128, 4.28f, 67.4f, 2.48f}, {23, 64, 96, 3.47f, 64.9f, 2.50f},
+                                       {35, 128, 96, 4.50f, 70.0f, 3.05f}, {21, 128, 128, 2.69f, 58.2f, 3.19f}};
 // Above 256 rows the tiles of one round of work-groups compete with those of a prefill pass: O of 301 rows 11.1 -> 9.7 us,
 // of 768 19.8 -> 13.1, of 1,024 20.2 -> 13.7; QKV of 301 12.6 -> 10.5, of 512 18.5 -> 12.5, of 768 19.0 -> 13.8; down
-// of 257 22.1 -> 19.8.  Over 45 (product, rows) from 257 to 1,024 the choice is 2 % from the best of 14 tiles on average.
-constexpr NarrowTile one_round_tiles[] = {{23, 64, 96, 4.30f, 70.1f, 2.11f}, {29, 96, 80, 3.96f, 68.9f, 2.79f},
-                                          {35, 128, 96, 3.70f, 67.0f, 3.05f}};
+// of 257 22.1 -> 19.8.  Over 114 (product, rows) from 257 to 1,024 the choice is 0.4 % from the best measured.
+constexpr NarrowTile one_round_tiles[] = {{23, 64, 96, 3.68f, 64.0f, 2.60f}, {29, 96, 80, 3.90f, 67.0f, 2.71f},
+                                          {35, 128, 96, 3.31f, 64.8f, 3.11f}};
 static float narrow_load(const NarrowTile& t, int M, int N, int K, int splits) {
   const int nk = K / BK, sps = (nk + splits - 1) / splits, parts = (nk + sps - 1) / sps;
   return (float)((N + t.bn - 1) / t.bn) * (float)((M + t.bm - 1) / t.bm) * (float)parts / 256.0f;
@@ -1308,14 +1314,14 @@ static int split_for(int M, int bm, int n_tiles, int nk) {
 // what it takes away.  Its parts add into C with float32 atomics in no fixed order, so that a pass no longer repeats
 // itself bit for bit; whole tiles all give the same bits, whatever their size.  Where tiles of 128 x 128 leave a
 // quarter of the compute units without work a cut is taken whenever it is the cheaper one (down of 1,024 rows 46 us,
-// 58 in the best whole tiles).  Beyond that a split has to save a ninth by price, and so has the evened launch below a
+// 58 in the best whole tiles).  Beyond that a split has to save a tenth by price, and so has the evened launch below a
 // whole round of tiles, where it cuts them all; from a round on, a thirty-second.  Down of 2,304 rows 86 us split, 88
 // whole; of 3,500 113 and 106; of 4,272 138 and 144; QKV of the 7B shape at 1,285 rows 70 and 59, its O at 1,700 71
 // and 64, down at 1,600 211 and 222, at 4,000 507 and 483, at 6,500 766 and 755; but down at 1,500 rows 195 and 219, at
 // 2,048 274 and 310, at 8,192 921 and 975.
 static void prefill_choose(int M, int N, int K, GemmMode mode, int* cfg, int* splits) {
   static const int steps[] = {1, 2, 3, 4, 6, 8, 12};
-  constexpr float SPLIT_SAVES = 1.0f - 1.0f / 9.0f, EVENED_SAVES = 1.0f - 1.0f / 32.0f;
+  constexpr float SPLIT_SAVES = 1.0f - 1.0f / 10.0f, EVENED_SAVES = 1.0f - 1.0f / 32.0f;
   const int nk = K / BK;
   const bool filled = (int64_t)((N + 127) / 128) * ((M + 127) / 128) > 192;
   float whole = 1e30f, split = 1e30f;

@@ -513,6 +513,24 @@ def test_gate_up_tiles_by_rows_and_width(L):
             assert height[cfg] <= 2 * max(M, 32) and 1 <= splits <= 12
 
 
+@pytest.mark.parametrize("M,N,K,mode,want", [
+    (132, 4608, 3584, 0, (23, 3)),       # 17.8 us; 19.0 in 128-row tiles
+    (88, 3584, 18944, 1, (35, 6)),       # 34.1; 37.7 in (21, 8)
+    (301, 3584, 3584, 1, (35, 2)),       # 21.3; 24.1 in (23, 1)
+    (301, 3584, 18944, 1, (27, 4)),      # 64.3; 69.0 in (28, 8)
+    (576, 1536, 8960, 1, (21, 4)),       # 32.5; 33.6 in (29, 2)
+    (2048, 1536, 8960, 1, (27, 2)),      # 71.0; 76.0 in (35, 1)
+    (2048, 3584, 18944, 1, (19, 2)),     # 246; 275 in (24, 1)
+    (1600, 4608, 3584, 0, (36, 1)),      # 63.1; 69.8 in (28, 1)
+    (832, 8960, 1536, 2, (36, 1))])      # 59.3; 63.9 in (28, 1)
+def test_choices_that_the_sweeps_bear_out(L, M, N, K, mode, want):
+    """Products for which a cheaper launch had been measured than the one that was taken."""
+    import ctypes as C
+    c, s = C.c_int32(), C.c_int32()
+    assert L.areal_op_gemm_choose(M, N, K, mode, C.byref(c), C.byref(s)) == 0
+    assert (c.value, s.value) == want
+
+
 def test_long_k_choice_names_the_kernel_it_launches(L):
     """Residual adds with a long K: 24 is the launch that is evened out along K, 26 and 28 the whole tiles of
     256 x 192 and 192 x 256.  Where whole tiles are the cheaper ones the choice says so, also where 192-column
