@@ -804,8 +804,12 @@ int attn_prefill_tile_rows(int n_q_heads, int n_kv_heads, int tiles32) {
   // (7B shape, 7 query heads per KV head: 532 TFLOP/s with 16 positions against 377 with 32)
   const int G = n_q_heads / n_kv_heads;
   if (forced && (forced == 16 || G <= 8)) return forced;
-  // Up to one 32-row work-group per compute unit: 16 rows, their heads over two work-groups (launch_attn_prefill)
-  return G <= 6 && tiles32 * n_kv_heads > 256 ? 32 : 16;
+  // Up to one 32-row work-group per compute unit: 16 rows where that leaves a wave fewer row-groups, one of 3 or 4 heads and
+  // of 5 or 6 dealt to two work-groups (launch_attn_prefill).  One launch, head_dim 128, a prompt of 301 / 1,000 /
+  // 2,000 tokens in 32 rows -> 16: 3 heads per KV head 16.9 / 37.4 / 67.2 -> 12.9 / 27.4 / 48.8 us, 4 heads 17.0 / 38.0 /
+  // 67.6 -> 13.2 / 27.9 / 49.8, 6 heads 17.9 / 39.4 / 71.2 -> 13.0 / 28.1 / 52.5.  1 or 2 heads have one row-group a wave in
+  // 32 rows too, and 16 only fetch every K/V tile twice as often: 12 prompts of 300 13.2 -> 14.0 and 13.9 -> 14.6.
+  return G > 6 || (G > 2 && tiles32 * n_kv_heads <= 256) ? 16 : 32;
 }
 
 hipError_t launch_attn_prefill(hipStream_t s, const f16* q, const AttnWork* work, int n_work,
