@@ -257,13 +257,12 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const f16* __restric
 }
 
 
-// Epilogue of the direct-to-LDS kernels: the wave's accumulators to C.  FULL: the tile lies wholly
+// Epilogue of dma_tile: the wave's accumulators to C.  FULL: the tile lies wholly
 // inside the matrix and no element is checked.  Row addresses are wave-uniform (scalar registers);
-// a lane adds one 32-bit offset.  With 24 slabs per tile (K = 1,536) the two waves of a SIMD spent about
-// a seventh of a gate/up tile here on bounds, 64-bit addresses, divisions and half-word stores:
-// 8,192 x 17,920 x 1,536 took 454 us, 424 with this form (on one card, with the loads and the slab order of that
-// time: dma_tile; wide_tile has these products now).  The division in silu is 16 us of such a product: 422 us with an approximate reciprocal
-// in its place, 437 with it.
+// a lane adds one 32-bit offset.  With bounds, 64-bit addresses and half-word stores instead, the two waves of a
+// SIMD spend about a seventh of a gate/up tile of 24 slabs (K = 1,536) here: 8,192 x 17,920 x 1,536 in 256 x 256 tiles
+// of dma_tile 454 us, 424 with this form.  The division in silu is 16 us of such a product: 422 us with an approximate
+// reciprocal in its place, 437 with it.
 template <int BM, int BN, int WM, int WN, int MODE, bool FULL>
 __device__ __forceinline__ void store_tile_part(const f32x16 (&acc)[BM / WM / 32][BN / WN / 32],
                                                 void* __restrict__ Cv, int M, int N, int ldc, int tile_m,
@@ -380,7 +379,7 @@ __device__ __forceinline__ void lse_pair_combine(float& m, float& s, float m2, f
 }
 
 // ---- direct-to-LDS variant ---------------------------------------------------
-// Same tiling, but the K-slabs travel HBM -> LDS with buffer_load_dwordx4 ... lds
+// Products of up to 32 rows, and 128 x 128 tiles.  Same tiling, but the K-slabs travel HBM -> LDS with buffer_load_dwordx4 ... lds
 // (no register staging) into a ring of STAGES slab buffers, so STAGES-1 slabs
 // of loads stay in flight per work-group.  One wavefront instruction moves a
 // group of 8 tile rows x 128 B; lane s of the group lands at byte s*16 of the
@@ -483,12 +482,9 @@ __device__ __forceinline__ void dma_tile(const f16* __restrict__ A, const GemmW&
   };
   // One slab's four K-steps are software-pipelined across the slab boundary: the barrier that frees
   // the stage stands in front of the last K-step's MFMAs, whose operands are in registers by then, and
-  // the next slab's first fragments are read behind it, under those MFMAs.  A 256 x 256 x 64 slab is
-  // 2,048 cycles of MFMAs and about as many of LDS traffic (192 KB read, 64 KB written), so what is not
-  // overlapped shows: with the barrier at the slab's start and every wait for fragments a wait for all
-  // of them, gate/up at 8,192 rows took 444 us and at 2,048 rows 136; so 423 and 127 (7B shape, 4,096
-  // rows: 1,012 -> 961 us; its down projection 532 -> 500; another card than the 424 us of the epilogue's
-  // comment).  These products have since gone over to wide_tile.
+  // the next slab's first fragments are read behind it, under those MFMAs.  In a 256 x 256 tile, whose slab is
+  // 2,048 cycles of MFMAs and about as many of LDS traffic, a barrier at the slab's start and waits for all
+  // fragments at once cost 5 - 7 % (gate/up of 8,192 rows 444 us, 423 in this order; of 2,048 rows 136 and 127).
   Frags f0, f1;
   if (kt0 >= kt1) return;
   const int k_last = (kt1 - 1) * BK;
@@ -1109,7 +1105,7 @@ constexpr PrefillTile TILE_256x192 = {26, 256, 192, 1, 12.54f, 0.715f, 1.157f, 1
 constexpr PrefillTile prefill_tiles[] = {
     {19, 256, 256, 1, 15.0f, 0.878f, 1.549f, 1.691f, 0.911f}, {28, 192, 256, 1, 11.44f, 0.715f, 1.157f, 1.80f, 0.982f},
     TILE_256x192,                                             {27, 128, 192, 1, 8.62f, 0.471f, 0.711f, 1.682f, 0.968f},
-    {21, 128, 128, 1, 7.57f, 0.368f, 0.58f, 1.297f, 0.599f},  {36, 128, 128, 2, 10.2f, 0.49f, 1.02f, 1.252f, 0.532f},
+    {21, 128, 128, 1, 7.57f, 0.368f, 0.58f, 1.297f, 0.599f},  {20, 128, 128, 2, 10.2f, 0.49f, 1.02f, 1.252f, 0.532f},
 };
 static float prefill_us(const PrefillTile& t, int M, int N, int K, int mode, int splits) {
   const int cols = mode == GEMM_SWIGLU_F16 ? t.bn / 2 : t.bn, nk = K / BK;
@@ -1149,7 +1145,7 @@ static bool evened_192(int M, int N, int K) {
 // 32.8 -> 28.8 at 301; 7B shape: 58.5 -> 48.7 at 24, 66 -> 51 at 64, 80 -> 59.5 at 128, 133 -> 95 at 256.  Over 65 + 30 row
 // counts from 257 to 8,192 (1.5B and 7B shape) the choice is 0.5 % from the best of 14 tiles on average, 6 % at most.
 struct StreamTile { int cfg, bm, bn; };
-constexpr StreamTile stream_tiles[] = {{12, 32, 80},   {10, 64, 80},   {29, 96, 80},   {21, 128, 80},  {20, 128, 144},
+constexpr StreamTile stream_tiles[] = {{36, 32, 80},   {37, 64, 80},   {29, 96, 80},   {38, 128, 80},  {39, 128, 144},
                                        {30, 64, 160},  {31, 96, 160},  {32, 128, 160}, {33, 160, 160}, {34, 192, 160}};
 static float stream_us(const StreamTile& t, int M, int N, int K) {
   const float load = (float)((2 * N + t.bn - 1) / t.bn) * (float)((M + t.bm - 1) / t.bm) / 256.0f;
@@ -1161,7 +1157,7 @@ static float stream_us(const StreamTile& t, int M, int N, int K) {
 constexpr PrefillTile gateup_tiles[] = {
     {19, 256, 256, 1, 11.36f, 1.101f, 1.541f, 0.f, 0.f}, {28, 192, 256, 1, 9.03f, 0.833f, 1.17f, 0.f, 0.f},
     {26, 256, 192, 1, 9.83f, 0.724f, 1.211f, 0.f, 0.f},  {27, 128, 192, 1, 9.73f, 0.837f, 0.687f, 0.f, 0.f},
-    {36, 128, 128, 2, 7.50f, 0.733f, 1.073f, 0.f, 0.f},
+    {20, 128, 128, 2, 7.50f, 0.733f, 1.073f, 0.f, 0.f},
 };
 static int gateup_choose(int M, int N, int K) {
   int cfg = 0;
@@ -1205,6 +1201,8 @@ static float narrow_us(const NarrowTile& t, int M, int N, int K, int splits) {
          t.add * (float)M * (float)N * 1e-6f * (parts > 1 ? (float)parts : 0.4f);
 }
 
+// A number stands for one tile in every mode that it serves (26 and 27 deal it to the waves differently for gate/up).
+// No choice returns 1, 3 and 5 to 18: areal_op_gemm serves them, as yardsticks for sweeps.
 template <int MODE>
 hipError_t dispatch(hipStream_t s, int cfg, const f16* A, const GemmW& W, void* C, int M, int N, int K,
                     int ldc, int splits) {
@@ -1220,13 +1218,9 @@ hipError_t dispatch(hipStream_t s, int cfg, const f16* A, const GemmW& W, void* 
     case 7: return run_dma<128, 128, 2, 2, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 8: return run_dma<128, 128, 2, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 9: return run_dma<256, 128, 4, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
-    case 10:
-      if constexpr (MODE == GEMM_SWIGLU_F16) return run_wide<64, 80, 4, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
-      else return run_dma<64, 128, 1, 2, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
+    case 10: return run_dma<64, 128, 1, 2, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 11: return run_dma<64, 128, 1, 2, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
-    case 12:
-      if constexpr (MODE == GEMM_SWIGLU_F16) return run_wide<32, 80, 2, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
-      else return run_dma<32, 128, 1, 2, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
+    case 12: return run_dma<32, 128, 1, 2, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 13: return run_dma<128, 64, 2, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 14: return run_dma<256, 64, 4, 1, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 15: return run_dma<128, 128, 2, 2, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
@@ -1234,13 +1228,8 @@ hipError_t dispatch(hipStream_t s, int cfg, const f16* A, const GemmW& W, void* 
     case 17: return run_dma<256, 128, 2, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 18: return run_wide<256, 256, 4, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 19: return run_wide<256, 256, 2, 4, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
-    case 20:
-      if constexpr (MODE == GEMM_SWIGLU_F16) return run_wide<128, 144, 8, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
-      else if constexpr (MODE == GEMM_ADD_F32) return run_wide<256, 192, 4, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
-      else return run_dma<128, 128, 4, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
-    case 21:
-      if constexpr (MODE == GEMM_SWIGLU_F16) return run_wide<128, 80, 8, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
-      else return run_dma<128, 128, 4, 2, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
+    case 20: return run_dma<128, 128, 4, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
+    case 21: return run_dma<128, 128, 4, 2, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 22:   // one 32-column panel per wave: no room for a gate/up pair
       if constexpr (MODE != GEMM_SWIGLU_F16) return run_dma<32, 128, 1, 4, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
       else return hipErrorInvalidValue;
@@ -1265,7 +1254,7 @@ hipError_t dispatch(hipStream_t s, int cfg, const f16* A, const GemmW& W, void* 
       if constexpr (MODE != GEMM_SWIGLU_F16) return run_wide<128, 192, 4, 2, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
       else return run_wide<128, 192, 4, 1, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 28: return run_wide<192, 256, 2, 4, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
-    // gate/up by StreamTile; 29 and 35 also stored and added by NarrowTile
+    // gate/up by StreamTile; 29 and 35 also stored and added by NarrowTile, 30 to 34 the output projection
     case 29: return run_wide<96, 80, 6, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 30: return run_wide<64, 160, 4, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 31: return run_wide<96, 160, 6, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
@@ -1273,14 +1262,17 @@ hipError_t dispatch(hipStream_t s, int cfg, const f16* A, const GemmW& W, void* 
     case 33: return run_wide<160, 160, 5, 1, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 34: return run_wide<192, 160, 6, 1, 3, MODE>(s, A, W, C, M, N, K, ldc, splits);
     case 35: return run_wide<128, 96, 4, 2, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
-    case 36: return run_dma<128, 128, 4, 2, 2, MODE>(s, A, W, C, M, N, K, ldc, splits);
+    case 36: return run_wide<32, 80, 2, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
+    case 37: return run_wide<64, 80, 4, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
+    case 38: return run_wide<128, 80, 8, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
+    case 39: return run_wide<128, 144, 8, 1, 4, MODE>(s, A, W, C, M, N, K, ldc, splits);
     default: return hipErrorInvalidValue;
   }
 }
 
 }  // namespace
 
-int gemm_num_configs() { return 37; }
+int gemm_num_configs() { return 40; }
 
 // Tile configuration and K split for a product of this shape: the cheapest by prices fitted to
 // sweeps over the configurations on the MI355X at the decoder's shapes, a few rules by row count
@@ -1327,8 +1319,6 @@ static void prefill_choose(int M, int N, int K, GemmMode mode, int* cfg, int* sp
   float whole = 1e30f, split = 1e30f;
   int split_cfg = -1, parts = 1;
   auto take = [&](int c, int sp, float us) {
-    // residual adds: 20 is the 256 x 192 tile where K is short, 26 where it is long enough for configuration 24
-    if (c == 26 && mode == GEMM_ADD_F32 && K < EVENED_MIN_K) c = 20;
     if (sp == 1 && us < whole) { whole = us; *cfg = c; }
     if (sp > 1 && us < split) { split = us; split_cfg = c; parts = sp; }
   };

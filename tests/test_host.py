@@ -437,7 +437,7 @@ def test_tile_choice_for_the_decoder_shapes(L):
     """areal_op_gemm_choose (host only): the tile configuration and K split the library takes for
     the products of the 1.5B and 7B shapes, at the row counts where the rules change.  Pins the
     rules that were read off sweeps on the MI355X, so that an edit of one does not silently
-    move another: configuration numbers as in gemm.hip's dispatch."""
+    move another: configuration numbers as in gemm.hip's dispatch, where a number is one tile in every mode."""
     import ctypes as C
 
     def choose(M, N, K, mode):
@@ -452,9 +452,9 @@ def test_tile_choice_for_the_decoder_shapes(L):
     assert choose(8192, F, H, SWIGLU) == (19, 1)
     assert choose(8192, H, F, ADD) == (24, 1)
     assert choose(8192, 3584, 18944, ADD) == (24, 1)
-    assert choose(8192, H, H, ADD)[0] == 20
+    assert choose(8192, H, H, ADD) == (26, 1)                 # 256 x 192, as every residual add in that tile
     # decode steps: gate/up by row count, no K split (the SwiGLU epilogue needs whole sums)
-    assert [choose(M, F, H, SWIGLU) for M in (24, 48, 100, 200)] == [(12, 1), (10, 1), (21, 1), (20, 1)]
+    assert [choose(M, F, H, SWIGLU) for M in (24, 48, 100, 200)] == [(36, 1), (37, 1), (38, 1), (39, 1)]
     # narrow products split K; the down projection at few rows takes 64-column tiles
     assert choose(24, H, F, ADD) == (25, 8)
     assert choose(100, H, F, ADD) == (23, 8)
@@ -503,8 +503,8 @@ def test_gate_up_tiles_by_rows_and_width(L):
         return c.value, s.value
 
     rows = (1, 32, 33, 64, 65, 96, 97, 128, 256, 257, 320, 321, 384)
-    assert [choose(M, 8960, 1536, 2)[0] for M in rows] == [12, 12, 10, 10, 29, 29, 21, 21, 20, 33, 33, 34, 34]
-    assert [choose(M, 18944, 3584, 2)[0] for M in rows[:9]] == [12, 12, 30, 30, 31, 31, 32, 32, 32]
+    assert [choose(M, 8960, 1536, 2)[0] for M in rows] == [36, 36, 37, 37, 29, 29, 38, 38, 39, 33, 33, 34, 34]
+    assert [choose(M, 18944, 3584, 2)[0] for M in rows[:9]] == [36, 36, 30, 30, 31, 31, 32, 32, 32]
     assert all(choose(M, N, 1536, 2)[1] == 1 for M in rows for N in (344, 8960))
     height = {22: 32, 23: 64, 25: 32, 35: 128, 21: 128}
     for N, K, mode in ((2048, 1536, 0), (1536, 1536, 1), (1536, 8960, 1), (3584, 18944, 1)):
@@ -521,8 +521,8 @@ def test_gate_up_tiles_by_rows_and_width(L):
     (576, 1536, 8960, 1, (21, 4)),       # 32.5; 33.6 in (29, 2)
     (2048, 1536, 8960, 1, (27, 2)),      # 71.0; 76.0 in (35, 1)
     (2048, 3584, 18944, 1, (19, 2)),     # 246; 275 in (24, 1)
-    (1600, 4608, 3584, 0, (36, 1)),      # 63.1; 69.8 in (28, 1)
-    (832, 8960, 1536, 2, (36, 1))])      # 59.3; 63.9 in (28, 1)
+    (1600, 4608, 3584, 0, (20, 1)),      # 63.1; 69.8 in (28, 1)
+    (832, 8960, 1536, 2, (20, 1))])      # 59.3; 63.9 in (28, 1)
 def test_choices_that_the_sweeps_bear_out(L, M, N, K, mode, want):
     """Products for which a cheaper launch had been measured than the one that was taken."""
     import ctypes as C
