@@ -16,7 +16,9 @@ forward (2e-2 as everywhere), with
   left (which then walks all its blocks itself);
 * the same run with the sets switched off, which must agree with the first to
   rounding, and under the library's own rule (sets only while most of the
-  context tokens a step reads are shared)."""
+  context tokens a step reads are shared);
+* rows cut in pieces of 128 tokens or more for the first two, and by the library's
+  own prices next to sets, forced and by the rule."""
 import os
 
 import numpy as np
@@ -41,15 +43,20 @@ def _f16_weights(w):
                 layers=[{k: _f16(v) for k, v in lw.items()} for lw in w["layers"]])
 
 
-def _run(cfg, w, prompts_by_seq, forced, drop_at, groups_on):
+def _run(cfg, w, prompts_by_seq, forced, drop_at, groups_on, min_chunk):
     import torch
     from paper_2505_24298_amd import binding
-    saved = {k: os.environ.get(k) for k in ("AREAL_DECODE_GROUPS", "AREAL_DECODE_MIN_CHUNK")}
+    saved = {k: os.environ.get(k) for k in ("AREAL_DECODE_GROUPS", "AREAL_DECODE_MIN_CHUNK",
+                                            "AREAL_DECODE_SPLIT_TARGET")}
+    os.environ.pop("AREAL_DECODE_SPLIT_TARGET", None)
     if groups_on is None:                  # the library's own rule: sets where most of the context read is shared
         os.environ.pop("AREAL_DECODE_GROUPS", None)
     else:
         os.environ["AREAL_DECODE_GROUPS"] = "1" if groups_on else "0"
-    os.environ["AREAL_DECODE_MIN_CHUNK"] = "128"
+    if min_chunk is None:                  # rows are cut by price, as in use; the knob alone switches that off
+        os.environ.pop("AREAL_DECODE_MIN_CHUNK", None)
+    else:
+        os.environ["AREAL_DECODE_MIN_CHUNK"] = str(min_chunk)
     try:
         n = len(prompts_by_seq)
         eng = binding.Areal(cfg, max_seqs=n, max_seq_len=max(PROMPT_LENS) + N_DECODE + 8, max_batch_tokens=1024,
@@ -104,9 +111,10 @@ def test_shared_prompt_blocks_walked_once_per_set(nq, nkv, d):
         ref[i] = decoder.forward(seq, w16, cfg, rows=list(range(T - 1, T + steps)))
     by_seq = [prompts[p] for p in prompt_of]
     runs = {}
-    for groups_on in (True, False, None):
-        print(f"heads {nq}/{nkv} d={d} sets {groups_on}", flush=True)
-        got, counters = _run(cfg, w, by_seq, forced, drop_at, groups_on)
+    for groups_on, min_chunk in ((True, 128), (False, 128), (None, None), (True, None)):
+        print(f"heads {nq}/{nkv} d={d} sets {groups_on} rows cut {'by price' if min_chunk is None else min_chunk}",
+              flush=True)
+        got, counters = _run(cfg, w, by_seq, forced, drop_at, groups_on, min_chunk)
         # what the sets must have covered: per step, every prompt with a full block and two live samples
         rows = row_tokens = set_tokens = 0
         for t in range(N_DECODE):
@@ -120,7 +128,7 @@ def test_shared_prompt_blocks_walked_once_per_set(nq, nkv, d):
         if groups_on is None:
             # 84 % of the context tokens of the first steps are shared (the 16 samples of the 300-token
             # prompt), less once most of them have finished: some steps with sets, some without
-            assert 0 < counters[0] < runs[True][1][0]
+            assert 0 < counters[0] < runs[True, 128][1][0]
         else:
             assert counters == (rows, row_tokens, set_tokens)
         worst = 0.0
@@ -129,11 +137,13 @@ def test_shared_prompt_blocks_walked_once_per_set(nq, nkv, d):
                 worst = max(worst, float(np.abs(logits - ref[i][t]).max()))
         print(f"  logits against the oracle {worst:.2e}", flush=True)
         assert worst <= LOGIT_TOL
-        runs[groups_on] = (got, counters)
-    diff = max(float(np.abs(runs[True][0][t][i] - runs[False][0][t][i]).max())
-               for t in runs[True][0] for i in runs[True][0][t])
-    print(f"  sets on against off {diff:.2e}", flush=True)
-    assert diff <= 2e-3
+        runs[groups_on, min_chunk] = (got, counters)
+    off = runs[False, 128][0]
+    for min_chunk in (128, None):
+        on = runs[True, min_chunk][0]
+        diff = max(float(np.abs(on[t][i] - off[t][i]).max()) for t in on for i in on[t])
+        print(f"  sets on against off {diff:.2e}", flush=True)
+        assert diff <= 2e-3
 
 
 @pytest.mark.parametrize("T", [2000, 4000])
@@ -213,6 +223,54 @@ def test_more_slots_than_a_row_has_every_row_walks_its_own_blocks():
                 os.environ.pop(k, None)
             else:
                 os.environ[k] = v
+
+
+@pytest.mark.parametrize("nq,nkv,d,shared", [(6, 1, 128, 40), (14, 2, 128, 130), (4, 2, 32, 9)])
+def test_rows_cut_by_price_next_to_their_set(nq, nkv, d, shared):
+    """Seven sequences of 2,100 - 6,000 tokens that hold their first blocks together, cut by the library's own prices: rows
+    of several segments and of one, in the slots that the set leaves.  The K/V are whatever the arena holds (no
+    oracle): against the same step with the sets switched off."""
+    import torch
+    from paper_2505_24298_amd import binding
+    cfg = synth.shape("tiny", n_layers=1, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, hidden=256, ffn=512,
+                      rope_theta=1.0e6)
+    w = binding.weights_to_device(synth.make_weights(cfg, 3, qkv_bias=True, std=0.03), bf16=False)
+    lens = [6000, 2100, 2101, 4097, 3333, 2207, 5119]
+    ids = list(range(len(lens)))
+    # some row has several segments of its own, so that both kinds of partial meet in one merge
+    own = np.array([v + 1 - 16 * shared for v in lens], np.int32)
+    home, plan = np.zeros(len(lens), np.int32), np.zeros((512, 4), np.int32)
+    ptr = lambda x: x.ctypes.data_as(binding._I32P)
+    pieces = -(-16 * shared // max(64, -(-16 * shared // 512) * 64))
+    k = binding.host_lib().areal_plan_decode(len(lens), ptr(own), ptr(home), nkv, 32 - pieces, 0, 256, ptr(plan), len(plan))
+    assert 0 < k <= len(plan) and plan[:k][plan[:k, 0] >= 0, 3].max() >= 1
+    knobs = ("AREAL_DECODE_GROUPS", "AREAL_DECODE_MIN_CHUNK", "AREAL_DECODE_SPLIT_TARGET")
+    saved = {k: os.environ.pop(k, None) for k in knobs}
+    out = []
+    try:
+        for groups_on in (True, False):
+            os.environ["AREAL_DECODE_GROUPS"] = "1" if groups_on else "0"
+            eng = binding.Areal(cfg, max_seqs=len(lens), max_seq_len=max(lens) + 16, max_batch_tokens=256,
+                                kv_blocks=sum(v // 16 + 2 for v in lens), convert_weights=True)
+            eng.load_weights(w, 0)
+            g = torch.Generator(device="cuda").manual_seed(5)
+            eng.kv_arena.view(torch.float16).normal_(generator=g)
+            eng.adopt_seq(0, lens[0], 1)
+            for i in ids[1:]:
+                eng.adopt_seq(i, lens[i], 1, src_id=0, n_shared_blocks=shared)
+            toks = torch.arange(1, len(lens) + 1, dtype=torch.int32, device="cuda")
+            out.append(np.stack([eng.decode_step(ids, toks).cpu().numpy() for _ in range(2)]))
+            assert eng.decode_set_counters()[0] == (2 * len(lens) if groups_on else 0)
+            eng.close()
+    finally:
+        for k, v in saved.items():
+            if v is None:
+                os.environ.pop(k, None)
+            else:
+                os.environ[k] = v
+    diff = float(np.abs(out[0] - out[1]).max())
+    print(f"heads {nq}/{nkv} d={d}, {shared} shared blocks: sets on against off {diff:.2e}", flush=True)
+    assert np.isfinite(out[0]).all() and diff <= 2e-3
 
 
 def test_many_short_rows_next_to_long_ones():
