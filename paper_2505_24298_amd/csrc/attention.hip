@@ -205,7 +205,7 @@ __device__ __forceinline__ void rotate(RawHead<D>& r, const f16* __restrict__ bi
 // owns tile w of the set: 16 MFMA rows = floor(16 / G) sequences x their G query heads, so
 // every lane has its own sequence, position and query head.  Each wave walks all blocks of the
 // chunk (the four waves read the same tiles: one fetch from L2 per work-group) and writes
-// its rows' partial (max, sum, accumulator) into slot n_splits + chunk of those rows; the
+// its rows' partial (max, sum, accumulator) into slot n_own + u of those rows (n_own: the launch's most own segments); the
 // merge kernel folds them into the rows' own partials.  Every shared position precedes every
 // row's position, so nothing is masked but the tail of the last block pair.
 template <int D>

@@ -42,12 +42,7 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
-// Value of another lane of the same 16 (DPP): 0xB1 = lane ^ 1, 0x4E = lane ^ 2, 0x141 = lane ^ 7,
-// 0x128 = lane ^ 8.
-template <int CTRL>
-__device__ __forceinline__ float dpp_f32(float x) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xF, 0xF, false));
-}
+// Value of lane ^ 1 (DPP).
 __device__ __forceinline__ uint32_t dpp_xor1(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xF, 0xF, false);
 }
