@@ -45,9 +45,11 @@ SHAPE_LABEL = {"qwen2-1.5b": "Qwen2-1.5B", "qwen2-7b": "Qwen2-7B", "tiny": "tiny
 # HBM bytes the decode attention kernel moves, from rocprofv3 FETCH_SIZE / WRITE_SIZE runs
 # calibrated with a plain copy (profiles/attn_decode_kernel_hbm_traffic.md): bytes fetched per
 # byte of K/V that exists once in HBM (the samples of a prompt read the same prompt blocks; a
-# block is fetched about once per launch), and bytes written per per-sequence K/V byte read
+# block is fetched about once per launch), and bytes written per per-sequence K/V byte read: counted
+# 0.028 with rows cut at equal lengths, of which the stores of that cut are 0.026; the stores of the
+# present cut, whose segments are longer and whose uncut rows leave no partials, are 0.0114
 ATTN_DECODE_FETCH_OVER_DISTINCT = 1.033
-ATTN_DECODE_WRITE_OVER_ALGORITHMIC = 0.028
+ATTN_DECODE_WRITE_OVER_ALGORITHMIC = 0.0124
 
 
 def log(msg):
@@ -275,8 +277,8 @@ def summarise(args, cfg, wl, n, runs, warmups_done, copy_gbs, cpu_baseline, bind
                         traffic_unit="bytes per launch: rocprofv3 FETCH_SIZE + WRITE_SIZE of this kernel at this "
                                      "workload's context mixes and block sharing, taken on microbench.py (the counter "
                                      "profiler does not survive bench.py) as ratios to the K/V bytes that exist once "
-                                     "in HBM (fetch) and to the algorithmic bytes (write), applied to this run's bytes "
-                                     "per launch (profiles/attn_decode_kernel_hbm_traffic.md)",
+                                     "in HBM (fetch) and to the algorithmic bytes (write; scaled to the stores of the "
+                                     "present cut of the rows), applied to this run's bytes per launch (profiles/attn_decode_kernel_hbm_traffic.md)",
                         frac_of_measured_copy=None if not copy_gbs else round(achieved / copy_gbs, 4),
                         algorithmic_bytes_per_launch=int(alg_per_launch),
                         distinct_kv_bytes_per_launch=int(distinct_per_launch),
