@@ -1094,8 +1094,9 @@ hipError_t run(hipStream_t s, const f16* A, const GemmW& W, void* C, int M, int 
 // compute unit walks (slower the fuller the chip: clocks and L2 are shared), and the adds into C per
 // million elements (with atomics for every split, or read and written once).  Constants: fitted to sweeps of
 // 8 products (1.5B and 7B shape) x 18 - 50 row counts from 257 to 8,192 x tiles x splits; over the last one (10,458 times
-// on one card) the choice, small tiles, evened launch and whole tiles included, is 0.6 % from the best on average.
-// Farthest off are down of the 7B shape at 1,345 - 1,408 rows (212 us for 183 with a split that adds with atomics, see
+// on one card) the choice, small tiles, evened launch and whole tiles included, is 0.6 % from the best of these tiles on average.
+// Tiles of 160 columns, gate/up's, would be better at some row counts (O 7B of 1,700 rows 58 us in 160 x 160, 65 chosen).
+// Farthest off else are down of the 7B shape at 1,345 - 1,408 rows (212 us for 183 with a split that adds with atomics, see
 // prefill_choose), its O at 317 - 320 (24.1 for 21.5), and QKV of 3,969 - 4,096 rows (37.4 for 34.7).
 struct PrefillTile {
   int cfg, bm, bn, per_cu;        // work-groups of this tile a compute unit holds
@@ -1141,8 +1142,8 @@ static bool evened_192(int M, int N, int K) {
 // that (rows + columns) of a tile times 2 K bytes at 41 GB/s is its time, where all weights at 5.9 TB/s do not take longer.
 // So tiles are chosen whose work-groups come as close to 256 as the width allows (8,960 features: 224 of 40,
 // 125 x 2 of 72; 18,944: 237 of 80), with no more rows than the launch has.  Measured against tiles of
-// 64 features, 1.5B shape: 15.1 -> 13.4 us at 24 rows, 18.9 -> 15.4 at 64, 20.4 -> 18.4 at 88, 34.7 -> 24.8 at 256,
-// 32.8 -> 28.8 at 301; 7B shape: 58.5 -> 48.7 at 24, 66 -> 51 at 64, 80 -> 59.5 at 128, 133 -> 95 at 256.  Over 65 + 30 row
+// 64 features, 1.5B shape: 15.1 -> 13.3 us at 24 rows, 18.9 -> 15.4 at 64, 20.4 -> 17.4 at 88, 34.7 -> 24.7 at 256,
+// 32.8 -> 27.7 at 300; 7B shape: 58.5 -> 48.4 at 24, 66 -> 49 at 64, 80 -> 57 at 128, 133 -> 93 at 256.  Over 65 + 30 row
 // counts from 257 to 8,192 (1.5B and 7B shape) the choice is 0.5 % from the best of 14 tiles on average, 6 % at most.
 struct StreamTile { int cfg, bm, bn; };
 constexpr StreamTile stream_tiles[] = {{36, 32, 80},   {37, 64, 80},   {29, 96, 80},   {38, 128, 80},  {39, 128, 144},
