@@ -100,7 +100,7 @@ typedef struct {
  * float32 atomic adds in no fixed order (about 1e-7 of a sum), so that here and there an activation
  * rounds to the next half and logits can differ from run to run (4e-4 of their norm measured).  Split are the
  * projections of decode steps, those of passes that leave compute units idle (at the 1.5B shape up to
- * 2,048 rows), and the long-K down projection of larger passes where that saves more than it is worth (7B shape).
+ * 2,048 rows), and the long-K down projection of larger passes where whole tiles would take clearly longer (7B shape).
  * AREAL_GEMM_MAX_SPLITS=1 in the environment removes the splits,
  * and with them the run-to-run differences, at a cost in speed there.  The sampler is a
  * pure function of the logits it is given. */
