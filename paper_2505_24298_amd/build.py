@@ -15,7 +15,11 @@ SOURCES = ["elementwise.hip", "gemm.hip", "attention.hip", "sampler.hip", "scori
 HOST_SAN_LIB = os.path.join(OBJ, "libareal_host_san.so")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          # packed float32 VALU forms are kept out of the generated code
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # The first 14 words of a kernel's scalar arguments arrive in registers with its launch instead of being
+         # read from memory: 0.4 - 0.6 us less for a small kernel whose predecessor streamed through the caches.
+         # (A struct by value ends the run of such arguments, so kernels take what they need first as scalars.)
+         "-mllvm", "-amdgpu-kernarg-preload-count=16"]
 
 
 def _hipcc():

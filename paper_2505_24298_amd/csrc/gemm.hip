@@ -39,53 +39,103 @@ __device__ __forceinline__ const f16* w_row_ptr(const GemmW& W, int tile_n, int 
   }
 }
 
-// Rows of the matrix from row `b` of the W tile on (none or less: that row lies outside).
-template <int BN, int MODE>
-__device__ __forceinline__ int w_rows_left(int tile_n, int b, int N) {
-  if (MODE == GEMM_SWIGLU_F16) return N - (tile_n * (BN / 2) + (b >> 6) * 32 + (b & 31));
-  return N - (tile_n * BN + b);
-}
+// The weights as the direct-to-LDS kernels take them: scalar arguments, which arrive in registers with the launch.
+// What comes before the first load counts in a decode step, whose products of a few microseconds cannot start before
+// the kernel ahead of them ends: with the arguments read from memory (a struct, and one of its pointers again
+// for every row group) and divisions in the tile map, a wave of the 32 x 80 gate/up tile ran some 300 instructions and
+// ten dependent reads before its first load; with scalars, the map below and one resource per operand about 110 and
+// none.  Decode step of one row 1,370 -> 1,251 us, of 24 rows 2,183 -> 2,066, of 88 3,107 -> 3,011, one prompt of 301 tokens
+// 2,591 -> 2,525 (a part of it from the other kernels' arguments).
+struct WRows {
+  const f16 *p0, *p1, *p2;
+  int end0, end1;
+};
 
-// Block id -> (row tile, column tile, K split).  Work-groups are handed to the 8
-// XCDs round-robin, so ids equal mod 8 share one L2.
-//  * Above 256 rows (prefill): the tiles are numbered band by band (4 column tiles),
-//    inside a band in blocks of 8 row tiles, one K split after the other, and XCD x
+// Buffer resources of the row groups of a tile.  Rows outside the matrix lie outside the resource: they read as zero,
+// without touching memory, and feed only accumulator rows / columns that are never stored.
+template <int BM, int BN, int MODE>
+struct TileRsrc {
+  static constexpr int NC = MODE == GEMM_SWIGLU_F16 ? BN / 2 : BN;
+  __amdgpu_buffer_rsrc_t a, w0, w1;
+  uint64_t seg0, to1, to2;          // stored products: address of the first segment, and what leads on to the others
+  int end0, end1, n0, N, K;
+  __device__ __forceinline__ TileRsrc(const f16* A, WRows W, int M, int n, int k, int tile_m, int tile_n)
+      : seg0((uint64_t)W.p0), to1((uint64_t)W.p1 ^ (uint64_t)W.p0), to2((uint64_t)W.p2 ^ (uint64_t)W.p1), end0(W.end0),
+        end1(W.end1), n0(tile_n * NC), N(n), K(k) {
+    a = buffer_rsrc(A + (int64_t)(tile_m * BM) * K, (uint32_t)min(M - tile_m * BM, BM) * (uint32_t)K * 2u);
+    const uint32_t bytes = (uint32_t)min(N - n0, NC) * (uint32_t)K * 2u;
+    if (MODE != GEMM_STORE_F32) w0 = buffer_rsrc(W.p0 + (int64_t)n0 * K, bytes);
+    if (MODE == GEMM_SWIGLU_F16) w1 = buffer_rsrc(W.p1 + (int64_t)n0 * K, bytes);
+  }
+  // Rows b0 .. b0 + 7 of the W tile (stored products: of up to three segments, each of whole groups but the last; a
+  // group below the matrix takes its last one), or, of gate and up, the rows of the same features.
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t w(int b0, bool is_up) const {
+    if (MODE == GEMM_SWIGLU_F16) return is_up ? w1 : w0;
+    if (MODE != GEMM_STORE_F32) return w0;
+    const int n = min(n0 + b0, (N - 1) & ~7);
+    const bool in1 = n >= end0, in2 = in1 && n >= end1;              // (one segment: end0 = N, end1 unset)
+    const uint64_t p = seg0 ^ (in1 ? to1 : 0) ^ (in2 ? to2 : 0);
+    const int start = in2 ? end1 : (in1 ? end0 : 0);
+    return buffer_rsrc(reinterpret_cast<const f16*>(p) + (int64_t)(n - start) * K, (uint32_t)min(8, N - n) * (uint32_t)K * 2u);
+  }
+};
+
+// Arguments that a kernel needs late: read from memory where they are used.
+struct GemmLate {
+  void* C;
+  int ldc;
+  GemmLse lse;
+};
+
+// Block -> (row tile, column tile, K split).  Work-groups are handed to the 8 XCDs round-robin in launch order, x fastest,
+// so ids equal mod 8 share one L2.
+//  * Up to 256 rows (decode): a unit = (column tile, K split) with all its
+//    row tiles, so that the work-groups that read one W slab run side by side on
+//    one XCD; units go to the XCDs round-robin, which keeps the XCDs evenly
+//    loaded whatever the number of column tiles (1536 columns = 12 tiles).  The grid is (8, row tiles, units / 8), and the
+//    one division left is a multiplication by `map` = 2^32 / column tiles, rounded up (0: one column tile): such a
+//    launch is a few microseconds, and a wave needs about 0.1 us for each 64 instructions it runs before its first load.
+//  * Above 256 rows (prefill), map = kLinearMap, a grid of one dimension: the tiles are numbered band by band (4 column
+//    tiles), inside a band in blocks of 8 row tiles, one K split after the other, and XCD x
 //    takes the x-th eighth of that row of tiles: every XCD gets the same number of
 //    tiles whatever the shape, and the 32 work-groups resident on its compute units
 //    are neighbours that share A and W slabs in its L2.  (Column tiles handed out
 //    round-robin left XCDs idle where their number is not a multiple of 8: with 12
 //    tiles of 128 columns, four XCDs did two thirds of the O projection.)
-//  * Up to 256 rows (decode): a unit = (column tile, K split) with all its
-//    row tiles, so that the work-groups that read one W slab run side by side on
-//    one XCD; units go to the XCDs round-robin, which keeps the XCDs evenly
-//    loaded whatever the number of column tiles (1536 columns = 12 tiles).
 constexpr int BAND_N = 4, BAND_M = 8, DECODE_ROWS = 256;
-__host__ __device__ __forceinline__ int grid_blocks(int M, int m_tiles, int n_tiles, int splits) {
-  if (M <= DECODE_ROWS) return 8 * ((n_tiles * splits + 7) / 8) * m_tiles;
-  return 8 * ((m_tiles * n_tiles * splits + 7) / 8);
+constexpr uint32_t kLinearMap = 0xFFFFFFFFu;
+struct Grid { dim3 dim; uint32_t map; };
+static Grid make_grid(int M, int m_tiles, int n_tiles, int splits) {
+  const int64_t units = (int64_t)n_tiles * splits, deep = (units + 7) / 8;
+  // unit / column tiles by `map` is exact while (units + 8) * column tiles stays below 2^32
+  if (M <= DECODE_ROWS && deep < 65536 && (units + 8) * n_tiles < (int64_t)1 << 32)
+    return {dim3(8, m_tiles, (unsigned)deep), n_tiles == 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + n_tiles - 1) / n_tiles)};
+  return {dim3((unsigned)(8 * ((units * m_tiles + 7) / 8))), kLinearMap};
 }
-__device__ __forceinline__ bool tile_of_block(int id, int M, int m_tiles, int n_tiles, int splits, int& tile_m,
-                                              int& tile_n, int& split) {
-  const int xcd = id & 7, q = id >> 3;
-  if (M <= DECODE_ROWS) {
-    const int unit = (q / m_tiles) * 8 + xcd;
-    tile_m = q % m_tiles;
-    tile_n = unit % n_tiles;
-    split = unit / n_tiles;   // the up to 7 padding units get split >= the split count: an empty
-    return true;              // K range, on which the kernels return before touching memory
+__device__ __forceinline__ bool tile_of_block(uint32_t map, int m_tiles, int n_tiles, int nk, int sps, int& tile_m, int& tile_n,
+                                              int& split) {
+  if (map != kLinearMap) {
+    const uint32_t unit = blockIdx.z * 8 + blockIdx.x;
+    tile_m = blockIdx.y;
+    split = map ? __umulhi(unit, map) : unit;   // the up to 7 padding units get split >= the split count: an empty
+    tile_n = unit - split * n_tiles;            // K range, on which the kernels return before touching memory
+    return true;
   }
-  const int tiles = m_tiles * n_tiles;
+  const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
+  const int tiles = m_tiles * n_tiles, splits = sps < nk ? (nk + sps - 1) / sps : 1;
   const int64_t units = (int64_t)tiles * splits;
   const int u = (int)(units * xcd / 8) + q;
   if (u >= (int)(units * (xcd + 1) / 8)) return false;
-  split = u / tiles;
+  split = splits == 1 ? 0 : u / tiles;
   const int t = u - split * tiles;
   const int band = t / (BAND_N * m_tiles), in_band = t - band * BAND_N * m_tiles;
   const int width = min(BAND_N, n_tiles - band * BAND_N);
   const int blk = in_band / (BAND_M * width), in_blk = in_band - blk * BAND_M * width;
   const int height = min(BAND_M, m_tiles - blk * BAND_M);
-  tile_m = blk * BAND_M + in_blk % height;
-  tile_n = band * BAND_N + in_blk / height;
+  // scalars, whatever unit the compiler divides on: a buffer resource in vector registers makes a loop of every load
+  split = __builtin_amdgcn_readfirstlane(split);
+  tile_m = __builtin_amdgcn_readfirstlane(blk * BAND_M + in_blk % height);
+  tile_n = __builtin_amdgcn_readfirstlane(band * BAND_N + in_blk / height);
   return true;
 }
 
@@ -93,10 +143,9 @@ __device__ __forceinline__ bool tile_of_block(int id, int M, int m_tiles, int n_
 __device__ __forceinline__ float silu_f(float z) { return z / (1.0f + __expf(-z)); }
 
 template <int BM, int BN, int WM, int WN, int MODE, bool RAGGED_K>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const f16* __restrict__ A, GemmW W,
-                                                            void* __restrict__ Cv, int M, int N, int K,
-                                                            int ldc, int m_tiles, int n_tiles,
-                                                            int splits, int slabs_per_split, int atomic) {
+__global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const f16* __restrict__ A, int M, int N, int K,
+                                                            uint32_t map, int slabs_per_split, int ldc,
+                                                            void* __restrict__ Cv, int atomic, GemmW W) {
   constexpr int NT = WM * WN * 64;
   constexpr int TM = BM / WM / 32, TN = BN / WN / 32;   // 32x32 MFMA tiles per wave
   constexpr int ACH = BM * 8 / NT, BCH = BN * 8 / NT;   // 16-B chunks per thread per slab
@@ -105,10 +154,10 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const f16* __restric
   __shared__ __attribute__((aligned(16))) f16 sA[2][BM * LDS_K];
   __shared__ __attribute__((aligned(16))) f16 sB[2][BN * LDS_K];
 
-  // block id -> (row tile, column tile, K split): ids that differ by a multiple
-  // of 8 sit on the same XCD; the row tiles of one weight panel are adjacent there.
+  constexpr int NC = MODE == GEMM_SWIGLU_F16 ? BN / 2 : BN;
   int tile_m, tile_n, split;
-  if (!tile_of_block(blockIdx.x, M, m_tiles, n_tiles, splits, tile_m, tile_n, split)) return;
+  if (!tile_of_block(map, (M + BM - 1) / BM, (N + NC - 1) / NC, (K + BK - 1) / BK, slabs_per_split, tile_m, tile_n, split))
+    return;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
@@ -390,7 +439,7 @@ constexpr int GROUP_BYTES = 1024 + 128;   // 8 rows x 128 B, + 128 B skew betwee
 
 // One tile over the K slabs [kt0, kt1), through the ring in `lds` (STAGES * STAGE_BYTES bytes).
 template <int BM, int BN, int WM, int WN, int STAGES, int MODE>
-__device__ __forceinline__ void dma_tile(const f16* __restrict__ A, const GemmW& W, void* __restrict__ Cv, int M,
+__device__ __forceinline__ void dma_tile(const f16* __restrict__ A, const WRows& W, void* __restrict__ Cv, int M,
                                          int N, int K, int ldc, int tile_m, int tile_n, int kt0, int kt1,
                                          int atomic, char* lds) {
   constexpr int NW = WM * WN;
@@ -403,40 +452,38 @@ __device__ __forceinline__ void dma_tile(const f16* __restrict__ A, const GemmW&
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
-  const int m0 = tile_m * BM;
 
   // This wave's share of the row groups: GA/NW groups of A, then GB/NW of B.  The loads are buffer
   // loads (a scalar base, a lane's 32-bit offset and the slab's scalar offset), not global ones: these
   // are FLAT instructions to the compiler's wait insertion, which then waits for every LDS read in
-  // flight wherever it has to wait for one.  A is based at the tile's first row, a row group of W at
-  // its own first row (the 8 rows lie in one segment: dispatch checks that).
-  const auto a_rsrc = buffer_rsrc(A + (int64_t)m0 * K, (uint32_t)min(M - m0, BM) * (uint32_t)K * 2u);
+  // flight wherever it has to wait for one.
+  const TileRsrc<BM, BN, MODE> tile(A, W, M, N, K, tile_m, tile_n);
+  // A load's byte offset is a lane's (the same for all loads of A, and where they follow one another, of W) and a scalar one.
   __amdgpu_buffer_rsrc_t b_rsrc[GB / NW];
-  int src[LPS], dst_off[LPS];
+  int src[LPS], soff[LPS], dst_off[LPS];
   {
     const int rin = lane >> 3;                          // row inside the group
+    const int chunk = (lane & 7) ^ rin;
 #pragma unroll
     for (int i = 0; i < LPS; ++i) {
       const bool is_a = i < GA / NW;
-      const int gi = is_a ? wave * (GA / NW) + i : wave * (GB / NW) + (i - GA / NW);
-      const int chunk = (lane & 7) ^ rin;
-      if (is_a) {
-        src[i] = (min(gi * 8 + rin, M - 1 - m0) * K + chunk * 8) * 2;
-        dst_off[i] = gi * GROUP_BYTES;
-      } else {
-        // rows outside the matrix are replaced by one inside: their products are never stored
-        const int left = w_rows_left<BN, MODE>(tile_n, gi * 8, N);
-        const f16* p = left > 0 ? w_row_ptr<BN, MODE>(W, tile_n, gi * 8, N, K) : W.ptr[0];
-        b_rsrc[i - GA / NW] = buffer_rsrc(p, 8u * (uint32_t)K * 2u);
-        src[i] = ((rin < left ? rin : 0) * K + chunk * 8) * 2;
-        dst_off[i] = (GA + gi) * GROUP_BYTES;
+      const int first = wave * ((is_a ? GA : GB) / NW), k = is_a ? i : i - GA / NW;
+      int row = first * 8 + rin, ahead = k * 8;
+      if (!is_a) {
+        const int gi = first + k;
+        b_rsrc[k] = tile.w(gi * 8, (gi >> 2) & 1);
+        if (MODE == GEMM_SWIGLU_F16) { row = (gi >> 3) * 32 + (gi & 3) * 8 + rin; ahead = 0; }    // feature of the tile
+        if (MODE == GEMM_STORE_F32) { row = rin; ahead = 0; }
       }
+      src[i] = (row * K + chunk * 8) * 2;
+      soff[i] = ahead * K * 2;
+      dst_off[i] = ((is_a ? 0 : GA) + first + k) * GROUP_BYTES;
     }
   }
   auto issue = [&](int stage, int k0) {
 #pragma unroll
     for (int i = 0; i < LPS; ++i)
-      dma16(i < GA / NW ? a_rsrc : b_rsrc[i < GA / NW ? 0 : i - GA / NW], src[i], k0 * 2,
+      dma16(i < GA / NW ? tile.a : b_rsrc[i < GA / NW ? 0 : i - GA / NW], src[i], k0 * 2 + soff[i],
             lds + stage * STAGE_BYTES + dst_off[i]);
   };
 
@@ -486,7 +533,6 @@ __device__ __forceinline__ void dma_tile(const f16* __restrict__ A, const GemmW&
   // 2,048 cycles of MFMAs and about as many of LDS traffic, a barrier at the slab's start and waits for all
   // fragments at once cost 5 - 7 % (gate/up of 8,192 rows 444 us, 423 in this order; of 2,048 rows 136 and 127).
   Frags f0, f1;
-  if (kt0 >= kt1) return;
   const int k_last = (kt1 - 1) * BK;
   // prologue: STAGES slabs in flight (past the end: re-read the last slab, never consumed)
 #pragma unroll
@@ -537,18 +583,20 @@ __device__ __forceinline__ void dma_tile(const f16* __restrict__ A, const GemmW&
   wait_vmcnt(0);
 }
 
+// The first 14 words of the arguments (those before `late`) arrive in registers; nk_sps: K slabs | slabs per split << 16.
 template <int BM, int BN, int WM, int WN, int STAGES, int MODE>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_dma_kernel(const f16* __restrict__ A, GemmW W,
-                                                                void* __restrict__ Cv, int M, int N,
-                                                                int K, int ldc, int m_tiles,
-                                                                int n_tiles, int splits, int slabs_per_split,
-                                                                int atomic) {
+__global__ __launch_bounds__(WM * WN * 64) void gemm_dma_kernel(
+    const f16* __restrict__ A, const f16* __restrict__ w0, const f16* __restrict__ w1, const f16* __restrict__ w2,
+    int M, int N, uint32_t nk_sps, uint32_t map, int end0, int end1, GemmLate late) {
   __shared__ __attribute__((aligned(16))) char lds[STAGES * (BM / 8 + BN / 8) * GROUP_BYTES];
+  constexpr int NC = MODE == GEMM_SWIGLU_F16 ? BN / 2 : BN;
+  const int nk = nk_sps & 0xFFFF, sps = nk_sps >> 16;
   int tile_m, tile_n, split;
-  if (!tile_of_block(blockIdx.x, M, m_tiles, n_tiles, splits, tile_m, tile_n, split)) return;
-  const int kt0 = split * slabs_per_split;
-  dma_tile<BM, BN, WM, WN, STAGES, MODE>(A, W, Cv, M, N, K, ldc, tile_m, tile_n, kt0,
-                                         min(K / BK, kt0 + slabs_per_split), atomic, lds);
+  if (!tile_of_block(map, (M + BM - 1) / BM, (N + NC - 1) / NC, nk, sps, tile_m, tile_n, split)) return;
+  const int kt0 = split * sps, kt1 = min(nk, kt0 + sps);
+  if (kt0 >= kt1) return;
+  dma_tile<BM, BN, WM, WN, STAGES, MODE>(A, WRows{w0, w1, w2, end0, end1}, late.C, M, N, nk * BK, late.ldc, tile_m,
+                                         tile_n, kt0, kt1, sps < nk, lds);
 }
 
 // ---- direct-to-LDS tiles on the 16x16x32 MFMA: the prefill sizes --------------
@@ -768,7 +816,7 @@ __device__ __forceinline__ void store_wide_lse(const f32x4 (&acc)[BM / WM / 16][
 }
 
 template <int BM, int BN, int WM, int WN, int STAGES, int MODE>
-__device__ __forceinline__ void wide_tile(const f16* __restrict__ A, const GemmW& W, void* __restrict__ Cv, int M,
+__device__ __forceinline__ void wide_tile(const f16* __restrict__ A, const WRows& W, void* __restrict__ Cv, int M,
                                           int N, int K, int ldc, int tile_m, int tile_n, int kt0, int kt1,
                                           int atomic, const GemmLse& lse, char* lds) {
   constexpr int NW = WM * WN;
@@ -783,45 +831,39 @@ __device__ __forceinline__ void wide_tile(const f16* __restrict__ A, const GemmW
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
-  const int m0 = tile_m * BM;
 
-  // Groups of 8 rows are dealt to the waves in turn, A's first.  A is based at the tile's first row, a group of W at its
-  // own first row (its rows lie in one segment).
+  // Groups of 8 rows are dealt to the waves in turn, A's first.
+  const TileRsrc<BM, BN, MODE> tile(A, W, M, N, K, tile_m, tile_n);
+  // A load's byte offset is a lane's (one for all loads of A, and one for those of W where their rows follow one another) and
+  // a scalar one.
   __amdgpu_buffer_rsrc_t rsrc[LPS];
-  int src[LPS], dst_off[LPS];
+  int src[LPS], soff[LPS], dst_off[LPS];
   {
     const int rin = lane >> 3, chunk = (lane & 7) ^ rin;
 #pragma unroll
     for (int i = 0; i < LPS; ++i) {
-      const int gi = min(i * NW + wave, GA + GB - 1);
-      dst_off[i] = gi * WIDE_GROUP;
-      if (gi < GA) {
-        rsrc[i] = buffer_rsrc(A + (int64_t)m0 * K, (uint32_t)min(M - m0, BM) * (uint32_t)K * 2u);
-        src[i] = (min(gi * 8 + rin, M - 1 - m0) * K + chunk * 8) * 2;
-      } else {
-        // rows outside the matrix are replaced by one inside: their products are never stored
-        const int b0 = (gi - GA) * 8;
-        int row0, down, span = 8;
-        const f16* p;
-        if (MODE == GEMM_SWIGLU_F16) {
-          row0 = tile_n * (BN / 2) + wide_feature<TN>(b0);
-          down = wide_feature<TN>(b0 + rin) - wide_feature<TN>(b0);
-          span = TN % 4 ? 8 : 12;
-          p = W.ptr[wide_is_up<TN>(b0)];
-          if (row0 < N) p += (int64_t)row0 * K;
-        } else {
-          row0 = tile_n * BN + b0;
-          down = rin;
-          p = row0 < N ? w_row_ptr<BN, MODE>(W, tile_n, b0, N, K) : W.ptr[0];
-        }
-        rsrc[i] = buffer_rsrc(p, (uint32_t)span * (uint32_t)K * 2u);
-        src[i] = ((down < N - row0 ? down : 0) * K + chunk * 8) * 2;
+      const int gi = i * NW + wave, b0 = (gi - GA) * 8;
+      // all of the waves' i-th groups are A's, all W's, or (at one i, where they do not divide) this wave's decides
+      const bool all_a = i * NW + NW <= GA, is_a = all_a || (i * NW < GA && gi < GA);
+      int row = wave * 8 + rin, ahead = i * NW * 8;
+      rsrc[i] = tile.a;
+      if (!is_a) {
+        rsrc[i] = tile.w(b0, MODE == GEMM_SWIGLU_F16 && wide_is_up<TN>(b0));
+        if (MODE == GEMM_STORE_F32) { row = rin; ahead = 0; }
+        else if (MODE != GEMM_SWIGLU_F16) ahead -= GA * 8;
+        else if (TN % 4 != 0 && NW % 2 == 0) { row = (wave >> 1) * 8 + rin; ahead = (i * NW - GA) * 4; }
+        else if (TN % 4 == 0 && NW % 4 == 0 && GA % 8 == 0) { row = wide_feature<TN>((wave & 3) * 8 + rin); ahead = ((i * NW - GA) >> 3) * 32; }
+        else { row = wide_feature<TN>(b0 + rin); ahead = 0; }
+        if (!all_a && i * NW < GA) { row += ahead; ahead = 0; }
       }
+      dst_off[i] = gi * WIDE_GROUP;
+      src[i] = (row * K + chunk * 8) * 2;
+      soff[i] = ahead * K * 2;
     }
   }
   auto issue1 = [&](int stage, int k0, int i) {
     if (SHORT == 0 || i < LPS - 1 || wave < SHORT)      // wave-uniform
-      dma16(rsrc[i], src[i], k0 * 2, lds + stage * STAGE_BYTES + dst_off[i]);
+      dma16(rsrc[i], src[i], k0 * 2 + soff[i], lds + stage * STAGE_BYTES + dst_off[i]);
   };
   // waits until at most `slabs` slabs of this wave's loads are in flight
   auto wait_slabs = [&](auto slabs) {
@@ -860,7 +902,6 @@ __device__ __forceinline__ void wide_tile(const f16* __restrict__ A, const GemmW
     t.acc[i][j] = TRANS ? __builtin_amdgcn_mfma_f32_16x16x32_f16(f.b[j], f.a[i], t.acc[i][j], 0, 0, 0)
                         : __builtin_amdgcn_mfma_f32_16x16x32_f16(f.a[i], f.b[j], t.acc[i][j], 0, 0, 0);
   };
-  if (kt0 >= kt1) return;
   const int k_last = (kt1 - 1) * BK;
   // prologue: STAGES slabs in flight (past the end: re-read the last slab, never consumed)
 #pragma unroll
@@ -963,31 +1004,41 @@ __device__ __forceinline__ void wide_tile(const f16* __restrict__ A, const GemmW
 }
 
 template <int BM, int BN, int WM, int WN, int STAGES, int MODE>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_wide_kernel(const f16* __restrict__ A, GemmW W,
-                                                                 void* __restrict__ Cv, int M, int N, int K,
-                                                                 int ldc, int m_tiles, int n_tiles, int splits,
-                                                                 int slabs_per_split, int atomic, GemmLse lse) {
+__global__ __launch_bounds__(WM * WN * 64) void gemm_wide_kernel(
+    const f16* __restrict__ A, const f16* __restrict__ w0, const f16* __restrict__ w1, const f16* __restrict__ w2,
+    int M, int N, uint32_t nk_sps, uint32_t map, int end0, int end1, GemmLate late) {
   __shared__ __attribute__((aligned(16))) char lds[STAGES * (BM / 8 + BN / 8) * WIDE_GROUP];
+  constexpr int NC = MODE == GEMM_SWIGLU_F16 ? BN / 2 : BN;
+  const int nk = nk_sps & 0xFFFF, sps = nk_sps >> 16;
   int tile_m, tile_n, split;
-  if (!tile_of_block(blockIdx.x, M, m_tiles, n_tiles, splits, tile_m, tile_n, split)) return;
-  const int kt0 = split * slabs_per_split;
-  wide_tile<BM, BN, WM, WN, STAGES, MODE>(A, W, Cv, M, N, K, ldc, tile_m, tile_n, kt0,
-                                                                min(K / BK, kt0 + slabs_per_split), atomic, lse, lds);
+  if (!tile_of_block(map, (M + BM - 1) / BM, (N + NC - 1) / NC, nk, sps, tile_m, tile_n, split)) return;
+  const int kt0 = split * sps, kt1 = min(nk, kt0 + sps);
+  if (kt0 >= kt1) return;
+  wide_tile<BM, BN, WM, WN, STAGES, MODE>(A, WRows{w0, w1, w2, end0, end1}, late.C, M, N, nk * BK, late.ldc, tile_m,
+                                          tile_n, kt0, kt1, sps < nk, late.lse, lds);
+}
+
+// Tiles, K split and grid of a launch.
+struct Cut { int m_tiles, n_tiles, splits, sps; Grid grid; };
+static Cut make_cut(int M, int N, int nk, int bm, int cols, int splits) {
+  Cut c;
+  c.n_tiles = (N + cols - 1) / cols;
+  c.m_tiles = (M + bm - 1) / bm;
+  splits = std::max(1, std::min(splits, nk));
+  c.sps = (nk + splits - 1) / splits;
+  c.splits = (nk + c.sps - 1) / c.sps;
+  c.grid = make_grid(M, c.m_tiles, c.n_tiles, c.splits);
+  return c;
 }
 
 template <int BM, int BN, int WM, int WN, int STAGES, int MODE>
 hipError_t run_wide(hipStream_t s, const f16* A, const GemmW& W, void* C, int M, int N, int K, int ldc,
                     int splits, GemmLse lse = GemmLse{nullptr, nullptr, 1.f}) {
-  if (K % BK) return hipErrorInvalidValue;
-  constexpr int n_out_per_tile = MODE == GEMM_SWIGLU_F16 ? BN / 2 : BN;
-  const int n_tiles = (N + n_out_per_tile - 1) / n_out_per_tile, m_tiles = (M + BM - 1) / BM;
-  const int nk = K / BK;
-  splits = std::max(1, std::min(splits, nk));
-  const int sps = (nk + splits - 1) / splits;
-  splits = (nk + sps - 1) / sps;
-  const int grid = grid_blocks(M, m_tiles, n_tiles, splits);
-  gemm_wide_kernel<BM, BN, WM, WN, STAGES, MODE><<<grid, WM * WN * 64, 0, s>>>(
-      A, W, C, M, N, K, ldc, m_tiles, n_tiles, splits, sps, splits > 1 ? 1 : 0, lse);
+  if (K % BK || K / BK > 0xFFFF) return hipErrorInvalidValue;
+  const Cut c = make_cut(M, N, K / BK, BM, MODE == GEMM_SWIGLU_F16 ? BN / 2 : BN, splits);
+  gemm_wide_kernel<BM, BN, WM, WN, STAGES, MODE><<<c.grid.dim, WM * WN * 64, 0, s>>>(
+      A, W.ptr[0], W.ptr[1], W.ptr[2], M, N, (uint32_t)(K / BK) | (uint32_t)c.sps << 16, c.grid.map, W.end[0], W.end[1],
+      GemmLate{C, ldc, lse});
   return hipGetLastError();
 }
 
@@ -1002,17 +1053,18 @@ hipError_t run_wide(hipStream_t s, const f16* A, const GemmW& W, void* C, int M,
 // tile count leaves compute units idle in the last round (1,536 output columns: 192 tiles of
 // 256 x 256 at 8,192 rows on 256 units).
 template <int BM, int BN, int WM, int WN, int STAGES>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_even_kernel(const f16* __restrict__ A, GemmW W,
-                                                                     float* __restrict__ C, int M, int N, int K,
-                                                                     int ldc, int n_tiles, int tiles) {
+__global__ __launch_bounds__(WM * WN * 64) void gemm_even_kernel(const f16* __restrict__ A, const f16* __restrict__ w0,
+                                                                     int M, int N, int K, int n_tiles, int tiles, int G,
+                                                                     int ldc, float* __restrict__ C) {
   __shared__ __attribute__((aligned(16))) char lds[STAGES * (BM / 8 + BN / 8) * WIDE_GROUP];
   const int nk = K / BK;
-  const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3, G = gridDim.x >> 3;
+  const WRows W{w0, nullptr, nullptr, N, N};
+  const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
   const int t0 = (int)((int64_t)tiles * xcd / 8), t1 = (int)((int64_t)tiles * (xcd + 1) / 8);
-  const int rounds = (t1 - t0) / G, rem = (t1 - t0) % G;
+  const int rounds = __builtin_amdgcn_readfirstlane((t1 - t0) / G), rem = t1 - t0 - rounds * G;
   const GemmLse none{nullptr, nullptr, 1.f};
   const int last = t0 + rounds * G;
-  const int S = (rem * nk + G - 1) / G;                  // slabs per work-group in the last round, < nk
+  const int S = __builtin_amdgcn_readfirstlane((rem * nk + G - 1) / G);   // slabs per work-group in the last round, < nk
   const int tail = nk - S;                               // slabs left of each of the rem tiles
   int r = 0, u = (j - rem) * S;
   const int u_end = min((j - rem + 1) * S, rem * tail);
@@ -1036,7 +1088,11 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_even_kernel(const f16* __re
       u += k1 - k0;
     }
     ++r;
-    wide_tile<BM, BN, WM, WN, STAGES, GEMM_ADD_F32>(A, W, C, M, N, K, ldc, tile / n_tiles, tile % n_tiles, k0,
+    // scalars, as in tile_of_block
+    auto scalar = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
+    tile = scalar(tile), k0 = scalar(k0), k1 = scalar(k1);
+    const int tile_m = scalar(tile / n_tiles);
+    wide_tile<BM, BN, WM, WN, STAGES, GEMM_ADD_F32>(A, W, C, M, N, K, ldc, tile_m, tile - tile_m * n_tiles, k0,
                                                            k1, k1 - k0 < nk, none, lds);
     __syncthreads();            // every wave is done with the ring before the next piece refills it
   }
@@ -1047,43 +1103,33 @@ hipError_t run_even(hipStream_t s, const f16* A, const GemmW& W, float* C, int M
                         int n_groups) {
   if (K % BK || n_groups <= 0 || n_groups % 8) return hipErrorInvalidValue;
   const int n_tiles = (N + BN - 1) / BN, m_tiles = (M + BM - 1) / BM;
-  gemm_even_kernel<BM, BN, WM, WN, STAGES><<<n_groups, WM * WN * 64, 0, s>>>(A, W, C, M, N, K, ldc, n_tiles,
-                                                                               n_tiles * m_tiles);
+  gemm_even_kernel<BM, BN, WM, WN, STAGES><<<n_groups, WM * WN * 64, 0, s>>>(A, W.ptr[0], M, N, K, n_tiles,
+                                                                               n_tiles * m_tiles, n_groups / 8, ldc, C);
   return hipGetLastError();
 }
 
 template <int BM, int BN, int WM, int WN, int STAGES, int MODE>
 hipError_t run_dma(hipStream_t s, const f16* A, const GemmW& W, void* C, int M, int N, int K, int ldc,
                    int splits) {
-  if (K % BK) return hipErrorInvalidValue;
-  constexpr int n_out_per_tile = MODE == GEMM_SWIGLU_F16 ? BN / 2 : BN;
-  const int n_tiles = (N + n_out_per_tile - 1) / n_out_per_tile, m_tiles = (M + BM - 1) / BM;
-  const int nk = K / BK;
-  splits = std::max(1, std::min(splits, nk));
-  const int sps = (nk + splits - 1) / splits;
-  splits = (nk + sps - 1) / sps;
-  const int grid = grid_blocks(M, m_tiles, n_tiles, splits);
-  gemm_dma_kernel<BM, BN, WM, WN, STAGES, MODE><<<grid, WM * WN * 64, 0, s>>>(
-      A, W, C, M, N, K, ldc, m_tiles, n_tiles, splits, sps, splits > 1 ? 1 : 0);
+  if (K % BK || K / BK > 0xFFFF) return hipErrorInvalidValue;
+  const Cut c = make_cut(M, N, K / BK, BM, MODE == GEMM_SWIGLU_F16 ? BN / 2 : BN, splits);
+  gemm_dma_kernel<BM, BN, WM, WN, STAGES, MODE><<<c.grid.dim, WM * WN * 64, 0, s>>>(
+      A, W.ptr[0], W.ptr[1], W.ptr[2], M, N, (uint32_t)(K / BK) | (uint32_t)c.sps << 16, c.grid.map, W.end[0], W.end[1],
+      GemmLate{C, ldc, GemmLse{}});
   return hipGetLastError();
 }
 
 template <int BM, int BN, int WM, int WN, int MODE>
 hipError_t run(hipStream_t s, const f16* A, const GemmW& W, void* C, int M, int N, int K, int ldc,
                int splits) {
-  constexpr int n_out_per_tile = MODE == GEMM_SWIGLU_F16 ? BN / 2 : BN;
-  const int n_tiles = (N + n_out_per_tile - 1) / n_out_per_tile, m_tiles = (M + BM - 1) / BM;
-  const int nk = (K + BK - 1) / BK;
-  splits = std::max(1, std::min(splits, nk));
-  const int sps = (nk + splits - 1) / splits;
-  splits = (nk + sps - 1) / sps;
-  const int grid = grid_blocks(M, m_tiles, n_tiles, splits);
+  const Cut c = make_cut(M, N, (K + BK - 1) / BK, BM, MODE == GEMM_SWIGLU_F16 ? BN / 2 : BN, splits);
+  const int atomic = c.splits > 1 || MODE == GEMM_ADD_F32;
   if (K % BK)
-    gemm_kernel<BM, BN, WM, WN, MODE, true><<<grid, WM * WN * 64, 0, s>>>(A, W, C, M, N, K, ldc, m_tiles,
-                                                                          n_tiles, splits, sps, (splits > 1 || MODE == GEMM_ADD_F32) ? 1 : 0);
+    gemm_kernel<BM, BN, WM, WN, MODE, true><<<c.grid.dim, WM * WN * 64, 0, s>>>(A, M, N, K, c.grid.map, c.sps,
+                                                                                ldc, C, atomic, W);
   else
-    gemm_kernel<BM, BN, WM, WN, MODE, false><<<grid, WM * WN * 64, 0, s>>>(A, W, C, M, N, K, ldc, m_tiles,
-                                                                           n_tiles, splits, sps, (splits > 1 || MODE == GEMM_ADD_F32) ? 1 : 0);
+    gemm_kernel<BM, BN, WM, WN, MODE, false><<<c.grid.dim, WM * WN * 64, 0, s>>>(A, M, N, K, c.grid.map, c.sps,
+                                                                                 ldc, C, atomic, W);
   return hipGetLastError();
 }
 
