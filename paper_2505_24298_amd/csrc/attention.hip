@@ -13,6 +13,7 @@
 //                                       B-operand layout, so nothing is
 //                                       transposed or staged through LDS.
 #include "kernels.hpp"
+#include <algorithm>
 #include <cstdlib>
 #include <type_traits>
 
@@ -32,6 +33,16 @@ __device__ __forceinline__ f32x4 mfma_qk(f16x8 a, f16x8 b, f32x4 c) {
 }
 __device__ __forceinline__ f32x4 mfma_pv(f16x4 p, f16x4 v, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x16f16(p, v, c, 0, 0, 0);
+}
+
+// Folded over the four lanes (lane & 15 the same) that share a row.
+__device__ __forceinline__ float max_over_groups(float v) {
+  auto f = [](float a, float b) { return fmaxf(a, b); };
+  return xor_lanes<32>(xor_lanes<16>(v, f), f);
+}
+__device__ __forceinline__ float sum_over_groups(float v) {
+  auto f = [](float a, float b) { return a + b; };
+  return xor_lanes<32>(xor_lanes<16>(v, f), f);
 }
 
 // One online-softmax update over the NB blocks held in `f`.
@@ -58,8 +69,7 @@ __device__ __forceinline__ void attend_group(const KvFrag<D>& f, const f16x8 (&q
       mx = fmaxf(mx, s[u][v]);
     }
   }
-  mx = fmaxf(mx, __shfl_xor(mx, 16));
-  mx = fmaxf(mx, __shfl_xor(mx, 32));
+  mx = max_over_groups(mx);
   const float m_new = fmaxf(m, mx);
   const float m_use = m_new == -INFINITY ? 0.f : m_new;
   const float alpha = __builtin_amdgcn_exp2f(m - m_use);   // m = -inf -> 0
@@ -95,37 +105,33 @@ __device__ __forceinline__ void attend_group(const KvFrag<D>& f, const f16x8 (&q
 }
 
 // ------------------------------------------------------------------ decode
-// Block ids of a split, fetched once: lane l of every wave holds the ids of
-// blocks b0 + l and b0 + 64 + l (a split spans at most 128 blocks).
+// Block ids of a segment, fetched once: lane l of every wave holds the ids of
+// blocks b0 + l and b0 + 64 + l (a segment spans at most 128 blocks).  Entries past the table's end read as zero.
 struct BlockIds { int lo, hi; };
-__device__ __forceinline__ int block_id(const BlockIds& t, int rel) {
-  const int v = rel < 64 ? t.lo : t.hi;
-  return __shfl(v, rel & 63);
+__device__ __forceinline__ BlockIds load_ids(const int32_t* table, int n, int lane) {
+  const auto r = buffer_rsrc(table, (uint32_t)n * 4u);
+  return BlockIds{buf1(r, lane * 4), buf1(r, lane * 4 + 256)};
+}
+__device__ __forceinline__ int block_id(const BlockIds& t, int rel) {      // rel: the same in all lanes
+  const int lo = __builtin_amdgcn_readlane(t.lo, rel & 63), hi = __builtin_amdgcn_readlane(t.hi, rel & 63);
+  return rel < 64 ? lo : hi;
 }
 
+// K and V tiles of blocks b and b + 1 for this wave's next update.  A block past b_end is an empty buffer: it reads as
+// zero.  `tiles`: the kv head's K tile in block 0.
 template <int D>
-__device__ __forceinline__ void load_group_ids(KvFrag<D>& f, const f16* __restrict__ arena,
-                                               const KvGeom& geom, const BlockIds& ids, int b0, int b,
-                                               int b_end, int kvh, int lane) {
-  const f16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
+__device__ __forceinline__ void load_group_ids(KvFrag<D>& f, const f16* tiles, int block_stride, const BlockIds& ids,
+                                               int b0, int b, int b_end, int lane) {
+  constexpr int TILE_B = kBlockTokens * D * 2;
 #pragma unroll
   for (int u = 0; u < NB; ++u) {
-    if (b + u < b_end) {                               // wave-uniform
-      const int blk = block_id(ids, b + u - b0);
-      // both tiles are stored chunk-major in operand order: load c of a wave reads 1 KiB in a row
-      const f16* kt = arena + kv_tile_off(geom, blk, kvh, 0) + lane * 8;
-      const f16* vt = arena + kv_tile_off(geom, blk, kvh, 1) + lane * 8;
+    const int blk = block_id(ids, b + u - b0);
+    // both tiles are stored chunk-major in operand order: load c of a wave reads 1 KiB in a row
+    const auto r = buffer_rsrc(tiles + (int64_t)blk * block_stride, b + u < b_end ? 2u * TILE_B : 0u);
 #pragma unroll
-      for (int c = 0; c < D / 32; ++c) {
-        f.k[u][c] = ld8(kt + c * 512);
-        f.v[u][c] = ld8(vt + c * 512);
-      }
-    } else {
-#pragma unroll
-      for (int c = 0; c < D / 32; ++c) {
-        f.k[u][c] = zero8;
-        f.v[u][c] = zero8;
-      }
+    for (int c = 0; c < D / 32; ++c) {
+      f.k[u][c] = buf8(r, lane * 16 + c * 1024);
+      f.v[u][c] = buf8(r, lane * 16 + TILE_B + c * 1024);
     }
   }
 }
@@ -200,6 +206,21 @@ __device__ __forceinline__ void rotate(RawHead<D>& r, const f16* __restrict__ bi
   }
 }
 
+// What a decode work-group needs besides its segment (read from memory while descriptor and block ids travel).
+struct DecodeArgs {
+  const float* qkv;
+  const f16 *bq, *bk, *bv;
+  const float *cos_tab, *sin_tab;
+  f16* arena;
+  int block_stride, nq, max_own;
+  float scale_log2;
+  float *part_o, *part_ml;
+  f16* out;
+  const int32_t* pos;
+  DecodeGroups grp;
+};
+constexpr int kSegRows = 32768;      // most work-groups along a grid's second dimension
+
 // The leading KV blocks that a set of rows has in common (the work-groups of the decode launch behind the
 // segments': u = chunk of the shared part).  Wave w
 // owns tile w of the set: 16 MFMA rows = floor(16 / G) sequences x their G query heads, so
@@ -209,31 +230,31 @@ __device__ __forceinline__ void rotate(RawHead<D>& r, const f16* __restrict__ bi
 // merge kernel folds them into the rows' own partials.  Every shared position precedes every
 // row's position, so nothing is masked but the tail of the last block pair.
 template <int D>
-__device__ __forceinline__ void decode_shared_set(
-    const float* __restrict__ qkv, const RowMeta& rm, const f16* __restrict__ bq,
-    const float* __restrict__ cos_tab, const float* __restrict__ sin_tab,
-    const f16* __restrict__ arena, const KvGeom& geom, int nq, int n_own, int n_slots,
-    float scale_log2, float* __restrict__ part_o, float* __restrict__ part_ml, const DecodeGroups& grp, int set, int kvh,
-    int u) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+__device__ __forceinline__ void decode_shared_set(const DecodeArgs& A, int nkv, int n_slots, int set, int kvh, int u) {
+  const float* __restrict__ qkv = A.qkv;
+  const int nq = A.nq, n_own = A.max_own;
+  const float *__restrict__ cos_tab = A.cos_tab, *__restrict__ sin_tab = A.sin_tab;
+  const f16* __restrict__ bq = A.bq;
+  const float scale_log2 = A.scale_log2;
+  float *__restrict__ part_o = A.part_o, *__restrict__ part_ml = A.part_ml;
+  const DecodeGroups& grp = A.grp;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, j = lane & 15;
-  const int nkv = geom.n_kv_heads, G = nq / nkv, P = 16 / G;
+  const int G = nq / nkv, P = 16 / G;
   const int chunk = grp.sh_chunk;
   const int t0 = u * chunk, b0 = t0 / kBlockTokens;
-  const int32_t* table = grp.set_table + (int64_t)set * grp.set_stride;
-  const int b_cap = min(b0 + chunk / kBlockTokens, grp.set_stride);
-  BlockIds ids;
-  ids.lo = b0 + lane < b_cap ? table[b0 + lane] : 0;
-  ids.hi = b0 + 64 + lane < b_cap ? table[b0 + 64 + lane] : 0;
+  const BlockIds ids = load_ids(grp.set_table + (int64_t)set * grp.set_stride + b0,
+                                max(0, min(chunk / kBlockTokens, grp.set_stride - b0)), lane);
   const int sq = j / G;                                  // sequence of this lane's row inside the tile
   const int r = sq < P ? grp.set_rows[((int64_t)set * kGroupTiles + wave) * 16 + sq] : -1;
   const int ts = grp.set_start[set];
   if (t0 >= ts) return;
   if (__ballot(r >= 0) == 0) return;                     // no tile for this wave
+  const f16* tiles = A.arena + kvh * 2 * (kBlockTokens * D);
   const int t1 = min(ts, t0 + chunk);
   const int b1 = (t1 + kBlockTokens - 1) / kBlockTokens;
   const int rr = max(r, 0);                              // empty rows read row 0 and are zeroed below
-  const int pos = rm.pos[rr];
+  const int pos = A.pos[rr];
   const int head = kvh * G + (j - sq * G);
   RawHead<D> qraw;
   load_raw<D>(qraw, qkv + ((int64_t)rr * (nq + 2 * nkv) + head) * D, g);
@@ -241,7 +262,7 @@ __device__ __forceinline__ void decode_shared_set(
   load_angles<D>(ang, cos_tab + (int64_t)pos * (D / 2), sin_tab + (int64_t)pos * (D / 2), g);
   int b = b0;
   KvFrag<D> cur, nxt;
-  load_group_ids<D>(cur, arena, geom, ids, b0, b, b1, kvh, lane);
+  load_group_ids<D>(cur, tiles, A.block_stride, ids, b0, b, b1, lane);
   f16x8 qf[D / 32];
   rotate<D>(qraw, bq ? bq + head * D : nullptr, ang, g, qf);
   if (r < 0) {
@@ -255,13 +276,12 @@ __device__ __forceinline__ void decode_shared_set(
   for (int n = 0; n < D / 16; ++n) o[n] = f32x4{0.f, 0.f, 0.f, 0.f};
   while (b < b1) {
     const int bn = b + NB;
-    if (bn < b1) load_group_ids<D>(nxt, arena, geom, ids, b0, bn, b1, kvh, lane);
+    if (bn < b1) load_group_ids<D>(nxt, tiles, A.block_stride, ids, b0, bn, b1, lane);
     attend_group<D>(cur, qf, b, t1 - 1, scale_log2, m, l, o, lane);
     cur = nxt;
     b = bn;
   }
-  l += __shfl_xor(l, 16);
-  l += __shfl_xor(l, 32);
+  l = sum_over_groups(l);
   const int slot = n_own + u;
   if (g == 0 && r >= 0) {
     const int64_t pi = ((int64_t)r * nq + head) * n_slots + slot;
@@ -289,47 +309,51 @@ __device__ __forceinline__ void decode_shared_set(
 // pos: its last wave, which has the fewest blocks, rotates and rounds the new key and stores key and value into the
 // sequence's block for later steps, and the new token is folded into the softmax
 // state as one more (score, value) pair.
+// The first arguments arrive in registers with the launch: where the segment's descriptor and block ids lie.  base x: first
+// segment of XCD x (the first XCD's is 0).  A work-group lives for some 20 us, of which two round trips before its first
+// K/V tile cannot be helped; the argument reads before them (a third one), divisions, exec masks around loads and block ids
+// passed through LDS could.  With them gone, in the merge too, and the wave's index and block addresses in scalar
+// registers: step of 24 rows 2,066 -> 2,007 us, 88 3,011 -> 2,927, 256 2,921 -> 2,796, 7B of 128 7,356 -> 7,074, 16 rows of
+// 26,000 tokens 7,497 -> 7,333.
 template <int D>
 __global__ __launch_bounds__(256) void attn_decode_kernel(
-    const float* __restrict__ qkv, RowMeta rm, const f16* __restrict__ bq,
-    const f16* __restrict__ bk, const f16* __restrict__ bv, const float* __restrict__ cos_tab,
-    const float* __restrict__ sin_tab, f16* __restrict__ arena, KvGeom geom, int nq, DecodeSegs sg,
-    float scale_log2, float* __restrict__ part_o, float* __restrict__ part_ml,
-    f16* __restrict__ out, DecodeGroups grp) {
+    const int4* __restrict__ desc, const int32_t* __restrict__ seg_table, int base1, int base2, int base3, int base4,
+    int base5, int base6, int base7, int base8, int depth, uint32_t shape, DecodeArgs) {
+  constexpr int kArgs = 56;                              // offset of the struct
+  static_assert(alignof(DecodeArgs) == 8, "offset of the struct");
   __shared__ float sm[4][16], sl[4][16];
   __shared__ float so[4][16][D];
   __shared__ float s_new[16], v_new[D];
-  const int nkv = geom.n_kv_heads;
-  const int n_slots = sg.max_own + grp.n_shared;         // partial slots per (row, head)
-  // segment q of XCD x: work-groups 8 (q nkv .. q nkv + nkv - 1) + x, one per kv head
-  const int id = blockIdx.x, n_seg_wgs = 8 * sg.depth * nkv;
-  if (id >= n_seg_wgs) {                                 // the shared leading blocks of a set of rows
-    const int r = id - n_seg_wgs, u = r % grp.n_shared, rest = r / grp.n_shared;
-    decode_shared_set<D>(qkv, rm, bq, cos_tab, sin_tab, arena, geom, nq, sg.max_own, n_slots,
-                         scale_log2, part_o, part_ml, grp, rest / nkv, rest % nkv, u);
+  // grid (8 nkv, .., ..): work-groups 8 (q nkv .. q nkv + nkv - 1) + x are segment q of XCD x, one per kv head
+  const int xcd = blockIdx.x & 7, kvh = blockIdx.x >> 3;
+  const int stride = shape & 255, G = (shape >> 8) & 31, nkv = shape >> 13, nq = G * nkv;
+  const int q_seg = blockIdx.z * kSegRows + blockIdx.y;
+  if (q_seg >= depth) {                                  // the shared leading blocks of a set of rows
+    const DecodeArgs A = late_args<DecodeArgs>(kArgs);
+    const int n_shared = A.grp.n_shared, w = (q_seg - depth) * 8 + xcd;
+    const int set = n_shared > 0 ? w / n_shared : 0;
+    if (n_shared > 0 && set < A.grp.n_sets)
+      decode_shared_set<D>(A, nkv, A.max_own + n_shared, set, kvh, w - set * n_shared);
     return;
   }
-  const int kvh = (id >> 3) % nkv;
-  int seg = sg.base[0], seg_end = sg.base[1];
-#pragma unroll
-  for (int x = 1; x < 8; ++x) {
-    seg = (id & 7) == x ? sg.base[x] : seg;
-    seg_end = (id & 7) == x ? sg.base[x + 1] : seg_end;
-  }
-  seg += (id >> 3) / nkv;
+  // base of XCD x and of the next one, by the bits of x
+  const bool x1 = xcd & 1, x2 = xcd & 2, x4 = xcd & 4;
+  const int seg = (x4 ? (x2 ? (x1 ? base7 : base6) : (x1 ? base5 : base4)) : (x2 ? (x1 ? base3 : base2) : (x1 ? base1 : 0))) + q_seg;
+  const int seg_end = x4 ? (x2 ? (x1 ? base8 : base7) : (x1 ? base6 : base5)) : (x2 ? (x1 ? base4 : base3) : (x1 ? base2 : base1));
   if (seg >= seg_end) return;                            // this XCD has fewer
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, j = lane & 15;
-  const int G = nq / nkv;
-  const int32_t* table = sg.table + (int64_t)seg * sg.stride;
-  BlockIds ids;
-  ids.lo = lane < sg.stride ? table[lane] : 0;
-  ids.hi = 64 + lane < sg.stride ? table[64 + lane] : 0;
-  const int4 d = sg.desc[seg];
-  const int i = __builtin_amdgcn_readfirstlane(d.x);
+  const BlockIds ids = load_ids(seg_table + (int64_t)seg * stride, stride, lane);
+  const int4 d = desc[seg];
+  const DecodeArgs A = late_args<DecodeArgs>(kArgs);
+  const float* __restrict__ qkv = A.qkv;
+  const f16 *__restrict__ bq = A.bq, *__restrict__ bk = A.bk, *__restrict__ bv = A.bv;
+  f16* __restrict__ arena = A.arena;
+  const int n_slots = A.max_own + A.grp.n_shared;        // partial slots per (row, head)
+  const float scale_log2 = A.scale_log2;
+  const f16* tiles = arena + kvh * 2 * (kBlockTokens * D);
   // Token and block indices below are relative to the first position this row's own work-groups cover.
-  const int pos_abs = __builtin_amdgcn_readfirstlane(d.y), pos = __builtin_amdgcn_readfirstlane(d.z);
-  const int packed = __builtin_amdgcn_readfirstlane(d.w);
+  const int i = d.x, pos_abs = d.y, pos = d.z, packed = d.w;
   const int t0 = (packed & 0xFFF) * 32, n_tok = ((packed >> 12) & 0x7F) * 32, slot = (packed >> 19) & 31;
   const bool single = (packed >> 24) & 1;              // the row has no other partial
   const int b0 = t0 / kBlockTokens;
@@ -345,11 +369,11 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(
   // wave w takes block groups w, w+4, ... of this segment
   int b = b0 + wave * NB;
   KvFrag<D> cur, nxt;
-  if (b < b1) load_group_ids<D>(cur, arena, geom, ids, b0, b, b1, kvh, lane);
+  if (b < b1) load_group_ids<D>(cur, tiles, A.block_stride, ids, b0, b, b1, lane);
   RawHead<D> qraw;
   load_raw<D>(qraw, row + head * D, g);
   RopeAngles<D> ang;
-  load_angles<D>(ang, cos_tab + (int64_t)pos_abs * (D / 2), sin_tab + (int64_t)pos_abs * (D / 2), g);
+  load_angles<D>(ang, A.cos_tab + (int64_t)pos_abs * (D / 2), A.sin_tab + (int64_t)pos_abs * (D / 2), g);
 
   f16x8 qf[D / 32];
   rotate<D>(qraw, bq ? bq + head * D : nullptr, ang, g, qf);
@@ -368,16 +392,15 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(
     for (int c = 0; c < D / 32; ++c)
 #pragma unroll
       for (int e = 0; e < 8; ++e) dot += h2f(qf[c][e]) * h2f(kf[c][e]);
-    dot += __shfl_xor(dot, 16);
-    dot += __shfl_xor(dot, 32);
+    dot = sum_over_groups(dot);
     if (g == 0) s_new[j] = dot * scale_log2;
     const int blk = block_id(ids, pos / kBlockTokens - b0), tin = pos % kBlockTokens;
+    f16* kt = arena + (int64_t)blk * A.block_stride + kvh * 2 * (kBlockTokens * D);
     if (j == 0) {
-      f16* kt = arena + kv_tile_off(geom, blk, kvh, 0);
 #pragma unroll
       for (int c = 0; c < D / 32; ++c) *reinterpret_cast<f16x8*>(kt + k_tile_index(tin, 32 * c + 8 * g)) = kf[c];
     }
-    f16* vt = arena + kv_tile_off(geom, blk, kvh, 1);
+    f16* vt = kt + kBlockTokens * D;
     const float* vrow = row + (nq + nkv + kvh) * D;
     for (int dim = lane; dim < D; dim += 64) {
       float v = vrow[dim];
@@ -394,13 +417,12 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(
 
   while (b < b1) {
     const int bn = b + 4 * NB;
-    if (bn < b1) load_group_ids<D>(nxt, arena, geom, ids, b0, bn, b1, kvh, lane);
+    if (bn < b1) load_group_ids<D>(nxt, tiles, A.block_stride, ids, b0, bn, b1, lane);
     attend_group<D>(cur, qf, b, pos - 1, scale_log2, m, l, o, lane);
     cur = nxt;
     b = bn;
   }
-  l += __shfl_xor(l, 16);
-  l += __shfl_xor(l, 32);
+  l = sum_over_groups(l);
 
   if (g == 0) { sm[wave][j] = m; sl[wave][j] = l; }
 #pragma unroll
@@ -429,17 +451,17 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(
     }
     const int head = kvh * G + h;
     if (single) {
-      out[((int64_t)i * nq + head) * D + dd] = f2h_sat(O / L);
+      A.out[((int64_t)i * nq + head) * D + dd] = f2h_sat(O / L);
     } else {
       const int64_t pi = ((int64_t)i * nq + head) * n_slots + slot;
-      part_o[pi * D + dd] = O;
-      if (dd == 0) { part_ml[pi * 2] = M; part_ml[pi * 2 + 1] = L; }
+      A.part_o[pi * D + dd] = O;
+      if (dd == 0) { A.part_ml[pi * 2] = M; A.part_ml[pi * 2 + 1] = L; }
     }
   }
 }
 
 // Combine the split partials of one (row, head): out = sum_s O_s 2^(M_s-M) / sum_s L_s 2^(M_s-M).
-// Every load address depends only on the launch shape, so the row's slot count, the
+// Bound by latency, one round trip: every load address depends only on the launch shape, so the row's slot count, the
 // statistics (lane s fetches (M_s, L_s)) and the first eight partial rows all go out
 // together; which slots really exist for this row is applied afterwards by selection.  The
 // other slots hold stale values of earlier launches: selected away, never multiplied.
@@ -451,25 +473,27 @@ __global__ __launch_bounds__(D < 64 ? 64 : D) void attn_merge_kernel(const float
                                                        const int32_t* __restrict__ t_start, f16* __restrict__ out) {
   constexpr int BATCH = 8;
   const int n_slots = max_own + n_shared;                     // <= 32
-  const int i = blockIdx.x / nq;
-  const int64_t base = (int64_t)blockIdx.x * n_slots;
+  const int i = blockIdx.y;                                   // grid (heads, rows)
+  const int64_t pair = (int64_t)i * nq + blockIdx.x;
   const int lane = threadIdx.x & 63;
   const int dd = min((int)threadIdx.x, D - 1);
-  const float* po = part_o + base * D + dd;
-  const int ns = own[i];
-  const int ts = t_start ? t_start[i] : 0;
-  float2 ml = {0.f, 0.f};
-  if (lane < n_slots) ml = *reinterpret_cast<const float2*>(part_ml + (base + lane) * 2);
+  const auto po = buffer_rsrc(part_o + pair * n_slots * D, (uint32_t)(n_slots * D) * 4u);    // past its end: zero
+  const auto pml = buffer_rsrc(part_ml + pair * n_slots * 2, (uint32_t)n_slots * 8u);
+  auto row = [&](int slot) { return __builtin_bit_cast(float, buf1(po, (slot * D + dd) * 4)); };
+  const b64_t mlb = __builtin_amdgcn_raw_buffer_load_b64(pml, lane * 8, 0, 0);
+  const uint32_t mb = mlb[0], lb = mlb[1];
   float v[BATCH], vn[BATCH];
 #pragma unroll
-  for (int u = 0; u < BATCH; ++u) v[u] = u < n_slots ? po[(int64_t)u * D] : 0.f;
+  for (int u = 0; u < BATCH; ++u) v[u] = row(u);
+  const int ns = own[i];
+  const int ts = t_start ? t_start[i] : 0;
 
   // slots of this row: its own segments 0 .. ns - 1, then the chunks of
   // the part it shares with its set (slot max_own + u exists while u * sh_chunk < ts)
   if (ns == 1 && ts == 0) return;                             // nothing to combine: `out` is written
   const bool mine = lane < max_own ? lane < ns : (lane < n_slots && (lane - max_own) * sh_chunk < ts);
   const uint64_t have = __ballot(mine);                       // slots live in lanes 0 .. 31
-  const float ms = mine ? ml.x : -INFINITY, ls = mine ? ml.y : 0.f;
+  const float ms = mine ? __builtin_bit_cast(float, mb) : -INFINITY, ls = mine ? __builtin_bit_cast(float, lb) : 0.f;
   const float M = wave_max(ms);                               // whole waves only: blockDim >= 64
   const float sc = __builtin_amdgcn_exp2f(ms - M);           // other lanes: 2^-inf = 0
   const float L = wave_sum(ls * sc);
@@ -478,18 +502,19 @@ __global__ __launch_bounds__(D < 64 ? 64 : D) void attn_merge_kernel(const float
     const bool more = (have >> (s0 + BATCH)) != 0 && s0 + BATCH < n_slots;
     if (more) {                                               // next batch in flight while this one is used
 #pragma unroll
-      for (int u = 0; u < BATCH; ++u) vn[u] = s0 + BATCH + u < n_slots ? po[(int64_t)(s0 + BATCH + u) * D] : 0.f;
+      for (int u = 0; u < BATCH; ++u) vn[u] = row(s0 + BATCH + u);
     }
 #pragma unroll
     for (int u = 0; u < BATCH; ++u) {
-      const float w = __shfl(sc, (s0 + u) & 31);
+      const float w = __builtin_bit_cast(
+          float, __builtin_amdgcn_readlane((int)__builtin_bit_cast(uint32_t, sc), (s0 + u) & 31));
       O += ((have >> (s0 + u)) & 1u) ? v[u] * w : 0.f;
     }
     if (!more) break;
 #pragma unroll
     for (int u = 0; u < BATCH; ++u) v[u] = vn[u];
   }
-  if (threadIdx.x < D) out[(int64_t)blockIdx.x * D + dd] = f2h_sat(O / L);
+  if (threadIdx.x < D) out[pair * D + dd] = f2h_sat(O / L);
 }
 
 // ----------------------------------------------------------------- prefill
@@ -761,10 +786,17 @@ hipError_t launch_attn_decode(hipStream_t s, const float* qkv, int M, RowMeta rm
       (((uintptr_t)qkv | (uintptr_t)bq | (uintptr_t)bk | (uintptr_t)bv | (uintptr_t)arena_layer) & 15))
     return hipErrorInvalidValue;
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)geom.head_dim);
-  const unsigned grid = (unsigned)((8 * segs.depth + grp.n_sets * grp.n_shared) * geom.n_kv_heads);
+  const int nkv = geom.n_kv_heads;
+  const int64_t rows = segs.depth + ((int64_t)grp.n_sets * grp.n_shared + 7) / 8;
+  if (rows > (int64_t)kSegRows * 65535 || nkv >= 1 << 19) return hipErrorInvalidValue;
+  const dim3 grid(8 * nkv, (unsigned)std::min<int64_t>(rows, kSegRows), (unsigned)((rows + kSegRows - 1) / kSegRows));
+  const DecodeArgs args{qkv, bq, bk, bv, cos_tab, sin_tab, arena_layer, geom.block_stride, n_q_heads, segs.max_own,
+                        scale_log2, part_o, part_ml, out, rm.pos, grp};
+  const int* base = segs.base;
+  const uint32_t shape = (uint32_t)segs.stride | (uint32_t)(n_q_heads / nkv) << 8 | (uint32_t)nkv << 13;
 #define AREAL_DEC(DD)                                                                              \
-  attn_decode_kernel<DD><<<grid, 256, 0, s>>>(qkv, rm, bq, bk, bv, cos_tab, sin_tab, arena_layer, geom, n_q_heads, \
-                                               segs, scale_log2, part_o, part_ml, out, grp);
+  attn_decode_kernel<DD><<<grid, 256, 0, s>>>(segs.desc, segs.table, base[1], base[2], base[3], base[4], base[5], base[6], \
+                                               base[7], base[8], segs.depth, shape, args);
   switch (geom.head_dim) {
     case 32: AREAL_DEC(32) break;
     case 64: AREAL_DEC(64) break;
@@ -780,10 +812,12 @@ hipError_t launch_attn_merge(hipStream_t s, int M, int head_dim, int n_q_heads, 
   if (M <= 0 || segs.max_own < 1 || n_slots < 2 || n_slots > 32 || !segs.own || !part_o || !part_ml || !out ||
       (grp.n_shared > 0 && (!grp.t_start || grp.sh_chunk <= 0)) || (head_dim != 32 && head_dim != 64 && head_dim != 128))
     return hipErrorInvalidValue;
+  const int64_t row_slots = (int64_t)n_q_heads * n_slots;
 #define AREAL_MRG(DD)                                                                              \
-  attn_merge_kernel<DD><<<M * n_q_heads, DD < 64 ? 64 : DD, 0, s>>>(part_o, part_ml, segs.own, n_q_heads, \
-                                                                    segs.max_own, grp.n_shared, grp.sh_chunk, \
-                                                                    grp.t_start, out);
+  for (int r = 0; r < M; r += kSegRows)                                                            \
+    attn_merge_kernel<DD><<<dim3(n_q_heads, std::min(M - r, kSegRows)), DD < 64 ? 64 : DD, 0, s>>>( \
+        part_o + r * row_slots * DD, part_ml + r * row_slots * 2, segs.own + r, n_q_heads, segs.max_own, grp.n_shared, \
+        grp.sh_chunk, grp.t_start ? grp.t_start + r : nullptr, out + (int64_t)r * n_q_heads * DD);
   switch (head_dim) {
     case 32: AREAL_MRG(32) break;
     case 64: AREAL_MRG(64) break;

@@ -31,15 +31,45 @@ __device__ __forceinline__ f16 f2h_sat(float x) {
 // 16-byte global load of 8 halves
 __device__ __forceinline__ f16x8 ld8(const f16* p) { return *reinterpret_cast<const f16x8*>(p); }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+// f(value of this lane, value of lane ^ O), O = 32, 16 by a swap of lane halves or rows, without the LDS crossbar that
+// __shfl_xor goes through (about 60 ns each); f has to be commutative.
+template <int O, class F>
+__device__ __forceinline__ float xor_lanes(float v, F f) {
+  static_assert(O == 32 || O == 16, "lane distance");
+  const uint32_t x = __builtin_bit_cast(uint32_t, v);
+  if constexpr (O == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    const uint32_t a = r[0], b = r[1];
+    return f(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b));
+  } else {
+    const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    const uint32_t a = r[0], b = r[1];
+    return f(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b));
+  }
+}
+// Value of the lane that a DPP control names (within the 16 lanes of a row; every lane reads an existing one).
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp((int)__builtin_bit_cast(uint32_t, v), CTRL, 0xF, 0xF, false));
+}
+// All 64 lanes folded by a commutative f, every lane gets the result, with the pairs (and so the roundings) of a butterfly
+// over lane distances 32, 16, 8, 4, 2, 1: after a step both lanes of a pair hold the same value, so rotations of a
+// row by 8 and 4 lanes stand for exchanges at these distances.
+template <class F>
+__device__ __forceinline__ float wave_fold(float v, F f) {
+  v = xor_lanes<32>(v, f);
+  v = xor_lanes<16>(v, f);
+  v = f(v, dpp<0x128>(v));      // row_ror:8
+  v = f(v, dpp<0x124>(v));      // row_ror:4
+  v = f(v, dpp<0x4E>(v));       // quad_perm 2 3 0 1
+  v = f(v, dpp<0xB1>(v));       // quad_perm 1 0 3 2
   return v;
 }
+__device__ __forceinline__ float wave_sum(float v) {
+  return wave_fold(v, [](float a, float b) { return a + b; });
+}
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-  return v;
+  return wave_fold(v, [](float a, float b) { return fmaxf(a, b); });
 }
 
 // Value of lane ^ 1 (DPP).
@@ -58,6 +88,30 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_rsrc(const void* base, 
 __device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t src, int lane_off, int wave_off, void* dst_wave_base) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void*)dst_wave_base, 16,
                                            lane_off, wave_off, 0, 0);
+}
+
+// 16 (8) bytes per lane at byte `off` of a buffer; past its end: zero, no access.
+typedef uint32_t b128_t __attribute__((ext_vector_type(4)));
+typedef uint32_t b64_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ f16x8 buf8(__amdgpu_buffer_rsrc_t r, int off) {
+  return __builtin_bit_cast(f16x8, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+}
+__device__ __forceinline__ f32x4 buf4f(__amdgpu_buffer_rsrc_t r, int off) {
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+}
+__device__ __forceinline__ f16x4 buf4(__amdgpu_buffer_rsrc_t r, int off) {
+  return __builtin_bit_cast(f16x4, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+}
+__device__ __forceinline__ int buf1(__amdgpu_buffer_rsrc_t r, int off) {
+  return (int)__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
+}
+
+// An argument struct of the kernel, `offset` bytes into its arguments, read here and not on entry: the reads of a by-value
+// parameter all start there, and a wave that needs few of them first waits for all.
+template <class T>
+__device__ __forceinline__ T late_args(int offset) {
+  typedef const __attribute__((address_space(4))) T* ptr;
+  return *(const T*)(ptr)((const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr() + offset);
 }
 
 // Every LDS read of this wave has returned (s_waitcnt with only lgkmcnt constrained).
