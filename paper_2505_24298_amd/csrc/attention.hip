@@ -528,111 +528,215 @@ __global__ __launch_bounds__(D < 64 ? 64 : D) void attn_merge_kernel(const float
 // over the two blocks of a stage (slots 0-3: tokens 4g..4g+3 of the first
 // block, slots 4-7: of the second), which is the order the S^T accumulators and
 // the stored V tiles already have.
-constexpr int PF_STAGES = 3;   // eight of them, for passes of few work-groups: 15 -> 19 us for one prompt of 301 tokens
+//
+// A launch lives on its longest walks (122 steps of 32 tokens for the last tile of 3,900), whose waves have few
+// others beside them, so a wave overlaps its own work: step p holds the scores of pair p and issues
+//   A: the score MFMAs of pair p + 1, a score's exponential (of pair p) between two of them,
+//   B: the value MFMAs of pair p, between them scale, mask and maximum of the scores of pair p + 1
+// (one after another they are 768 cycles of MFMAs and about 650 of float32 arithmetic per step of three row-groups).
+//
+// Issue bounds the step: an MFMA takes 8 cycles of a SIMD's issue, an exponential 8, other vector instructions 4, a
+// fragment read about 14, and with one wave to a SIMD nothing hides the barrier (170 cycles) and the step's loads (250):
+// 1,240 cycles of A and B, some 1,900 in all.  In order of phases and with the mask for every pair it was 2,150: one launch
+// of a prompt of 4,096 tokens 163 -> 136 us, two 166 -> 152, 4 of 2,048 91 -> 79, 8 of 1,024 50 -> 44, 32 of 256 22 -> 20.5
+// (12 / 2 heads of 128); a prefill of 1,000 tokens 2,508 -> 2,486 us in whole.  Slower: the 32x32x16 MFMA with a wave's 32
+// positions (156 us), ten stages (one work-group on a compute unit: 211), a barrier between A and B (149).
+constexpr int PF_STAGES = 5;   // two work-groups of 80 KB on a compute unit at head_dim 128
 
-
-// One online-softmax update of all RGW row-groups of a wave over the two blocks
-// in `f`.  The three phases run over all row-groups at a time, so that their
-// independent MFMA chains and reductions overlap and the value operands are
-// assembled once.  The running maximum is a reference, not an exact maximum: it
-// is raised (two cross-lane exchanges and a rescale of the accumulator) only
-// when some score of the wave exceeds it by more than 2^kMaxSlack, so
-// probabilities stay below 2^kMaxSlack in half precision and the common step
-// has no cross-lane traffic at all.
+// The running maximum is a reference, not an exact maximum: it is raised (two cross-lane exchanges and a rescale of
+// the accumulator) only when some score of the wave exceeds it by more than 2^kMaxSlack, so
+// probabilities stay below 2^kMaxSlack in half precision and the common step has no cross-lane traffic at all.
 constexpr float kMaxSlack = 8.0f;
 
-template <int D, int RGW, bool MASK>
-__device__ __forceinline__ void attend_pairs(const char* __restrict__ stage, const int (&k_off)[D / 32],
-                                             const int (&v_off)[D / 32], const f16x8 (&qf)[RGW][D / 32],
-                                             int b, const int (&rpos)[RGW], float scale_log2,
-                                             float (&m)[RGW], float (&l)[RGW], f32x4 (&o)[RGW][D / 16],
-                                             int lane) {
-  constexpr int TILE_B = 16 * D * 2;
-  const int g = lane >> 4;
-  // K fragments now, V fragments only once the probabilities exist: the two sets never
-  // occupy registers together
-  f16x8 kf[2][D / 32];
-#pragma unroll
-  for (int u = 0; u < 2; ++u)
-#pragma unroll
-    for (int c = 0; c < D / 32; ++c)
-      kf[u][c] = *reinterpret_cast<const f16x8*>(stage + (u * 2) * TILE_B + k_off[c]);
-  f32x4 acc[RGW][2];
-#pragma unroll
-  for (int r = 0; r < RGW; ++r)
-#pragma unroll
-    for (int u = 0; u < 2; ++u) acc[r][u] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int c = 0; c < D / 32; ++c)
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int r = 0; r < RGW; ++r) acc[r][u] = mfma_qk(kf[u][c], qf[r][c], acc[r][u]);
-
-  // scores stay unscaled (s = q.k); the 1/sqrt(d) log2(e) factor rides in the exponent's fma.
-  // MASK = false: every token of the pair is visible to every row of the wave.
-  f16x8 p[RGW];
-#pragma unroll
-  for (int r = 0; r < RGW; ++r) {
-    float s[2][4];
-    float mx = -INFINITY;
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int t = (b + u) * kBlockTokens + 4 * g + v;
-        s[u][v] = (!MASK || t <= rpos[r]) ? acc[r][u][v] : -INFINITY;
-        mx = fmaxf(mx, s[u][v]);
-      }
-    mx *= scale_log2;
-    if (__any(mx > m[r] + kMaxSlack)) {                 // wave-uniform; m = -inf at the start
-      mx = fmaxf(mx, __shfl_xor(mx, 16));
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
-      const float m_new = fmaxf(m[r], mx);
-      const float m_use = m_new == -INFINITY ? 0.f : m_new;
-      const float alpha = __builtin_amdgcn_exp2f(m[r] - m_use);   // m = -inf -> 0
-      m[r] = m_new;
-      l[r] *= alpha;
-      float ao[4];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) ao[v] = __shfl(alpha, 4 * g + v);
-#pragma unroll
-      for (int n = 0; n < D / 16; ++n)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) o[r][n][v] *= ao[v];
-    }
-    const float m_use = m[r] == -INFINITY ? 0.f : m[r];
-    float psum = 0.f;
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(s[u][v], scale_log2, -m_use));
-        psum += e;
-        p[r][u * 4 + v] = f2h(e);
-      }
-    l[r] += psum;
-  }
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int c = 0; c < D / 32; ++c) {
-    const f16x8 v0 = *reinterpret_cast<const f16x8*>(stage + 1 * TILE_B + v_off[c]);
-    const f16x8 v1 = *reinterpret_cast<const f16x8*>(stage + 3 * TILE_B + v_off[c]);
-    const f16x8 ve = f16x8{v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-    const f16x8 vo = f16x8{v0[4], v0[5], v0[6], v0[7], v1[4], v1[5], v1[6], v1[7]};
-#pragma unroll
-    for (int r = 0; r < RGW; ++r) o[r][2 * c] = mfma_qk(p[r], ve, o[r][2 * c]);
-#pragma unroll
-    for (int r = 0; r < RGW; ++r) o[r][2 * c + 1] = mfma_qk(p[r], vo, o[r][2 * c + 1]);
-  }
+// A value that is computed where it stands in the program (not moved behind the barrier, next to its use).
+template <class T>
+__device__ __forceinline__ T stay(T x) {
+  asm volatile("" : "+v"(x));
+  return x;
 }
 
 template <int D, int RGW>
+struct PfState {
+  static constexpr int DC = D / 32, NO = D / 16, TILE_B = 16 * D * 2;
+  f16x8 qf[RGW][DC];            // queries
+  f32x4 o[RGW][NO];             // accumulators: lane (g, j) holds rows 4g + v, dims 16n + j
+  float nm[RGW], l[RGW];        // minus the reference maximum (log2 domain), this lane's share of the sums
+  float mx[RGW];                // largest scaled score of this lane relative to the reference
+  int rpos[RGW];                // last token that this lane's row sees
+  f32x4 s[RGW][2];              // raw scores q.k of the pair whose turn is next: lane (g, j) holds tokens 4g + v of row j
+  f32x4 t[RGW][2];              // the same scaled, minus the reference: exponents of 2; -inf where masked
+  // K fragments f = u * DC + c (MFMA c of block u) are read KD ahead of their use, V fragments VD ahead: few other waves
+  // fill the time of an LDS read.
+  static constexpr int KD = 2 * DC < 4 ? 2 * DC : 4, VD = DC < 2 ? DC : 2;
+  int g;
+
+  __device__ __forceinline__ f16x8 tile(const char* base, int c, int lane) const {
+    return *reinterpret_cast<const f16x8*>(base + c * 1024 + lane * 16);
+  }
+  __device__ __forceinline__ f16x8 k_frag(const char* stage, int f, int lane) const {
+    return tile(stage + (f / DC) * 2 * TILE_B, f % DC, lane);
+  }
+  // t from s for score z = r * 8 + u * 4 + v of pair `pair`
+  template <bool MASK>
+  __device__ __forceinline__ void scale_one(int z, int pair, float scale_log2) {
+    const int r = z >> 3, u = (z >> 2) & 1, v = z & 3;
+    const float x = __builtin_fmaf(s[r][u][v], scale_log2, nm[r]);
+    t[r][u][v] = !MASK || (2 * pair + u) * kBlockTokens + 4 * g + v <= rpos[r] ? x : -INFINITY;
+  }
+  // Scores of row-group r, whose raw values are in s, against the reference -nm; raises it where t says so.
+  __device__ __forceinline__ void raise(int r, float scale_log2, bool first) {
+    float x = max_over_groups(mx[r]);                     // relative to the present reference
+    const float up = first ? x : fmaxf(x, 0.f);
+    const float by = up == -INFINITY ? 0.f : up;          // a wave without rows: nothing is visible
+    const float alpha = first ? 0.f : __builtin_amdgcn_exp2f(-by);
+    nm[r] -= by;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        t[r][u][v] = t[r][u][v] == -INFINITY ? -INFINITY : __builtin_fmaf(s[r][u][v], scale_log2, nm[r]);
+    if (first) return;
+    l[r] *= alpha;
+    float ao[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) ao[v] = __shfl(alpha, 4 * g + v);
+#pragma unroll
+    for (int n = 0; n < NO; ++n)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) o[r][n][v] *= ao[v];
+  }
+  // First pair: scores, scale, mask, reference; first fragments of the second.
+  __device__ __forceinline__ void start(const char* stage, float scale_log2, int lane) {
+#pragma unroll
+    for (int c = 0; c < DC; ++c)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const f16x8 k = tile(stage + u * 2 * TILE_B, c, lane);
+#pragma unroll
+        for (int r = 0; r < RGW; ++r) s[r][u] = mfma_qk(k, qf[r][c], c ? s[r][u] : f32x4{0.f, 0.f, 0.f, 0.f});
+      }
+#pragma unroll
+    for (int r = 0; r < RGW; ++r) {
+      mx[r] = -INFINITY;
+#pragma unroll
+      for (int z = 0; z < 8; ++z) {
+        scale_one<true>(r * 8 + z, 0, scale_log2);
+        mx[r] = fmaxf(mx[r], t[r][z >> 2][z & 3]);
+      }
+      raise(r, scale_log2, true);
+      mx[r] = 0.f;
+    }
+  }
+  // Step of `pair`, whose scores are in t.  NEXT: pair + 1 exists, its K tiles in k_stage; MASK: some of its tokens may
+  // lie behind a row of this wave.
+  template <bool NEXT, bool MASK>
+  __device__ __forceinline__ void step(const char* v_stage, const char* k_stage, int pair, float scale_log2, int lane) {
+    bool over = false;
+#pragma unroll
+    for (int r = 0; r < RGW; ++r) over |= mx[r] > kMaxSlack;
+    if (__any(over)) {                                    // wave-uniform, rare
+#pragma unroll
+      for (int r = 0; r < RGW; ++r) raise(r, scale_log2, false);
+    }
+    f16x8 p[RGW], v0[VD], v1[VD];
+    float psum[RGW];
+#pragma unroll
+    for (int r = 0; r < RGW; ++r) psum[r] = 0.f;
+    auto read_v = [&](int c) {
+      v0[c % VD] = tile(v_stage + TILE_B, c, lane);
+      v1[c % VD] = tile(v_stage + 3 * TILE_B, c, lane);
+    };
+    // A, block by block: exponential z of the present pair (block z / (4 RGW), row-group z / 4 % RGW) behind a score MFMA
+    // of the same block of the next, its sum and its rounding one and two later, so that nothing waits for the
+    // exponential's latency and the two pairs' scores hardly overlap in registers.
+    constexpr int NS = RGW * 8, NQ = RGW * 2 * DC, PER = NS / NQ, LEAD = NS / 4;
+    auto exp_part = [&](int z) {                          // z = 0 .. NS + 1
+      if (z < NS) {
+        f32x4& x = t[(z >> 2) % RGW][z / (4 * RGW)];
+        x[z & 3] = stay(__builtin_amdgcn_exp2f(x[z & 3]));
+      }
+      if (z >= 2) {
+        const int y = z - 2, r = (y >> 2) % RGW, u = y / (4 * RGW), v = y & 3;
+        psum[r] = stay(psum[r] + t[r][u][v]);
+        if (v & 1) {
+          const f16x2 h = {f2h(t[r][u][v - 1]), f2h(t[r][u][v])};
+          const uint32_t w = stay(__builtin_bit_cast(uint32_t, h));
+          p[r][u * 4 + v - 1] = __builtin_bit_cast(f16x2, w)[0];
+          p[r][u * 4 + v] = __builtin_bit_cast(f16x2, w)[1];
+        }
+      }
+    };
+    if (NEXT) {
+      f16x8 k[KD + 1];
+#pragma unroll
+      for (int f = 0; f < KD; ++f) k[f] = k_frag(k_stage, f, lane);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int z = 0; z < LEAD; ++z) exp_part(z);         // while the first fragments travel
+#pragma unroll
+      for (int f = 0; f < 2 * DC; ++f) {
+        if (f + KD < 2 * DC) k[(f + KD) % (KD + 1)] = k_frag(k_stage, f + KD, lane);
+        if (f >= 2 * DC - 2 * VD && (f - (2 * DC - 2 * VD)) % 2 == 0) read_v((f - (2 * DC - 2 * VD)) / 2);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int r = 0; r < RGW; ++r) {
+          const int c = f % DC, u = f / DC;
+          s[r][u] = mfma_qk(k[f % (KD + 1)], qf[r][c], c ? s[r][u] : f32x4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+          for (int e = 0; e < PER; ++e)
+            if ((f * RGW + r) * PER + e + LEAD < NS) exp_part((f * RGW + r) * PER + e + LEAD);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < VD; ++c) read_v(c);
+#pragma unroll
+      for (int z = 0; z < NS; ++z) exp_part(z);
+    }
+    exp_part(NS);
+    exp_part(NS + 1);
+#pragma unroll
+    for (int r = 0; r < RGW; ++r) {
+      l[r] += psum[r];
+      mx[r] = -INFINITY;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // B.
+    constexpr int NV = RGW * NO, PERV = NS / NV;
+    auto scale_part = [&](int z) {
+      if (!NEXT) return;
+      scale_one<MASK>(z, pair + 1, scale_log2);
+      if (z & 1) mx[z >> 3] = fmaxf(fmaxf(mx[z >> 3], t[z >> 3][(z >> 2) & 1][(z & 3) - 1]), t[z >> 3][(z >> 2) & 1][z & 3]);
+    };
+#pragma unroll
+    for (int c = 0; c < DC; ++c) {
+      const f16x8 a = v0[c % VD], b = v1[c % VD];
+      const f16x8 ve = f16x8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+      const f16x8 vo = f16x8{a[4], a[5], a[6], a[7], b[4], b[5], b[6], b[7]};
+      if (c + VD < DC) read_v(c + VD);
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int r = 0; r < RGW; ++r) {
+          o[r][2 * c + h] = mfma_qk(p[r], h ? vo : ve, o[r][2 * c + h]);
+#pragma unroll
+          for (int e = 0; e < PERV; ++e) scale_part(((2 * c + h) * RGW + r) * PERV + e);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+  }
+};
+
+// parts_magic: 2^32 / (kv heads x head parts), rounded up (0: one); shape: G | head parts << 5 | kv heads << 10;
+// inv_g: 2^16 / heads of a part, rounded up.
+template <int D, int RGW>
 __global__ __launch_bounds__(256, (D == 128 && RGW == 3) ? 2 : 1) void attn_prefill_kernel(
-    const f16* __restrict__ q, const AttnWork* __restrict__ work, SeqState st,
-    const f16* __restrict__ arena, KvGeom geom, int nq, int tile_pos, int head_parts, float scale_log2,
-    f16* __restrict__ out) {
-  constexpr int TILE_B = 16 * D * 2;      // bytes of one K or V tile
+    const AttnWork* __restrict__ work, const f16* __restrict__ q, const int32_t* __restrict__ tables,
+    const f16* __restrict__ arena, uint32_t parts_magic, uint32_t shape, uint32_t inv_g, int tile_pos, int max_blocks,
+    int block_stride, int n_wgs, float scale_log2, f16* __restrict__ out) {
+  typedef PfState<D, RGW> State;
+  constexpr int TILE_B = State::TILE_B;   // bytes of one K or V tile
   constexpr int STAGE_B = 4 * TILE_B;     // two blocks x (K, V)
   constexpr int NI = TILE_B / 1024;       // load instructions per tile = per wave per stage
   __shared__ __attribute__((aligned(16))) char lds[PF_STAGES * STAGE_B];
@@ -643,102 +747,114 @@ __global__ __launch_bounds__(256, (D == 128 && RGW == 3) ? 2 : 1) void attn_pref
   // second 256 are taken from the short end, so that long and short walks pair up; from then on a free place
   // takes the longest left.
   int rank = blockIdx.x;
-  if (rank >= 256 && rank < 512) rank = min(511, (int)gridDim.x - 1) - (rank - 256);
-  const int of_tile = geom.n_kv_heads * head_parts;
-  const AttnWork wk = work[rank / of_tile];
-  const int kvh = rank % of_tile / head_parts, part = rank % head_parts;
+  if (rank >= 256 && rank < 512) rank = min(511, n_wgs - 1) - (rank - 256);
+  const int g_all = shape & 31, head_parts = (shape >> 5) & 31, nkv = shape >> 10, nq = g_all * nkv;
+  int item = parts_magic ? __umulhi(rank, parts_magic) : rank;
+  if (item * (nkv * head_parts) > rank) --item;          // (a rank beyond 2^32 / parts may round up to the next item)
+  const int of_item = rank - item * (nkv * head_parts);
+  const AttnWork wk = work[item];
+  const int kvh = head_parts == 1 ? of_item : of_item >> 1, part = head_parts == 1 ? 0 : of_item & 1;   // one or two parts
   // this work-group's query heads: head0 .. head0 + n_heads - 1 of the G that share the kv head
-  const int G = (nq / geom.n_kv_heads + head_parts - 1) / head_parts;
-  const int head0 = kvh * (nq / geom.n_kv_heads) + part * G, n_heads = min(G, nq / geom.n_kv_heads - part * G);
+  const int G = (g_all + head_parts - 1) >> (head_parts - 1);
+  const int head0 = kvh * g_all + part * G, n_heads = min(G, g_all - part * G);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, j = lane & 15;
   const int n_rg = (tile_pos / 16) * G;
   const int last_pos = wk.pos0 + wk.n_rows - 1;
   const int b_end = last_pos / kBlockTokens + 1;
   const int n_pairs = (b_end + 1) >> 1;
-  const int32_t* table = st.table + (int64_t)wk.slot * st.max_blocks;
-
-  // ---- this wave's row-groups ----
-  f16x8 qf[RGW][D / 32];
-  float m[RGW], l[RGW];
-  f32x4 o[RGW][D / 16];
-  int rpos[RGW], gmax[RGW];
-#pragma unroll
-  for (int r = 0; r < RGW; ++r) {
-    const int rg = wave * RGW + r;
-    const int pos_blk = rg / G, head = head0 + rg % G;
-    const int row_in = pos_blk * 16 + j;
-    const bool active = rg < n_rg && rg % G < n_heads && pos_blk * 16 < wk.n_rows;
-    const bool ok = active && row_in < wk.n_rows;
-    gmax[r] = active ? wk.pos0 + min(wk.n_rows, pos_blk * 16 + 16) - 1 : -1;
-    rpos[r] = ok ? wk.pos0 + row_in : gmax[r];
-    const f16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
-    // MFMA c contracts dims [32c, 32c+32), lane group g its slice [32c + 8g, +8): the order of the K tiles
-    const f16* qp = q + ((int64_t)(wk.row0 + (ok ? row_in : 0)) * nq + (active ? head : 0)) * D + g * 8;
-#pragma unroll
-    for (int c = 0; c < D / 32; ++c) qf[r][c] = ok ? ld8(qp + c * 32) : zero8;
-    m[r] = -INFINITY;
-    l[r] = 0.f;
-#pragma unroll
-    for (int n = 0; n < D / 16; ++n) o[r][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
-
-  // pairs of blocks that lie wholly below the first query position of this wave need no mask
-  // (row-group r = 0 holds the wave's earliest positions; a wave without rows masks everything)
-  const int p_free = gmax[0] >= 0 ? (wk.pos0 + ((wave * RGW) / G) * 16 + 1) / (2 * kBlockTokens) : 0;
+  const auto table = buffer_rsrc(tables + (int64_t)wk.slot * max_blocks, (uint32_t)b_end * 4u);
 
   // ---- this wave's share of the loads: one tile of the stage (block u, K or V) ----
   const int u_ld = wave >> 1, isv_ld = wave & 1;
   // tiles are stored in operand order, chunk c of all lanes in a 1 KiB run: the copy into LDS
   // is verbatim and lane-linear, and so are the fragment reads (no bank conflicts, no swizzle)
-  int id_chunk = -1, ids = 0;
-  auto issue = [&](int pair, int stage) {
+  const f16* my_tiles = arena + (kvh * 2 + isv_ld) * (kBlockTokens * D);
+  int id_chunk = 0, ids = buf1(table, lane * 4);
+  auto issue = [&](int pair) {
     const int b = min(2 * pair + u_ld, b_end - 1);     // past the end: re-read the last block (masked anyway)
     if ((b >> 6) != id_chunk) {                        // wave-uniform
       id_chunk = b >> 6;
-      const int bb = id_chunk * 64 + lane;
-      ids = bb < b_end ? table[bb] : 0;
+      ids = buf1(table, (id_chunk * 64 + lane) * 4);
       // used here, so that the wait for this load stands here: behind the branch the compiler would
       // have to wait in every step, for all loads in flight, the ring's among them
       asm volatile("" : "+v"(ids));
     }
     const int blk = __builtin_amdgcn_readlane(ids, b & 63);
-    const auto tile = buffer_rsrc(arena + kv_tile_off(geom, blk, kvh, isv_ld), TILE_B);
-    char* dst = lds + stage * STAGE_B + (u_ld * 2 + isv_ld) * TILE_B;
+    const auto tile = buffer_rsrc(my_tiles + (int64_t)blk * block_stride, TILE_B);
+    char* dst = lds + (pair % PF_STAGES) * STAGE_B + (u_ld * 2 + isv_ld) * TILE_B;
 #pragma unroll
     for (int t = 0; t < NI; ++t) dma16(tile, lane * 16, t * 1024, dst + t * 1024);
   };
 
-  // ---- fragment addresses inside a stage ----
-  int k_off[D / 32], v_off[D / 32];
+  // ---- this wave's row-groups ----
+  State w;
+  w.g = g;
+  int gmax[RGW];
 #pragma unroll
-  for (int c = 0; c < D / 32; ++c) k_off[c] = v_off[c] = c * 1024 + lane * 16;
+  for (int r = 0; r < RGW; ++r) {
+    const int rg = wave * RGW + r;
+    const int pos_blk = (rg * inv_g) >> 16, hd = rg - pos_blk * G, head = head0 + hd;
+    const int row_in = pos_blk * 16 + j;
+    const bool active = rg < n_rg && hd < n_heads && pos_blk * 16 < wk.n_rows;
+    const bool ok = active && row_in < wk.n_rows;
+    gmax[r] = active ? wk.pos0 + min(wk.n_rows, pos_blk * 16 + 16) - 1 : -1;
+    w.rpos[r] = ok ? wk.pos0 + row_in : gmax[r];
+    // MFMA c contracts dims [32c, 32c+32), lane group g its slice [32c + 8g, +8): the order of the K tiles
+    const auto qr = buffer_rsrc(q + ((int64_t)wk.row0 * nq + (active ? head : 0)) * D,
+                                active ? (uint32_t)((wk.n_rows - 1) * nq + 1) * (D * 2u) : 0u);   // rows below: zero
+#pragma unroll
+    for (int c = 0; c < D / 32; ++c) w.qf[r][c] = buf8(qr, row_in * nq * (D * 2) + (c * 32 + g * 8) * 2);
+    w.nm[r] = 0.f;
+    w.l[r] = 0.f;
+#pragma unroll
+    for (int n = 0; n < D / 16; ++n) w.o[r][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  asm volatile("" : "+v"(ids));                        // (its wait here, not before every use)
+#pragma unroll
+  for (int s = 0; s < PF_STAGES - 1; ++s)
+    if (s < n_pairs) issue(s);
 
-#pragma unroll
-  for (int s = 0; s < PF_STAGES - 1; ++s) issue(min(s, n_pairs - 1), s);
+  // pairs of blocks that lie wholly below the first query position of this wave need no mask
+  // (row-group r = 0 holds the wave's earliest positions; a wave without rows masks everything)
+  const int p_free = gmax[0] >= 0 ? (wk.pos0 + ((wave * RGW * inv_g) >> 16) * 16 + 1) / (2 * kBlockTokens) : 0;
+
+  // waits until at most `pairs` of the pairs requested last are on their way
+  auto wait_pairs = [&](int pairs) {
+    static_assert(PF_STAGES == 5, "cases below");
+    if (pairs >= 3) wait_vmcnt(3 * NI);
+    else if (pairs == 2) wait_vmcnt(2 * NI);
+    else if (pairs == 1) wait_vmcnt(NI);
+    else wait_vmcnt(0);
+  };
+  // pair 0 has landed, for every wave
+  wait_pairs(min(n_pairs, PF_STAGES - 1) - 1);
+  __builtin_amdgcn_s_barrier();
+  auto stage = [&](int pair) { return lds + (pair % PF_STAGES) * STAGE_B; };
+  w.start(lds, scale_log2, lane);
   auto step = [&](int p, auto masked) {
-    // the stage that is refilled below was read in the step before: those reads are complete, for every wave
+    // the stage that is refilled below was read in the step before: those reads are complete, for every wave, and pair
+    // p + 1 has landed for every wave (the pairs after it may still be on their way)
     wait_lgkmcnt0();
-    wait_vmcnt((PF_STAGES - 2) * NI);
+    if (p + PF_STAGES - 1 <= n_pairs) wait_vmcnt((PF_STAGES - 3) * NI);
+    else wait_pairs(n_pairs - 2 - p);
     __builtin_amdgcn_s_barrier();
-    issue(min(p + PF_STAGES - 1, n_pairs - 1), (p + PF_STAGES - 1) % PF_STAGES);
-    attend_pairs<D, RGW, decltype(masked)::value>(lds + (p % PF_STAGES) * STAGE_B, k_off, v_off, qf, 2 * p,
-                                                  rpos, scale_log2, m, l, o, lane);
+    if (p + PF_STAGES - 1 < n_pairs) issue(p + PF_STAGES - 1);
+    w.template step<true, decltype(masked)::value>(stage(p), stage(p + 1), p, scale_log2, lane);
   };
   // all waves of the work-group run the same number of steps (the barrier is shared); each
   // wave's mask-free prefix is its own
-  const int p_split = min(p_free, n_pairs);
-  for (int p = 0; p < p_split; ++p) step(p, std::false_type{});
-  for (int p = p_split; p < n_pairs; ++p) step(p, std::true_type{});
-  wait_vmcnt(0);
+  const int p_split = min(p_free, n_pairs) - 1;
+  int p = 0;
+  for (; p < p_split; ++p) step(p, std::false_type{});
+  for (; p < n_pairs - 1; ++p) step(p, std::true_type{});
+  w.template step<false, false>(stage(p), nullptr, p, scale_log2, lane);
 
 #pragma unroll
   for (int r = 0; r < RGW; ++r) {
     const int rg = wave * RGW + r;
-    const int pos_blk = rg / G, head = head0 + rg % G;
-    float lr = l[r];
-    lr += __shfl_xor(lr, 16);
-    lr += __shfl_xor(lr, 32);
+    const int pos_blk = (rg * inv_g) >> 16, head = head0 + rg - pos_blk * G;
+    const float lr = sum_over_groups(w.l[r]);
     float lo[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) lo[v] = __shfl(lr, 4 * g + v);
@@ -750,7 +866,7 @@ __global__ __launch_bounds__(256, (D == 128 && RGW == 3) ? 2 : 1) void attn_pref
         f16* op = out + ((int64_t)(wk.row0 + row_in) * nq + head) * D;
         const float inv = 1.0f / lo[v];
 #pragma unroll
-        for (int n = 0; n < D / 16; ++n) op[16 * n + j] = f2h_sat(o[r][n][v] * inv);
+        for (int n = 0; n < D / 16; ++n) op[16 * n + j] = f2h_sat(w.o[r][n][v] * inv);
       }
     }
   }
@@ -861,9 +977,14 @@ hipError_t launch_attn_prefill(hipStream_t s, const f16* q, const AttnWork* work
   const int head_parts = tile == 16 && G >= 5 && G <= 8 && 2 * n_work * geom.n_kv_heads <= 1024 ? 2 : 1;
   const int rgw = ((tile / 16) * ((G + head_parts - 1) / head_parts) + 3) / 4;           // row-groups per wave: 1 .. 4
   const int grid = n_work * geom.n_kv_heads * head_parts;
+  const int of_item = geom.n_kv_heads * head_parts, heads = (G + head_parts - 1) / head_parts;
+  if ((int64_t)n_work * of_item >= (int64_t)1 << 31 || geom.n_kv_heads >= 1 << 22) return hipErrorInvalidValue;
+  const uint32_t magic = of_item == 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + of_item - 1) / of_item);
+  const uint32_t shape = (uint32_t)G | (uint32_t)head_parts << 5 | (uint32_t)geom.n_kv_heads << 10;
 #define AREAL_PF(DD, RR)                                                                          \
-  attn_prefill_kernel<DD, RR><<<grid, 256, 0, s>>>(q, work, st, arena_layer, geom, n_q_heads, tile, \
-                                                   head_parts, scale_log2, out)
+  attn_prefill_kernel<DD, RR><<<grid, 256, 0, s>>>(work, q, st.table, arena_layer, magic, shape,  \
+                                                   (65536u + heads - 1) / heads, tile, st.max_blocks, geom.block_stride, \
+                                                   grid, scale_log2, out)
 #define AREAL_PF_D(DD)                                                                            \
   switch (rgw) {                                                                                  \
     case 1: AREAL_PF(DD, 1); break;                                                               \
@@ -882,3 +1003,4 @@ hipError_t launch_attn_prefill(hipStream_t s, const f16* q, const AttnWork* work
 }
 
 }  // namespace areal
+

@@ -86,3 +86,32 @@ def test_head_dim_128_deep_mixed_contexts(nq, nkv, layers, DEPTHS):
                 os.environ.pop(k, None)
             else:
                 os.environ[k] = v
+
+
+@pytest.mark.parametrize("head_dim,nq,nkv", [(32, 1, 1), (64, 3, 1), (128, 6, 2), (128, 8, 1), (128, 16, 1)])
+def test_prefill_around_the_length_of_the_kv_ring(head_dim, nq, nkv):
+    """Prompts around the 5 pairs of KV blocks that a prefill attention work-group holds, with an odd block and a ragged
+    last one, in one pass (tiles of 32 or 16 positions, one or two head parts, 1 to 4 row-groups a wave), and the longest
+    cut into passes that start inside a block.  Queries 16 times as large spread the scores over some 40 powers of two,
+    so that the running maximum is raised in the middle of a walk.  One layer, so the logits' error is the halves' that
+    hold queries, keys and values: relative 2^-11 of scores up to 20 moves a probability by 1 %, within 2e-2 for logits
+    of order 0.5."""
+    from oracle import decoder
+    from paper_2505_24298_amd import binding
+    lens = [1, 31, 32, 33, 97, 128, 129, 160, 161, 192, 209, 330]
+    cfg = synth.shape("tiny", n_layers=1, n_q_heads=nq, n_kv_heads=nkv, head_dim=head_dim, hidden=256, ffn=256)
+    w = synth.make_weights(cfg, 40 + nq, qkv_bias=True, std=0.03)
+    w["layers"][0]["wq"] *= np.float32(16)
+    rng = np.random.default_rng(nq)
+    prompts = [rng.integers(0, cfg["vocab"], size=T).astype(np.int32) for T in lens]
+    w16 = _f16_weights(w)
+    ref = np.stack([decoder.forward(p, w16, cfg, rows=[len(p) - 1])[0] for p in prompts])
+    for batch in (2048, 77):
+        eng = binding.Areal(cfg, max_seqs=len(lens), max_seq_len=max(lens) + 8, max_batch_tokens=batch,
+                            kv_blocks=sum(T // 16 + 2 for T in lens), convert_weights=True)
+        eng.load_weights(binding.weights_to_device(w, bf16=False), 0)
+        got = eng.prefill(list(range(len(lens))), prompts).cpu().numpy()
+        eng.close()
+        worst = float(np.abs(got - ref).max())
+        print(f"heads {nq}/{nkv} x {head_dim}, passes of {batch}: {worst:.2e}", flush=True)
+        assert worst <= LOGIT_TOL
