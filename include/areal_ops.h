@@ -33,6 +33,18 @@ int areal_op_gemm_num_configs(void);
 int areal_op_gemm_choose(int32_t M, int32_t N, int32_t K, int32_t mode, int32_t* cfg_out,
                          int32_t* splits_out);
 
+/* The products of a pass of up to 8 rows (no tiles; mode as above):
+ *   mode 0: C float32 [M,N]  = norm(x) W^T,  W = W0, or the rows of W0 | W1 | W2, of which the second and third
+ *           segment start at rows end0 and end1 (multiples of 8)
+ *   mode 1: C float32 [M,N] += x W0^T,       x half [M,K], gain NULL
+ *   mode 2: C half    [M,N]  = silu(norm(x) W0^T) * (norm(x) W1^T)
+ * norm(x) = x / sqrt(mean(x^2) + eps) * gain rounded to half, x float32 [M,K], gain half [K].
+ * areal_op_rows_serves: 1 where the library takes this path for M rows, 0 elsewhere (AREAL_E_INVAL there). */
+int areal_op_rows_serves(int32_t M, int32_t N, int32_t K, int32_t mode);
+int areal_op_rows_product(void* hip_stream, const void* x, const void* gain, float eps, const void* W0, const void* W1,
+                          const void* W2, int32_t end0, int32_t end1, void* C, int32_t M, int32_t N, int32_t K,
+                          int32_t mode);
+
 /* Calibration for the roofline of the streaming kernels (Section 3.2: decoding is
  * memory-IO bound): a kernel that reads `bytes` (multiple of 16, device, 16-byte
  * aligned) from `src` and does nothing else, launched like the decode kernels

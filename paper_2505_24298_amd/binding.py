@@ -96,6 +96,9 @@ _SIGNATURES = {
                                 C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32]),
     "areal_op_gemm_num_configs": (C.c_int, []),
     "areal_op_gemm_choose": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.c_int32, _I32P, _I32P]),
+    "areal_op_rows_serves": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.c_int32]),
+    "areal_op_rows_product": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_float, C.c_void_p, C.c_void_p, C.c_void_p,
+                                        C.c_int32, C.c_int32, C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_int32]),
     "areal_op_stream_read": (C.c_int, [C.c_void_p, C.c_void_p, C.c_uint64, C.c_void_p]),
     # include/areal_host.h
     "areal_kvalloc_create": (C.c_void_p, [C.c_int64, C.c_int32, C.c_int32]),
@@ -422,6 +425,20 @@ def op_gemm(A, W0, W1, C_out, mode, cfg=-1, splits=-1):
                              None if W1 is None else W1.data_ptr(), C_out.data_ptr(), M, N, K, mode, cfg, splits)
     if rc != OK:
         raise ArealError(rc, "areal_op_gemm")
+
+
+def op_rows_product(x, gain, eps, W, C_out, mode):
+    """areal_op_rows_product on torch tensors (current stream); W: one to three matrices."""
+    import torch
+    M, K = x.shape
+    W = list(W) + [None] * (3 - len(W))
+    end0 = W[0].shape[0]
+    end1 = end0 + (W[1].shape[0] if W[1] is not None else 0)
+    p = lambda t: None if t is None else t.data_ptr()
+    rc = lib().areal_op_rows_product(torch.cuda.current_stream().cuda_stream, x.data_ptr(), p(gain), float(eps), p(W[0]),
+                                     p(W[1]), p(W[2]), end0, end1, C_out.data_ptr(), M, C_out.shape[1], K, mode)
+    if rc != OK:
+        raise ArealError(rc, "areal_op_rows_product")
 
 
 def op_stream_read(buf, offset, nbytes, sink):

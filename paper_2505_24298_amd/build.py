@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libareal.so")
-SOURCES = ["elementwise.hip", "gemm.hip", "attention.hip", "sampler.hip", "scoring.hip", "runtime.hip",
+SOURCES = ["elementwise.hip", "gemm.hip", "rows.hip", "attention.hip", "sampler.hip", "scoring.hip", "runtime.hip",
            "host_api.cpp"]
 HOST_SAN_LIB = os.path.join(OBJ, "libareal_host_san.so")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",

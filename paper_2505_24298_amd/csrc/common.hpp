@@ -77,6 +77,9 @@ __device__ __forceinline__ uint32_t dpp_xor1(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xF, 0xF, false);
 }
 
+// A correctly rounded quotient, in every tile: the hardware's reciprocal (1 ulp) times z is another half now and then.
+__device__ __forceinline__ float silu_f(float z) { return z / (1.0f + __expf(-z)); }
+
 // Base and size of a range for buffer loads (raw, 32-bit offsets, reads past the end return zero).
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_rsrc(const void* base, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00027000);

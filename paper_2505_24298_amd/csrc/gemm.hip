@@ -139,9 +139,6 @@ __device__ __forceinline__ bool tile_of_block(uint32_t map, int m_tiles, int n_t
   return true;
 }
 
-// A correctly rounded quotient, in every tile: the hardware's reciprocal (1 ulp) times z is another half now and then.
-__device__ __forceinline__ float silu_f(float z) { return z / (1.0f + __expf(-z)); }
-
 template <int BM, int BN, int WM, int WN, int MODE, bool RAGGED_K>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const f16* __restrict__ A, int M, int N, int K,
                                                             uint32_t map, int slabs_per_split, int ldc,

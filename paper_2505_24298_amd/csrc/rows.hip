@@ -1,0 +1,326 @@
+// Products of a handful of rows (the decode steps of a few sequences): C (+)= X W^T, with the RMSNorm that makes X inside.
+//
+// Bound by the stream of the weights and by what stands before and after it.  Matrix cores need 16 rows to pay, and a tile
+// that passes its weights through LDS pays for barriers, for float32 atomics of K splits and, at 1 row, for 31 rows of
+// nothing.  Here a lane takes 16 bytes of a weight row straight into registers, one instruction of a wave 1 KiB in a
+// row, multiplies them with its part of the few input rows, which it holds in registers for the whole launch
+// (v_dot2_f32_f16: exact products, float32 sums), and the lanes' sums are folded once per weight row.  One work-group of
+// 4 waves per compute unit takes an equal run of weight rows, so that every unit streams the same number of bytes, and
+// each output has one owner: no atomics, nothing to clear beforehand.  The first weights are in flight before the RMSNorm
+// is computed, every work-group for itself, so that the norm has no launch of its own.
+//
+// Bytes in flight: a plain read of 108 (216) KB per compute unit, a launch after an empty one, takes 5.2 (9.7) us with 32 KB in
+// flight on each, 5.7 (10.1) with 112 KB.  Two batches of 1 or 2 weight rows per wave (24 - 48 KB): step of one row 1,070 us;
+// four batches 1,145 with 8 waves, 1,086 with 4; two work-groups per unit 1,071 - 1,121.
+// Against the tiles of gemm.hip and two RMSNorm launches per layer, 1.5B shape, steps of 1, 2, 3, 4 rows of 700 tokens 1,215 -> 1,060,
+// 1,234 -> 1,086, 1,255 -> 1,161, 1,261 -> 1,161 us; 7B shape, 2,000 tokens 3,006 -> 2,858, 3,071 -> 2,974, 3,086 -> 3,069, 3,151 ->
+// 3,137.  From 5 rows on the dot products' issue slots cost more than the launches (8 rows 1,288 -> 1,386), but where K
+// is at most 512: nothing streams there, and a launch is a launch.
+#include "kernels.hpp"
+
+namespace areal {
+
+namespace {
+
+constexpr int WAVES = 4, TPB = WAVES * 64;
+constexpr int UNITS = 256;                       // compute units: work-groups of a launch
+constexpr int MAX_PAIRS = 80, MAX_COLS = 64;     // features (of two weight rows) and plain outputs per work-group at most
+
+struct Late {
+  void* C;
+  int ldc;
+  float eps;
+};
+
+// Sums over the wave of 4 (2) values at once: exchanged halves and rows of 16 lanes put one value into each row
+// (half): folded_value.
+template <int CB>
+__device__ __forceinline__ float fold_values(const float (&v)[CB]) {
+  static_assert(CB == 2 || CB == 4, "values per fold");
+  auto swap32 = [](float a, float b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+    const uint32_t lo = r[0], hi = r[1];
+    return __builtin_bit_cast(float, lo) + __builtin_bit_cast(float, hi);
+  };
+  float s = swap32(v[0], v[1]);
+  if constexpr (CB == 4) {
+    const float t = swap32(v[2], v[3]);
+    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, s), __builtin_bit_cast(uint32_t, t), false, false);
+    const uint32_t lo = r[0], hi = r[1];
+    s = __builtin_bit_cast(float, lo) + __builtin_bit_cast(float, hi);
+  } else {
+    s = xor_lanes<16>(s, [](float a, float b) { return a + b; });
+  }
+  s += dpp<0x128>(s);
+  s += dpp<0x124>(s);
+  s += dpp<0x4E>(s);
+  s += dpp<0xB1>(s);
+  return s;
+}
+// Which of four values a lane holds after fold_values (of two: lane >> 5).
+__device__ __forceinline__ int folded_value(int lane) { return ((lane >> 5) & 1) | ((lane >> 3) & 2); }
+
+// LDS only: the weights in flight stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// NR input rows (n of them exist); WPC waves share a weight row, a lane holds NCH times 16 bytes of it.
+// NORM: x float32, normalised with `gain`; else halves.  The weights: one matrix, or (stored products) up to three row
+// segments, of end8 & 0xFFFF and end8 >> 16 times 8 rows up to the second and third, or (SwiGLU) gate p0 and up p1.
+template <int NR, int NCH, int WPC, int MODE, bool NORM>
+__global__ __launch_bounds__(TPB) void rows_kernel(const void* __restrict__ x, const f16* __restrict__ gain,
+                                                   const f16* __restrict__ p0, const f16* __restrict__ p1,
+                                                   const f16* __restrict__ p2, uint32_t end8, int N, int K, uint32_t shape,
+                                                   Late late) {
+  constexpr int GROUPS = WAVES / WPC;
+  constexpr int CB = NCH > 3 ? 1 : 2, DEPTH = 2;           // weight rows per batch of loads, batches in flight
+  constexpr int KP = NCH * WPC * 512;                      // K and what is masked
+  constexpr int COLS = MODE == GEMM_SWIGLU_F16 ? 2 * MAX_PAIRS : MAX_COLS;
+  __shared__ __attribute__((aligned(16))) f16 xs[NORM ? NR * KP : 8];
+  __shared__ float red[NR][WPC][COLS];
+
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int grp = wave / WPC, sub = wave % WPC;
+  const int n = shape & 255, per_wg = shape >> 8;
+  const int c0 = blockIdx.x * per_wg, cnt = min(per_wg, N - c0);
+  const int cols = MODE == GEMM_SWIGLU_F16 ? 2 * cnt : cnt;
+
+  // the input rows first: they are needed first, and loads return in order
+  constexpr int NV = NORM ? KP / 256 : 1, RPW = (NR + WAVES - 1) / WAVES;      // rows r = wave, wave + 4, .. are a wave's
+  f32x4 hv[RPW][NV];
+  f16x4 gv[NV];
+  f16x8 xr[NR][NCH];
+  const int lane_off = (sub * 64 + lane) * 16;
+  if constexpr (NORM) {
+    const auto gr = buffer_rsrc(gain, wave < n ? (uint32_t)K * 2u : 0u);
+#pragma unroll
+    for (int k = 0; k < RPW; ++k) {
+      const int r = wave + k * WAVES;
+      const auto hr = buffer_rsrc((const float*)x + (int64_t)r * K, r < n ? (uint32_t)K * 4u : 0u);
+#pragma unroll
+      for (int i = 0; i < NV; ++i) hv[k][i] = buf4f(hr, (i * 64 + lane) * 16);
+    }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) gv[i] = buf4(gr, (i * 64 + lane) * 8);
+  } else {
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const auto rr = buffer_rsrc((const f16*)x + (int64_t)r * K, r < n ? (uint32_t)K * 2u : 0u);
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) xr[r][c] = buf8(rr, lane_off + c * WPC * 1024);
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+
+  // column q of this work-group's; past the end: an empty range, which reads nothing
+  const int mid = (int)(end8 & 0xFFFFu) * 8, last = (int)(end8 >> 16) * 8;
+  auto load = [&](f16x8 (&w)[CB][NCH], int b) {
+#pragma unroll
+    for (int u = 0; u < CB; ++u) {
+      const int q = (b * GROUPS + grp) * CB + u;
+      const f16* p;
+      int64_t row;
+      if (MODE == GEMM_SWIGLU_F16) {
+        p = q & 1 ? p1 : p0;
+        row = c0 + (q >> 1);
+      } else {
+        const int c = c0 + q;
+        if (MODE == GEMM_STORE_F32) {
+          p = c >= last ? p2 : (c >= mid ? p1 : p0);
+          row = c - (c >= last ? last : (c >= mid ? mid : 0));
+        } else {
+          p = p0;
+          row = c;
+        }
+      }
+      const auto wr = buffer_rsrc(p + row * K, q < cols ? (uint32_t)K * 2u : 0u);
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) w[u][c] = buf8(wr, lane_off + c * WPC * 1024);
+    }
+  };
+  f16x8 w[DEPTH][CB][NCH];
+#pragma unroll
+  for (int d = 0; d < DEPTH; ++d) load(w[d], d);
+  __builtin_amdgcn_sched_barrier(0);
+  void* const C = late.C;
+  const int ldc = late.ldc;
+  asm volatile("" : : "s"(C), "s"(ldc));                    // read here, not where the launch ends
+  // the residual's old values: one owner per output, wave r has rows r, r + 4, ..
+  float old[RPW];
+  if constexpr (MODE == GEMM_ADD_F32) {
+#pragma unroll
+    for (int k = 0; k < RPW; ++k) {
+      const int r = wave + k * WAVES;
+      const auto cr = buffer_rsrc((const float*)C + (int64_t)r * ldc + c0, r < n ? (uint32_t)cnt * 4u : 0u);
+      old[k] = __builtin_bit_cast(float, buf1(cr, lane * 4));
+    }
+  }
+
+  if constexpr (NORM) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) asm volatile("" : "+v"(gv[i]));    // else their loads sink below the weights', and wait for all
+#pragma unroll
+    for (int k = 0; k < RPW; ++k) {
+      const f32x4(&v)[NV] = hv[k];
+      float ss = 0.f;
+#pragma unroll
+      for (int i = 0; i < NV; ++i) ss += v[i][0] * v[i][0] + v[i][1] * v[i][1] + v[i][2] * v[i][2] + v[i][3] * v[i][3];
+      ss = wave_sum(ss);
+      const float rs = 1.0f / sqrtf(ss / (float)K + late.eps);
+      const int r = wave + k * WAVES;
+      if (r < NR) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+          f16x4 o;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[e] = f2h_sat(v[i][e] * rs * h2f(gv[i][e]));
+          *reinterpret_cast<f16x4*>(&xs[r * KP + (i * 64 + lane) * 4]) = o;       // zeros from K on
+        }
+      }
+    }
+    lds_barrier();
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) xr[r][c] = *reinterpret_cast<const f16x8*>(&xs[r * KP + lane_off / 2 + c * WPC * 512]);
+  }
+
+  auto compute = [&](const f16x8 (&wt)[CB][NCH], int b) {
+    float acc[NR][CB];
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+#pragma unroll
+      for (int u = 0; u < CB; ++u) acc[r][u] = 0.f;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c)
+#pragma unroll
+      for (int e = 0; e < 8; e += 2)
+#pragma unroll
+        for (int r = 0; r < NR; ++r)
+#pragma unroll
+          for (int u = 0; u < CB; ++u)
+            acc[r][u] = __builtin_amdgcn_fdot2(f16x2{wt[u][c][e], wt[u][c][e + 1]}, f16x2{xr[r][c][e], xr[r][c][e + 1]},
+                                               acc[r][u], false);
+    const int q0 = (b * GROUPS + grp) * CB;
+    if constexpr (NR == 1 && CB == 1) {
+      const float s = wave_sum(acc[0][0]);
+      if (lane == 0 && q0 < cols) red[0][sub][q0] = s;
+    } else if constexpr (CB == 1) {
+#pragma unroll
+      for (int r = 0; r < NR; r += 2) {
+        const float v[2] = {acc[r][0], acc[r + 1][0]};
+        const float s = fold_values<2>(v);
+        if ((lane & 31) == 0 && q0 < cols) red[r + (lane >> 5)][sub][q0] = s;
+      }
+    } else if constexpr (NR == 1) {
+      const float s = fold_values<2>(acc[0]);
+      const int q = q0 + (lane >> 5);
+      if ((lane & 31) == 0 && q < cols) red[0][sub][q] = s;
+    } else {
+#pragma unroll
+      for (int r = 0; r < NR; r += 2) {
+        const float v[4] = {acc[r][0], acc[r][1], acc[r + 1][0], acc[r + 1][1]};
+        const float s = fold_values<4>(v);
+        const int k = folded_value(lane), q = q0 + (k & 1);
+        if ((lane & 15) == 0 && q < cols) red[r + (k >> 1)][sub][q] = s;
+      }
+    }
+  };
+  const int batches = (cols + CB - 1) / CB;
+  for (int b = 0; b * GROUPS + grp < batches; b += DEPTH) {
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {
+      if (d > 0 && (b + d) * GROUPS + grp >= batches) break;
+      compute(w[d], b + d);
+      load(w[d], b + d + DEPTH);
+    }
+  }
+  lds_barrier();
+
+#pragma unroll
+  for (int k = 0; k < RPW; ++k) {
+    const int r = wave + k * WAVES;
+    if (r >= n) break;
+    for (int i = lane; i < cnt; i += 64) {
+      auto sum = [&](int q) {
+        float s = red[r][0][q];
+#pragma unroll
+        for (int p = 1; p < WPC; ++p) s += red[r][p][q];
+        return s;
+      };
+      const int64_t at = (int64_t)r * ldc + c0 + i;
+      if constexpr (MODE == GEMM_SWIGLU_F16) {
+        ((f16*)C)[at] = f2h_sat(silu_f(sum(2 * i)) * sum(2 * i + 1));
+      } else if constexpr (MODE == GEMM_ADD_F32) {
+        ((float*)C)[at] = old[k] + sum(i);                  // at most 64 outputs a work-group
+      } else {
+        ((float*)C)[at] = sum(i);
+      }
+    }
+  }
+}
+
+// Chunks of 16 bytes per lane and waves per weight row, by the largest K of each, and the most rows of it (measured at the head
+// of this file).  A wave has a weight row to itself as long as its chunks fit: with four waves to a row of K = 3,584 every one of
+// them folds every sum (7B shape, 1 row 2,913 us, with one 2,871; 4 rows 3,305 and 3,146).
+struct Layout { int K, nch, wpc, rows; };
+constexpr Layout kLayouts[] = {{512, 1, 1, 8}, {1536, 3, 1, 4}, {2048, 4, 1, 4}, {3584, 7, 1, 4}, {4096, 8, 1, 4}, {12288, 6, 4, 4}, {20480, 10, 4, 4}};
+constexpr int kNormLayouts = 5;
+int layout(int M, int K, bool norm) {
+  for (int l = 0; l < (norm ? kNormLayouts : 7); ++l)
+    if (K <= kLayouts[l].K) return M <= kLayouts[l].rows ? l : -1;
+  return -1;
+}
+
+template <int NR, int MODE, bool NORM, int LAY>
+void launch(int lay, int grid, hipStream_t s, const void* x, const f16* gain, const GemmW& W, uint32_t end8, int N, int K,
+            uint32_t shape, Late late) {
+  if constexpr (LAY < (NORM ? kNormLayouts : 7)) {
+    if (lay != LAY) return launch<NR, MODE, NORM, LAY + 1>(lay, grid, s, x, gain, W, end8, N, K, shape, late);
+    if constexpr (NR <= kLayouts[LAY].rows)
+      rows_kernel<NR, kLayouts[LAY].nch, kLayouts[LAY].wpc, MODE, NORM>
+          <<<grid, TPB, 0, s>>>(x, gain, W.ptr[0], W.ptr[1], W.ptr[2], end8, N, K, shape, late);
+  }
+}
+
+}  // namespace
+
+bool rows_product_serves(int M, int N, int K, GemmMode mode, bool norm) {
+  if (M < 1 || N < 1 || K < 8 || K % 8 || layout(M, K, norm) < 0) return false;
+  return (N + UNITS - 1) / UNITS <= (mode == GEMM_SWIGLU_F16 ? MAX_PAIRS : MAX_COLS);
+}
+
+hipError_t launch_rows_product(hipStream_t s, const void* x, const f16* gain, float eps, GemmW W, void* C, int M, int N, int K,
+                               int ldc, GemmMode mode) {
+  const bool norm = gain != nullptr;
+  if (!rows_product_serves(M, N, K, mode, norm) || !x || !C || ldc < N || !W.ptr[0]) return hipErrorInvalidValue;
+  // modes in use: the norm before stored and SwiGLU products, none before residual adds
+  if (norm != (mode != GEMM_ADD_F32)) return hipErrorInvalidValue;
+  uint32_t end8 = 0xFFFFFFFFu;                                                    // beyond any column
+  if (mode == GEMM_SWIGLU_F16) {
+    if (!W.ptr[1]) return hipErrorInvalidValue;
+  } else if (mode == GEMM_STORE_F32 && W.ptr[1]) {
+    if (!W.ptr[2] || W.end[0] % 8 || W.end[1] % 8 || W.end[0] < 0 || W.end[1] < W.end[0] || W.end[2] != N ||
+        W.end[1] > N || N >= 0xFFFF * 8)
+      return hipErrorInvalidValue;
+    end8 = (uint32_t)(W.end[0] / 8) | (uint32_t)(W.end[1] / 8) << 16;
+  }
+  const int per_wg = (N + UNITS - 1) / UNITS, grid = (N + per_wg - 1) / per_wg, lay = layout(M, K, norm);
+  const uint32_t shape = (uint32_t)M | (uint32_t)per_wg << 8;
+  const Late late{C, ldc, eps};
+#define AREAL_MODE(NR)                                                                                               \
+  (mode == GEMM_STORE_F32    ? launch<NR, GEMM_STORE_F32, true, 0>(lay, grid, s, x, gain, W, end8, N, K, shape, late)    \
+   : mode == GEMM_SWIGLU_F16 ? launch<NR, GEMM_SWIGLU_F16, true, 0>(lay, grid, s, x, gain, W, end8, N, K, shape, late)   \
+                             : launch<NR, GEMM_ADD_F32, false, 0>(lay, grid, s, x, gain, W, end8, N, K, shape, late))
+  if (M == 1) AREAL_MODE(1);
+  else if (M == 2) AREAL_MODE(2);
+  else if (M <= 4) AREAL_MODE(4);
+  else AREAL_MODE(8);
+#undef AREAL_MODE
+  return hipGetLastError();
+}
+
+}  // namespace areal

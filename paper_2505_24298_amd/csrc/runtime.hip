@@ -349,9 +349,16 @@ int run_pass(areal_ctx* c, const PassArgs& a) {
     ProfScope ps(c, AREAL_K_EMBED, -1, sampled, rows);
     HIP_TRY(c, launch_embed(s, w.embed, H, g.vocab, a.M, a.rm, a.tokens_in, a.new_block, st, h));
   }
+  // h += x W^T
+  auto residual_add = [&](const f16* x, const GemmW& wt, int K) {
+    return rows_product_serves(a.M, H, K, GEMM_ADD_F32, false)
+               ? launch_rows_product(s, x, nullptr, 0.f, wt, h, a.M, H, K, H, GEMM_ADD_F32)
+               : launch_gemm_cfg(s, x, wt, h, a.M, H, K, H, GEMM_ADD_F32, -1, -1);
+  };
   for (int l = 0; l < g.n_layers; ++l) {
     f16* arena_l = arena + (int64_t)l * c->geom.layer_stride;
-    {
+    const bool few_qkv = rows_product_serves(a.M, qd + 2 * kd, H, GEMM_STORE_F32, true);
+    if (!few_qkv) {
       ProfScope ps(c, AREAL_K_RMSNORM, l, sampled, rows);
       // the QKV product may split K and accumulate atomically: then its output is cleared here
       int qkv_cfg, qkv_splits;
@@ -362,7 +369,10 @@ int run_pass(areal_ctx* c, const PassArgs& a) {
     {
       ProfScope ps(c, AREAL_K_GEMM_QKV, l, sampled, rows);
       GemmW wqkv{{w.wq[l], w.wk[l], w.wv[l]}, {qd, qd + kd, qd + 2 * kd}};
-      HIP_TRY(c, launch_gemm_cfg(s, xn, wqkv, qkv, a.M, qd + 2 * kd, H, qd + 2 * kd, GEMM_STORE_F32, -1, -1));
+      if (few_qkv)
+        HIP_TRY(c, launch_rows_product(s, h, w.norm_attn[l], g.rms_eps, wqkv, qkv, a.M, qd + 2 * kd, H, qd + 2 * kd, GEMM_STORE_F32));
+      else
+        HIP_TRY(c, launch_gemm_cfg(s, xn, wqkv, qkv, a.M, qd + 2 * kd, H, qd + 2 * kd, GEMM_STORE_F32, -1, -1));
     }
     const f16 *bq = w.has_bias ? w.bq[l] : nullptr, *bk = w.has_bias ? w.bk[l] : nullptr,
               *bv = w.has_bias ? w.bv[l] : nullptr;
@@ -389,18 +399,22 @@ int run_pass(areal_ctx* c, const PassArgs& a) {
     {
       ProfScope ps(c, AREAL_K_GEMM_O, l, sampled, rows);
       GemmW wo{{w.wo[l], nullptr, nullptr}, {H, 0, 0}};
-      HIP_TRY(c, launch_gemm_cfg(s, attn, wo, h, a.M, H, qd, H, GEMM_ADD_F32, -1, -1));
+      HIP_TRY(c, residual_add(attn, wo, qd));
     }
-    HIP_TRY(c, launch_rmsnorm(s, h, w.norm_ffn[l], xn, a.M, H, g.rms_eps, nullptr));
+    const bool few_gu = rows_product_serves(a.M, F, H, GEMM_SWIGLU_F16, true);
+    if (!few_gu) HIP_TRY(c, launch_rmsnorm(s, h, w.norm_ffn[l], xn, a.M, H, g.rms_eps, nullptr));
     {
       ProfScope ps(c, AREAL_K_GEMM_GATEUP, l, sampled, rows);
       GemmW wgu{{w.wgate[l], w.wup[l], nullptr}, {F, 0, 0}};
-      HIP_TRY(c, launch_gemm_cfg(s, xn, wgu, act, a.M, F, H, F, GEMM_SWIGLU_F16, -1, -1));
+      if (few_gu)
+        HIP_TRY(c, launch_rows_product(s, h, w.norm_ffn[l], g.rms_eps, wgu, act, a.M, F, H, F, GEMM_SWIGLU_F16));
+      else
+        HIP_TRY(c, launch_gemm_cfg(s, xn, wgu, act, a.M, F, H, F, GEMM_SWIGLU_F16, -1, -1));
     }
     {
       ProfScope ps(c, AREAL_K_GEMM_DOWN, l, sampled, rows);
       GemmW wd{{w.wdown[l], nullptr, nullptr}, {H, 0, 0}};
-      HIP_TRY(c, launch_gemm_cfg(s, act, wd, h, a.M, H, F, H, GEMM_ADD_F32, -1, -1));
+      HIP_TRY(c, residual_add(act, wd, F));
     }
   }
   if (a.target) {
@@ -1325,6 +1339,19 @@ int areal_op_gemm_choose(int32_t M, int32_t N, int32_t K, int32_t mode, int32_t*
   *cfg_out = c;
   *splits_out = sp;
   return AREAL_OK;
+}
+
+int areal_op_rows_serves(int32_t M, int32_t N, int32_t K, int32_t mode) {
+  return mode >= 0 && mode <= 2 && rows_product_serves(M, N, K, (GemmMode)mode, mode != 1);
+}
+int areal_op_rows_product(void* hip_stream, const void* x, const void* gain, float eps, const void* W0, const void* W1,
+                          const void* W2, int32_t end0, int32_t end1, void* C, int32_t M, int32_t N, int32_t K,
+                          int32_t mode) {
+  if (mode < 0 || mode > 2) return AREAL_E_INVAL;
+  const GemmW w{{(const f16*)W0, (const f16*)W1, (const f16*)W2}, {end0, end1, N}};
+  const hipError_t e = launch_rows_product((hipStream_t)hip_stream, x, (const f16*)gain, eps, w, C, M, N, K, N, (GemmMode)mode);
+  if (e == hipErrorInvalidValue) return AREAL_E_INVAL;
+  return e == hipSuccess ? AREAL_OK : AREAL_E_HIP;
 }
 
 int areal_op_stream_read(void* hip_stream, const void* src, uint64_t bytes, void* sink16) {

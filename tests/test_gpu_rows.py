@@ -1,0 +1,97 @@
+"""The products of a pass of up to 8 rows against float64 products of the same half-precision inputs, at the edges of the
+layouts over K, of the work-groups' runs of weight rows and of the row counts that are compiled."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _normed(x, gain, eps):
+    """The float64 RMSNorm, rounded once to half: what the product multiplies, up to a rounding here and there."""
+    xd = x.double()
+    y = xd / (xd.pow(2).mean(dim=1, keepdim=True) + eps).sqrt() * gain.double()
+    return y.to(dtype=y.dtype).clamp(-65504, 65504)
+
+
+# K: below, at and above each layout's end (512, 1536, 2048, 4096, 12288, 20480), with masked lanes and without
+@pytest.mark.parametrize("M,N,K", [(1, 344, 128), (8, 300, 8), (5, 257, 512), (1, 2048, 1536), (4, 1536, 1536), (3, 515, 520),
+                                   (4, 1000, 1544), (2, 264, 2048), (4, 700, 3584), (3, 4608, 4096), (2, 5, 3592),
+                                   (1, 1536, 8960), (4, 1536, 8960), (3, 72, 12288), (4, 3584, 18944), (3, 40, 20480)])
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_rows_product(M, N, K, mode):
+    import torch
+    from paper_2505_24298_amd import binding
+    L = binding.lib()
+    g = torch.Generator(device="cuda").manual_seed(M * 7 + N + K)
+    rand = lambda *s: torch.randn(s, generator=g, device="cuda")
+    W0, W1 = (rand(N, K) * 0.05).half(), (rand(N, K) * 0.05).half()
+    gain = (rand(K) * 0.1 + 1).half()
+    x = rand(M, K) * 3
+    if mode == 1:
+        x, gain = x.half(), None
+    served = K <= 4096 or mode == 1
+    assert L.areal_op_rows_serves(M, N, K, mode) == int(served)
+    C = rand(M, N)
+    base = C.clone()
+    if mode == 2:
+        C = C.half()
+    if not served:
+        with pytest.raises(binding.ArealError):
+            binding.op_rows_product(x, gain, 1e-6, [W0, W1][:1 + mode // 2], C, mode)
+        return
+    binding.op_rows_product(x, gain, 1e-6, [W0, W1] if mode == 2 else [W0], C, mode)
+    A = x.double() if mode == 1 else _normed(x, gain, 1e-6)
+    ref0, ref1 = A @ W0.double().T, A @ W1.double().T
+    # sums of K products: float32 roundings, and half a unit (2^-11) of each normalised input
+    noise = (A.abs().max() * 0.05 * K ** 0.5).item() * (2.0 ** -11 if mode != 1 else 4e-7)
+    if mode == 0:
+        assert (C.double() - ref0).abs().max().item() <= 4 * noise
+    elif mode == 1:
+        want = base.double() + ref0
+        assert (C.double() - want).abs().max().item() <= 4 * noise + 2.0 ** -22 * want.abs().max().item()
+    else:
+        want = ref0 / (1 + torch.exp(-ref0)) * ref1
+        room = 4 * noise * (1.2 * ref1.abs() + ref0.abs()) + 2.0 ** -10 * want.abs() + 1e-6
+        assert ((C.double() - want).abs() <= room).all()
+
+
+@pytest.mark.parametrize("M,parts,K", [(m, (1536, 256, 256), 1536) for m in (1, 2, 3, 4)] +
+                         [(m, (8, 16, 5), 264) for m in (1, 5, 6, 7, 8)] + [(8, (128, 64, 64), 128), (2, (3584, 512, 512), 3584)])
+def test_rows_product_of_three_segments(M, parts, K):
+    """The segments' rows as one matrix: the same bits.  Untouched neighbours of C stay."""
+    import torch
+    from paper_2505_24298_amd import binding
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    W = [(torch.randn((p, K), generator=g, device="cuda") * 0.05).half() for p in parts]
+    x, gain = torch.randn((M, K), generator=g, device="cuda"), torch.ones(K, device="cuda").half()
+    N = sum(parts)
+    buf = torch.full((M + 1, N), 7.0, device="cuda")
+    one = torch.empty((M, N), device="cuda")
+    binding.op_rows_product(x, gain, 1e-6, W, buf[:M], 0)
+    binding.op_rows_product(x, gain, 1e-6, [torch.cat(W)], one, 0)
+    assert torch.equal(buf[:M], one) and (buf[M] == 7.0).all()
+
+
+def test_rows_product_takes_subnormal_halves_and_saturates():
+    """Products of subnormal halves count, as on the matrix cores; a normalised value beyond the half range is its largest."""
+    import torch
+    from paper_2505_24298_amd import binding
+    K, N = 1536, 64
+    W = torch.full((N, K), 2.0 ** -24, device="cuda").half()             # the smallest subnormal
+    x = torch.full((1, K), 1.5, device="cuda").half()
+    C = torch.zeros((1, N), device="cuda")
+    binding.op_rows_product(x, None, 0.0, [W], C, 1)
+    assert np.allclose(C.cpu().numpy(), K * 1.5 * 2.0 ** -24, rtol=1e-6)
+    xf = torch.zeros((1, K), device="cuda")
+    xf[0, 0] = 100.0                                                     # normalised: sqrt(K) = 39.2
+    gain = torch.full((K,), 60000.0, device="cuda").half()
+    binding.op_rows_product(xf, gain, 0.0, [torch.ones((N, K), device="cuda").half()], C, 0)
+    assert (C == 65504.0).all()
+
+
+@pytest.mark.parametrize("M,N,K", [(9, 64, 128), (0, 64, 128), (1, 64, 100), (1, 64, 20488), (5, 64, 520), (1, 16385, 128)])
+def test_rows_product_refuses(M, N, K):
+    from paper_2505_24298_amd import binding
+    L = binding.lib()
+    assert L.areal_op_rows_serves(M, N, K, 1) == 0
+    assert L.areal_op_rows_product(None, 16, None, 0.0, 16, None, None, N, N, 16, M, N, K, 1) != 0
