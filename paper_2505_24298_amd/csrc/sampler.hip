@@ -53,9 +53,12 @@ typedef unsigned long long u64;
 // by 2^32 in the exponent (p in [0.7, 1.42], n >= -36: no subnormal, the product is exact); below
 // x = -25 the clamped argument gives 2^32 e^-25 = 0.06, which truncates to the specified 0; and
 // min(w, 1) is the comparison with 2^32 below.
+// The rounding to an integer is an addition of 1.5 * 2^23 + 32: in that range floats are integers, to nearest and
+// ties to even like rint (the constant is even), and the low bits of the sum are n + 32, shifted into the exponent as they are.
 __device__ __forceinline__ float scaled_sexp(float x) {
   const float xs = fmaxf(x, -25.0f);
-  const float n = __builtin_rintf(xs * 1.44269502162933349609375f);          // 0x3FB8AA3B
+  const float u = xs * 1.44269502162933349609375f + 12582944.0f;            // 0x3FB8AA3B
+  const float n = u - 12582944.0f;                                          // exact
   float r = xs - n * 0.693359375f;                                          // exact product
   r = r - n * -2.12194442749023437500e-4f;                                  // 0xB95E8083
   float p = 1.98412701138295233249664306640625e-4f;                         // 1/7!
@@ -66,7 +69,7 @@ __device__ __forceinline__ float scaled_sexp(float x) {
   p = p * r; p = p + 0.5f;
   p = p * r; p = p + 1.0f;
   p = p * r; p = p + 1.0f;
-  return __int_as_float(__float_as_int(p) + (((int)n + 32) << 23));
+  return __int_as_float(__float_as_int(p) + (__float_as_int(u) << 23));
 }
 __device__ __forceinline__ u64 mass_of_scaled(float w) {
   // below 2^32 the value fits the 32-bit truncating conversion; only w = 1 gives 2^32 itself
@@ -158,6 +161,77 @@ __device__ __forceinline__ void load_z4(const Row& r, int id0, float (&z)[4]) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) z[k] = id0 + k < r.V ? r.lp[id0 + k] * r.inv_t : -INFINITY;
   }
+}
+
+// f(segment, z of this lane's four ids) for segments first, first + step, .. below nseg, U at a time and the loads of the next
+// U ahead of them.  Buffer loads, which need no mask at the row's end, so that they go out in a run.
+template <int U, bool VEC, class F>
+__device__ __forceinline__ void walk_row(const Row& r, int first, int step, int nseg, int lane, F f) {
+  const auto buf = buffer_rsrc(r.lp, (uint32_t)r.V * 4u);
+  auto load = [&](int s) {
+    const int off = s * (SEG * 4) + lane * 16;
+    if (VEC) return buf4f(buf, off);
+    f32x4 v;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = __builtin_bit_cast(float, buf1(buf, off + 4 * k));
+    return v;
+  };
+  f32x4 cur[U], next[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) cur[u] = load(first + u * step);
+  for (int s = first; s < nseg; s += U * step) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) next[u] = load(s + (U + u) * step);     // past the end: zeros, not used
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int su = s + u * step;
+      if (u > 0 && su >= nseg) break;
+      float z[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) z[k] = cur[u][k] * r.inv_t;
+      if ((su + 1) * SEG > r.V) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (su * SEG + lane * 4 + k >= r.V) z[k] = -INFINITY;
+      }
+      f(su, z);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) cur[u] = next[u];
+  }
+}
+template <int U, class F>
+__device__ __forceinline__ void walk_row(const Row& r, int first, int step, int nseg, int lane, F f) {
+  first = __builtin_amdgcn_readfirstlane(first);
+  if (r.vec) walk_row<U, true>(r, first, step, nseg, lane, f);
+  else walk_row<U, false>(r, first, step, nseg, lane, f);
+}
+__device__ __forceinline__ float max4(const float (&z)[4], float mx) {
+  return fmaxf(fmaxf(mx, fmaxf(z[0], z[1])), fmaxf(z[2], z[3]));
+}
+// Masses of four scaled exponentials in 32 bits: the hardware's conversion truncates and stops at 2^32 - 1, which no
+// float below 2^32 gives, so that this value stands for 2^32.  Returns whether any lane of the wave has one.
+__device__ __forceinline__ bool masses4(const float (&w)[4], uint32_t (&c)[4]) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) asm("v_cvt_u32_f32 %0, %1" : "=v"(c[k]) : "v"(w[k]));
+  // as integers, which order floats from 0 on as they are
+  const int hi = max(max(__float_as_int(w[0]), __float_as_int(w[1])), max(__float_as_int(w[2]), __float_as_int(w[3])));
+  return __any(hi >= 0x4F800000);
+}
+// Sum of the masses of a segment, in every lane.
+__device__ __forceinline__ u64 segment_mass(const float (&z)[4], float m) {
+  float w[4];
+  uint32_t c[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) w[k] = scaled_sexp(z[k] - m);
+  const bool whole = masses4(w, c);
+  u64 sum = ((u64)c[0] + c[1]) + ((u64)c[2] + c[3]);
+  if (whole) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) sum += c[k] == 0xFFFFFFFFu;
+  }
+  return wave_sum_u64(sum);
 }
 
 // Highest bin b with  sum_{b' >= b} hist[b'] >= need ; returns b and the mass
@@ -432,11 +506,7 @@ __global__ __launch_bounds__(TPB) void sampler_kernel(
 
   // ---- pass A: m = max z ----------------------------------------------------
   float mx = -INFINITY;
-  for (int s = wave; s < nseg; s += NWAVES) {
-    float z[4];
-    load_z4(R, s * SEG + lane * 4, z);
-    mx = fmaxf(fmaxf(mx, fmaxf(z[0], z[1])), fmaxf(z[2], z[3]));
-  }
+  walk_row<4>(R, wave, NWAVES, nseg, lane, [&](int, const float (&z)[4]) { mx = max4(z, mx); });
   mx = wave_max(mx);
   if (lane == 0) wave_max_s[wave] = mx;
   __syncthreads();
@@ -445,15 +515,10 @@ __global__ __launch_bounds__(TPB) void sampler_kernel(
   for (int w = 1; w < NWAVES; ++w) m = fmaxf(m, wave_max_s[w]);
 
   // ---- pass B: per-segment mass, S = total mass --------------------------------
-  for (int s = wave; s < nseg; s += NWAVES) {
-    float z[4];
-    load_z4(R, s * SEG + lane * 4, z);
-    u64 c = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) c += mass_of(z[k], m);
-    c = wave_sum_u64(c);
+  walk_row<1>(R, wave, NWAVES, nseg, lane, [&](int s, const float (&z)[4]) {
+    const u64 c = segment_mass(z, m);
     if (lane == 0) L.segmass[s] = c;
-  }
+  });
   __syncthreads();
   u64 S_total;
   block_incl_scan_u64(tid < nseg ? L.segmass[tid] : 0, L.wave_tot, S_total);
@@ -494,9 +559,14 @@ static_assert(sizeof(SplitScratch) == SAMPLER_SCRATCH_ROW && sizeof(SplitScratch
 
 // Bin of the mass of a scaled exponential w >= 0: c itself below 64, else octave and next six bits of c = trunc(w), which
 // are exponent and leading fraction bits of w, for truncation leaves the leading seven bits of a number of 64 and more.
+// The bits' bin is below c for w < 64 and equal to it or below from there on, so that the middle one of c, that bin and 64 is
+// the one meant (c saturates at 2^31 - 1).
 __device__ __forceinline__ int log_bin(float w) {
-  const int top = (__float_as_int(fminf(w, 4294967296.0f)) >> 17) - ((127 + 5) << 6);
-  return w < 64.0f ? (int)w : top;
+  const int top = (min(__float_as_int(w), 0x4F800000) >> 17) - ((127 + 5) << 6);
+  int c, bin;
+  asm("v_cvt_i32_f32 %0, %1" : "=v"(c) : "v"(w));
+  asm("v_med3_i32 %0, %1, %2, 64" : "=v"(bin) : "v"(c), "v"(top));
+  return bin;
 }
 __device__ __forceinline__ u64 log_bin_low(int b) {    // smallest mass of a bin
   return b < 64 ? (u64)b : (u64)(64 + (b & 63)) << ((b >> 6) - 1);
@@ -528,11 +598,7 @@ __global__ __launch_bounds__(SPLIT_TPB) void sampler_split_max_kernel(int V, con
     if (part == 0 && threadIdx.x == 0) sc.n_list = 0;
   }
   float mx = -INFINITY;
-  for (int sg = part * SPLIT_WAVES + wave; sg < nseg; sg += parts * SPLIT_WAVES) {
-    float z[4];
-    load_z4(R, sg * SEG + lane * 4, z);
-    mx = fmaxf(fmaxf(mx, fmaxf(z[0], z[1])), fmaxf(z[2], z[3]));
-  }
+  walk_row<4>(R, part * SPLIT_WAVES + wave, parts * SPLIT_WAVES, nseg, lane, [&](int, const float (&z)[4]) { mx = max4(z, mx); });
   mx = wave_max(mx);
   if (lane == 0) wmax[wave] = mx;
   __syncthreads();
@@ -552,15 +618,10 @@ __global__ __launch_bounds__(SPLIT_TPB) void sampler_split_mass_kernel(int V, co
   SplitScratch& sc = scratch[row];
   const int nseg = (V + SEG - 1) / SEG;
   const float m = row_max_of_parts(sc, parts);
-  for (int sg = part * SPLIT_WAVES + wave; sg < nseg; sg += parts * SPLIT_WAVES) {
-    float z[4];
-    load_z4(R, sg * SEG + lane * 4, z);
-    u64 c = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) c += mass_of(z[k], m);
-    c = wave_sum_u64(c);
+  walk_row<1>(R, part * SPLIT_WAVES + wave, parts * SPLIT_WAVES, nseg, lane, [&](int sg, const float (&z)[4]) {
+    const u64 c = segment_mass(z, m);
     if (lane == 0) sc.segmass[sg] = c;
-  }
+  });
 }
 
 __global__ __launch_bounds__(TPB) void sampler_split_pick_kernel(
@@ -607,23 +668,31 @@ __global__ __launch_bounds__(SPLIT_TPB) void sampler_split_hist_kernel(int V, co
   for (int b = threadIdx.x; b < LOG_BINS; b += SPLIT_TPB) hist[b] = 0;
   const float m = row_max_of_parts(sc, parts);
   __syncthreads();
-  for (int sg = part * SPLIT_WAVES + wave; sg < nseg; sg += parts * SPLIT_WAVES) {
-    float z[4];
-    load_z4(R, sg * SEG + lane * 4, z);
+  walk_row<1>(R, part * SPLIT_WAVES + wave, parts * SPLIT_WAVES, nseg, lane, [&](int, const float (&z)[4]) {
+    float w[4];
+    uint32_t c[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const float w = scaled_sexp(z[k] - m);
-      const u64 c = mass_of_scaled(w);                 // 0 beyond the vocabulary
-      const int bin = log_bin(w);
-      const int bin0 = __builtin_amdgcn_readfirstlane(bin);
-      if (__all(bin == bin0)) {                        // heavily tied logits: once per wave
-        const u64 tot = wave_sum_u64(c);
-        if (lane == 0) atomicAdd(&hist[bin0], tot);
-      } else if (c > 0) {
-        atomicAdd(&hist[bin], c);
+    for (int k = 0; k < 4; ++k) w[k] = scaled_sexp(z[k] - m);
+    const bool whole = masses4(w, c);                  // masses are 0 beyond the vocabulary
+    const int bin0 = log_bin(w[0]);
+    if (whole || __all(bin0 == __builtin_amdgcn_readfirstlane(bin0))) {   // 2^32 among them, or heavily tied logits
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const u64 ck = mass_of_scaled(w[k]);
+        const int b = log_bin(w[k]), b0 = __builtin_amdgcn_readfirstlane(b);
+        if (__all(b == b0)) {                          // once per wave
+          const u64 tot = wave_sum_u64(ck);
+          if (lane == 0) atomicAdd(&hist[b0], tot);
+        } else if (ck > 0) {
+          atomicAdd(&hist[b], ck);
+        }
       }
+      return;
     }
-  }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (c[k] > 0) atomicAdd(&hist[log_bin(w[k])], (u64)c[k]);
+  });
   __syncthreads();
   for (int b = threadIdx.x; b < LOG_BINS; b += SPLIT_TPB)
     if (hist[b]) atomicAdd(&sc.hist[b], hist[b]);
@@ -750,36 +819,58 @@ __global__ __launch_bounds__(SPLIT_TPB) void sampler_split_collect_kernel(int V,
   // evaluated: below x_skip their masses are less than the bin's lowest by a thousandth at least, far beyond
   // the specified exponential's error.
   const float x_skip = (float)(log((double)log_bin_low(tb)) - 32.0 * 0.69314718055994530942) - 1e-3f;   // -inf for bin 0
-  auto walk = [&](auto one_value) {
-    for (int sg = part * SPLIT_WAVES + wave; sg < nseg; sg += parts * SPLIT_WAVES) {
-      float z[4];
-      load_z4(R, sg * SEG + lane * 4, z);
+  auto append = [&](int id, uint32_t mass) {
+    const uint32_t at = atomicAdd(&n_list, 1u);
+    if (at < LIST_CAP) { list[at][0] = id; list[at][1] = mass; }
+  };
+  const int first = part * SPLIT_WAVES + wave, step = parts * SPLIT_WAVES;
+  if (log_bin_width(tb) == 0) {
+    walk_row<1>(R, first, step, nseg, lane, [&](int sg, const float (&z)[4]) {
       u64 gt = 0;
       int ties = 0;
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         if (!__any(!(z[k] - m < x_skip))) continue;
         const float w = scaled_sexp(z[k] - m);
-        const u64 c = mass_of_scaled(w);
         const int bin = log_bin(w);
-        const bool in = bin == tb && sg * SEG + lane * 4 + k < V;
-        if (bin > tb) gt += c;
-        if constexpr (decltype(one_value)::value) {
-          ties += __popcll(__ballot(in));
-        } else if (in) {
-          const uint32_t at = atomicAdd(&n_list, 1u);
-          if (at < LIST_CAP) { list[at][0] = sg * SEG + lane * 4 + k; list[at][1] = (uint32_t)c; }
-        }
+        if (bin > tb) gt += mass_of_scaled(w);
+        ties += __popcll(__ballot(bin == tb && sg * SEG + lane * 4 + k < V));
       }
       gt = wave_sum_u64(gt);
-      if (lane == 0) {
-        sc.segmass[sg] = gt;
-        if constexpr (decltype(one_value)::value) sc.segtie[sg] = ties;
+      if (lane == 0) { sc.segmass[sg] = gt; sc.segtie[sg] = ties; }
+    });
+  } else {
+    // The bin's masses [lo, hi) in 32 bits, lo >= 128: no id beyond the vocabulary, whose mass is 0, is among them.  2^32 - 1
+    // stands for 2^32 (masses4) and lies above every such bin.
+    const uint32_t lo = (uint32_t)log_bin_low(tb), hi = (uint32_t)min((u64)0xFFFFFFFFu, log_bin_low(tb + 1)), width = hi - lo;
+    walk_row<1>(R, first, step, nseg, lane, [&](int sg, const float (&z)[4]) {
+      u64 gt = 0;
+      if (__any(!(max4(z, -INFINITY) - m < x_skip))) {
+        float w[4];
+        uint32_t c[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) w[k] = scaled_sexp(z[k] - m);
+        const bool whole = masses4(w, c);
+        bool in = false;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          gt += c[k] >= hi ? c[k] : 0;
+          in |= c[k] - lo < width;
+        }
+        if (whole) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) gt += c[k] == 0xFFFFFFFFu;
+        }
+        if (in) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            if (c[k] - lo < width) append(sg * SEG + lane * 4 + k, c[k]);
+        }
+        gt = wave_sum_u64(gt);
       }
-    }
-  };
-  if (log_bin_width(tb) == 0) walk(std::true_type{});
-  else walk(std::false_type{});
+      if (lane == 0) sc.segmass[sg] = gt;
+    });
+  }
   __syncthreads();
   const uint32_t n = n_list;
   if (threadIdx.x == 0 && n) base = atomicAdd(&sc.n_list, n);
