@@ -164,21 +164,31 @@ __device__ __forceinline__ void load_z4(const Row& r, int id0, float (&z)[4]) {
 }
 
 // f(segment, z of this lane's four ids) for segments first, first + step, .. below nseg, U at a time and the loads of the next
-// U ahead of them.  Buffer loads, which need no mask at the row's end, so that they go out in a run.
-template <int U, bool VEC, class F>
-__device__ __forceinline__ void walk_row(const Row& r, int first, int step, int nseg, int lane, F f) {
+// U ahead of them.  Buffer loads, which need no mask at the row's end, so that they go out in a run.  U = 1: `head` is the first.
+template <bool VEC>
+__device__ __forceinline__ f32x4 load_segment(const Row& r, int s, int lane) {
   const auto buf = buffer_rsrc(r.lp, (uint32_t)r.V * 4u);
-  auto load = [&](int s) {
-    const int off = s * (SEG * 4) + lane * 16;
-    if (VEC) return buf4f(buf, off);
-    f32x4 v;
+  const int off = s * (SEG * 4) + lane * 16;
+  if (VEC) return buf4f(buf, off);
+  f32x4 v;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = __builtin_bit_cast(float, buf1(buf, off + 4 * k));
-    return v;
-  };
+  for (int k = 0; k < 4; ++k) v[k] = __builtin_bit_cast(float, buf1(buf, off + 4 * k));
+  return v;
+}
+// The first segment of a walk, for a caller that has something to wait for before it.
+__device__ __forceinline__ f32x4 first_segment(const Row& r, int first, int lane) {
+  first = __builtin_amdgcn_readfirstlane(first);
+  return r.vec ? load_segment<true>(r, first, lane) : load_segment<false>(r, first, lane);
+}
+template <int U, bool VEC, class F>
+__device__ __forceinline__ void walk_row(const Row& r, int first, int step, int nseg, int lane, f32x4 head, F f) {
+  auto load = [&](int s) { return load_segment<VEC>(r, s, lane); };
   f32x4 cur[U], next[U];
+  if constexpr (U == 1) cur[0] = head;
+  else {
 #pragma unroll
-  for (int u = 0; u < U; ++u) cur[u] = load(first + u * step);
+    for (int u = 0; u < U; ++u) cur[u] = load(first + u * step);
+  }
   for (int s = first; s < nseg; s += U * step) {
 #pragma unroll
     for (int u = 0; u < U; ++u) next[u] = load(s + (U + u) * step);     // past the end: zeros, not used
@@ -202,10 +212,10 @@ __device__ __forceinline__ void walk_row(const Row& r, int first, int step, int 
   }
 }
 template <int U, class F>
-__device__ __forceinline__ void walk_row(const Row& r, int first, int step, int nseg, int lane, F f) {
+__device__ __forceinline__ void walk_row(const Row& r, int first, int step, int nseg, int lane, f32x4 head, F f) {
   first = __builtin_amdgcn_readfirstlane(first);
-  if (r.vec) walk_row<U, true>(r, first, step, nseg, lane, f);
-  else walk_row<U, false>(r, first, step, nseg, lane, f);
+  if (r.vec) walk_row<U, true>(r, first, step, nseg, lane, head, f);
+  else walk_row<U, false>(r, first, step, nseg, lane, head, f);
 }
 __device__ __forceinline__ float max4(const float (&z)[4], float mx) {
   return fmaxf(fmaxf(mx, fmaxf(z[0], z[1])), fmaxf(z[2], z[3]));
@@ -304,6 +314,8 @@ __device__ __forceinline__ void choose_token(const Row& R, int row, int nseg, fl
   if (wave == 0) {
     float z[4];
     load_z4(R, sseg * SEG + lane * 4, z);
+    double log_nuc = log((double)S_nuc), log_total = log((double)S_total);
+    asm volatile("" : "+v"(log_nuc), "+v"(log_total));   // while the segment is on its way
     u64 c[4], kept[4];
     uint32_t tie_lane = 0;
 #pragma unroll
@@ -360,9 +372,9 @@ __device__ __forceinline__ void choose_token(const Row& R, int row, int nseg, fl
       for (int k = 0; k < 4; ++k)
         if (k == k_sel) { ct = c[k]; zt = z[k]; mem = member[k]; }
       tokens_out[row] = t;
-      logp_behav[row] = (mem && ct > 0) ? (float)(log((double)ct) - log((double)S_nuc)) : -INFINITY;
+      logp_behav[row] = (mem && ct > 0) ? (float)(log((double)ct) - log_nuc) : -INFINITY;
       if (logp_full)
-        logp_full[row] = (float)((double)(zt - m) - (log((double)S_total) - 32.0 * 0.69314718055994530942));
+        logp_full[row] = (float)((double)(zt - m) - (log_total - 32.0 * 0.69314718055994530942));
     }
   }
 }
@@ -506,7 +518,8 @@ __global__ __launch_bounds__(TPB) void sampler_kernel(
 
   // ---- pass A: m = max z ----------------------------------------------------
   float mx = -INFINITY;
-  walk_row<4>(R, wave, NWAVES, nseg, lane, [&](int, const float (&z)[4]) { mx = max4(z, mx); });
+  walk_row<4>(R, wave, NWAVES, nseg, lane, f32x4{}, [&](int, const float (&z)[4]) { mx = max4(z, mx); });
+  f32x4 head = first_segment(R, wave, lane);
   mx = wave_max(mx);
   if (lane == 0) wave_max_s[wave] = mx;
   __syncthreads();
@@ -515,7 +528,7 @@ __global__ __launch_bounds__(TPB) void sampler_kernel(
   for (int w = 1; w < NWAVES; ++w) m = fmaxf(m, wave_max_s[w]);
 
   // ---- pass B: per-segment mass, S = total mass --------------------------------
-  walk_row<1>(R, wave, NWAVES, nseg, lane, [&](int s, const float (&z)[4]) {
+  walk_row<1>(R, wave, NWAVES, nseg, lane, head, [&](int s, const float (&z)[4]) {
     const u64 c = segment_mass(z, m);
     if (lane == 0) L.segmass[s] = c;
   });
@@ -598,7 +611,7 @@ __global__ __launch_bounds__(SPLIT_TPB) void sampler_split_max_kernel(int V, con
     if (part == 0 && threadIdx.x == 0) sc.n_list = 0;
   }
   float mx = -INFINITY;
-  walk_row<4>(R, part * SPLIT_WAVES + wave, parts * SPLIT_WAVES, nseg, lane, [&](int, const float (&z)[4]) { mx = max4(z, mx); });
+  walk_row<4>(R, part * SPLIT_WAVES + wave, parts * SPLIT_WAVES, nseg, lane, f32x4{}, [&](int, const float (&z)[4]) { mx = max4(z, mx); });
   mx = wave_max(mx);
   if (lane == 0) wmax[wave] = mx;
   __syncthreads();
@@ -617,8 +630,9 @@ __global__ __launch_bounds__(SPLIT_TPB) void sampler_split_mass_kernel(int V, co
   const Row R = make_row(logits, row, V, inv_t);
   SplitScratch& sc = scratch[row];
   const int nseg = (V + SEG - 1) / SEG;
+  const f32x4 head = first_segment(R, part * SPLIT_WAVES + wave, lane);
   const float m = row_max_of_parts(sc, parts);
-  walk_row<1>(R, part * SPLIT_WAVES + wave, parts * SPLIT_WAVES, nseg, lane, [&](int sg, const float (&z)[4]) {
+  walk_row<1>(R, part * SPLIT_WAVES + wave, parts * SPLIT_WAVES, nseg, lane, head, [&](int sg, const float (&z)[4]) {
     const u64 c = segment_mass(z, m);
     if (lane == 0) sc.segmass[sg] = c;
   });
@@ -652,9 +666,12 @@ __global__ __launch_bounds__(TPB) void sampler_split_pick_kernel(
 // of logarithmic bins, which locates the bin the threshold falls into to 1.6 % of its value; (3) the
 // kept mass of the bins above, per segment, and the list of that one bin's ids; (4) per row, the exact
 // threshold by radix select over the list, ties in id order, the draw.  The exponential is evaluated
-// twice per id, on all compute units: 64 rows of 151,936 logits 566 -> 57 us, 1 row 530 -> 28, 128 rows
-// 576 -> 84 (bound by the exponential's arithmetic and four launches; 61 and 91 us with exchanges through LDS for the
-// wave sums, 64-bit shifts for the bins and 8 bits at a time in the list.  Loading four segments ahead: no change).  A bin of one value (every mass
+// twice per id, on all compute units: 64 rows of 151,936 logits 566 -> 49 us, 1 row 530 -> 24, 128 rows
+// 576 -> 69 (bound by the exponential's arithmetic and four launches).  On the way: 61 and 91 us (64, 128 rows) with exchanges
+// through LDS for the wave sums and 64-bit shifts for the bins; 56 and 82 with 55 instructions an id, 64-bit masses among
+// them; 50.3 and 71.0 with 37; 48.7 and 68.7 with a row's first segment and the list read ahead of what says which of
+// them count, rounds of a bin a thread in the list, and the logarithms while the chosen segment is on its way.  More segments
+// ahead: no change; ids above the bin packed before their exponentials: 48.2, but 49.7 for 48.9 where half of all are.  A bin of one value (every mass
 // below 128, and 2^32: the maximum itself) needs no list but its ids per segment; for a bin with more
 // ids than the list holds see nucleus_in_bin.
 __global__ __launch_bounds__(SPLIT_TPB) void sampler_split_hist_kernel(int V, const float* __restrict__ logits,
@@ -665,10 +682,11 @@ __global__ __launch_bounds__(SPLIT_TPB) void sampler_split_hist_kernel(int V, co
   const Row R = make_row(logits, row, V, inv_t);
   SplitScratch& sc = scratch[row];
   const int nseg = (V + SEG - 1) / SEG;
-  for (int b = threadIdx.x; b < LOG_BINS; b += SPLIT_TPB) hist[b] = 0;
+  const f32x4 head = first_segment(R, part * SPLIT_WAVES + wave, lane);
   const float m = row_max_of_parts(sc, parts);
+  for (int b = threadIdx.x; b < LOG_BINS; b += SPLIT_TPB) hist[b] = 0;
   __syncthreads();
-  walk_row<1>(R, part * SPLIT_WAVES + wave, parts * SPLIT_WAVES, nseg, lane, [&](int, const float (&z)[4]) {
+  walk_row<1>(R, part * SPLIT_WAVES + wave, parts * SPLIT_WAVES, nseg, lane, head, [&](int, const float (&z)[4]) {
     float w[4];
     uint32_t c[4];
 #pragma unroll
@@ -811,6 +829,8 @@ __global__ __launch_bounds__(SPLIT_TPB) void sampler_split_collect_kernel(int V,
   const Row R = make_row(logits, row, V, inv_t);
   SplitScratch& sc = scratch[row];
   const int nseg = (V + SEG - 1) / SEG;
+  const int first = part * SPLIT_WAVES + wave, step = parts * SPLIT_WAVES;
+  const f32x4 head = first_segment(R, first, lane);
   const float m = row_max_of_parts(sc, parts);
   if (threadIdx.x == 0) n_list = 0;
   u64 S_total, target, above;
@@ -823,9 +843,8 @@ __global__ __launch_bounds__(SPLIT_TPB) void sampler_split_collect_kernel(int V,
     const uint32_t at = atomicAdd(&n_list, 1u);
     if (at < LIST_CAP) { list[at][0] = id; list[at][1] = mass; }
   };
-  const int first = part * SPLIT_WAVES + wave, step = parts * SPLIT_WAVES;
   if (log_bin_width(tb) == 0) {
-    walk_row<1>(R, first, step, nseg, lane, [&](int sg, const float (&z)[4]) {
+    walk_row<1>(R, first, step, nseg, lane, head, [&](int sg, const float (&z)[4]) {
       u64 gt = 0;
       int ties = 0;
 #pragma unroll
@@ -843,7 +862,7 @@ __global__ __launch_bounds__(SPLIT_TPB) void sampler_split_collect_kernel(int V,
     // The bin's masses [lo, hi) in 32 bits, lo >= 128: no id beyond the vocabulary, whose mass is 0, is among them.  2^32 - 1
     // stands for 2^32 (masses4) and lies above every such bin.
     const uint32_t lo = (uint32_t)log_bin_low(tb), hi = (uint32_t)min((u64)0xFFFFFFFFu, log_bin_low(tb + 1)), width = hi - lo;
-    walk_row<1>(R, first, step, nseg, lane, [&](int sg, const float (&z)[4]) {
+    walk_row<1>(R, first, step, nseg, lane, head, [&](int sg, const float (&z)[4]) {
       u64 gt = 0;
       if (__any(!(max4(z, -INFINITY) - m < x_skip))) {
         float w[4];
@@ -895,7 +914,12 @@ __global__ __launch_bounds__(TPB) void sampler_split_nucleus_pick_kernel(
   const int nseg = (V + SEG - 1) / SEG;
   const float m = row_max_of_parts(sc, parts);
   const uint32_t n = sc.n_list;
-  uint32_t id[PER], d[PER];                            // this thread's ids of the threshold's bin, mass offsets
+  // this thread's ids of the threshold's bin and their masses (then mass offsets), and its segment's mass: read ahead of the bin
+  // that says whether they are in use, and of n (whatever lies behind the list is not used)
+  uint32_t id[PER], d[PER];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) { id[k] = sc.list[tid + k * TPB][0]; d[k] = sc.list[tid + k * TPB][1]; }
+  const u64 seg_above = sc.segmass[tid];
   u64 S_total, target, mass_above;
   const int tb = threshold_bin<NWAVES>(sc, top_p, L.wave_tot, &L.sh_u64[2], &L.sh_int[3], S_total, target, mass_above);
   u64 tau = 0, n_take = 0, S_nuc = 0;
@@ -907,24 +931,22 @@ __global__ __launch_bounds__(TPB) void sampler_split_nucleus_pick_kernel(
     tau = log_bin_low(tb);
     n_take = (target - mass_above + tau - 1) / tau;
     S_nuc = mass_above + n_take * tau;
-    if (tid < nseg) { L.segmass[tid] = sc.segmass[tid]; L.segtie[tid] = sc.segtie[tid]; }
+    if (tid < nseg) { L.segmass[tid] = seg_above; L.segtie[tid] = sc.segtie[tid]; }
     __syncthreads();
   } else if (n > LIST_CAP) {
     nucleus_in_bin(R, nseg, m, tb, target, mass_above, offset_hist, L, tau, n_take, S_nuc);
   } else {
     const u64 low = log_bin_low(tb);
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const uint32_t i = tid + k * TPB;
-      id[k] = i < n ? sc.list[i][0] : 0;
-      d[k] = i < n ? sc.list[i][1] - (uint32_t)low : 0;          // < 2^26: the width of the widest bin
-    }
-    if (tid < nseg) { L.segmass[tid] = sc.segmass[tid]; L.segtie[tid] = 0; }
-    // radix select on the offsets, 13 bits at a time from the bin's own width down: two rounds at the widest bin
+    for (int k = 0; k < PER; ++k) d[k] -= (uint32_t)low;         // < 2^26: the width of the widest bin
+    if (tid < nseg) { L.segmass[tid] = seg_above; L.segtie[tid] = 0; }
+    // radix select on the offsets, in rounds of up to 10 bits from the bin's own width down: a bin a thread, to clear and to
+    // scan (3 rounds at the widest bin; 13 bits a round take two, of eight bins a thread)
     uint32_t prefix = 0;
+    const int round = (log_bin_width(tb) + (log_bin_width(tb) + 9) / 10 - 1) / ((log_bin_width(tb) + 9) / 10);
     for (int top = log_bin_width(tb); top > 0;) {
-      const int shift = max(0, top - OFFSET_BITS), bits = top - shift;
-      for (int b = tid; b < OFFSET_BINS; b += TPB) offset_hist[b] = 0;
+      const int shift = max(0, top - round), bits = top - shift;
+      offset_hist[tid] = 0;
       __syncthreads();
 #pragma unroll
       for (int k = 0; k < PER; ++k)
@@ -932,7 +954,7 @@ __global__ __launch_bounds__(TPB) void sampler_split_nucleus_pick_kernel(
           atomicAdd(&offset_hist[(d[k] >> shift) & ((1u << bits) - 1u)], low + d[k]);
       __syncthreads();
       u64 above;
-      const int b = bin_from_top<NWAVES, OFFSET_BINS>(offset_hist, [&](u64) { return target - mass_above; }, L.wave_tot,
+      const int b = bin_from_top<NWAVES, TPB>(offset_hist, [&](u64) { return target - mass_above; }, L.wave_tot,
                                                       &L.sh_u64[2], &L.sh_int[3], above);
       mass_above += above;
       prefix = (prefix << bits) | (uint32_t)b;
