@@ -5,17 +5,21 @@
 // nothing.  Here a lane takes 16 bytes of a weight row straight into registers, one instruction of a wave 1 KiB in a
 // row, multiplies them with its part of the few input rows, which it holds in registers for the whole launch
 // (v_dot2_f32_f16: exact products, float32 sums), and the lanes' sums are folded once per weight row.  One work-group of
-// 4 waves per compute unit takes an equal run of weight rows, so that every unit streams the same number of bytes, and
-// each output has one owner: no atomics, nothing to clear beforehand.  The first weights are in flight before the RMSNorm
-// is computed, every work-group for itself, so that the norm has no launch of its own.
+// 4 waves per compute unit takes the same number of weight rows, and each output has one owner: no atomics, nothing to clear
+// beforehand.  The first weights are in flight before the RMSNorm is computed, every work-group for itself, so that the norm
+// has no launch of its own.
 //
 // Bytes in flight: a plain read of 108 (216) KB per compute unit, a launch after an empty one, takes 5.2 (9.7) us with 32 KB in
 // flight on each, 5.7 (10.1) with 112 KB.  Two batches of 1 or 2 weight rows per wave (24 - 48 KB): step of one row 1,070 us;
-// four batches 1,145 with 8 waves, 1,086 with 4; two work-groups per unit 1,071 - 1,121.
-// Against the tiles of gemm.hip and two RMSNorm launches per layer, 1.5B shape, steps of 1, 2, 3, 4 rows of 700 tokens 1,215 -> 1,060,
-// 1,234 -> 1,086, 1,255 -> 1,161, 1,261 -> 1,161 us; 7B shape, 2,000 tokens 3,006 -> 2,858, 3,071 -> 2,974, 3,086 -> 3,069, 3,151 ->
-// 3,137.  From 5 rows on the dot products' issue slots cost more than the launches (8 rows 1,288 -> 1,386), but where K
-// is at most 512: nothing streams there, and a launch is a launch.
+// four batches 1,145 with 8 waves, 1,086 with 4; two work-groups per unit 1,071 - 1,121.  The rows that all work-groups read
+// at a time follow one another in memory (round b of work-group w: chunk b G + w): with a run of its own for each
+// work-group, 256 places at once, one row 1,067 us, now 1,043, of the 7B shape 2,851 and 2,803.
+// Against the tiles of gemm.hip and two RMSNorm launches per layer, 1.5B shape, steps of 1, 2, 4 rows of 700 tokens 1,215 -> 1,043,
+// 1,234 -> 1,067, 1,261 -> 1,135 us; 7B shape, 2,000 tokens, 1 and 2 rows 3,006 -> 2,803, 3,071 -> 2,924, 4 rows about the same as
+// before (3,151 -> 3,137 with runs).  From 5 rows on the dot products' issue slots cost more than the launches (8
+// rows 1,288 -> 1,386), but where K is at most 512: nothing streams there, and a launch is a launch.
+#include <algorithm>
+
 #include "kernels.hpp"
 
 namespace areal {
@@ -84,9 +88,12 @@ __global__ __launch_bounds__(TPB) void rows_kernel(const void* __restrict__ x, c
 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int grp = wave / WPC, sub = wave % WPC;
-  const int n = shape & 255, per_wg = shape >> 8;
-  const int c0 = blockIdx.x * per_wg, cnt = min(per_wg, N - c0);
-  const int cols = MODE == GEMM_SWIGLU_F16 ? 2 * cnt : cnt;
+  const int n = shape & 255, rounds = (shape >> 8) & 255, G = shape >> 16;
+  // weight rows in the order of their outputs (SwiGLU: gate and up of a feature side by side); round b of this work-group
+  // takes RC of them from first(b) on
+  constexpr int PER_OUT = MODE == GEMM_SWIGLU_F16 ? 2 : 1, RC = GROUPS * CB, RO = RC / PER_OUT;
+  const int total = N * PER_OUT;
+  auto first = [&](int b) { return (b * G + (int)blockIdx.x) * RC; };
 
   // the input rows first: they are needed first, and loads return in order
   constexpr int NV = NORM ? KP / 256 : 1, RPW = (NR + WAVES - 1) / WAVES;      // rows r = wave, wave + 4, .. are a wave's
@@ -120,23 +127,20 @@ __global__ __launch_bounds__(TPB) void rows_kernel(const void* __restrict__ x, c
   auto load = [&](f16x8 (&w)[CB][NCH], int b) {
 #pragma unroll
     for (int u = 0; u < CB; ++u) {
-      const int q = (b * GROUPS + grp) * CB + u;
+      const int c = first(b) + grp * CB + u;
       const f16* p;
       int64_t row;
       if (MODE == GEMM_SWIGLU_F16) {
-        p = q & 1 ? p1 : p0;
-        row = c0 + (q >> 1);
+        p = c & 1 ? p1 : p0;
+        row = c >> 1;
+      } else if (MODE == GEMM_STORE_F32) {
+        p = c >= last ? p2 : (c >= mid ? p1 : p0);
+        row = c - (c >= last ? last : (c >= mid ? mid : 0));
       } else {
-        const int c = c0 + q;
-        if (MODE == GEMM_STORE_F32) {
-          p = c >= last ? p2 : (c >= mid ? p1 : p0);
-          row = c - (c >= last ? last : (c >= mid ? mid : 0));
-        } else {
-          p = p0;
-          row = c;
-        }
+        p = p0;
+        row = c;
       }
-      const auto wr = buffer_rsrc(p + row * K, q < cols ? (uint32_t)K * 2u : 0u);
+      const auto wr = buffer_rsrc(p + row * K, b < rounds && c < total ? (uint32_t)K * 2u : 0u);
 #pragma unroll
       for (int c = 0; c < NCH; ++c) w[u][c] = buf8(wr, lane_off + c * WPC * 1024);
     }
@@ -148,14 +152,16 @@ __global__ __launch_bounds__(TPB) void rows_kernel(const void* __restrict__ x, c
   void* const C = late.C;
   const int ldc = late.ldc;
   asm volatile("" : : "s"(C), "s"(ldc));                    // read here, not where the launch ends
+  // output i of this work-group's
+  auto output = [&](int i) { return ((i / RO) * G + (int)blockIdx.x) * RO + i % RO; };
   // the residual's old values: one owner per output, wave r has rows r, r + 4, ..
   float old[RPW];
   if constexpr (MODE == GEMM_ADD_F32) {
 #pragma unroll
     for (int k = 0; k < RPW; ++k) {
       const int r = wave + k * WAVES;
-      const auto cr = buffer_rsrc((const float*)C + (int64_t)r * ldc + c0, r < n ? (uint32_t)cnt * 4u : 0u);
-      old[k] = __builtin_bit_cast(float, buf1(cr, lane * 4));
+      const auto cr = buffer_rsrc((const float*)C + (int64_t)r * ldc, r < n ? (uint32_t)N * 4u : 0u);
+      old[k] = __builtin_bit_cast(float, buf1(cr, output(lane) * 4));
     }
   }
 
@@ -207,33 +213,32 @@ __global__ __launch_bounds__(TPB) void rows_kernel(const void* __restrict__ x, c
     const int q0 = (b * GROUPS + grp) * CB;
     if constexpr (NR == 1 && CB == 1) {
       const float s = wave_sum(acc[0][0]);
-      if (lane == 0 && q0 < cols) red[0][sub][q0] = s;
+      if (lane == 0) red[0][sub][q0] = s;
     } else if constexpr (CB == 1) {
 #pragma unroll
       for (int r = 0; r < NR; r += 2) {
         const float v[2] = {acc[r][0], acc[r + 1][0]};
         const float s = fold_values<2>(v);
-        if ((lane & 31) == 0 && q0 < cols) red[r + (lane >> 5)][sub][q0] = s;
+        if ((lane & 31) == 0) red[r + (lane >> 5)][sub][q0] = s;
       }
     } else if constexpr (NR == 1) {
       const float s = fold_values<2>(acc[0]);
       const int q = q0 + (lane >> 5);
-      if ((lane & 31) == 0 && q < cols) red[0][sub][q] = s;
+      if ((lane & 31) == 0) red[0][sub][q] = s;
     } else {
 #pragma unroll
       for (int r = 0; r < NR; r += 2) {
         const float v[4] = {acc[r][0], acc[r][1], acc[r + 1][0], acc[r + 1][1]};
         const float s = fold_values<4>(v);
         const int k = folded_value(lane), q = q0 + (k & 1);
-        if ((lane & 15) == 0 && q < cols) red[r + (k >> 1)][sub][q] = s;
+        if ((lane & 15) == 0) red[r + (k >> 1)][sub][q] = s;
       }
     }
   };
-  const int batches = (cols + CB - 1) / CB;
-  for (int b = 0; b * GROUPS + grp < batches; b += DEPTH) {
+  for (int b = 0; b < rounds; b += DEPTH) {
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) {
-      if (d > 0 && (b + d) * GROUPS + grp >= batches) break;
+      if (d > 0 && b + d >= rounds) break;
       compute(w[d], b + d);
       load(w[d], b + d + DEPTH);
     }
@@ -244,18 +249,20 @@ __global__ __launch_bounds__(TPB) void rows_kernel(const void* __restrict__ x, c
   for (int k = 0; k < RPW; ++k) {
     const int r = wave + k * WAVES;
     if (r >= n) break;
-    for (int i = lane; i < cnt; i += 64) {
+    for (int i = lane; i < rounds * RO; i += 64) {
+      const int o = output(i);
+      if (o >= N) continue;
       auto sum = [&](int q) {
         float s = red[r][0][q];
 #pragma unroll
         for (int p = 1; p < WPC; ++p) s += red[r][p][q];
         return s;
       };
-      const int64_t at = (int64_t)r * ldc + c0 + i;
+      const int64_t at = (int64_t)r * ldc + o;
       if constexpr (MODE == GEMM_SWIGLU_F16) {
         ((f16*)C)[at] = f2h_sat(silu_f(sum(2 * i)) * sum(2 * i + 1));
       } else if constexpr (MODE == GEMM_ADD_F32) {
-        ((float*)C)[at] = old[k] + sum(i);                  // at most 64 outputs a work-group
+        ((float*)C)[at] = old[k] + sum(i);                  // MAX_COLS: one round of this loop
       } else {
         ((float*)C)[at] = sum(i);
       }
@@ -275,6 +282,10 @@ int layout(int M, int K, bool norm) {
   return -1;
 }
 
+// Weight rows of a round of a work-group, and rounds of all.
+int chunk(int lay) { return WAVES / kLayouts[lay].wpc * (kLayouts[lay].nch > 3 ? 1 : 2); }
+int chunks_of(int N, GemmMode mode, int lay) { return (N * (mode == GEMM_SWIGLU_F16 ? 2 : 1) + chunk(lay) - 1) / chunk(lay); }
+
 template <int NR, int MODE, bool NORM, int LAY>
 void launch(int lay, int grid, hipStream_t s, const void* x, const f16* gain, const GemmW& W, uint32_t end8, int N, int K,
             uint32_t shape, Late late) {
@@ -290,13 +301,16 @@ void launch(int lay, int grid, hipStream_t s, const void* x, const f16* gain, co
 
 bool rows_product_serves(int M, int N, int K, GemmMode mode, bool norm) {
   if (M < 1 || N < 1 || K < 8 || K % 8 || layout(M, K, norm) < 0) return false;
-  return (N + UNITS - 1) / UNITS <= (mode == GEMM_SWIGLU_F16 ? MAX_PAIRS : MAX_COLS);
+  const int lay = layout(M, K, norm), most = mode == GEMM_SWIGLU_F16 ? 2 * MAX_PAIRS : MAX_COLS;
+  return N <= UNITS * most && (chunks_of(N, mode, lay) + UNITS - 1) / UNITS * chunk(lay) <= most;
 }
 
 hipError_t launch_rows_product(hipStream_t s, const void* x, const f16* gain, float eps, GemmW W, void* C, int M, int N, int K,
                                int ldc, GemmMode mode) {
   const bool norm = gain != nullptr;
   if (!rows_product_serves(M, N, K, mode, norm) || !x || !C || ldc < N || !W.ptr[0]) return hipErrorInvalidValue;
+  if (((uintptr_t)x | (uintptr_t)W.ptr[0] | (uintptr_t)W.ptr[1] | (uintptr_t)W.ptr[2]) & 15) return hipErrorInvalidValue;
+  if (mode == GEMM_ADD_F32 && W.end[0] != N) return hipErrorInvalidValue;
   // modes in use: the norm before stored and SwiGLU products, none before residual adds
   if (norm != (mode != GEMM_ADD_F32)) return hipErrorInvalidValue;
   uint32_t end8 = 0xFFFFFFFFu;                                                    // beyond any column
@@ -308,8 +322,8 @@ hipError_t launch_rows_product(hipStream_t s, const void* x, const f16* gain, fl
       return hipErrorInvalidValue;
     end8 = (uint32_t)(W.end[0] / 8) | (uint32_t)(W.end[1] / 8) << 16;
   }
-  const int per_wg = (N + UNITS - 1) / UNITS, grid = (N + per_wg - 1) / per_wg, lay = layout(M, K, norm);
-  const uint32_t shape = (uint32_t)M | (uint32_t)per_wg << 8;
+  const int lay = layout(M, K, norm), chunks = chunks_of(N, mode, lay), grid = std::min(UNITS, chunks);
+  const uint32_t shape = (uint32_t)M | (uint32_t)((chunks + grid - 1) / grid) << 8 | (uint32_t)grid << 16;
   const Late late{C, ldc, eps};
 #define AREAL_MODE(NR)                                                                                               \
   (mode == GEMM_STORE_F32    ? launch<NR, GEMM_STORE_F32, true, 0>(lay, grid, s, x, gain, W, end8, N, K, shape, late)    \
