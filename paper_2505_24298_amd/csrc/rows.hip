@@ -10,14 +10,12 @@
 // has no launch of its own.
 //
 // Bytes in flight: a plain read of 108 (216) KB per compute unit, a launch after an empty one, takes 5.2 (9.7) us with 32 KB in
-// flight on each, 5.7 (10.1) with 112 KB.  Two batches of 1 or 2 weight rows per wave (24 - 48 KB): step of one row 1,070 us;
-// four batches 1,145 with 8 waves, 1,086 with 4; two work-groups per unit 1,071 - 1,121.  The rows that all work-groups read
-// at a time follow one another in memory (round b of work-group w: chunk b G + w): with a run of its own for each
-// work-group, 256 places at once, one row 1,067 us, now 1,043, of the 7B shape 2,851 and 2,803.
-// Against the tiles of gemm.hip and two RMSNorm launches per layer, 1.5B shape, steps of 1, 2, 4 rows of 700 tokens 1,215 -> 1,043,
-// 1,234 -> 1,067, 1,261 -> 1,135 us; 7B shape, 2,000 tokens, 1 and 2 rows 3,006 -> 2,803, 3,071 -> 2,924, 4 rows about the same as
-// before (3,151 -> 3,137 with runs).  From 5 rows on the dot products' issue slots cost more than the launches (8
-// rows 1,288 -> 1,386), but where K is at most 512: nothing streams there, and a launch is a launch.
+// flight on each, 5.7 (10.1) with 112 KB.  Two batches of 1 or 2 weight rows per wave (24 - 48 KB): step of one row 965 us, three
+// batches 1,026, four 1,043.  The rows that all work-groups read at a time follow one another in memory (round b of work-group w:
+// chunk b G + w): with a run of its own for each work-group, 256 places at once, 2 % more (7B shape 2 %).
+// Against the tiles of gemm.hip and two RMSNorm launches per layer, steps of n rows, 1.5B shape, 700 tokens: 1 row 1,215 -> 965 us,
+// 2 rows 1,234 -> 1,003, 4 rows 1,261 -> 1,046, 8 rows 1,279 -> 1,204; 7B shape, 2,000 tokens: 3,006 -> 2,731, 3,071 -> 2,872, 3 rows
+// 3,043 -> 2,832, 4 rows 3,156 -> 2,988.  More rows do not fit a lane's registers at these K.
 #include <algorithm>
 
 #include "kernels.hpp"
@@ -71,6 +69,13 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// The loads before this stay before it (a fence that costs no instruction): the compiler moves loads down to their first use, behind
+// the weights' or into the loop, and then waits for all.
+__device__ __forceinline__ void issue_here() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 // NR input rows (n of them exist); WPC waves share a weight row, a lane holds NCH times 16 bytes of it.
 // NORM: x float32, normalised with `gain`; else halves.  The weights: one matrix, or (stored products) up to three row
 // segments, of end8 & 0xFFFF and end8 >> 16 times 8 rows up to the second and third, or (SwiGLU) gate p0 and up p1.
@@ -83,7 +88,7 @@ __global__ __launch_bounds__(TPB) void rows_kernel(const void* __restrict__ x, c
   constexpr int CB = NCH > 3 ? 1 : 2, DEPTH = 2;           // weight rows per batch of loads, batches in flight
   constexpr int KP = NCH * WPC * 512;                      // K and what is masked
   constexpr int COLS = MODE == GEMM_SWIGLU_F16 ? 2 * MAX_PAIRS : MAX_COLS;
-  __shared__ __attribute__((aligned(16))) f16 xs[NORM ? NR * KP : 8];
+  __shared__ __attribute__((aligned(16))) f16 xs[NORM && NR > 1 ? NR * KP : 8];
   __shared__ float red[NR][WPC][COLS];
 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -96,12 +101,22 @@ __global__ __launch_bounds__(TPB) void rows_kernel(const void* __restrict__ x, c
   auto first = [&](int b) { return (b * G + (int)blockIdx.x) * RC; };
 
   // the input rows first: they are needed first, and loads return in order
-  constexpr int NV = NORM ? KP / 256 : 1, RPW = (NR + WAVES - 1) / WAVES;      // rows r = wave, wave + 4, .. are a wave's
+  // A single row is normalised by every wave for itself, in the order in which it holds it: nothing goes through LDS and no wave
+  // waits for another (1,041 -> 1,015 us).  Of several rows, r = wave, wave + 4, .. are a wave's.
+  constexpr bool ALONE = NORM && NR == 1 && WPC == 1;
+  constexpr int NV = NORM ? KP / 256 : 1, RPW = (NR + WAVES - 1) / WAVES;
   f32x4 hv[RPW][NV];
   f16x4 gv[NV];
   f16x8 xr[NR][NCH];
   const int lane_off = (sub * 64 + lane) * 16;
-  if constexpr (NORM) {
+  f16x8 g8[ALONE ? NCH : 1];
+  if constexpr (ALONE) {
+    const auto hr = buffer_rsrc(x, (uint32_t)K * 4u), gr = buffer_rsrc(gain, (uint32_t)K * 2u);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) hv[0][i] = buf4f(hr, (i >> 1) * 2048 + lane * 32 + (i & 1) * 16);
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) g8[c] = buf8(gr, lane_off + c * 1024);
+  } else if constexpr (NORM) {
     const auto gr = buffer_rsrc(gain, wave < n ? (uint32_t)K * 2u : 0u);
 #pragma unroll
     for (int k = 0; k < RPW; ++k) {
@@ -120,7 +135,7 @@ __global__ __launch_bounds__(TPB) void rows_kernel(const void* __restrict__ x, c
       for (int c = 0; c < NCH; ++c) xr[r][c] = buf8(rr, lane_off + c * WPC * 1024);
     }
   }
-  __builtin_amdgcn_sched_barrier(0);
+  issue_here();
 
   // column q of this work-group's; past the end: an empty range, which reads nothing
   const int mid = (int)(end8 & 0xFFFFu) * 8, last = (int)(end8 >> 16) * 8;
@@ -148,7 +163,7 @@ __global__ __launch_bounds__(TPB) void rows_kernel(const void* __restrict__ x, c
   f16x8 w[DEPTH][CB][NCH];
 #pragma unroll
   for (int d = 0; d < DEPTH; ++d) load(w[d], d);
-  __builtin_amdgcn_sched_barrier(0);
+  issue_here();
   void* const C = late.C;
   const int ldc = late.ldc;
   asm volatile("" : : "s"(C), "s"(ldc));                    // read here, not where the launch ends
@@ -165,9 +180,18 @@ __global__ __launch_bounds__(TPB) void rows_kernel(const void* __restrict__ x, c
     }
   }
 
-  if constexpr (NORM) {
+  if constexpr (ALONE) {
+    float ss = 0.f;
 #pragma unroll
-    for (int i = 0; i < NV; ++i) asm volatile("" : "+v"(gv[i]));    // else their loads sink below the weights', and wait for all
+    for (int i = 0; i < NV; ++i)
+      ss += hv[0][i][0] * hv[0][i][0] + hv[0][i][1] * hv[0][i][1] + hv[0][i][2] * hv[0][i][2] + hv[0][i][3] * hv[0][i][3];
+    ss = wave_sum(ss);
+    const float rs = 1.0f / sqrtf(ss / (float)K + late.eps);
+#pragma unroll
+    for (int c = 0; c < NCH; ++c)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) xr[0][c][e] = f2h_sat(hv[0][2 * c + (e >> 2)][e & 3] * rs * h2f(g8[c][e]));
+  } else if constexpr (NORM) {
 #pragma unroll
     for (int k = 0; k < RPW; ++k) {
       const f32x4(&v)[NV] = hv[k];
@@ -235,13 +259,16 @@ __global__ __launch_bounds__(TPB) void rows_kernel(const void* __restrict__ x, c
       }
     }
   };
-  for (int b = 0; b < rounds; b += DEPTH) {
-#pragma unroll
-    for (int d = 0; d < DEPTH; ++d) {
-      if (d > 0 && b + d >= rounds) break;
-      compute(w[d], b + d);
-      load(w[d], b + d + DEPTH);
-    }
+  static_assert(DEPTH == 2, "two batches in turn");
+  // One way out after each half, so that the wait of a half always finds the other's loads behind its own.  (Left in the middle
+  // for the loop's head instead, the first half waited for all loads: 1,010 us.)
+  for (int b = 0;; b += 2) {
+    compute(w[0], b);
+    load(w[0], b + 2);
+    if (b + 1 >= rounds) break;
+    compute(w[1], b + 1);
+    load(w[1], b + 3);
+    if (b + 2 >= rounds) break;
   }
   lds_barrier();
 
@@ -274,7 +301,8 @@ __global__ __launch_bounds__(TPB) void rows_kernel(const void* __restrict__ x, c
 // of this file).  A wave has a weight row to itself as long as its chunks fit: with four waves to a row of K = 3,584 every one of
 // them folds every sum (7B shape, 1 row 2,913 us, with one 2,871; 4 rows 3,305 and 3,146).
 struct Layout { int K, nch, wpc, rows; };
-constexpr Layout kLayouts[] = {{512, 1, 1, 8}, {1536, 3, 1, 4}, {2048, 4, 1, 4}, {3584, 7, 1, 4}, {4096, 8, 1, 4}, {12288, 6, 4, 4}, {20480, 10, 4, 4}};
+constexpr Layout kLayouts[] = {{512, 1, 1, 8},  {1536, 3, 1, 8},  {2048, 4, 1, 8}, {3584, 7, 1, 4},
+                                {4096, 8, 1, 4}, {12288, 6, 4, 8}, {20480, 10, 4, 4}};
 constexpr int kNormLayouts = 5;
 int layout(int M, int K, bool norm) {
   for (int l = 0; l < (norm ? kNormLayouts : 7); ++l)
@@ -332,6 +360,7 @@ hipError_t launch_rows_product(hipStream_t s, const void* x, const f16* gain, fl
   if (M == 1) AREAL_MODE(1);
   else if (M == 2) AREAL_MODE(2);
   else if (M <= 4) AREAL_MODE(4);
+  else if (M <= 6) AREAL_MODE(6);
   else AREAL_MODE(8);
 #undef AREAL_MODE
   return hipGetLastError();

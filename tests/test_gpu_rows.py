@@ -14,9 +14,9 @@ def _normed(x, gain, eps):
 
 
 # K: below, at and above each layout's end (512, 1536, 2048, 4096, 12288, 20480), with masked lanes and without
-@pytest.mark.parametrize("M,N,K", [(1, 344, 128), (8, 300, 8), (5, 257, 512), (1, 2048, 1536), (4, 1536, 1536), (3, 515, 520),
-                                   (4, 1000, 1544), (2, 264, 2048), (4, 700, 3584), (3, 4608, 4096), (2, 5, 3592),
-                                   (1, 1536, 8960), (4, 1536, 8960), (3, 72, 12288), (4, 3584, 18944), (3, 40, 20480)])
+@pytest.mark.parametrize("M,N,K", [(1, 344, 128), (8, 300, 8), (5, 257, 512), (1, 2048, 1536), (8, 1536, 1536), (3, 515, 520), (6, 344, 1536),
+                                   (7, 1000, 1544), (2, 264, 2048), (4, 700, 3584), (3, 4608, 4096), (2, 5, 3592),
+                                   (1, 1536, 8960), (8, 1536, 8960), (5, 72, 12288), (4, 3584, 18944), (3, 40, 20480)])
 @pytest.mark.parametrize("mode", [0, 1, 2])
 def test_rows_product(M, N, K, mode):
     import torch
@@ -55,7 +55,7 @@ def test_rows_product(M, N, K, mode):
         assert ((C.double() - want).abs() <= room).all()
 
 
-@pytest.mark.parametrize("M,parts,K", [(m, (1536, 256, 256), 1536) for m in (1, 2, 3, 4)] +
+@pytest.mark.parametrize("M,parts,K", [(m, (1536, 256, 256), 1536) for m in (1, 2, 3, 4, 8)] +
                          [(m, (8, 16, 5), 264) for m in (1, 5, 6, 7, 8)] + [(8, (128, 64, 64), 128), (2, (3584, 512, 512), 3584)])
 def test_rows_product_of_three_segments(M, parts, K):
     """The segments' rows as one matrix: the same bits.  Untouched neighbours of C stay."""
@@ -89,7 +89,7 @@ def test_rows_product_takes_subnormal_halves_and_saturates():
     assert (C == 65504.0).all()
 
 
-@pytest.mark.parametrize("M,N,K", [(9, 64, 128), (0, 64, 128), (1, 64, 100), (1, 64, 20488), (5, 64, 520), (1, 16385, 128)])
+@pytest.mark.parametrize("M,N,K", [(9, 64, 128), (0, 64, 128), (1, 64, 100), (1, 64, 20488), (5, 64, 3584), (5, 64, 12296), (1, 16385, 128)])
 def test_rows_product_refuses(M, N, K):
     from paper_2505_24298_amd import binding
     L = binding.lib()
