@@ -15,7 +15,8 @@
 // chunk b G + w): with a run of its own for each work-group, 256 places at once, 2 % more (7B shape 2 %).
 // Against the tiles of gemm.hip and two RMSNorm launches per layer, steps of n rows, 1.5B shape, 700 tokens: 1 row 1,215 -> 965 us,
 // 2 rows 1,234 -> 1,003, 4 rows 1,261 -> 1,046, 8 rows 1,279 -> 1,204; 7B shape, 2,000 tokens: 3,006 -> 2,731, 3,071 -> 2,872, 3 rows
-// 3,043 -> 2,832, 4 rows 3,156 -> 2,988.  More rows do not fit a lane's registers at these K.
+// 3,043 -> 2,832, 4 rows 3,156 -> 2,988.  More rows do not fit a lane's registers at these K.  The output projection and its norm, which
+// the tiles stream at 5.9 TB/s, gain 3 - 13 us (2, 4, 8 rows: 998 -> 992, 1,046 -> 1,038, 1,208 -> 1,194 us a step).
 #include <algorithm>
 
 #include "kernels.hpp"
@@ -26,7 +27,9 @@ namespace {
 
 constexpr int WAVES = 4, TPB = WAVES * 64;
 constexpr int UNITS = 256;                       // compute units: work-groups of a launch
-constexpr int MAX_PAIRS = 80, MAX_COLS = 64;     // features (of two weight rows) and plain outputs per work-group at most
+// Weight rows of a work-group at most (sums in LDS; an added output's old value is a lane's).
+template <int MODE>
+constexpr int max_cols() { return MODE == GEMM_SWIGLU_F16 ? 160 : MODE == GEMM_ADD_F32 ? 64 : 640; }
 
 struct Late {
   void* C;
@@ -87,7 +90,7 @@ __global__ __launch_bounds__(TPB) void rows_kernel(const void* __restrict__ x, c
   constexpr int GROUPS = WAVES / WPC;
   constexpr int CB = NCH > 3 ? 1 : 2, DEPTH = 2;           // weight rows per batch of loads, batches in flight
   constexpr int KP = NCH * WPC * 512;                      // K and what is masked
-  constexpr int COLS = MODE == GEMM_SWIGLU_F16 ? 2 * MAX_PAIRS : MAX_COLS;
+  constexpr int COLS = max_cols<MODE>();
   __shared__ __attribute__((aligned(16))) f16 xs[NORM && NR > 1 ? NR * KP : 8];
   __shared__ float red[NR][WPC][COLS];
 
@@ -289,7 +292,7 @@ __global__ __launch_bounds__(TPB) void rows_kernel(const void* __restrict__ x, c
       if constexpr (MODE == GEMM_SWIGLU_F16) {
         ((f16*)C)[at] = f2h_sat(silu_f(sum(2 * i)) * sum(2 * i + 1));
       } else if constexpr (MODE == GEMM_ADD_F32) {
-        ((float*)C)[at] = old[k] + sum(i);                  // MAX_COLS: one round of this loop
+        ((float*)C)[at] = old[k] + sum(i);                  // one round of this loop
       } else {
         ((float*)C)[at] = sum(i);
       }
@@ -329,7 +332,8 @@ void launch(int lay, int grid, hipStream_t s, const void* x, const f16* gain, co
 
 bool rows_product_serves(int M, int N, int K, GemmMode mode, bool norm) {
   if (M < 1 || N < 1 || K < 8 || K % 8 || layout(M, K, norm) < 0) return false;
-  const int lay = layout(M, K, norm), most = mode == GEMM_SWIGLU_F16 ? 2 * MAX_PAIRS : MAX_COLS;
+  const int lay = layout(M, K, norm), most = mode == GEMM_SWIGLU_F16 ? max_cols<GEMM_SWIGLU_F16>()
+                                               : mode == GEMM_ADD_F32 ? max_cols<GEMM_ADD_F32>() : max_cols<GEMM_STORE_F32>();
   return N <= UNITS * most && (chunks_of(N, mode, lay) + UNITS - 1) / UNITS * chunk(lay) <= most;
 }
 

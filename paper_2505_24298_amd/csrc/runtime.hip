@@ -457,7 +457,11 @@ int run_pass(areal_ctx* c, const PassArgs& a) {
       }
     }
   }
-  if (a.n_out > 0) {
+  if (a.n_out > 0 && !a.last_rows && rows_product_serves(a.n_out, g.vocab, H, GEMM_STORE_F32, true)) {
+    ProfScope ps(c, AREAL_K_GEMM_LMHEAD, -1, sampled, (double)a.n_out);
+    GemmW wl{{w.lm_head, nullptr, nullptr}, {g.vocab, 0, 0}};
+    HIP_TRY(c, launch_rows_product(s, h, w.final_norm, g.rms_eps, wl, a.logits, a.n_out, g.vocab, H, g.vocab, GEMM_STORE_F32));
+  } else if (a.n_out > 0) {
     HIP_TRY(c, launch_rmsnorm(s, h, w.final_norm, xlast, a.n_out, H, g.rms_eps, a.last_rows));
     ProfScope ps(c, AREAL_K_GEMM_LMHEAD, -1, sampled, (double)a.n_out);
     GemmW wl{{w.lm_head, nullptr, nullptr}, {g.vocab, 0, 0}};

@@ -95,3 +95,18 @@ def test_rows_product_refuses(M, N, K):
     L = binding.lib()
     assert L.areal_op_rows_serves(M, N, K, 1) == 0
     assert L.areal_op_rows_product(None, 16, None, 0.0, 16, None, None, N, N, 16, M, N, K, 1) != 0
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 151936, 64), (4, 32003, 1536), (8, 163840, 8)])
+def test_rows_product_of_many_outputs(M, N, K):
+    """The output projection: as many rounds as the sums in LDS hold; one more is refused."""
+    import torch
+    from paper_2505_24298_amd import binding
+    g = torch.Generator(device="cuda").manual_seed(N)
+    W = (torch.randn((N, K), generator=g, device="cuda") * 0.05).half()
+    x, gain = torch.randn((M, K), generator=g, device="cuda"), torch.ones(K, device="cuda").half()
+    C = torch.empty((M, N), device="cuda")
+    binding.op_rows_product(x, gain, 1e-6, [W], C, 0)
+    ref = _normed(x, gain, 1e-6) @ W.double().T
+    assert (C.double() - ref).abs().max().item() <= 4 * 2.0 ** -11 * ref.abs().max().item()
+    assert binding.lib().areal_op_rows_serves(M, 163841, K, 0) == 0
