@@ -328,7 +328,7 @@ int areal_adopt_seq_shared(areal_ctx* ctx, int32_t seq_id, int32_t len, int32_t 
  * and their summed work units: context tokens read (attention decode),
  * query-key pairs (attention prefill), rows (everything else). */
 #define AREAL_K_EMBED 0
-#define AREAL_K_RMSNORM 1
+#define AREAL_K_RMSNORM 1        /* passes of up to 8 rows have it inside their products: no launch */
 #define AREAL_K_GEMM_QKV 2
 #define AREAL_K_ROPE_KVWRITE 3
 #define AREAL_K_ATTN_DECODE 4
