@@ -54,6 +54,13 @@ int32_t areal_plan_passes(int32_t n_spans, const int32_t* lens, int32_t max_rows
 int32_t areal_plan_decode(int32_t n, const int32_t* own, const int32_t* home, int32_t n_kv_heads, int32_t max_slots,
                           int32_t target, int32_t min_tokens, int32_t* out, int32_t cap);
 
+/* Where a load of the tiled products points: a group of 8 rows (128 bytes of each) of an operand of which `rows` rows of
+ * row_bytes (a multiple of 128) exist from the tile's first row on.  kind 0: the group that begins at row `row`; 1: one whose
+ * second half lies four rows further (gate/up tiles of whole 64-row groups); 2: one whose rows the lanes hold.  Writes 66
+ * values to out (host): byte offset of the buffer resource from the tile's first row, the resource's size, and the
+ * offsets of the 64 lanes; the K slab's offset in a row is the load's scalar offset.  0, or AREAL_E_INVAL. */
+int areal_plan_tile_load(int32_t row, int32_t kind, int32_t rows, int32_t row_bytes, uint32_t* out);
+
 /* Section 5.1 (staleness-aware training): the rollout controller submits the
  * N-th generation request only if floor((N-1)/B) <= i + eta, with B the
  * training batch size, i the current policy version and eta the maximum

@@ -110,12 +110,13 @@ _SIGNATURES = {
     "areal_kvalloc_table": (C.c_int32, [C.c_void_p, C.c_int32, _I32P, C.c_int32]),
     "areal_kvalloc_shuffle": (None, [C.c_void_p, C.c_uint64]),
     "areal_plan_passes": (C.c_int32, [C.c_int32, _I32P, C.c_int32, _I32P, C.c_int32]),
+    "areal_plan_tile_load": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_uint32)]),
     "areal_plan_decode": (C.c_int32, [C.c_int32, _I32P, _I32P, C.c_int32, C.c_int32, C.c_int32, C.c_int32, _I32P,
                                       C.c_int32]),
 }
 
 _HOST_NAMES = [n for n in _SIGNATURES if n.startswith(("areal_kvalloc_", "areal_gate_"))] + [
-    "areal_plan_passes", "areal_plan_decode", "areal_dynamic_batching"]
+    "areal_plan_passes", "areal_plan_decode", "areal_plan_tile_load", "areal_dynamic_batching"]
 
 _lib = None
 _host_lib = None

@@ -10,6 +10,7 @@
 #include <cmath>
 
 #include "kernels.hpp"
+#include "row_groups.hpp"
 #include <cstdlib>
 #include <type_traits>
 
@@ -43,40 +44,50 @@ __device__ __forceinline__ const f16* w_row_ptr(const GemmW& W, int tile_n, int 
 // What comes before the first load counts in a decode step, whose products of a few microseconds cannot start before
 // the kernel ahead of them ends: with the arguments read from memory (a struct, and one of its pointers again
 // for every row group) and divisions in the tile map, a wave of the 32 x 80 gate/up tile ran some 300 instructions and
-// ten dependent reads before its first load; with scalars, the map below and one resource per operand about 110 and
-// none.  Decode step of one row 1,370 -> 1,251 us, of 24 rows 2,183 -> 2,066, of 88 3,107 -> 3,011, one prompt of 301 tokens
-// 2,591 -> 2,525 (a part of it from the other kernels' arguments).
+// ten dependent reads before its first load; with scalars and the map below about 110 and none (the resources of a wave's
+// later row groups, some ten instructions each, are made while its first loads travel).  Decode step of one row 1,370 ->
+// 1,251 us, of 24 rows 2,183 -> 2,066, of 88 3,107 -> 3,011, one prompt of 301 tokens 2,591 -> 2,525 (a part of it from the
+// other kernels' arguments).
 struct WRows {
   const f16 *p0, *p1, *p2;
   int end0, end1;
 };
 
-// Buffer resources of the row groups of a tile.  Rows outside the matrix lie outside the resource: they read as zero,
-// without touching memory, and feed only accumulator rows / columns that are never stored.
+// Buffer resources of the row groups of a tile (row_groups.hpp).  Rows outside the matrix read as zero or as its last row and
+// feed only accumulator rows / columns that are never stored.
 template <int BM, int BN, int MODE>
 struct TileRsrc {
   static constexpr int NC = MODE == GEMM_SWIGLU_F16 ? BN / 2 : BN;
-  __amdgpu_buffer_rsrc_t a, w0, w1;
+  const char *pa, *pw0, *pw1;       // first rows of the tile
+  uint32_t row_bytes, a_bytes, w_bytes;   // of a row, and of those of the matrix from there on, as far as the tile reaches
   uint64_t seg0, to1, to2;          // stored products: address of the first segment, and what leads on to the others
-  int end0, end1, n0, N, K;
-  __device__ __forceinline__ TileRsrc(const f16* A, WRows W, int M, int n, int k, int tile_m, int tile_n)
-      : seg0((uint64_t)W.p0), to1((uint64_t)W.p1 ^ (uint64_t)W.p0), to2((uint64_t)W.p2 ^ (uint64_t)W.p1), end0(W.end0),
-        end1(W.end1), n0(tile_n * NC), N(n), K(k) {
-    a = buffer_rsrc(A + (int64_t)(tile_m * BM) * K, (uint32_t)min(M - tile_m * BM, BM) * (uint32_t)K * 2u);
-    const uint32_t bytes = (uint32_t)min(N - n0, NC) * (uint32_t)K * 2u;
-    if (MODE != GEMM_STORE_F32) w0 = buffer_rsrc(W.p0 + (int64_t)n0 * K, bytes);
-    if (MODE == GEMM_SWIGLU_F16) w1 = buffer_rsrc(W.p1 + (int64_t)n0 * K, bytes);
+  int end0, end1, n0, N;
+  __device__ __forceinline__ TileRsrc(const f16* A, WRows W, int M, int n, int K, int tile_m, int tile_n)
+      : row_bytes((uint32_t)K * 2u), seg0((uint64_t)W.p0), to1((uint64_t)W.p1 ^ (uint64_t)W.p0),
+        to2((uint64_t)W.p2 ^ (uint64_t)W.p1), end0(W.end0), end1(W.end1), n0(tile_n * NC), N(n) {
+    pa = reinterpret_cast<const char*>(A + (int64_t)(tile_m * BM) * K);
+    a_bytes = (uint32_t)min(M - tile_m * BM, BM) * row_bytes;
+    w_bytes = (uint32_t)min(N - n0, NC) * row_bytes;
+    if (MODE != GEMM_STORE_F32) pw0 = reinterpret_cast<const char*>(W.p0 + (int64_t)n0 * K);
+    if (MODE == GEMM_SWIGLU_F16) pw1 = reinterpret_cast<const char*>(W.p1 + (int64_t)n0 * K);
   }
-  // Rows b0 .. b0 + 7 of the W tile (stored products: of up to three segments, each of whole groups but the last; a
-  // group below the matrix takes its last one), or, of gate and up, the rows of the same features.
-  __device__ __forceinline__ __amdgpu_buffer_rsrc_t w(int b0, bool is_up) const {
-    if (MODE == GEMM_SWIGLU_F16) return is_up ? w1 : w0;
-    if (MODE != GEMM_STORE_F32) return w0;
-    const int n = min(n0 + b0, (N - 1) & ~7);
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const char* p, int row, uint32_t bytes) const {
+    const RowRange g = row_range(row, row_bytes, bytes);
+    return buffer_rsrc(p + g.first, g.bytes);
+  }
+  // The group that begins at row r of the A tile; all of its rows.
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t a(int r) const { return rsrc(pa, r, a_bytes); }
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t a() const { return buffer_rsrc(pa, a_bytes); }
+  // The group that begins at row r of the W tile, or at its feature r of gate or up.  Stored products: of up to three segments,
+  // each of whole groups but the last; a group below the matrix takes its last one.
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t w(int r, bool is_up) const {
+    if (MODE == GEMM_SWIGLU_F16) return rsrc(is_up ? pw1 : pw0, r, w_bytes);
+    if (MODE != GEMM_STORE_F32) return rsrc(pw0, r, w_bytes);
+    const int n = min(n0 + r, (N - 1) & ~7);
     const bool in1 = n >= end0, in2 = in1 && n >= end1;              // (one segment: end0 = N, end1 unset)
     const uint64_t p = seg0 ^ (in1 ? to1 : 0) ^ (in2 ? to2 : 0);
     const int start = in2 ? end1 : (in1 ? end0 : 0);
-    return buffer_rsrc(reinterpret_cast<const f16*>(p) + (int64_t)(n - start) * K, (uint32_t)min(8, N - n) * (uint32_t)K * 2u);
+    return buffer_rsrc(reinterpret_cast<const char*>(p) + (int64_t)(n - start) * row_bytes, (uint32_t)min(8, N - n) * row_bytes);
   }
 };
 
@@ -455,33 +466,26 @@ __device__ __forceinline__ void dma_tile(const f16* __restrict__ A, const WRows&
   // are FLAT instructions to the compiler's wait insertion, which then waits for every LDS read in
   // flight wherever it has to wait for one.
   const TileRsrc<BM, BN, MODE> tile(A, W, M, N, K, tile_m, tile_n);
-  // A load's byte offset is a lane's (the same for all loads of A, and where they follow one another, of W) and a scalar one.
-  __amdgpu_buffer_rsrc_t b_rsrc[GB / NW];
-  int src[LPS], soff[LPS], dst_off[LPS];
-  {
-    const int rin = lane >> 3;                          // row inside the group
-    const int chunk = (lane & 7) ^ rin;
+  // Where a wave has more than six groups, those of A share a resource and a lane holds its rows: with four scalar registers
+  // for each they do not fit.
+  constexpr bool LANE_ROWS = LPS > 6;
+  __amdgpu_buffer_rsrc_t rsrc[LPS];
+  int src[LPS], dst_off[LPS];
 #pragma unroll
-    for (int i = 0; i < LPS; ++i) {
-      const bool is_a = i < GA / NW;
-      const int first = wave * ((is_a ? GA : GB) / NW), k = is_a ? i : i - GA / NW;
-      int row = first * 8 + rin, ahead = k * 8;
-      if (!is_a) {
-        const int gi = first + k;
-        b_rsrc[k] = tile.w(gi * 8, (gi >> 2) & 1);
-        if (MODE == GEMM_SWIGLU_F16) { row = (gi >> 3) * 32 + (gi & 3) * 8 + rin; ahead = 0; }    // feature of the tile
-        if (MODE == GEMM_STORE_F32) { row = rin; ahead = 0; }
-      }
-      src[i] = (row * K + chunk * 8) * 2;
-      soff[i] = ahead * K * 2;
-      dst_off[i] = ((is_a ? 0 : GA) + first + k) * GROUP_BYTES;
-    }
+  for (int i = 0; i < LPS; ++i) {
+    const bool is_a = i < GA / NW;
+    const int gi = is_a ? wave * (GA / NW) + i : wave * (GB / NW) + (i - GA / NW);
+    src[i] = is_a && LANE_ROWS ? tile_lane_offset(lane, gi * 8, min(M - tile_m * BM, BM), K * 2) : group_lane_offset(lane, false, K * 2);
+    if (is_a) rsrc[i] = LANE_ROWS ? tile.a() : tile.a(gi * 8);
+    else if (MODE == GEMM_SWIGLU_F16) rsrc[i] = tile.w((gi >> 3) * 32 + (gi & 3) * 8, (gi >> 2) & 1);
+    else rsrc[i] = tile.w(gi * 8, false);
+    dst_off[i] = ((is_a ? 0 : GA) + gi) * GROUP_BYTES;
+    dma16(rsrc[i], src[i], kt0 * BK * 2, lds + dst_off[i]);     // the first slab: the later groups' addresses behind its loads
+    __builtin_amdgcn_sched_barrier(0);
   }
   auto issue = [&](int stage, int k0) {
 #pragma unroll
-    for (int i = 0; i < LPS; ++i)
-      dma16(i < GA / NW ? tile.a : b_rsrc[i < GA / NW ? 0 : i - GA / NW], src[i], k0 * 2 + soff[i],
-            lds + stage * STAGE_BYTES + dst_off[i]);
+    for (int i = 0; i < LPS; ++i) dma16(rsrc[i], src[i], k0 * 2, lds + stage * STAGE_BYTES + dst_off[i]);
   };
 
   f32x16 acc[TM][TN];
@@ -533,7 +537,7 @@ __device__ __forceinline__ void dma_tile(const f16* __restrict__ A, const WRows&
   const int k_last = (kt1 - 1) * BK;
   // prologue: STAGES slabs in flight (past the end: re-read the last slab, never consumed)
 #pragma unroll
-  for (int s = 0; s < STAGES; ++s) issue(s, min((kt0 + s) * BK, k_last));
+  for (int s = 1; s < STAGES; ++s) issue(s, min((kt0 + s) * BK, k_last));
   wait_vmcnt((STAGES - 1) * LPS);
   __builtin_amdgcn_s_barrier();
   read_frags(f0, lds, 0);
@@ -831,37 +835,27 @@ __device__ __forceinline__ void wide_tile(const f16* __restrict__ A, const WRows
 
   // Groups of 8 rows are dealt to the waves in turn, A's first.
   const TileRsrc<BM, BN, MODE> tile(A, W, M, N, K, tile_m, tile_n);
-  // A load's byte offset is a lane's (one for all loads of A, and one for those of W where their rows follow one another) and
-  // a scalar one.
+  // Gate/up tiles of whole 64-row groups: the rows of a group are two runs of four features (wide_feature).
+  constexpr bool SPREAD = MODE == GEMM_SWIGLU_F16 && TN % 4 == 0;
   __amdgpu_buffer_rsrc_t rsrc[LPS];
-  int src[LPS], soff[LPS], dst_off[LPS];
-  {
-    const int rin = lane >> 3, chunk = (lane & 7) ^ rin;
-#pragma unroll
-    for (int i = 0; i < LPS; ++i) {
-      const int gi = i * NW + wave, b0 = (gi - GA) * 8;
-      // all of the waves' i-th groups are A's, all W's, or (at one i, where they do not divide) this wave's decides
-      const bool all_a = i * NW + NW <= GA, is_a = all_a || (i * NW < GA && gi < GA);
-      int row = wave * 8 + rin, ahead = i * NW * 8;
-      rsrc[i] = tile.a;
-      if (!is_a) {
-        rsrc[i] = tile.w(b0, MODE == GEMM_SWIGLU_F16 && wide_is_up<TN>(b0));
-        if (MODE == GEMM_STORE_F32) { row = rin; ahead = 0; }
-        else if (MODE != GEMM_SWIGLU_F16) ahead -= GA * 8;
-        else if (TN % 4 != 0 && NW % 2 == 0) { row = (wave >> 1) * 8 + rin; ahead = (i * NW - GA) * 4; }
-        else if (TN % 4 == 0 && NW % 4 == 0 && GA % 8 == 0) { row = wide_feature<TN>((wave & 3) * 8 + rin); ahead = ((i * NW - GA) >> 3) * 32; }
-        else { row = wide_feature<TN>(b0 + rin); ahead = 0; }
-        if (!all_a && i * NW < GA) { row += ahead; ahead = 0; }
-      }
-      dst_off[i] = gi * WIDE_GROUP;
-      src[i] = (row * K + chunk * 8) * 2;
-      soff[i] = ahead * K * 2;
-    }
-  }
+  int src[LPS], dst_off[LPS];
   auto issue1 = [&](int stage, int k0, int i) {
     if (SHORT == 0 || i < LPS - 1 || wave < SHORT)      // wave-uniform
-      dma16(rsrc[i], src[i], k0 * 2 + soff[i], lds + stage * STAGE_BYTES + dst_off[i]);
+      dma16(rsrc[i], src[i], k0 * 2, lds + stage * STAGE_BYTES + dst_off[i]);
   };
+#pragma unroll
+  for (int i = 0; i < LPS; ++i) {
+    const int gi = i * NW + wave, b0 = (gi - GA) * 8;
+    // all of the waves' i-th groups are A's, all W's, or (at one i, where they do not divide) this wave's decides
+    const bool is_a = i * NW + NW <= GA || (i * NW < GA && gi < GA);
+    if (is_a) rsrc[i] = tile.a(gi * 8);
+    else if (MODE == GEMM_SWIGLU_F16) rsrc[i] = tile.w(wide_feature<TN>(b0), wide_is_up<TN>(b0));
+    else rsrc[i] = tile.w(b0, false);
+    src[i] = group_lane_offset(lane, SPREAD && !is_a, K * 2);
+    dst_off[i] = gi * WIDE_GROUP;
+    issue1(0, kt0 * BK, i);          // the first slab: the later groups' addresses behind its loads
+    __builtin_amdgcn_sched_barrier(0);
+  }
   // waits until at most `slabs` slabs of this wave's loads are in flight
   auto wait_slabs = [&](auto slabs) {
     constexpr int S = decltype(slabs)::value;
@@ -902,7 +896,7 @@ __device__ __forceinline__ void wide_tile(const f16* __restrict__ A, const WRows
   const int k_last = (kt1 - 1) * BK;
   // prologue: STAGES slabs in flight (past the end: re-read the last slab, never consumed)
 #pragma unroll
-  for (int s = 0; s < STAGES; ++s)
+  for (int s = 1; s < STAGES; ++s)
 #pragma unroll
     for (int i = 0; i < LPS; ++i) issue1(s, min((kt0 + s) * BK, k_last), i);
   wait_slabs(std::integral_constant<int, STAGES - 1>{});

@@ -12,6 +12,7 @@
 #include "decode_plan.hpp"
 #include "gate.hpp"
 #include "kv_alloc.hpp"
+#include "row_groups.hpp"
 
 using namespace areal;
 
@@ -56,6 +57,19 @@ int32_t areal_plan_decode(int32_t n, const int32_t* own, const int32_t* home, in
   } catch (const std::bad_alloc&) {
     return AREAL_E_NOMEM;
   }
+}
+
+int areal_plan_tile_load(int32_t row, int32_t kind, int32_t rows, int32_t row_bytes, uint32_t* out) {
+  if (row < 0 || row > 4096 || kind < 0 || kind > 2 || rows < 1 || rows > 4096 || row_bytes < 128 || row_bytes % 128 ||
+      row_bytes >= 1 << 18 || !out)
+    return AREAL_E_INVAL;
+  const uint32_t bytes = (uint32_t)rows * (uint32_t)row_bytes;
+  const RowRange g = kind == 2 ? RowRange{0, bytes} : row_range(row, row_bytes, bytes);
+  out[0] = g.first;
+  out[1] = g.bytes;
+  for (int lane = 0; lane < 64; ++lane)
+    out[2 + lane] = (uint32_t)(kind == 2 ? tile_lane_offset(lane, row, rows, row_bytes) : group_lane_offset(lane, kind == 1, row_bytes));
+  return AREAL_OK;
 }
 
 struct areal_gate { StalenessGate g; };

@@ -565,3 +565,53 @@ def test_refused_products_stay_refused(L):
     assert all(refused(3, 24, K, mode, n_cfg) for K in (128, 1 << 22) for mode in (0, 1))
     assert all(refused(3, 24, K, 0, 24) for K in (128, 1 << 22))
     assert all(refused(3, 24, (1 << 22) + 8, mode, 12) for mode in (0, 1, 2))
+
+
+# ------------------------------------------------------------- addresses of the tiled products' loads
+RANGE_CHECKS = {
+    "lane offset alone": lambda lane, scalar, size: lane < size,
+    "lane and scalar offset": lambda lane, scalar, size: lane + scalar < size,
+    "lane offset against the rest, which wraps": lambda lane, scalar, size: lane < (size - scalar) % 2 ** 32,
+}
+
+
+def _load_faults(check, row, spread, rows, row_bytes, base, size, lane_off, row_scalar=0):
+    """Lanes of one load (first and last K slab) that touch what does not exist or miss what does, if the range of a buffer
+    load is checked as `check` says."""
+    lane = np.arange(64, dtype=np.int64)
+    r = lane >> 3
+    r = row + (8 * (r >> 2) + (r & 3) if spread else r)
+    chunk = ((lane & 7) ^ (lane >> 3)) * 16
+    bad = 0
+    for slab in (0, row_bytes - 128):
+        scalar = row_scalar + slab
+        taken = RANGE_CHECKS[check](lane_off, scalar, size)
+        at = base + lane_off + scalar
+        bad += int((taken & ((at < 0) | (at + 16 > rows * row_bytes))).sum())
+        bad += int(((r < rows) & (~taken | (at != r * row_bytes + chunk + slab))).sum())
+    return bad
+
+
+@pytest.mark.parametrize("check", RANGE_CHECKS)
+@pytest.mark.parametrize("row_bytes", [128, 3072, 37888])
+def test_loads_of_edge_tiles_stay_inside_the_matrix(HL, check, row_bytes):
+    """Every group of a tile of up to 256 rows, whatever part of the tile exists: no lane reads behind the operand's last row and
+    every existing row is read where it lies, whichever offsets the hardware holds against a resource's range."""
+    out = (C.c_uint32 * 66)()
+    for rows in [1, 2, 7, 8, 9, 15, 16, 17, 23, 24, 31, 33, 63, 72, 100, 128, 255, 256]:
+        for first in range(0, 256, 4):
+            for kind in (0, 1, 2):
+                assert HL.areal_plan_tile_load(first, kind, rows, row_bytes, out) == 0
+                v = np.array(out[:], dtype=np.int64)
+                assert _load_faults(check, first, kind == 1, rows, row_bytes, v[0], v[1], v[2:]) == 0, (rows, first, kind)
+    assert HL.areal_plan_tile_load(0, 3, 8, 128, out) == HL.areal_plan_tile_load(0, 0, 0, 128, out) == binding.E_INVAL
+
+
+def test_a_row_in_the_scalar_offset_would_not_be_inside():
+    """The form that the loads must not have: one resource for a tile's rows, a group's place in the scalar offset.  It needs a
+    check that includes the scalar offset and does not wrap."""
+    lane = np.arange(64, dtype=np.int64)
+    off = (lane >> 3) * 3072 + ((lane & 7) ^ (lane >> 3)) * 16
+    faults = {c: _load_faults(c, 24, False, 20, 3072, 0, 20 * 3072, off, row_scalar=24 * 3072) for c in RANGE_CHECKS}
+    assert faults["lane and scalar offset"] == 0
+    assert faults["lane offset alone"] > 0 and faults["lane offset against the rest, which wraps"] > 0
