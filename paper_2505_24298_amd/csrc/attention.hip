@@ -319,8 +319,7 @@ template <int D>
 __global__ __launch_bounds__(256) void attn_decode_kernel(
     const int4* __restrict__ desc, const int32_t* __restrict__ seg_table, int base1, int base2, int base3, int base4,
     int base5, int base6, int base7, int base8, int depth, uint32_t shape, DecodeArgs) {
-  constexpr int kArgs = 56;                              // offset of the struct
-  static_assert(alignof(DecodeArgs) == 8, "offset of the struct");
+  typedef decltype(attn_decode_kernel<D>) Kernel;
   __shared__ float sm[4][16], sl[4][16];
   __shared__ float so[4][16][D];
   __shared__ float s_new[16], v_new[D];
@@ -329,7 +328,7 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(
   const int stride = shape & 255, G = (shape >> 8) & 31, nkv = shape >> 13, nq = G * nkv;
   const int q_seg = blockIdx.z * kSegRows + blockIdx.y;
   if (q_seg >= depth) {                                  // the shared leading blocks of a set of rows
-    const DecodeArgs A = late_args<DecodeArgs>(kArgs);
+    const DecodeArgs A = late_args<Kernel>();
     const int n_shared = A.grp.n_shared, w = (q_seg - depth) * 8 + xcd;
     const int set = n_shared > 0 ? w / n_shared : 0;
     if (n_shared > 0 && set < A.grp.n_sets)
@@ -345,7 +344,7 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(
   const int g = lane >> 4, j = lane & 15;
   const BlockIds ids = load_ids(seg_table + (int64_t)seg * stride, stride, lane);
   const int4 d = desc[seg];
-  const DecodeArgs A = late_args<DecodeArgs>(kArgs);
+  const DecodeArgs A = late_args<Kernel>();
   const float* __restrict__ qkv = A.qkv;
   const f16 *__restrict__ bq = A.bq, *__restrict__ bk = A.bk, *__restrict__ bv = A.bv;
   f16* __restrict__ arena = A.arena;

@@ -109,12 +109,34 @@ __device__ __forceinline__ int buf1(__amdgpu_buffer_rsrc_t r, int off) {
   return (int)__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
 }
 
-// An argument struct of the kernel, `offset` bytes into its arguments, read here and not on entry: the reads of a by-value
-// parameter all start there, and a wave that needs few of them first waits for all.
-template <class T>
-__device__ __forceinline__ T late_args(int offset) {
+// Where a kernel's last parameter lies in its arguments (one after the other, each at its own alignment), and its type.
+template <class Kernel>
+struct LastParam;
+template <class... P>
+struct LastParam<void(P...)> {
+  template <class A, class... R>
+  static constexpr int offset_of(int at) {
+    at = (at + (int)alignof(A) - 1) / (int)alignof(A) * (int)alignof(A);
+    if constexpr (sizeof...(R) == 0) return at;
+    else return offset_of<R...>(at + (int)sizeof(A));
+  }
+  static constexpr int offset = offset_of<P...>(0);
+  template <class A, class... R>
+  struct Last : Last<R...> {};
+  template <class A>
+  struct Last<A> { typedef A type; };
+  typedef typename Last<P...>::type type;
+};
+static_assert(LastParam<void(void*, int, double)>::offset == 16 && LastParam<void(void*, int, int, double)>::offset == 16 &&
+              LastParam<void(void*, char, short, float)>::offset == 12, "an argument starts at its alignment");
+// The last parameter of Kernel (the type of the kernel that calls this), a struct by value, read here and not on entry: the reads
+// of a by-value parameter all start there, and a wave that needs few of them first waits for all.
+template <class Kernel>
+__device__ __forceinline__ typename LastParam<Kernel>::type late_args() {
+  typedef typename LastParam<Kernel>::type T;
   typedef const __attribute__((address_space(4))) T* ptr;
-  return *(const T*)(ptr)((const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr() + offset);
+  return *(const T*)(ptr)((const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr() +
+                          LastParam<Kernel>::offset);
 }
 
 // Every LDS read of this wave has returned (s_waitcnt with only lgkmcnt constrained).
