@@ -38,7 +38,8 @@ int areal_op_gemm_choose(int32_t M, int32_t N, int32_t K, int32_t mode, int32_t*
  *           segment start at rows end0 and end1 (multiples of 8)
  *   mode 1: C float32 [M,N] += x W0^T,       x half [M,K], gain NULL
  *   mode 2: C half    [M,N]  = silu(norm(x) W0^T) * (norm(x) W1^T)
- * norm(x) = x / sqrt(mean(x^2) + eps) * gain rounded to half, x float32 [M,K], gain half [K].
+ * norm(x) = x / sqrt(mean(x^2) + eps) * gain rounded to half, x float32 [M,K], gain half [K].  x, gain and W0 to W2
+ * 16-byte aligned, C on its elements (AREAL_E_INVAL otherwise).
  * areal_op_rows_serves: 1 where the library takes this path for M rows, 0 elsewhere (AREAL_E_INVAL there). */
 int areal_op_rows_serves(int32_t M, int32_t N, int32_t K, int32_t mode);
 int areal_op_rows_product(void* hip_stream, const void* x, const void* gain, float eps, const void* W0, const void* W1,

@@ -82,7 +82,8 @@ int gemm_num_configs();
 // ---- rows.hip -----------------------------------------------------------------
 // The products of a pass of up to 8 rows, with no tiles: C (+)= X W^T, x = half [M, K] for residual adds (gain null), and for
 // stored products (one or three segments of W, the first two of a multiple of 8 rows) and SwiGLU the RMSNorm with `gain`
-// of the float32 rows x [M, K].  Every output is written by one work-group: nothing has to be cleared.
+// of the float32 rows x [M, K].  Every output is written by one work-group: nothing has to be cleared.  x, gain and W on 16
+// bytes, C on its elements: refused otherwise.
 bool rows_product_serves(int M, int N, int K, GemmMode mode, bool norm);
 hipError_t launch_rows_product(hipStream_t s, const void* x, const f16* gain, float eps, GemmW W, void* C, int M, int N, int K,
                                int ldc, GemmMode mode);

@@ -341,7 +341,9 @@ hipError_t launch_rows_product(hipStream_t s, const void* x, const f16* gain, fl
                                int ldc, GemmMode mode) {
   const bool norm = gain != nullptr;
   if (!rows_product_serves(M, N, K, mode, norm) || !x || !C || ldc < N || !W.ptr[0]) return hipErrorInvalidValue;
-  if (((uintptr_t)x | (uintptr_t)W.ptr[0] | (uintptr_t)W.ptr[1] | (uintptr_t)W.ptr[2]) & 15) return hipErrorInvalidValue;
+  if (((uintptr_t)x | (uintptr_t)gain | (uintptr_t)W.ptr[0] | (uintptr_t)W.ptr[1] | (uintptr_t)W.ptr[2]) & 15 ||
+      (uintptr_t)C & (mode == GEMM_SWIGLU_F16 ? 1 : 3))
+    return hipErrorInvalidValue;
   if (mode == GEMM_ADD_F32 && W.end[0] != N) return hipErrorInvalidValue;
   // modes in use: the norm before stored and SwiGLU products, none before residual adds
   if (norm != (mode != GEMM_ADD_F32)) return hipErrorInvalidValue;

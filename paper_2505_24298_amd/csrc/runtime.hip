@@ -355,9 +355,14 @@ int run_pass(areal_ctx* c, const PassArgs& a) {
                ? launch_rows_product(s, x, nullptr, 0.f, wt, h, a.M, H, K, H, GEMM_ADD_F32)
                : launch_gemm_cfg(s, x, wt, h, a.M, H, K, H, GEMM_ADD_F32, -1, -1);
   };
+  // Products of a few rows with their RMSNorm inside read the gains 16 bytes at a time: those of a set that is read in place and
+  // start elsewhere keep the launch of their own.
+  auto few = [&](int M, int N, GemmMode mode, const f16* gain) {
+    return rows_product_serves(M, N, H, mode, true) && ((uintptr_t)gain & 15) == 0;
+  };
   for (int l = 0; l < g.n_layers; ++l) {
     f16* arena_l = arena + (int64_t)l * c->geom.layer_stride;
-    const bool few_qkv = rows_product_serves(a.M, qd + 2 * kd, H, GEMM_STORE_F32, true);
+    const bool few_qkv = few(a.M, qd + 2 * kd, GEMM_STORE_F32, w.norm_attn[l]);
     if (!few_qkv) {
       ProfScope ps(c, AREAL_K_RMSNORM, l, sampled, rows);
       // the QKV product may split K and accumulate atomically: then its output is cleared here
@@ -401,7 +406,7 @@ int run_pass(areal_ctx* c, const PassArgs& a) {
       GemmW wo{{w.wo[l], nullptr, nullptr}, {H, 0, 0}};
       HIP_TRY(c, residual_add(attn, wo, qd));
     }
-    const bool few_gu = rows_product_serves(a.M, F, H, GEMM_SWIGLU_F16, true);
+    const bool few_gu = few(a.M, F, GEMM_SWIGLU_F16, w.norm_ffn[l]);
     if (!few_gu) HIP_TRY(c, launch_rmsnorm(s, h, w.norm_ffn[l], xn, a.M, H, g.rms_eps, nullptr));
     {
       ProfScope ps(c, AREAL_K_GEMM_GATEUP, l, sampled, rows);
@@ -457,7 +462,7 @@ int run_pass(areal_ctx* c, const PassArgs& a) {
       }
     }
   }
-  if (a.n_out > 0 && !a.last_rows && rows_product_serves(a.n_out, g.vocab, H, GEMM_STORE_F32, true)) {
+  if (a.n_out > 0 && !a.last_rows && ((uintptr_t)a.logits & 3) == 0 && few(a.n_out, g.vocab, GEMM_STORE_F32, w.final_norm)) {
     ProfScope ps(c, AREAL_K_GEMM_LMHEAD, -1, sampled, (double)a.n_out);
     GemmW wl{{w.lm_head, nullptr, nullptr}, {g.vocab, 0, 0}};
     HIP_TRY(c, launch_rows_product(s, h, w.final_norm, g.rms_eps, wl, a.logits, a.n_out, g.vocab, H, g.vocab, GEMM_STORE_F32));

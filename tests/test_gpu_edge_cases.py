@@ -456,3 +456,47 @@ def test_half_precision_weights_in_place_and_tied_output_projection(torch, bindi
             _, logits, _ = eng.update_weights_interrupt(dw2, 1)
     _check_step(torch, eng, wk, ids, logits)
     eng.close()
+
+
+@pytest.mark.parametrize("at", [1, 2, 4, 8])
+def test_gains_read_in_place_start_at_any_element(torch, binding, at):
+    """Half-precision gains anywhere in a larger buffer (`at` halves behind a 16-byte boundary), as views of a flat parameter
+    buffer have them: steps of a few rows, whose products read them 16 bytes at a time, and a pass of many, against the oracle.
+    Gains drawn between 0.5 and 1.5, so that a shift by one shows: logits of order 0.5, tolerance as stated."""
+    from oracle import rollout
+    cfg = synth.shape("tiny")
+    w = synth.make_weights(cfg, 77, qkv_bias=True)
+    rng = np.random.default_rng(at)
+    gain = lambda: rng.uniform(0.5, 1.5, size=cfg["hidden"]).astype(np.float32)
+    w["final_norm"] = gain()
+    for lw in w["layers"]:
+        lw["norm_attn"], lw["norm_ffn"] = gain(), gain()
+
+    def moved(t):
+        buf = torch.full((t.numel() + 64,), 7.0, dtype=t.dtype, device=t.device)
+        buf[at:at + t.numel()] = t
+        view = buf[at:at + t.numel()]
+        assert view.data_ptr() % 16 == 2 * at % 16
+        return view
+
+    dw = binding.weights_to_device(w, f16=True)
+    dw["final_norm"] = moved(dw["final_norm"])
+    for lw in dw["layers"]:
+        lw["norm_attn"], lw["norm_ffn"] = moved(lw["norm_attn"]), moved(lw["norm_ffn"])
+    eng = binding.Areal(cfg, max_seqs=4, max_seq_len=96, max_batch_tokens=64, kv_blocks=24, convert_weights=False)
+    eng.load_weights(dw, 0)
+    wk = rollout.RolloutWorker(cfg, _f16_weights(w), version=0, seed=0)
+    ids = [0, 1, 2]
+    prompts = synth.make_prompts(cfg, 3, 1, 10, 40, seed=13)
+    for s, p in zip(ids, prompts):
+        wk.add(s, p)
+    logits = eng.prefill(ids, prompts)
+    for step in range(4):
+        toks = _check_step(torch, eng, wk, ids, logits)
+        logits = eng.decode_step(ids, toks)
+        if step == 1:                     # one row from here on
+            eng.free_seq(1)
+            eng.free_seq(2)
+            ids, logits = [0], logits[:1].contiguous()
+    _check_step(torch, eng, wk, ids, logits)
+    eng.close()

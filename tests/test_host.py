@@ -567,6 +567,21 @@ def test_refused_products_stay_refused(L):
     assert all(refused(3, 24, (1 << 22) + 8, mode, 12) for mode in (0, 1, 2))
 
 
+def test_products_of_a_few_rows_refuse_addresses_they_cannot_load_from(L):
+    """areal_op_rows_product reads x, the gains and the weights 16 bytes at a time and stores single elements: what does not
+    start there is refused before anything reaches a launch."""
+    def rc(mode, x=16, gain=16, W0=16, W1=16, Cp=16):
+        p = [C.c_void_p(4096 * k + at) for k, at in zip(range(1, 6), (x, gain, W0, W1, Cp))]
+        gain_p = None if mode == 1 else p[1]
+        W1_p = p[3] if mode == 2 else None
+        return L.areal_op_rows_product(None, p[0], gain_p, 1e-6, p[2], W1_p, None, 24, 24, p[4], 1, 24, 128, mode)
+
+    for mode in (0, 1, 2):
+        bad = [dict(x=8), dict(W0=8), dict(Cp=1)] + [dict(Cp=2)] * (mode != 2) + [dict(W1=2)] * (mode == 2)
+        bad += [dict(gain=at) for at in (2, 4, 8)] * (mode != 1)
+        assert all(rc(mode, **b) == binding.E_INVAL for b in bad), mode
+
+
 # ------------------------------------------------------------- addresses of the tiled products' loads
 RANGE_CHECKS = {
     "lane offset alone": lambda lane, scalar, size: lane < size,
