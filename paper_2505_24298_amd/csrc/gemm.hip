@@ -75,9 +75,10 @@ struct TileRsrc {
     const RowRange g = row_range(row, row_bytes, bytes);
     return buffer_rsrc(p + g.first, g.bytes);
   }
-  // The group that begins at row r of the A tile; all of its rows.
+  // The group that begins at row r of the A tile; all of its rows (and those of a W tile of one matrix).
   __device__ __forceinline__ __amdgpu_buffer_rsrc_t a(int r) const { return rsrc(pa, r, a_bytes); }
   __device__ __forceinline__ __amdgpu_buffer_rsrc_t a() const { return buffer_rsrc(pa, a_bytes); }
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t w() const { return buffer_rsrc(pw0, w_bytes); }
   // The group that begins at row r of the W tile, or at its feature r of gate or up.  Stored products: of up to three segments,
   // each of whole groups but the last; a group below the matrix takes its last one.
   __device__ __forceinline__ __amdgpu_buffer_rsrc_t w(int r, bool is_up) const {
@@ -90,6 +91,15 @@ struct TileRsrc {
     return buffer_rsrc(reinterpret_cast<const char*>(p) + (int64_t)(n - start) * row_bytes, (uint32_t)min(8, N - n) * row_bytes);
   }
 };
+
+// Whether a group's place in its tile stands in the lanes' offsets (one register a load, one resource an operand) or in a base of its
+// own (four scalar registers a load).  Residual adds take the former: where rows are a multiple of 4,096 bytes apart, so that all
+// of a slab's lines lie on few memory channels, it is the faster one whatever the reason (128 x 96 tiles, 128 x 1,536 x 28,672 in 8 splits
+// 48.0 us with bases, 38.4 with lanes; 128 x 4,128 x 14,336 43.2 and 41.5, x 18,944 52.0 and 50.9, x 11,008 33.4 and 34.2), except
+// where the accumulators leave no register for it (256 x 256).  Gate/up and stored products take bases (8,960 features of K = 1,536,
+// 128 rows 18.5 us with one resource and scalar places, 17.9; QKV 4.05 and 3.9 us at 8 rows, 9.15 and 9.0 at 256).
+template <int BM, int BN, int NW, int MODE>
+constexpr bool lane_rows() { return MODE == GEMM_ADD_F32 && BM * BN < 128 * 64 * NW; }
 
 // Arguments that a kernel needs late: read from memory where they are used.
 struct GemmLate {
@@ -466,17 +476,20 @@ __device__ __forceinline__ void dma_tile(const f16* __restrict__ A, const WRows&
   // are FLAT instructions to the compiler's wait insertion, which then waits for every LDS read in
   // flight wherever it has to wait for one.
   const TileRsrc<BM, BN, MODE> tile(A, W, M, N, K, tile_m, tile_n);
-  // Where a wave has more than six groups, those of A share a resource and a lane holds its rows: with four scalar registers
-  // for each they do not fit.
-  constexpr bool LANE_ROWS = LPS > 6;
+  // A lane holds its rows, of one resource, in residual adds (lane_rows) and, of A, where a wave has more than six groups: with
+  // four scalar registers for each they do not fit.
+  constexpr bool W_LANES = lane_rows<BM, BN, NW, MODE>(), A_LANES = LPS > 6 || W_LANES;
   __amdgpu_buffer_rsrc_t rsrc[LPS];
   int src[LPS], dst_off[LPS];
 #pragma unroll
   for (int i = 0; i < LPS; ++i) {
     const bool is_a = i < GA / NW;
     const int gi = is_a ? wave * (GA / NW) + i : wave * (GB / NW) + (i - GA / NW);
-    src[i] = is_a && LANE_ROWS ? tile_lane_offset(lane, gi * 8, min(M - tile_m * BM, BM), K * 2) : group_lane_offset(lane, false, K * 2);
-    if (is_a) rsrc[i] = LANE_ROWS ? tile.a() : tile.a(gi * 8);
+    src[i] = (is_a ? A_LANES : W_LANES)
+                 ? tile_lane_offset(lane, gi * 8, is_a ? min(M - tile_m * BM, BM) : min(N - tile_n * BN, BN), K * 2)
+                 : group_lane_offset(lane, false, K * 2);
+    if (is_a) rsrc[i] = A_LANES ? tile.a() : tile.a(gi * 8);
+    else if (W_LANES) rsrc[i] = tile.w();
     else if (MODE == GEMM_SWIGLU_F16) rsrc[i] = tile.w((gi >> 3) * 32 + (gi & 3) * 8, (gi >> 2) & 1);
     else rsrc[i] = tile.w(gi * 8, false);
     dst_off[i] = ((is_a ? 0 : GA) + gi) * GROUP_BYTES;
@@ -848,10 +861,15 @@ __device__ __forceinline__ void wide_tile(const f16* __restrict__ A, const WRows
     const int gi = i * NW + wave, b0 = (gi - GA) * 8;
     // all of the waves' i-th groups are A's, all W's, or (at one i, where they do not divide) this wave's decides
     const bool is_a = i * NW + NW <= GA || (i * NW < GA && gi < GA);
-    if (is_a) rsrc[i] = tile.a(gi * 8);
-    else if (MODE == GEMM_SWIGLU_F16) rsrc[i] = tile.w(wide_feature<TN>(b0), wide_is_up<TN>(b0));
-    else rsrc[i] = tile.w(b0, false);
-    src[i] = group_lane_offset(lane, SPREAD && !is_a, K * 2);
+    if (lane_rows<BM, BN, NW, MODE>()) {
+      rsrc[i] = is_a ? tile.a() : tile.w();
+      src[i] = tile_lane_offset(lane, is_a ? gi * 8 : b0, is_a ? min(M - tile_m * BM, BM) : min(N - tile_n * BN, BN), K * 2);
+    } else {
+      if (is_a) rsrc[i] = tile.a(gi * 8);
+      else if (MODE == GEMM_SWIGLU_F16) rsrc[i] = tile.w(wide_feature<TN>(b0), wide_is_up<TN>(b0));
+      else rsrc[i] = tile.w(b0, false);
+      src[i] = group_lane_offset(lane, SPREAD && !is_a, K * 2);
+    }
     dst_off[i] = gi * WIDE_GROUP;
     issue1(0, kt0 * BK, i);          // the first slab: the later groups' addresses behind its loads
     __builtin_amdgcn_sched_barrier(0);
