@@ -328,7 +328,8 @@ int areal_adopt_seq_shared(areal_ctx* ctx, int32_t seq_id, int32_t len, int32_t 
  * and their summed work units: context tokens read (attention decode),
  * query-key pairs (attention prefill), rows (everything else). */
 #define AREAL_K_EMBED 0
-#define AREAL_K_RMSNORM 1        /* passes of up to 8 rows have it inside their products: no launch */
+#define AREAL_K_RMSNORM 1        /* no launch where the product after it has it inside: passes of up to 8 rows at a hidden
+                                  * size of up to 2,048, of up to 4 at up to 4,096 (areal_op_rows_serves) */
 #define AREAL_K_GEMM_QKV 2
 #define AREAL_K_ROPE_KVWRITE 3
 #define AREAL_K_ATTN_DECODE 4

@@ -22,7 +22,8 @@ def _normed(x, gain, eps):
 
 def _room(A, off, W, K):
     """Error bound of every sum A W^T: inputs that rounded the other way, and the float32 roundings of at most K / 64 additions in
-    a lane (two for a pair of products) and ten over lanes and waves."""
+    a lane (two for a pair of products) and ten over lanes and waves.  A reference whose norm is not rounded, or rounded twice, is 4
+    to 1,300 times beyond it (K = 4,096 to 8)."""
     W = W.double().abs()
     return (0 if off is None else off @ W.T) + (K / 64 + 10) * U * (A.abs() @ W.T)
 
